@@ -126,6 +126,9 @@ int dispatch(const bsp_weights* w, const ConvParams& p, void* stream, const Fixe
     if (rc != BSP_ERR_UNSUPPORTED) return rc;
     if (chunked && (allow & BSP_KERNEL_TILE)) rc = bsp_launch_tile(p, w->dtype, st);
     if (rc != BSP_ERR_UNSUPPORTED) return rc;
+  } else if (!w->kernels) {
+    const int rc = bsp_launch_f32(p, w->nnzb, w->bo, w->bi, (hipStream_t)stream);
+    if (rc != BSP_ERR_UNSUPPORTED) return rc;
   }
   return bsp_launch_general(p, w->dtype, w->bo, w->bi, (hipStream_t)stream);
 }

@@ -9,6 +9,9 @@
 
 int bsp_launch_general(const ConvParams& p, int dtype, int bo, int bi, hipStream_t st);
 
+// Single-precision layers of any shape (4x4x1 matrix tiles on the compressed block rows).
+int bsp_launch_f32(const ConvParams& p, int64_t nnzb, int bo, int bi, hipStream_t st);
+
 // LDS-tiled bf16 kernels (need the plan's step section and I % 8 == 0).
 // BSP_ERR_UNSUPPORTED means "use the general kernel", nothing was launched.
 bool bsp_tile_supported(const ConvParams& p, int dtype);
