@@ -1,0 +1,635 @@
+// Layers of any shape on 16x16 matrix tiles, activations staged in LDS: bf16 layers whose channel
+// counts are no multiple of eight, int8 layers (exact 32-bit sums, int8 or int32 results), and bf16
+// layers of any channel count that are too small to fill the chip (bsp_any_preferred).
+//
+// The weights come from the plan's step section (four (chunk, tap) pairs per step, a step's
+// 16 x 64-byte operand contiguous), so only chunks that some block of a strip keeps have steps.  A
+// chunk is 16 bytes of a pixel: eight bf16 channels or sixteen codes.
+//
+// What bounds it: on small layers the chain opening - patch - products - results, about 4 us with
+// the launch, which the split of a strip's steps over waves shortens; on large ones LDS (a step reads
+// 1 KB per matrix instruction, half the matrix rate at best) and, with few steps per tile, the same
+// chain times the tiles a CU works through, so what counts there is how many workgroups it holds:
+// every instance keeps to 128 registers (144 in the four-tile one: 1x1 28x28x128->512 int8 28 us
+// instead of 19).  Measured (general kernel / here): bf16 3x3 47x33x100->76 batch 3 36.9 / 7.1 us;
+// 3x3 14x14x300->300 batch 16 150 / 22; 5x5 100x90x37->50 batch 2 52 / 9.4; 1x1 14x14x1001->333 batch 8
+// 51 / 10.4; FC 32 x 1001 -> 999 28.6 / 5.4; int8 3x3 28x28x136->200 batch 8 28 / 8.2; 1x1
+// 56x56x40->200 batch 16 15.9 / 17.0, the one of 27 shapes that gained nothing.
+#include "bsp_launch.h"
+#include "bsp_tile.h"
+
+#include <algorithm>
+#include <array>
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+#include <mutex>
+
+namespace {
+
+typedef __attribute__((ext_vector_type(4))) int i32x4_t;
+enum { kBf16 = 0, kI8 = 1 };
+
+struct AnyArgs {
+  const unsigned char* X;
+  unsigned char* Y;
+  const void* bias;                // fp32 or int32
+  const unsigned char* residual;   // bf16
+  const int32_t* slab_ptr;
+  const unsigned char* xdesc;
+  const unsigned char* wfrag;
+  int32_t relu, shift, y32;        // y32: int32 results
+  int32_t L, J, I, O, H, M, N;
+  int32_t sh, sw, ph, pw, gsh, gsw, lsh, lsw;  // input pixels per staged pixel, staged pixels per output pixel
+  int32_t CW, nchunk, tpc;         // output columns per chunk of columns, such chunks per row, tiles per chunk
+  int32_t TPW, pitch, ppp;         // staged pixels per row, bytes per staged pixel, 16-byte pieces staged of each
+  int32_t nslabs, spst, nstages, slab_bytes;   // the plan's slabs, how many are staged at a time
+  int32_t nstrips, NS, PG, ks, nset;           // strips per workgroup, pixel groups, waves that share a strip's steps
+  int32_t total, per_xcd;
+  int32_t opitch, stream;          // bytes per pixel of the output image; its pieces are whole output lines
+  FastDiv d_nset, d_tpc, d_nchunk, d_cw, d_tpw, d_ppp, d_opp;
+};
+
+// 16 bytes from any address (the hardware has no alignment rule for them)
+__device__ __forceinline__ u32x4_t load16(const unsigned char* p) {
+  u32x4_t v;
+  __builtin_memcpy(&v, p, 16);
+  return v;
+}
+// drops the low n bytes (0 .. 15), zeros come in from above
+__device__ __forceinline__ u32x4_t drop_low(u32x4_t v, int n) {
+  if (n & 8) v = u32x4_t{v.z, v.w, 0u, 0u};
+  if (n & 4) v = u32x4_t{v.y, v.z, v.w, 0u};
+  const uint32_t b = (uint32_t)(n & 3) * 8u;
+  return u32x4_t{__builtin_amdgcn_alignbit(v.y, v.x, b), __builtin_amdgcn_alignbit(v.z, v.y, b),
+                 __builtin_amdgcn_alignbit(v.w, v.z, b), v.w >> b};
+}
+// The bytes [off, off + 16) of a pixel of `row` >= 16 bytes, zeros past its end; nothing outside the
+// pixel is read.  The first half asks for them (a chunk that reaches past the end is read from 16
+// bytes before it), the second puts them in place.
+__device__ __forceinline__ u32x4_t piece_ask(const unsigned char* px, int off, int row) {
+  return load16(px + min(off, row - 16));
+}
+__device__ __forceinline__ u32x4_t piece_place(u32x4_t v, int off, int row) {
+  return drop_low(v, max(off - (row - 16), 0));
+}
+
+template <int KIND>
+__device__ __forceinline__ f32x4_t mma(u32x4_t a, u32x4_t b, f32x4_t c) {
+  if constexpr (KIND == kI8)
+    return __builtin_bit_cast(f32x4_t, __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4_t, a),
+                                                                           __builtin_bit_cast(i32x4_t, b),
+                                                                           __builtin_bit_cast(i32x4_t, c), 0, 0, 0));
+  else
+    return mfma_bf16_16x16x32(a, b, c);
+}
+// the sum of two partial results, bit patterns of int32 or floats
+template <int KIND>
+__device__ __forceinline__ f32x4_t add4(f32x4_t a, f32x4_t b) {
+  if constexpr (KIND == kI8)
+    return __builtin_bit_cast(f32x4_t, __builtin_bit_cast(i32x4_t, a) + __builtin_bit_cast(i32x4_t, b));
+  else
+    return a + b;
+}
+
+// The first n of 16 bytes at any address (n >= 16: all of them).
+__device__ __forceinline__ void store_first(unsigned char* p, u32x4_t v, int n, bool stream) {
+  if (n >= 16) {
+    if (stream)
+      __builtin_nontemporal_store(v, (u32x4_t*)p);
+    else
+      __builtin_memcpy(p, &v, 16);
+    return;
+  }
+  if (n & 8) {
+    __builtin_memcpy(p, &v, 8);
+    v = drop_low(v, 8);
+    p += 8;
+  }
+  if (n & 4) {
+    __builtin_memcpy(p, &v, 4);
+    v = drop_low(v, 4);
+    p += 4;
+  }
+  if (n & 2) {
+    *(uint16_t*)p = (uint16_t)v.x;
+    v = drop_low(v, 2);
+    p += 2;
+  }
+  if (n & 1) *p = (uint8_t)v.x;
+}
+// The first n bytes (an even number) at any address, zeros for the others.
+__device__ __forceinline__ u32x4_t load_first(const unsigned char* p, int n) {
+  if (n >= 16) return load16(p);
+  u32x4_t v = {0u, 0u, 0u, 0u};
+  if (n & 8) {
+    __builtin_memcpy(&v, p, 8);
+    p += 8;
+  }
+  uint32_t lo = 0;
+  if (n & 4) {
+    __builtin_memcpy(&lo, p, 4);
+    p += 4;
+  }
+  const uint32_t hi = n & 2 ? *(const uint16_t*)p : 0u;
+  const uint32_t a = n & 4 ? lo : hi, b = n & 4 ? hi : 0u;
+  if (n & 8)
+    v.z = a, v.w = b;
+  else
+    v.x = a, v.y = b;
+  return v;
+}
+
+template <int KIND>
+__device__ __forceinline__ f32x4_t bias4(const AnyArgs& a, int ch) {
+  uint32_t b[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) b[r] = a.bias && ch + r < a.O ? ((const uint32_t*)a.bias)[ch + r] : 0u;
+  return __builtin_bit_cast(f32x4_t, u32x4_t{b[0], b[1], b[2], b[3]});
+}
+
+// One (tile of PT * 16 * PG output pixels) x (NS strips) per workgroup.  A tile is consecutive
+// pixels of a chunk of image columns; its input patch, halo included, is staged as whole pixels
+// (zeros outside the image and past the last channel), as many of the plan's slabs at a time as
+// LDS takes.  A staged pixel is an odd number of 16-byte pieces, so the sixteen pixels of a matrix
+// tile read different banks.  Wave = (strip, pixel group, share of the strip's steps): a step's
+// weights come from the plan through a register ring of D, its activations from LDS one step ahead.
+template <int KIND, int PT, bool VEC>
+__global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
+  kernarg_touch<AnyArgs>();
+  extern __shared__ __align__(16) unsigned char lds[];
+  constexpr int D = 4, ES = KIND == kI8 ? 1 : 2;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, jn = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nthreads = (int)blockDim.x;
+  // workgroups of one tile (other strips) are neighbours on one XCD: its L2 has the patch
+  const uint32_t q = (blockIdx.x & 7u) * (uint32_t)a.per_xcd + (blockIdx.x >> 3);
+  if (q >= (uint32_t)a.total) return;
+  const uint32_t tile = fdiv(q, a.d_nset);
+  const int set = (int)(q - tile * (uint32_t)a.nset);
+  const uint32_t ic = fdiv(tile, a.d_tpc);
+  const int px = PT * 16 * a.PG;
+  const int p0 = (int)(tile - ic * (uint32_t)a.tpc) * px;
+  const int img = (int)fdiv(ic, a.d_nchunk);
+  const int col0 = (int)(ic - (uint32_t)img * (uint32_t)a.nchunk) * a.CW;
+  const int m0 = (int)fdiv((uint32_t)p0, a.d_cw);
+  const int plast = min(p0 + px, a.M * a.CW) - 1;
+  const int rows = ((int)fdiv((uint32_t)plast, a.d_cw) - m0) * a.lsh + a.H;  // staged rows
+
+  const int k = wave % a.ks, sp = wave / a.ks, pg = sp % a.PG, si = sp / a.PG;
+  const int strip = set * a.NS + si;
+  const bool active = si < a.NS && strip < a.nstrips;
+  // the strip's step ranges, one slab boundary per lane
+  const int tab = a.slab_ptr[(active ? strip : 0) * (a.nslabs + 1) + min(lane, a.nslabs)];
+
+  int base[PT];
+#pragma unroll
+  for (int t = 0; t < PT; ++t) {
+    const int p = min(p0 + (pg * PT + t) * 16 + jn, plast);
+    const int y = (int)fdiv((uint32_t)p, a.d_cw), x = p - y * a.CW;
+    base[t] = ((y - m0) * a.lsh * a.TPW + x * a.lsw) * a.pitch;
+  }
+  f32x4_t acc[PT];
+#pragma unroll
+  for (int t = 0; t < PT; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  const int iy0 = m0 * a.sh - a.ph, ix0 = col0 * a.sw - a.pw;
+  const int pieces = rows * a.TPW * a.ppp;
+  const int rowb = a.I * ES;  // bytes of a pixel
+  const unsigned char* xim = a.X + (int64_t)img * a.L * a.J * rowb;
+  const int rowpitch = a.TPW * a.pitch;
+
+  for (int stg = 0; stg < a.nstages; ++stg) {
+    const int sl0 = stg * a.spst, sl1 = min(sl0 + a.spst, a.nslabs);
+    const int slo = __builtin_amdgcn_readlane(tab, sl0), shi = __builtin_amdgcn_readlane(tab, sl1);
+    const int n = active && shi - slo > k ? (shi - slo - k + a.ks - 1) / a.ks : 0;  // this wave's steps
+
+    // ---- weights: a ring of D steps
+    u32x4_t wr[D];
+    int dr[D], add[D], one[D];  // descriptors; where the step's slab lies in a staged pixel; is it its slab's first step
+    int fcs = slo + k, fsl = sl0, fadd = 0, fbeg = slo, fend = __builtin_amdgcn_readlane(tab, sl0 + 1);
+    auto fetch = [&](int d) {
+      const int cs = min(fcs, shi - 1);  // (past the end: the last step again, never used)
+      fcs += a.ks;
+      while (cs >= fend) {
+        fadd += a.slab_bytes;
+        ++fsl;
+        fbeg = fend;
+        fend = __builtin_amdgcn_readlane(tab, fsl + 1);
+      }
+      dr[d] = *(const int*)(a.xdesc + ((uint32_t)cs * 16u + (uint32_t)g * 4u));
+      wr[d] = *(const u32x4_t*)(a.wfrag + ((uint32_t)cs * 1024u + (uint32_t)lane * 16u));
+      add[d] = fadd;
+      one[d] = cs == fbeg;
+    };
+    if (n > 0) {  // their latency passes while the patch is staged
+#pragma unroll
+      for (int d = 0; d < D; ++d) fetch(d);
+    }
+
+    // ---- stage: four 16-byte pieces per thread in flight
+    const int c0 = sl0 * a.slab_bytes;  // first byte of a pixel that is staged
+    if (stg > 0) __syncthreads();
+    for (int f0 = tid; f0 < pieces; f0 += 4 * nthreads) {
+      u32x4_t v[4];
+      int dst[4], off[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int f = f0 + u * nthreads;
+        const int pix = (int)fdiv((uint32_t)f, a.d_ppp), part = f - pix * a.ppp;
+        const int r = (int)fdiv((uint32_t)pix, a.d_tpw), x = pix - r * a.TPW;
+        const int iy = iy0 + r * a.gsh, ix = ix0 + x * a.gsw;
+        off[u] = c0 + part * 16;
+        dst[u] = f < pieces && off[u] < rowb ? pix * a.pitch + part * 16 : -1;
+        v[u] = u32x4_t{0u, 0u, 0u, 0u};
+        if (dst[u] >= 0 && (unsigned)iy < (unsigned)a.L && (unsigned)ix < (unsigned)a.J) {
+          const unsigned char* src = xim + (uint32_t)(iy * a.J + ix) * (uint32_t)rowb;
+          v[u] = VEC ? *(const u32x4_t*)(src + off[u]) : piece_ask(src, off[u], rowb);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (!VEC) {
+          __builtin_amdgcn_sched_barrier(0);  // (one shift after the other: all at once take 40 registers)
+          v[u] = piece_place(v[u], off[u], rowb);
+        }
+        if (dst[u] >= 0) *(u32x4_t*)(lds + dst[u]) = v[u];
+      }
+    }
+    __syncthreads();
+
+    // ---- products
+    auto read = [&](int d, u32x4_t (&f)[PT]) {
+      uint32_t desc = (uint32_t)dr[d];
+      asm volatile("" : "+v"(desc));  // decoded here, not where it is loaded: no early wait
+      const uint32_t o = ((desc & 0xFFFFu) << 4) + (uint32_t)add[d] + ((desc >> 16) & 0xFFu) * (uint32_t)rowpitch +
+                         (desc >> 24) * (uint32_t)a.pitch;
+#pragma unroll
+      for (int t = 0; t < PT; ++t) f[t] = *(const u32x4_t*)(lds + base[t] + o);
+      if constexpr (KIND == kBf16) {
+        // a pair that fills up a slab's last step multiplies zeros with zeros, not with whatever
+        // (an infinity) lies at its descriptor's address
+        const bool real = desc != 0u || (g == 0 && one[d]);
+#pragma unroll
+        for (int t = 0; t < PT; ++t) f[t] = real ? f[t] : u32x4_t{0u, 0u, 0u, 0u};
+      }
+    };
+    auto mfmas = [&](int d, const u32x4_t (&f)[PT]) {
+#pragma unroll
+      for (int t = 0; t < PT; ++t) acc[t] = mma<KIND>(wr[d], f[t], acc[t]);
+    };
+    u32x4_t fa[PT], fb[PT];
+    int i = 0;
+    if (n > 0) read(0, fa);
+    for (; i + D < n; i += D) {
+#pragma unroll
+      for (int d = 0; d < D; d += 2) {
+        read(d + 1, fb);
+        mfmas(d, fa);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(d);
+        __builtin_amdgcn_sched_barrier(0);
+        read((d + 2) % D, fa);
+        mfmas(d + 1, fb);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(d + 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < D; d += 2) {
+      if (i + d + 1 < n) read(d + 1, fb);
+      if (i + d < n) mfmas(d, fa);
+      if (d + 2 < D && i + d + 2 < n) read(d + 2, fa);
+      if (i + d + 1 < n) mfmas(d + 1, fb);
+    }
+  }
+
+  // ---- waves that share a strip: partial sums through LDS
+  if (a.ks > 1) {
+    __syncthreads();
+    f32x4_t* red = (f32x4_t*)lds;  // [wave][PT][64]
+    if (k > 0) {
+#pragma unroll
+      for (int t = 0; t < PT; ++t) red[(wave * PT + t) * 64 + lane] = acc[t];
+    }
+    __syncthreads();
+    if (k == 0) {
+      for (int s = 1; s < a.ks; ++s) {
+#pragma unroll
+        for (int t = 0; t < PT; ++t) acc[t] = add4<KIND>(acc[t], red[((wave + s) * PT + t) * 64 + lane]);
+      }
+    }
+  }
+  __syncthreads();  // everybody is done with the patch (the partial sums)
+
+  // ---- results: bias and the one rounding (or the rescale), into an LDS image of the tile's
+  // output; then all waves copy that out, 16 contiguous bytes per lane, with the residual and ReLU
+  const int opitch = a.opitch;
+  if (active && k == 0) {
+    const f32x4_t bv = bias4<KIND>(a, strip * BSP_STRIP + 4 * g);
+    unsigned char* ot = lds + (pg * PT * 16 + jn) * opitch;
+#pragma unroll
+    for (int t = 0; t < PT; ++t, ot += 16 * opitch) {
+      const f32x4_t v = add4<KIND>(acc[t], bv);
+      const int c = si * BSP_STRIP + 4 * g;
+      if constexpr (KIND == kBf16) {
+        *(u32x2_t*)(ot + c * 2) = u32x2_t{pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)};
+      } else if (a.y32) {
+        *(f32x4_t*)(ot + c * 4) = v;
+      } else {
+        const i32x4_t s = __builtin_bit_cast(i32x4_t, v);
+        const long long half = a.shift > 0 ? 1ll << (a.shift - 1) : 0;
+        uint32_t packed = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const long long w = ((long long)s[r] + half) >> a.shift;  // 64 bits: adding the half cannot wrap
+          const int b = w < -128 ? -128 : (w > 127 ? 127 : (int)w);
+          packed |= (uint32_t)(b & 0xFF) << (8 * r);
+        }
+        *(uint32_t*)(ot + c) = packed;
+      }
+    }
+  }
+  __syncthreads();
+  const int os = KIND == kBf16 ? 2 : a.y32 ? 4 : 1;  // bytes per result
+  const int run = min(a.NS * BSP_STRIP, a.O - set * a.NS * BSP_STRIP) * os;  // a pixel's bytes here
+  const int opp = a.NS * os;                         // 16-byte pieces per pixel
+  const int npix = plast + 1 - p0;
+  const int64_t ybase = ((int64_t)img * a.M * a.N) * a.O + set * a.NS * BSP_STRIP;
+  for (int i = tid; i < npix * opp; i += nthreads) {
+    const int pix = (int)fdiv((uint32_t)i, a.d_opp), off = (i - pix * opp) * 16;
+    const int y = (int)fdiv((uint32_t)(p0 + pix), a.d_cw), x = col0 + p0 + pix - y * a.CW;
+    const int n = run - off;
+    if (n <= 0 || x >= a.N) continue;
+    const int64_t o = (ybase + ((int64_t)y * a.N + x) * a.O) * os + off;
+    u32x4_t v = *(const u32x4_t*)(lds + pix * opitch + off);
+    if constexpr (KIND == kBf16) {
+      if (a.residual || a.relu) {
+        u32x4_t r = {0u, 0u, 0u, 0u};
+        if (a.residual) r = load_first(a.residual + o, n);
+        const u32x2_t lo = post_bf16x4_reg(u32x2_t{v.x, v.y}, u32x2_t{r.x, r.y}, a.residual != nullptr, a.relu);
+        const u32x2_t hi = post_bf16x4_reg(u32x2_t{v.z, v.w}, u32x2_t{r.z, r.w}, a.residual != nullptr, a.relu);
+        v = u32x4_t{lo.x, lo.y, hi.x, hi.y};
+      }
+    }
+    store_first(a.Y + o, v, n, a.stream);
+  }
+}
+
+inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+
+struct Pick {
+  int32_t PT, PG, NS, ks, CW, nchunk, tpc, TPW, spst, lds;
+};
+
+// Tile, staging and split by a model of the busiest CU in clocks: the workgroups it runs, each with
+// its steps (their latency, or their share of the issue slots and LDS), the bytes it stages and the
+// fixed chain, which resident workgroups hide of each other.  On 12 shapes its choice measured
+// within 4 % of the best of 48 to 384 candidates, but for wide 1x1 layers on many pixels (8 to 15 %).
+Pick choose(int B, int M, int N, int os, int nstrips, int steps, int nslabs, int slab_pieces, int pieces, int H, int K, int lsh,
+            int lsw, bool flat) {
+  Pick best{};
+  double best_cost = 1e30;
+  for (int PT : {1, 2, 4})
+    for (int PG : {1, 2, 4, 8}) {
+      const int px = PT * 16 * PG;
+      for (int nc = 1; nc <= (flat ? 1 : cdiv(N, 8)); ++nc) {
+        const int cw = flat ? px : cdiv(N, nc);
+        if (!flat && cw > 64) continue;
+        const int64_t nchunk = cdiv(N, cw), tpc = cdiv((int64_t)M * cw, px), tiles = (int64_t)B * nchunk * tpc;
+        const int orows = std::min(M, px % cw == 0 ? px / cw : (px - 2) / cw + 2);
+        const int trows = (orows - 1) * lsh + H, tpw = (cw - 1) * lsw + K;
+        const int64_t pix = (int64_t)trows * tpw;
+        for (int spst = nslabs;; spst = (spst + 1) / 2) {
+          const int ppp = std::min(spst * slab_pieces, pieces), nstages = cdiv(nslabs, spst);
+          const int64_t patch = pix * ((ppp | 1) * 16);
+          if (patch <= 160 * 1024)
+            for (int ks : {1, 2, 4, 8}) {
+              if (PG * ks > 8) continue;
+              const int nsmax = std::min(nstrips, 8 / (PG * ks));
+              const int NS = cdiv(nstrips, cdiv(nstrips, nsmax)), waves = NS * PG * ks;
+              const int64_t ldsb = std::max({patch, ks > 1 ? (int64_t)waves * PT * 1024 : 0, (int64_t)px * (NS * 16 * os + 16)});
+              if (ldsb > 160 * 1024) continue;
+              const int64_t wgs = tiles * cdiv(nstrips, NS);
+              const int resident = std::max(1, std::min((int)(160 * 1024 / ldsb), 16 / waves));
+              const double percu = std::max(1.0, (double)cdiv(wgs, 256)), live = std::min<double>(percu, resident);
+              const double mine = (double)steps / ks;
+              // a wave's step: its latency, or its share of a CU's issue, LDS and weight traffic
+              const double wstep = 24.0 + 10.0 * PT;
+              const double comp = mine * std::max(wstep * waves * live, 120.0 + 24.0 * PT) / live;
+              const double stage = (double)pix * pieces * 16 / 20.0;
+              const double fix = (nstages * 1600.0 + 4000.0 + (ks > 1 ? 500.0 : 0.0)) / live;
+              const double cost = percu * (comp + stage + fix);
+              if (cost < best_cost) {
+                best_cost = cost;
+                best = Pick{PT, PG, NS, ks, cw, (int32_t)nchunk, (int32_t)tpc, tpw, spst, (int32_t)ldsb};
+              }
+            }
+          if (spst == 1) break;
+        }
+      }
+    }
+  return best;
+}
+
+template <int KIND, int PT, bool VEC>
+int launch_inst(const AnyArgs& a, int threads, size_t ldsb, hipStream_t st) {
+  static bool raised = false;  // dynamic LDS above 64 KB has to be allowed once per kernel
+  if (!raised) {
+    if (hipFuncSetAttribute((const void*)conv_any<KIND, PT, VEC>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) !=
+        hipSuccess)
+      return BSP_ERR_HIP;
+    raised = true;
+  }
+  hipLaunchKernelGGL((conv_any<KIND, PT, VEC>), dim3((unsigned)(a.per_xcd * 8)), dim3(threads), ldsb, st, a);
+  return hipGetLastError() == hipSuccess ? BSP_OK : BSP_ERR_HIP;
+}
+// vec: pixels of X are whole 16-byte pieces
+template <int KIND, int PT>
+int launch_conv(const AnyArgs& a, bool vec, int threads, size_t ldsb, hipStream_t st) {
+  return vec ? launch_inst<KIND, PT, true>(a, threads, ldsb, st) : launch_inst<KIND, PT, false>(a, threads, ldsb, st);
+}
+
+template <int KIND>
+int launch_kind(const ConvParams& p, const int32_t* hdr, int y32, int shift, hipStream_t st) {
+  constexpr int ES = KIND == kI8 ? 1 : 2;
+  if (hdr[BSP_PLAN_NSTEPS_W] < 1 || p.I * ES < 16) return BSP_ERR_UNSUPPORTED;
+  if ((int64_t)p.L * p.J * p.I * ES >= (1ll << 31) || (int64_t)hdr[BSP_PLAN_NSTEPS_W] * 1024 >= (1ll << 32))
+    return BSP_ERR_UNSUPPORTED;
+  AnyArgs a{};
+  a.X = (const unsigned char*)p.X;
+  a.Y = (unsigned char*)p.Y;
+  a.bias = p.bias;
+  a.residual = (const unsigned char*)p.residual;
+  a.slab_ptr = p.plan + hdr[BSP_PLAN_OFF_SLAB_W];
+  a.xdesc = (const unsigned char*)(p.plan + hdr[BSP_PLAN_OFF_XDESC_W]);
+  a.wfrag = (const unsigned char*)(p.plan + hdr[BSP_PLAN_OFF_WFRAG_W]);
+  a.relu = p.relu;
+  a.shift = shift;
+  a.y32 = y32;
+  a.I = p.I;
+  a.O = p.O;
+  a.H = p.H;
+  a.nstrips = hdr[BSP_PLAN_NSTRIPS_W];
+  a.nslabs = hdr[BSP_PLAN_NSLABS_W];
+  if (a.nslabs > 63) return BSP_ERR_UNSUPPORTED;
+  a.slab_bytes = hdr[BSP_PLAN_SLAB_W] * ES;
+  const bool vec = (p.I * ES) % 16 == 0 && (reinterpret_cast<uintptr_t>(p.X) & 15u) == 0;
+  const bool flat = p.H == 1 && p.K == 1 && p.ph == 0 && p.pw == 0 && p.sh == 1 && p.sw == 1;
+  int B = p.B;
+  a.L = p.L;
+  a.J = p.J;
+  a.M = p.M;
+  a.N = p.N;
+  if (flat) {  // a plain matrix product over all pixels
+    B = 1;
+    a.L = a.M = 1;
+    a.J = a.N = p.P;
+    if ((int64_t)p.P * p.I * ES >= (1ll << 31)) return BSP_ERR_UNSUPPORTED;
+  }
+  a.sh = p.sh;
+  a.sw = p.sw;
+  a.ph = p.ph;
+  a.pw = p.pw;
+  // a window of one row (column) needs only the rows (columns) it visits
+  a.lsh = p.H == 1 ? 1 : p.sh;
+  a.gsh = p.H == 1 ? p.sh : 1;
+  a.lsw = p.K == 1 ? 1 : p.sw;
+  a.gsw = p.K == 1 ? p.sw : 1;
+  const int os = KIND == kBf16 ? 2 : y32 ? 4 : 1;
+  const int pieces = cdiv(p.I * ES, 16), slab_pieces = a.slab_bytes / 16;
+  Pick best;
+  {
+    // the search is a pure function of its arguments: remember its answers
+    static std::mutex mu;
+    static std::map<std::array<int32_t, 12>, Pick> memo;
+    const int steps = cdiv(hdr[BSP_PLAN_NSTEPS_W], a.nstrips);
+    const std::array<int32_t, 12> key = {B, a.M, a.N, p.I, p.O, p.H, p.K, p.sh * 2 + flat, p.sw, steps, a.nslabs, os};
+    std::lock_guard<std::mutex> lock(mu);
+    auto it = memo.find(key);
+    if (it == memo.end()) {
+      if (memo.size() > 4096) memo.clear();
+      it = memo.emplace(key, choose(B, a.M, a.N, os, a.nstrips, steps, a.nslabs, slab_pieces, pieces, p.H, p.K, a.lsh, a.lsw, flat))
+               .first;
+    }
+    best = it->second;
+  }
+#ifdef BSP_ROWS_TUNE  // experiments only: never defined in the product build
+  if (const char* e = std::getenv("BSP_ANY_TUNE")) {
+    int t[6];  // PT, PG, NS, ks, chunks of columns, slabs per stage
+    if (sscanf(e, "%d,%d,%d,%d,%d,%d", t, t + 1, t + 2, t + 3, t + 4, t + 5) == 6) {
+      Pick b{};
+      b.PT = t[0]; b.PG = t[1]; b.NS = t[2]; b.ks = t[3]; b.spst = std::min(t[5], a.nslabs);
+      const int px = b.PT * 16 * b.PG;
+      b.CW = flat ? px : cdiv(a.N, t[4]);
+      b.nchunk = cdiv(a.N, b.CW);
+      b.tpc = cdiv((int64_t)a.M * b.CW, px);
+      const int orows = std::min(a.M, px % b.CW == 0 ? px / b.CW : (px - 2) / b.CW + 2);
+      b.TPW = (b.CW - 1) * a.lsw + p.K;
+      const int ppp = std::min(b.spst * slab_pieces, pieces);
+      const int64_t patch = (int64_t)((orows - 1) * a.lsh + p.H) * b.TPW * ((ppp | 1) * 16);
+      const int64_t l = std::max({patch, b.ks > 1 ? (int64_t)b.NS * b.PG * b.ks * b.PT * 1024 : 0, (int64_t)px * (b.NS * 16 * os + 16)});
+      if (l > 160 * 1024 || b.NS * b.PG * b.ks > 8 || b.NS > a.nstrips) return BSP_ERR_UNSUPPORTED;
+      b.lds = (int)l;
+      best = b;
+    }
+  }
+  if (std::getenv("BSP_ROWS_VERBOSE"))
+    fprintf(stderr, "any: PT=%d PG=%d NS=%d ks=%d CW=%d nchunk=%d tpc=%d spst=%d/%d lds=%d\n", best.PT, best.PG, best.NS,
+            best.ks, best.CW, best.nchunk, best.tpc, best.spst, a.nslabs, best.lds);
+#endif
+  if (best.PT == 0) return BSP_ERR_UNSUPPORTED;
+  a.CW = best.CW;
+  a.nchunk = best.nchunk;
+  a.tpc = best.tpc;
+  a.TPW = best.TPW;
+  a.spst = best.spst;
+  a.nstages = cdiv(a.nslabs, best.spst);
+  a.ppp = std::min(best.spst * slab_pieces, pieces);
+  a.pitch = (a.ppp | 1) * 16;
+  a.NS = best.NS;
+  a.PG = best.PG;
+  a.ks = best.ks;
+  a.nset = cdiv(a.nstrips, best.NS);
+  const int px = best.PT * 16 * best.PG;
+  const int64_t tiles = (int64_t)B * a.nchunk * a.tpc, total = tiles * a.nset;
+  if (total >= (1ll << 30)) return BSP_ERR_UNSUPPORTED;
+  a.total = (int32_t)total;
+  a.per_xcd = cdiv(total, 8);
+  // multiply-high divisions are exact while dividend * divisor < 2^32 (the staging loop runs up
+  // to four rounds of threads past the pieces, of which LDS holds at most 10240)
+  const int64_t over = 10240 + 4 * 512;
+  if ((total + 8) * a.nset >= (1ll << 32) || tiles * a.tpc >= (1ll << 32) ||
+      (int64_t)B * a.nchunk * a.nchunk >= (1ll << 32) || (int64_t)a.tpc * px * a.CW >= (1ll << 32) ||
+      over * std::max(a.ppp, a.TPW) >= (1ll << 32) ||
+      ((int64_t)px * best.NS * os + 512) * best.NS * os >= (1ll << 32))
+    return BSP_ERR_UNSUPPORTED;
+  a.d_nset = make_fastdiv((uint32_t)a.nset);
+  a.d_tpc = make_fastdiv((uint32_t)a.tpc);
+  a.d_nchunk = make_fastdiv((uint32_t)a.nchunk);
+  a.d_cw = make_fastdiv((uint32_t)a.CW);
+  a.d_tpw = make_fastdiv((uint32_t)a.TPW);
+  a.d_ppp = make_fastdiv((uint32_t)a.ppp);
+  a.d_opp = make_fastdiv((uint32_t)(best.NS * os));
+  a.opitch = best.NS * BSP_STRIP * os + 16;
+  // whole 128-byte lines leave as streaming stores (nothing dirty is left for the kernel's end)
+  a.stream = p.O * os % 16 == 0 && (reinterpret_cast<uintptr_t>(p.Y) & 15u) == 0 &&
+             (best.NS >= a.nstrips ? flat || p.O * os >= 128 : p.O * os % 128 == 0 && best.NS * BSP_STRIP * os % 128 == 0);
+  const int threads = 64 * best.NS * best.PG * best.ks;
+  switch (best.PT) {
+    case 1: return launch_conv<KIND, 1>(a, vec, threads, (size_t)best.lds, st);
+    case 2: return launch_conv<KIND, 2>(a, vec, threads, (size_t)best.lds, st);
+    case 4: return launch_conv<KIND, 4>(a, vec, threads, (size_t)best.lds, st);
+  }
+  return BSP_ERR_UNSUPPORTED;
+}
+
+const int32_t* plan_of(const ConvParams& p, int dtype, const void* plan_host) {
+  const int32_t* hdr = (const int32_t*)plan_host;
+  if (!hdr || hdr[BSP_PLAN_MAGIC_W] != BSP_PLAN_MAGIC || hdr[BSP_PLAN_VERSION_W] != BSP_PLAN_VERSION ||
+      hdr[BSP_PLAN_O_W] != p.O || hdr[BSP_PLAN_I_W] != p.I || hdr[BSP_PLAN_H_W] != p.H || hdr[BSP_PLAN_K_W] != p.K ||
+      hdr[BSP_PLAN_DTYPE_W] != dtype)
+    return nullptr;
+  return hdr;
+}
+
+}  // namespace
+
+// Where both this kernel and a specialised one take a layer: the specialised ones share a patch or
+// a weight fragment among more products, which pays once the chip is full of work; this one splits
+// small layers finer (pixels, strips, contraction) and has the shorter opening.  The lines were drawn
+// by timing both sides on 220 layers (the networks' layers and random ones), in matrix instructions
+// of a layer.  `best of others / here` in microseconds, on either side of a line:
+//   1x7 17x17x128 batch 16 10.8 / 7.8, 1x7 stride 2 53x53x360 batch 23 63 / 39: windows of five and
+//   more columns in one row have no line, nor have 5x5 windows (15x15x248 batch 4 41 / 12)
+//   1x3 8x8x384 batch 16 (41 K) 11.1 / 7.7; 81x67x288 batch 3 (164 K) 13.7 / 17.5
+//   7x1 18x18x296 batch 5 (199 K) 13.8 / 13.8; 58x81x280 batch 2 (233 K) 12.7 / 19.8; stride 2: no line
+//   3x1 22x26x304 batch 2 (35 K) 9.6 / 7.1; 24x27x184 batch 20 (94 K) 11.5 / 11.6
+//   3x3 14x14x256 batch 1 (10 K) 8.2 / 6.0; 21x21x88 batch 13 (63 K) 7.4 / 10.2
+//   3x3 stride 2 36x23x496 batch 3 (43 K) 21 / 12; 70x70x128 batch 1 (63 K) 8.6 / 9.7
+// int8 against the LDS-resident kernel, which keeps one slab's weights in LDS: several slabs always
+// (7x7x512 batch 32 15.2 / 11.5), one slab below 20 K (1x1 56x56x64->256 batch 2 6.4 / 5.0, batch 32
+// 21 / 31).
+bool bsp_any_preferred(const ConvParams& p, const void* plan_host, int dtype) {
+  const int32_t* hdr = plan_of(p, dtype, plan_host);
+  if (!hdr) return false;
+  const int64_t mm = (int64_t)((p.P + 15) / 16) * hdr[BSP_PLAN_NSTEPS_W];
+  if (dtype == BSP_I8) return hdr[BSP_PLAN_NSLABS_W] > 1 || mm <= 20000;
+  const bool strided = p.sh > 1 || p.sw > 1;
+  if (p.H == 1 && p.K == 1) return false;
+  if (p.H == 1) return p.K >= 5 || mm <= 100000;
+  if (p.K == 1) return p.H >= 5 ? strided || mm <= 100000 : mm <= 45000;
+  if (p.H >= 5 || p.K >= 5) return true;
+  return mm <= (strided ? 60000 : 30000);
+}
+
+int bsp_launch_any(const ConvParams& p, const void* plan_host, hipStream_t st) {
+  const int32_t* hdr = plan_of(p, BSP_BF16, plan_host);
+  return hdr ? launch_kind<kBf16>(p, hdr, 0, 0, st) : BSP_ERR_UNSUPPORTED;
+}
+
+int bsp_launch_any_i8(const ConvParams& p, const void* plan_host, int y_i8, int shift, hipStream_t st) {
+  const int32_t* hdr = plan_of(p, BSP_I8, plan_host);
+  return hdr ? launch_kind<kI8>(p, hdr, !y_i8, shift, st) : BSP_ERR_UNSUPPORTED;
+}

@@ -12,6 +12,14 @@ int bsp_launch_general(const ConvParams& p, int dtype, int bo, int bi, hipStream
 // Single-precision layers of any shape (4x4x1 matrix tiles on the compressed block rows).
 int bsp_launch_f32(const ConvParams& p, int64_t nnzb, int bo, int bi, hipStream_t st);
 
+// Layers of any shape with at least 16 bytes of channels per pixel, from the plan's step section
+// and its host copy.  int8: y_i8 and shift as in bsp_launch_i8.  BSP_ERR_UNSUPPORTED = not
+// applicable, nothing launched.
+int bsp_launch_any(const ConvParams& p, const void* plan_host, hipStream_t st);
+int bsp_launch_any_i8(const ConvParams& p, const void* plan_host, int y_i8, int shift, hipStream_t st);
+// whether these are the faster ones on a layer that a specialised kernel takes too
+bool bsp_any_preferred(const ConvParams& p, const void* plan_host, int dtype);
+
 // LDS-tiled bf16 kernels (need the plan's step section and I % 8 == 0).
 // BSP_ERR_UNSUPPORTED means "use the general kernel", nothing was launched.
 bool bsp_tile_supported(const ConvParams& p, int dtype);

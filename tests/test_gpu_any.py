@@ -1,0 +1,98 @@
+"""The any-shape kernel (bf16 layers with ragged channels, small layers, int8) at the sizes where
+its tiles, chunks, slabs and output pieces end, against the oracle (needs a GPU)."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2407_09453_amd as bsp
+from synthetic import draw_layer
+
+from gpu_util import assert_close, make_layer, to_device, to_host
+
+pytestmark = pytest.mark.gpu
+
+# B, L, J, I, O, H, K, stride, pad
+SHAPES = [
+    (1, 1, 1, 9, 1, 1, 1, 1, 0),            # one pixel, one channel out, a chunk and a bit
+    (1, 3, 5, 17, 15, 1, 1, 1, 0),          # fewer pixels than a tile, a strip that is not full
+    (1, 1, 65, 130, 33, 1, 1, 1, 0),        # one pixel past four tiles, three strips
+    (3, 16, 16, 40, 76, 1, 1, 2, 0),        # strided pointwise
+    (2, 9, 16, 24, 40, 3, 3, 1, 1),         # rows of exactly one tile
+    (1, 5, 65, 19, 9, 3, 3, 1, 1),          # rows of two chunks
+    (1, 31, 63, 47, 66, 3, 3, 2, 1),
+    (2, 13, 11, 70, 136, 5, 5, 1, 2),       # two slabs, the second one short
+    (1, 20, 20, 33, 24, 1, 7, 2, 3),        # one-row window, strided: rows in between are not staged
+    (1, 20, 20, 33, 24, 7, 1, 2, 3),
+    (1, 7, 7, 512, 64, 3, 3, 1, 1),         # few pixels, long contraction: a strip shared by waves
+    (1, 5, 40, 3001, 8, 5, 5, 1, 2),        # a pixel's channels staged in several pieces
+    (1, 3, 3, 4101, 8, 3, 3, 1, 1),         # more slabs than the kernel takes: the general one
+    (2, 50, 50, 61, 130, 3, 3, 1, 1),       # many tiles, several workgroups per tile
+    (1, 6, 7, 16, 16, 3, 3, 1, 4),          # padding wider than the window
+]
+
+
+def _pad(H, K, p):
+    return (p if H > 1 or K == 1 else 0, p if K > 1 or H == 1 else 0)
+
+
+@pytest.mark.parametrize("bo,bi", [(8, 8), (4, 16), (16, 4)])
+@pytest.mark.parametrize("fused", [False, True], ids=["plain", "fused"])
+def test_bf16_shapes(bo, bi, fused):
+    import torch
+    for n, (B, L, J, I, O, H, K, s, p) in enumerate(SHAPES):
+        c = draw_layer("t", B=B, L=L, J=J, I=I, O=O, H=H, K=K, stride=(s, s), pad=_pad(H, K, p), bo=bo, bi=bi, dtype="bf16",
+                       mask_kind="bernoulli", density=0.5, seed=9300 + n, b_std=0.5)
+        print("case", n, SHAPES[n], bo, bi, fused, flush=True)
+        layer = make_layer(c)
+        Y = torch.full((c.B, c.M, c.N, c.O), float("nan"), device="cuda", dtype=torch.bfloat16)
+        if not fused:
+            layer.conv2d(to_device(c), c.stride, c.pad, out=Y)
+            torch.cuda.synchronize()
+            assert_close(to_host(Y), oracle.conv2d(c.X, c.W, c.bias, c.gamma, bo, bi, c.stride, c.pad), "bf16", f"shape {n}")
+            continue
+        # bit for bit the plain call followed by torch's add and relu, each rounding once
+        R = torch.randn(Y.shape, device="cuda", generator=torch.Generator("cuda").manual_seed(n)).bfloat16()
+        layer.conv2d(to_device(c), c.stride, c.pad, out=Y, residual=R, relu=True)
+        Y0 = layer.conv2d(to_device(c), c.stride, c.pad)
+        torch.cuda.synchronize()
+        assert torch.equal(Y, torch.relu(Y0.float() + R.float()).bfloat16()), n
+
+
+@pytest.mark.parametrize("bo,bi", [(8, 8), (4, 16), (16, 4)])
+def test_i8_shapes_bit_exact(bo, bi):
+    import torch
+    for n, (B, L, J, I, O, H, K, s, p) in enumerate(SHAPES):
+        rng = np.random.default_rng(9400 + n)
+        X = rng.integers(-128, 128, (B, L, J, I), dtype=np.int8)
+        W = rng.integers(-128, 128, (O, H, K, I), dtype=np.int8)
+        bias = rng.integers(-2 ** 18, 2 ** 18, O).astype(np.int32)
+        gamma = (rng.random((-(-O // bo), -(-I // bi))) < 0.5).astype(np.uint8)
+        print("case", n, SHAPES[n], bo, bi, flush=True)
+        layer = bsp.BspLayerI8(W, gamma, bo, bi, bias=bias)
+        # an input that starts eight bytes into its allocation, and one that is aligned
+        buf = torch.zeros(X.size + 8, dtype=torch.int8, device="cuda")
+        Xo = buf[8:].view(X.shape)
+        Xo.copy_(torch.from_numpy(X))
+        pad = _pad(H, K, p)
+        Y32 = layer.conv2d(Xo, (s, s), pad)
+        Y8 = layer.conv2d(torch.from_numpy(X).cuda(), (s, s), pad, shift=9)
+        torch.cuda.synchronize()
+        want = oracle.conv2d_i8(X, W, bias, gamma, bo, bi, (s, s), pad)
+        assert (Y32.cpu().numpy().astype(np.int64) == want).all(), n
+        assert (Y8.cpu().numpy() == oracle.conv2d_i8(X, W, bias, gamma, bo, bi, (s, s), pad, shift=9)).all(), n
+
+
+def test_infinities_in_dropped_channels_stay_out():
+    """Channels whose blocks are all dropped are never multiplied, also where a step of the plan
+    has fewer pairs than a matrix instruction takes."""
+    import torch
+    for I, H in ((41, 3), (73, 1), (200, 3)):
+        c = draw_layer("t", B=1, L=9, J=9, I=I, O=24, H=H, K=H, stride=(1, 1), pad=(H // 2, H // 2), bo=8, bi=8, dtype="bf16",
+                       mask_kind="bernoulli", density=0.5, seed=9500 + I)
+        c.gamma[:, 0] = 0
+        c.gamma[:, -1] = 0
+        X = c.X.copy()
+        c.X[..., :8] = np.inf
+        c.X[..., (I - 1) // 8 * 8:] = np.nan
+        y = to_host(make_layer(c).conv2d(to_device(c), c.stride, c.pad))
+        assert_close(y, oracle.conv2d(X, c.W, c.bias, c.gamma, 8, 8, c.stride, c.pad), "bf16", f"{I} channels")
