@@ -15,6 +15,7 @@
 #include "bsp_device.h"
 #include "bsp_launch.h"
 #include <algorithm>
+#include <cmath>
 #ifdef BSP_ROWS_TUNE
 #include <cstdlib>
 #endif
@@ -302,6 +303,258 @@ __global__ __launch_bounds__(512) void spgemm_nt_bf16(SpParams q) {
 #endif
 }
 
+// ---------------------------------------------------------------------------------------------
+// The same product as a tiled dense one, absent blocks staged as zeros.  A 16 x 16 tile of the
+// kernel above can skip a column only if both rows of a side drop it, (1 - d)^2 of them, and its
+// operands serve no other tile, so LDS gives it a quarter of the matrix rate; here a fragment
+// serves a whole wave tile.  4096^3, half of the blocks kept on both sides: 355 -> 123 us (1.1 PFLOP/s
+// of multiply-adds issued), all kept 533 -> 128, a quarter 159 -> 113, a tenth 98 / 111 (the kernel
+// above stays); 1024^3 52 -> 9.9, 512^3 19.9 -> 7.0.
+//
+// A workgroup owns GM x GN wave tiles of 16 MI x 16 NI elements and walks the block columns eight
+// at a time.  MV waves only move data: lane group l / 8 of a request brings the eight 16-byte rows
+// of one block, from its place in the compressed row or from a line of zeros, so a request fills
+// 1 KiB of LDS: the blocks of eight block rows in one block column.  They run NBUF - 1 steps ahead.
+// Blocks lie column by column in LDS ([column][row]), which puts the two blocks that sixteen lanes
+// read side by side.  Which blocks a row keeps in a step, and where they start, is a word per (step,
+// row) of a table that all waves build first from seg_ptr and col_idx.
+//
+// What bounds it: the requests' issue, nine instructions each (128 x 128 tiles with two, four and
+// eight movers at 2048^3: 43, 32, 25 us), then LDS: operands read and staged take 2048 clocks of a
+// 256 x 256 tile's step, its products as many.  Reading half a step ahead of the products changed
+// nothing.
+//
+// Zero times infinity: a product of an absent block with an infinity or NaN is no part of the
+// result.  It leaves a non-finite sum, so a 16 x 16 tile with one is computed once more from
+// the columns that both of its sides keep (redo_tile), the kernel above's rule.
+__device__ const u32x4_t g_zeros[1] = {};
+
+struct DnParams {
+  const int32_t* sa;
+  const int32_t* sb;
+  const int32_t* ca;
+  const int32_t* cb;
+  const unsigned char* pa;
+  const unsigned char* pb;
+  float* C;
+  int32_t ra, rb, nsub, nsteps;   // nsteps: eights of block columns
+  int32_t nnzb_a, nnzb_b;         // both positive
+  int32_t tiles_i, tiles_j, per_xcd, total;
+  int32_t band;                   // tile rows that consecutive workgroups share operand columns over
+};
+
+// One 16 x 16 tile (block rows r0, r0 + 1 of A against c0, c0 + 1 of B) from the columns that one of
+// the two rows of each side keeps; one column at a time, seldom called.
+template <typename Q>
+__device__ __forceinline__ f32x4_t redo_tile(const Q& q, int r0, int c0, int lane) {
+  const int jn = lane & 15, g = lane >> 4, h = jn >> 3;
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  // next and end of the four rows' blocks (rows past the matrix have none)
+  int pos[4], end[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int row = (k < 2 ? r0 : c0) + (k & 1);
+    const bool ok = row < (k < 2 ? q.ra : q.rb);
+    const int32_t* sp = (k < 2 ? q.sa : q.sb) + (int64_t)(ok ? row : 0) * (q.nsub + 1);
+    pos[k] = ok ? sp[0] : 0;
+    end[k] = ok ? sp[q.nsub] : 0;
+  }
+  const int kNone = 0x7FFFFFFF;
+  for (;;) {
+    int c[4], next = kNone;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      c[k] = pos[k] < end[k] ? (k < 2 ? q.ca : q.cb)[pos[k]] : kNone;
+      next = min(next, c[k]);
+    }
+    if (next == kNone) break;
+    if ((c[0] == next || c[1] == next) && (c[2] == next || c[3] == next)) {
+      u32x4_t a = {0u, 0u, 0u, 0u}, b = {0u, 0u, 0u, 0u};
+      if (g == 0) {  // eight of the instruction's 32 products, the others are zeros
+        if ((h ? c[1] : c[0]) == next) a = *(const u32x4_t*)(q.pa + (int64_t)(h ? pos[1] : pos[0]) * 128 + (jn & 7) * 16);
+        if ((h ? c[3] : c[2]) == next) b = *(const u32x4_t*)(q.pb + (int64_t)(h ? pos[3] : pos[2]) * 128 + (jn & 7) * 16);
+      }
+      acc = mfma_bf16_16x16x32(b, a, acc);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) pos[k] += c[k] == next;
+  }
+  return acc;
+}
+
+template <int MI, int NI, int GM, int GN, int MV, int NBUF>
+__global__ __launch_bounds__((GM * GN + MV) * 64) void spgemm_dense_bf16(DnParams q) {
+  kernarg_touch<DnParams>();
+  extern __shared__ __align__(16) unsigned char lds[];
+  constexpr int RA = GM * MI * 2, RB = GN * NI * 2, R = RA + RB;  // block rows
+  constexpr int NC = GM * GN, kBuf = R * 1024;                    // compute waves; bytes of a step
+  // a mover brings GPM groups of eight rows, eight columns of them or a share of the eight
+  constexpr int CS = MV > R / 8 ? MV / (R / 8) : 1, NCOL = 8 / CS, GPM = R / 8 * CS / MV;
+  static_assert(GPM * MV == R / 8 * CS && NCOL * CS == 8 && (RA / 8) % GPM == 0, "movers share the rows evenly");
+  constexpr int kAhead = (NBUF - 2) * GPM * NCOL;                   // requests that may be in flight while a step is used
+  static_assert(kAhead <= 63, "vmcnt counts to 63");
+  uint32_t* tab = (uint32_t*)(lds + NBUF * kBuf);                 // [step][R]: kept columns, first block << 8
+  const int tid = threadIdx.x, lane = tid & 63, jn = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // an XCD takes a run of tiles: bands of `band` tile rows, column by column, whose operands its L2 keeps
+  const int qi = (int)(blockIdx.x & 7u) * q.per_xcd + (int)(blockIdx.x >> 3);
+  if (qi >= q.total) return;
+  const int bt = q.band * q.tiles_j, b0 = qi / bt, rem = qi - b0 * bt;
+  const int bh = min(q.band, q.tiles_i - b0 * q.band);
+  const int ti = b0 * q.band + rem % bh, tj = rem / bh;
+
+  // seg_ptr row of the tile's block row r (A's, then B's); past the matrix, the last row's, and ok = false
+  auto seg_row = [&](int r, bool* ok) {
+    const bool isA = r < RA;
+    const int row = isA ? ti * RA + r : tj * RB + r - RA, rows = isA ? q.ra : q.rb;
+    *ok = row < rows;
+    return (isA ? q.sa : q.sb) + (int64_t)min(row, rows - 1) * (q.nsub + 1);
+  };
+
+  // ---- the table: sixteen lanes per (row, sixteen columns), four of those in flight per lane
+  constexpr int kPer = 4 * (NC + MV);  // entries per round of the workgroup
+  for (int e0 = tid >> 4; e0 < R * q.nsub; e0 += 4 * kPer) {
+    int first[4], n[4], rel[4], c[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int e = min(e0 + u * kPer, R * q.nsub - 1), r = e % R, x = e / R;
+      bool ok;
+      const int32_t* sp = seg_row(r, &ok);
+      first[u] = sp[x];
+      n[u] = sp[x + 1];
+      rel[u] = sp[0];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int e = min(e0 + u * kPer, R * q.nsub - 1), r = e % R;
+      // (every lane loads, those past the row's blocks an entry they do not use)
+      c[u] = (r < RA ? q.ca : q.cb)[min(first[u] + jn, (r < RA ? q.nnzb_a : q.nnzb_b) - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int e = e0 + u * kPer, r = e % R, x = e / R;
+      bool ok;
+      seg_row(r, &ok);
+      uint32_t m = ok && jn < n[u] - first[u] ? 1u << ((c[u] - x * kSub) & 15) : 0u;
+#pragma unroll
+      for (int s = 1; s < 16; s <<= 1) m |= __shfl_xor(m, s);
+      if (jn < 2 && e < R * q.nsub && 2 * x + jn < q.nsteps)
+        tab[(2 * x + jn) * R + r] = (uint32_t)(first[u] - rel[u] + (jn ? __popc(m & 0xFFu) : 0)) << 8 | ((m >> (8 * jn)) & 0xFFu);
+    }
+  }
+  __syncthreads();
+
+  if (wave >= NC) {
+    // =================================================================== data movers
+    const int grp0 = (wave - NC) / CS * GPM, c0 = (wave - NC) % CS * NCOL;
+    const bool isA = grp0 * 8 < RA;  // (all of a mover's groups are one operand's)
+    const unsigned char* src[GPM];
+    uint32_t tb[GPM];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
+#pragma unroll
+    for (int k = 0; k < GPM; ++k) {
+      const int r = (grp0 + k) * 8 + (lane >> 3);
+      bool ok;
+      src[k] = (isA ? q.pa : q.pb) + (int64_t)seg_row(r, &ok)[0] * 128 + (lane & 7) * 16;
+      tb[k] = lds0 + (uint32_t)(NBUF * kBuf + r * 4);
+    }
+    const unsigned char* zero = (const unsigned char*)g_zeros;
+    auto issue = [&](int s, int buf) {
+#pragma unroll
+      for (int k = 0; k < GPM; ++k) {
+        // (read and waited for in one: the compiler would wait for the requests in flight as well)
+        uint32_t w;
+        asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(w) : "v"(tb[k] + (uint32_t)(s * R * 4)) : "memory");
+        if (CS > 1) w += (uint32_t)__popc(w & ((1u << c0) - 1u)) << 8;
+        const unsigned char* p = src[k] + (w >> 8) * 128u;
+        const uint32_t dst = lds0 + (uint32_t)(buf * kBuf + (isA ? (grp0 + k) * 1024 : RA * 1024 + ((grp0 + k) * 8 - RA) * 128));
+#pragma unroll
+        for (int c = 0; c < NCOL; ++c) {
+          const bool kept = (w >> (c0 + c)) & 1u;
+          __builtin_amdgcn_global_load_lds((gptr_t)(kept ? p : zero),
+                                           (lptr_t)(uintptr_t)(dst + (uint32_t)((c0 + c) * (isA ? RA : RB) * 128)), 16, 0, 0);
+          p += kept ? 128 : 0;
+        }
+      }
+    };
+#pragma unroll
+    for (int s = 0; s < NBUF - 1; ++s)
+      if (s < q.nsteps) issue(s, s);
+    int buf = NBUF - 1;
+    if (NBUF - 2 < q.nsteps)
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kAhead) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    for (int s = 0; s < q.nsteps; ++s) {
+      __builtin_amdgcn_s_barrier();  // step s is there; everyone is done with step s - 1
+      if (s + NBUF - 1 < q.nsteps) {
+        issue(s + NBUF - 1, buf);
+        buf = buf + 1 == NBUF ? 0 : buf + 1;
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kAhead) : "memory");  // step s + 1 has landed
+      } else {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
+    }
+    return;
+  }
+
+  // ===================================================================== compute waves
+  const int wm = wave / GN, wn = wave - wm * GN;
+  f32x4_t acc[MI][NI];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const unsigned char* la = lds + ((g * RA + wm * MI * 2 + (jn >> 3)) * 128 + (jn & 7) * 16);
+  const unsigned char* lb = lds + (RA * 1024 + (g * RB + wn * NI * 2 + (jn >> 3)) * 128 + (jn & 7) * 16);
+  int off = 0;
+  for (int s = 0; s < q.nsteps; ++s) {
+    __builtin_amdgcn_s_barrier();  // step s has landed
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      u32x4_t a[MI], b[NI];
+#pragma unroll
+      for (int i = 0; i < MI; ++i) a[i] = *(const u32x4_t*)(la + off + kk * 4 * RA * 128 + i * 256);
+#pragma unroll
+      for (int j = 0; j < NI; ++j) b[j] = *(const u32x4_t*)(lb + off + kk * 4 * RB * 128 + j * 256);
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) acc[i][j] = mfma_bf16_16x16x32(b[j], a[i], acc[i][j]);
+    }
+    off = off + kBuf == NBUF * kBuf ? 0 : off + kBuf;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (no read of the step may still be out at the next barrier)
+  }
+
+  // ---- results: the lane has C[row jn][columns 4 g .. 4 g + 3] of each 16 x 16 tile
+  const int64_t ncol = (int64_t)q.rb * 8;
+  auto put = [&](int r0, int c0, f32x4_t v) {
+    if (r0 + (jn >> 3) < q.ra && c0 + (g >> 1) < q.rb)
+      __builtin_memcpy(q.C + (int64_t)(r0 * 8 + jn) * ncol + c0 * 8 + 4 * g, &v, 16);
+  };
+  const int ar0 = ti * RA + wm * MI * 2, bc0 = tj * RB + wn * NI * 2;  // the wave's first block rows
+  uint32_t redo = 0;
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      const f32x4_t v = acc[i][j];
+      // (x - x is not zero for an infinity or NaN)
+      const bool bad = !(v.x - v.x == 0.f) || !(v.y - v.y == 0.f) || !(v.z - v.z == 0.f) || !(v.w - v.w == 0.f);
+      if (__ballot(bad))
+        redo |= 1u << (i * NI + j);
+      else
+        put(ar0 + 2 * i, bc0 + 2 * j, v);
+    }
+  while (redo) {
+    const int t = __ffs((int)redo) - 1;
+    redo &= redo - 1;
+    const int r0 = ar0 + 2 * (t / NI), c0 = bc0 + 2 * (t % NI);
+    put(r0, c0, redo_tile(q, r0, c0, lane));
+  }
+}
+
 constexpr int kU = 2;  // MFMA steps whose fragments are asked for together
 
 template <int U>
@@ -314,6 +567,30 @@ int launch_u(const SpParams& q, unsigned grid, hipStream_t st) {
     raised = true;
   }
   hipLaunchKernelGGL((spgemm_nt_bf16<U>), dim3(grid), dim3(512), kLdsBytes, st, q);
+  return hipGetLastError() == hipSuccess ? BSP_OK : BSP_ERR_HIP;
+}
+
+template <int MI, int NI, int GM, int GN, int MV, int NBUF>
+int launch_dense(DnParams q, hipStream_t st) {
+  constexpr int RA = GM * MI * 2, RB = GN * NI * 2;
+  const int64_t ldsb = (int64_t)NBUF * (RA + RB) * 1024 + (int64_t)q.nsteps * (RA + RB) * 4;
+  if (ldsb > 160 * 1024) return BSP_ERR_UNSUPPORTED;
+  q.tiles_i = (q.ra + RA - 1) / RA;
+  q.tiles_j = (q.rb + RB - 1) / RB;
+  const int64_t total = (int64_t)q.tiles_i * q.tiles_j;
+  if (total > 1 << 28) return BSP_ERR_UNSUPPORTED;
+  q.total = (int32_t)total;
+  q.per_xcd = (q.total + 7) / 8;
+  q.band = std::min(q.tiles_i, 8);
+  static bool raised = false;  // dynamic LDS above 64 KB has to be allowed once per kernel
+  if (!raised) {
+    if (hipFuncSetAttribute((const void*)spgemm_dense_bf16<MI, NI, GM, GN, MV, NBUF>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+      return BSP_ERR_HIP;
+    raised = true;
+  }
+  hipLaunchKernelGGL((spgemm_dense_bf16<MI, NI, GM, GN, MV, NBUF>), dim3((unsigned)(q.per_xcd * 8)),
+                     dim3((GM * GN + MV) * 64), (size_t)ldsb, st, q);
   return hipGetLastError() == hipSuccess ? BSP_OK : BSP_ERR_HIP;
 }
 
@@ -358,6 +635,37 @@ extern "C" int bsp_spgemm_nt(const bsp_bcsr* A, const bsp_bcsr* B, float* C, voi
   const int64_t nsb = (int64_t)((q.tiles_i + 7) / 8) * q.sbj;
   if (nsb * 64 > 0x7FFFFFFF) return BSP_ERR_SHAPE;
   q.nsb = (int32_t)nsb;
+  DnParams d{q.sa, q.sb, q.ca, q.cb, q.pa, q.pb, C, q.ra, q.rb, q.nsub, (A->cols + 7) / 8, q.nnzb_a, q.nnzb_b, 0, 0, 0, 0, 0};
+  // Which kernel and tile: the fastest by a model in us, rounds of workgroups times (fixed part +
+  // time per eight block columns), from timings at 512 to 4096 and ragged sizes.  For the kernel that
+  // selects columns the time grows with the share of columns that both sides of a tile keep.
+  {
+    const double n = d.nsteps;
+    auto rounds = [&](int ra, int rb, int slots) {
+      const double t = (double)((d.ra + ra - 1) / ra) * ((d.rb + rb - 1) / rb);
+      return std::ceil(t / slots);
+    };
+    const double da = (double)A->nnzb / ((double)A->rows * A->cols), db = (double)B->nnzb / ((double)B->rows * B->cols);
+    const double both = (1 - (1 - da) * (1 - da)) * (1 - (1 - db) * (1 - db));
+    const double sparse = rounds(16, 16, 512) * (2 + n * (0.6 + 3.6 * both));
+    const double t256 = rounds(32, 32, 256) * (6 + n * 1.8);
+    const double t128w = rounds(16, 32, 256) * (5 + n * 0.98);
+    const double t128 = rounds(16, 16, 256) * (4 + n * 0.62);
+    const double t64 = rounds(8, 8, 256) <= 1 ? 3.5 + n * 0.38 : rounds(8, 8, 512) * (3 + n * 0.48);
+    const double best = std::min({sparse, t256, t128w, t128, t64});
+    hipStream_t st = (hipStream_t)stream;
+    int rc = BSP_ERR_UNSUPPORTED;
+    if (best == t64)
+      rc = launch_dense<2, 2, 2, 2, 4, 4>(d, st);
+    else if (best == t128)
+      rc = launch_dense<2, 4, 4, 2, 8, 3>(d, st);
+    else if (best == t128w)
+      rc = launch_dense<4, 4, 2, 4, 6, 3>(d, st);
+    else if (best == t256)
+      rc = launch_dense<8, 4, 2, 4, 4, 2>(d, st);
+    if (best != sparse && rc == BSP_ERR_UNSUPPORTED) rc = launch_dense<2, 2, 2, 2, 4, 4>(d, st);  // (the smallest table)
+    if (rc != BSP_ERR_UNSUPPORTED) return rc;
+  }
 #ifdef BSP_ROWS_TUNE
   q.trace = nullptr;
   if (const char* e = std::getenv("BSP_PW_TRACE_PTR")) q.trace = (long long*)std::strtoull(e, nullptr, 16);

@@ -68,3 +68,41 @@ def test_spgemm_ignores_masked_contents_and_writes_every_element():
     C1 = bsp.BspMatrix(A2, gamma).matmul_nt(bsp.BspMatrix(B, omega), out=out)
     torch.cuda.synchronize()
     assert torch.equal(C0, C1) and not torch.isnan(C1).any()
+
+
+def _pair_union_product(A, gamma, B, omega):
+    """C where a 16 x 16 tile multiplies the block columns that one of its two rows of A and one of
+    its two rows of B keep: absent blocks are zeros there, other columns take no part."""
+    Ra, N = gamma.shape
+    Rb = omega.shape[0]
+    Am = np.where(np.kron(gamma, np.ones((8, 8))) > 0, A, 0.0).astype(np.float64)
+    Bm = np.where(np.kron(omega, np.ones((8, 8))) > 0, B, 0.0).astype(np.float64)
+    C = np.zeros((Ra * 8, Rb * 8))
+    with np.errstate(invalid="ignore"):
+        for i in range(0, Ra, 2):
+            for j in range(0, Rb, 2):
+                cols = np.flatnonzero(gamma[i:i + 2].any(0) & omega[j:j + 2].any(0))
+                k = (cols[:, None] * 8 + np.arange(8)).ravel()
+                C[i * 8:i * 8 + 16, j * 8:j * 8 + 16] = Am[i * 8:i * 8 + 16][:, k] @ Bm[j * 8:j * 8 + 16][:, k].T
+    return C
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Ra,Rb,N", [(1, 1, 1), (9, 8, 9), (64, 65, 20), (130, 150, 33), (300, 300, 17), (512, 520, 24)])
+def test_spgemm_tiles_and_infinities(Ra, Rb, N):
+    """The sizes at which the tiles of the staged product change and end; infinities and NaNs reach
+    the elements they are multiplied for and no others."""
+    import torch
+    A, gamma, B, omega = _draw(Ra, Rb, N, Ra + N, 0.5, 0.5)
+    for bad in (False, True):
+        if bad:
+            rng = np.random.default_rng(N)
+            for M, v in ((A, np.inf), (B, -np.inf), (A, np.nan)):
+                M[rng.integers(M.shape[0]), rng.integers(M.shape[1])] = v
+        out = torch.full((Ra * 8, Rb * 8), float("nan"), device="cuda")
+        got = bsp.BspMatrix(A, gamma).matmul_nt(bsp.BspMatrix(B, omega), out=out).cpu().numpy().astype(np.float64)
+        want = _pair_union_product(A, gamma, B, omega)
+        ok = np.isfinite(want)
+        assert (np.isnan(got) == np.isnan(want)).all() and (got[~ok & ~np.isnan(want)] == want[~ok & ~np.isnan(want)]).all()
+        scale = np.maximum(np.abs(want[ok]), np.sqrt(np.mean(want[ok] ** 2)) + 1e-30)
+        assert (np.abs(got[ok] - want[ok]) <= 1e-5 * scale + 1e-30).all()
