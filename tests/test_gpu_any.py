@@ -96,3 +96,14 @@ def test_infinities_in_dropped_channels_stay_out():
         c.X[..., (I - 1) // 8 * 8:] = np.nan
         y = to_host(make_layer(c).conv2d(to_device(c), c.stride, c.pad))
         assert_close(y, oracle.conv2d(X, c.W, c.bias, c.gamma, 8, 8, c.stride, c.pad), "bf16", f"{I} channels")
+
+
+def test_calls_go_to_the_current_stream():
+    import torch
+    from paper_2407_09453_amd.binding import _current_stream
+    t = torch.zeros(8, device="cuda")
+    for s in (torch.cuda.current_stream(), torch.cuda.Stream()):
+        with torch.cuda.stream(s):
+            assert _current_stream(t) == torch.cuda.current_stream().cuda_stream == s.cuda_stream
+    with pytest.raises(ValueError):
+        _current_stream(torch.zeros(8))
