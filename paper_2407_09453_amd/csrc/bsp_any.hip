@@ -331,23 +331,14 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
     unsigned char* ot = lds + (pg * PT * 16 + jn) * opitch;
 #pragma unroll
     for (int t = 0; t < PT; ++t, ot += 16 * opitch) {
-      const f32x4_t v = add4<KIND>(acc[t], bv);
+      const f32x4_t v = add4<KIND>(acc[t], bv);  // (int32 results)
       const int c = si * BSP_STRIP + 4 * g;
       if constexpr (KIND == kBf16) {
         *(u32x2_t*)(ot + c * 2) = u32x2_t{pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)};
       } else if (a.y32) {
         *(f32x4_t*)(ot + c * 4) = v;
       } else {
-        const i32x4_t s = __builtin_bit_cast(i32x4_t, v);
-        const long long half = a.shift > 0 ? 1ll << (a.shift - 1) : 0;
-        uint32_t packed = 0;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const long long w = ((long long)s[r] + half) >> a.shift;  // 64 bits: adding the half cannot wrap
-          const int b = w < -128 ? -128 : (w > 127 ? 127 : (int)w);
-          packed |= (uint32_t)(b & 0xFF) << (8 * r);
-        }
-        *(uint32_t*)(ot + c) = packed;
+        *(uint32_t*)(ot + c) = rescale_i8x4(__builtin_bit_cast(i32x4_t, acc[t]), __builtin_bit_cast(i32x4_t, bv), a.shift);
       }
     }
   }

@@ -100,10 +100,11 @@ int dispatch(const bsp_weights* w, const ConvParams& p, void* stream, const Fixe
     const bool chunked = bsp_tile_supported(p, w->dtype);  // whole 8-channel chunks
     hipStream_t st = (hipStream_t)stream;
     int rc = BSP_ERR_UNSUPPORTED;
-    // 17..64 pixels and short rows: staged once and split over strips and contraction (7x7x2048->512
-    // 9.0 -> 6.5 us, FC 64 x 2048 -> 1000 10.0 -> 6.7, 32 x 256 -> 256 4.8 -> 4.5; the streaming
-    // kernels stay ahead at 16 pixels, 5.6 against 6.5, and where weights are the bulk)
-    const bool few = p.P > 16 && p.P <= 64 && p.I <= 2048;
+    // up to 64 pixels and short rows: staged once and split over strips and contraction (7x7x2048->512
+    // 9.0 -> 6.5 us, FC 64 x 2048 -> 1000 10.1 -> 6.8; from 17 pixels with 4x16 blocks, 7.7 -> 6.7; from
+    // 24 to 32 with 8x8 blocks, whose streaming kernel takes 6.0 against 6.5 at 17 and 7.2 against 6.5
+    // at 32; where the weights are the bulk the streaming kernels stay ahead)
+    const bool few = p.P > (w->bo == 8 ? 28 : 16) && p.P <= 64 && p.I <= 2048;
     if (!w->kernels && chunked && (few || bsp_any_preferred(p, w->plan_host, w->dtype)))
       rc = bsp_launch_any(p, w->plan_host, st);
     if (rc != BSP_ERR_UNSUPPORTED) return rc;
@@ -289,6 +290,10 @@ int bsp_conv2d_i8(const bsp_weights* w, const int8_t* X, const int32_t* bias, vo
   if (y_dtype != BSP_I8 && y_dtype != BSP_I32) return BSP_ERR_DTYPE;
   if (y_dtype == BSP_I8 && (shift < 0 || shift > 31)) return BSP_ERR_SHAPE;
   if (p.P == 0) return BSP_OK;
+  if (y_dtype == BSP_I8 && (!w->kernels || (w->kernels & BSP_KERNEL_PW)) && aligned16(X)) {
+    const int rc = bsp_launch_pw_i8(p, w->plan_host, shift, (hipStream_t)stream);
+    if (rc != BSP_ERR_UNSUPPORTED) return rc;
+  }
   if (y_dtype == BSP_I8 && (w->kernels ? w->kernels & BSP_KERNEL_LDS : !bsp_any_preferred(p, w->plan_host, BSP_I8)) &&
       aligned16(X)) {
     const int rc = bsp_launch_lds_i8(p, w->plan_host, shift, (hipStream_t)stream);

@@ -12,7 +12,7 @@
 
 bool bsp_rows_wanted(int32_t O, int32_t H, int32_t K, int32_t I, int32_t bo, int32_t bi,
                      int32_t dtype);
-int bsp_rows_section(const int32_t* row_ptr, const int32_t* col_idx, const uint16_t* payload,
+int bsp_rows_section(const int32_t* row_ptr, const int32_t* col_idx, const void* payload, int32_t dtype,
                      int32_t O, int32_t H, int32_t K, int32_t I, int32_t bo, int32_t bi,
                      std::vector<int32_t>* sec);
 bool bsp_first_wanted(int32_t O, int32_t H, int32_t K, int32_t I, int32_t bo, int32_t bi, int32_t dtype);
@@ -470,7 +470,7 @@ static int plan_walk(const int32_t* row_ptr, const int32_t* col_idx, const void*
   const int64_t off_rows = (off_wfrag + nsteps * 64 * 4 + 3) & ~int64_t(3);
   std::vector<int32_t> rows;
   if (bsp_rows_wanted(O, H, K, I, bo, bi, dtype))
-    if (int rc = bsp_rows_section(row_ptr, col_idx, out ? (const uint16_t*)payload : nullptr, O, H,
+    if (int rc = bsp_rows_section(row_ptr, col_idx, out ? payload : nullptr, dtype, O, H,
                                   K, I, bo, bi, &rows))
       return rc;
   const int64_t off_first = (off_rows + (int64_t)rows.size() + 3) & ~int64_t(3);

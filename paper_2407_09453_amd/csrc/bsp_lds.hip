@@ -504,13 +504,7 @@ __global__ __launch_bounds__(kThreads, 1) void conv_lds(ConvParams p, TileCfg t,
       for (int nt = 0; nt < NT; ++nt) {
         if constexpr (I8) {
           // exact sum + 32-bit bias, rounding right shift (ties upward), saturation to int8
-          uint32_t packed = 0;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const long long sft = ((long long)acc[nt][r] + bv[r] + (c.shift > 0 ? 1ll << (c.shift - 1) : 0)) >> c.shift;
-            const int q = sft < -128 ? -128 : (sft > 127 ? 127 : (int)sft);
-            packed |= (uint32_t)(q & 0xFF) << (8 * r);
-          }
+          const uint32_t packed = rescale_i8x4(acc[nt], i32x4_t{bv[0], bv[1], bv[2], bv[3]}, c.shift);
           *(uint32_t*)(lds + orow + nt * 16 * OUT_ROW) = packed;
         } else {
           u32x2_t v;

@@ -78,7 +78,8 @@ enum {
   BSP_PLAN_OFF_FIRST_W = 25,  // first word of the thin-input section, 0 when there is none
 };
 
-// Row-band section (bf16 layers with whole 8-channel groups; read by bsp_rows.hip).
+// Row-band section (bf16 layers with whole 8-channel groups; read by bsp_rows.hip and bsp_pw.hip;
+// and pointwise int8 layers with whole 16-channel groups, read by bsp_pw.hip).
 //
 // Strips here are groups of block rows chosen by the builder so that rows sharing many kept
 // columns sit together (a 16-row matrix-core tile multiplies one activation operand with all
@@ -88,7 +89,9 @@ enum {
 // a list of items (unit, dx): a unit is a group of `cw` input channels (8, or 4 for 16x4
 // blocks, where every kept block is then exactly one unit and nothing is zero-filled), dx a
 // column of the kernel window; all H rows of the window belong to the item, which is what
-// lets the kernel reuse one activation fragment for H output rows.  `32 / cw` consecutive
+// lets the kernel reuse one activation fragment for H output rows.  int8: cw is 16, so a unit may
+// span four, two or one blocks, and a lane's 16 bytes of weights are sixteen codes; the layout is
+// the same with 64 / cw items per step.  `32 / cw` consecutive
 // items form a column step (one MFMA's K extent per window row).  Input channels are cut
 // into slabs of `slab` channels; a column step never crosses a slab.
 //   [0..23]                     header, see enum

@@ -1,4 +1,5 @@
-// Pointwise (1x1) bf16 layers as a block-sparse matrix product, fp32 accumulation:
+// Pointwise (1x1) layers as a block-sparse matrix product, bf16 with fp32 accumulation or int8 codes
+// with exact 32-bit sums:
 // Y[pixel][o] = bias[o] + sum over the kept blocks of row o of W[o][i] * X[pixel][i]
 // (paper Eq. (5) with H = K = 1; only kept blocks are multiplied, Section I advantages 3-4).
 //
@@ -14,6 +15,10 @@
 // from the accumulators; two lane tiles exchange halves across lane rows first so that every
 // lane stores the 16 contiguous bytes of one 8-channel block row.
 //
+// int8: a 16-byte piece is sixteen codes and a step's product is the i32 16x16x64 one, so staging,
+// weights and steps are byte for byte the same; the launcher counts input channels in pairs of codes.
+// A lane's four results are four bytes, so they always leave through the LDS image of the output.
+//
 // Staged pixels past the layer's last pixel are never written to LDS and never stored: each
 // MFMA column depends on its own pixel only.
 #include "bsp_launch.h"
@@ -22,8 +27,11 @@
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
+#include <type_traits>
 
 namespace {
+
+typedef __attribute__((ext_vector_type(4))) int i32x4_t;
 
 struct PwArgs {
   const unsigned char* X;
@@ -34,7 +42,8 @@ struct PwArgs {
   const int32_t* rslab;
   const unsigned char* rdesc;
   const unsigned char* rfrag;
-  int32_t relu, nstrips;
+  int32_t relu, nstrips;           // relu: int8 layers keep their rounding right shift here (a word more in this
+                                   // block moves the others over line borders: 0.08 us per launch)
   int32_t P, I, O;
   int32_t S, L, J, N, MN;          // S > 1: output pixel (img, y, x) reads input pixel (img, y*S, x*S)
   int32_t pitch, swz_shift, swz_mask;
@@ -61,8 +70,10 @@ struct PwArgs {
 typedef __attribute__((address_space(1))) const void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
-template <int PT, bool CW4, int D, int MAXT>
+// KIND: 8 or 4, the channels per unit of a bf16 layer; 16, an int8 layer.
+template <int PT, int KIND, int D, int MAXT>
 __global__ __launch_bounds__(MAXT) void conv_pw(PwArgs a) {
+  constexpr bool CW4 = KIND == 4, I8 = KIND == 16;
   kernarg_touch<PwArgs>();
   extern __shared__ __align__(16) unsigned char lds[];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
@@ -154,12 +165,15 @@ __global__ __launch_bounds__(MAXT) void conv_pw(PwArgs a) {
     wr[d] = u32x4_t{0, 0, 0, 0};
     if (d < nsteps) fetch(d);
   }
-  f32x4_t bv = {0.f, 0.f, 0.f, 0.f};
-  if (a.bias && chan >= 0) bv = f32x4_t{a.bias[chan], a.bias[chan + 1], a.bias[chan + 2], a.bias[chan + 3]};
+  using acc_t = typename std::conditional<I8, i32x4_t, f32x4_t>::type;
+  using bias_t = typename std::conditional<I8, int32_t, float>::type;
+  acc_t bv = {0, 0, 0, 0};
+  const bias_t* bp = (const bias_t*)a.bias;
+  if (bp && chan >= 0) bv = acc_t{bp[chan], bp[chan + 1], bp[chan + 2], bp[chan + 3]};
 
-  f32x4_t acc[PT];
+  acc_t acc[PT];
 #pragma unroll
-  for (int t = 0; t < PT; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < PT; ++t) acc[t] = acc_t{0, 0, 0, 0};
 
   PW_MARK(3);
   __builtin_amdgcn_s_waitcnt(0);  // this wave's requests have landed
@@ -197,7 +211,13 @@ __global__ __launch_bounds__(MAXT) void conv_pw(PwArgs a) {
   };
   auto mfmas = [&](int d, const u32x4_t (&f)[PT]) {
 #pragma unroll
-    for (int t = 0; t < PT; ++t) acc[t] = mfma_bf16_16x16x32(wr[d], f[t], acc[t]);
+    for (int t = 0; t < PT; ++t) {
+      if constexpr (I8)
+        acc[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4_t, wr[d]), __builtin_bit_cast(i32x4_t, f[t]),
+                                                       acc[t], 0, 0, 0);
+      else
+        acc[t] = mfma_bf16_16x16x32(wr[d], f[t], acc[t]);
+    }
   };
 
   // A step's fragments are read from LDS while the step before it is in the matrix cores.
@@ -231,12 +251,34 @@ __global__ __launch_bounds__(MAXT) void conv_pw(PwArgs a) {
   }
 
   // ---- results: bias, one rounding, then the optional residual add and ReLU
+  if constexpr (!I8) {
 #pragma unroll
-  for (int t = 0; t < PT; ++t) acc[t] += bv;
+    for (int t = 0; t < PT; ++t) acc[t] += bv;
+  }
 #ifdef BSP_ROWS_TUNE
   asm volatile("" ::"v"(acc[0]));
 #endif
   PW_MARK(6);
+  if constexpr (I8) {
+    // + bias, rounding right shift (ties upward), saturation, into the image of the output lines
+    unsigned char* ot = lds + a.out_off;
+    const int range0 = ns * a.NS * 16, lpix = pg * (PT * 16) + c;
+#pragma unroll
+    for (int t = 0; t < PT; ++t) {
+      const uint32_t v = rescale_i8x4(acc[t], bv, a.relu);
+      if (chan >= 0) *(uint32_t*)(ot + (lpix + t * 16) * a.opitch + (chan - range0)) = v;
+    }
+    __syncthreads();
+    const int cpp = a.NS, total = a.MT * cpp;  // 16-byte pieces per pixel, of the tile
+    for (int i = tid; i < total; i += (int)blockDim.x) {
+      const int pixel = (int)fdiv((uint32_t)i, a.d_cpp), k = i - pixel * cpp;
+      const int ch = range0 + k * 16, gp = pix0 + pixel;
+      if (gp < a.P && ch < a.O)
+        __builtin_nontemporal_store(*(const u32x4_t*)(ot + pixel * a.opitch + k * 16),
+                                    (u32x4_t*)(a.Y + ((uint32_t)gp * (uint32_t)a.O + (uint32_t)ch)));
+    }
+    return;
+  }
   const int ptile0 = pix0 + pg * (PT * 16);
   // lane rows 0/1 (and 2/3) hold the two halves of one 8-channel block row: after an exchange
   // an even row has all eight channels of lane tile t, an odd row those of lane tile t + 1
@@ -353,42 +395,42 @@ __global__ __launch_bounds__(MAXT) void conv_pw(PwArgs a) {
 
 constexpr int kLdsLimit = 160 * 1024;
 
-template <int PT, bool CW4, int D, int MAXT>
+template <int PT, int KIND, int D, int MAXT>
 int launch_inst(const PwArgs& a, dim3 grid, int threads, size_t ldsb, hipStream_t st) {
   static bool raised = false;  // dynamic LDS above 64 KB has to be allowed once per kernel
   if (!raised) {
-    if (hipFuncSetAttribute((const void*)conv_pw<PT, CW4, D, MAXT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    if (hipFuncSetAttribute((const void*)conv_pw<PT, KIND, D, MAXT>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             kLdsLimit) != hipSuccess)
       return BSP_ERR_HIP;
     raised = true;
   }
-  hipLaunchKernelGGL((conv_pw<PT, CW4, D, MAXT>), grid, dim3(threads), ldsb, st, a);
+  hipLaunchKernelGGL((conv_pw<PT, KIND, D, MAXT>), grid, dim3(threads), ldsb, st, a);
   return hipGetLastError() == hipSuccess ? BSP_OK : BSP_ERR_HIP;
 }
 
 // Ring depth D: strips of at most 2 (4) steps take instances with as many registers for
 // weights, which leaves room for more waves per SIMD; deep asks for 16 (workgroups of at most
 // 512 threads, which may then use 256 registers per lane); otherwise 8.
-template <bool CW4, int D, int MAXT>
+template <int KIND, int D, int MAXT>
 int launch_d(const PwArgs& a, int PT, dim3 grid, int threads, size_t ldsb, hipStream_t st) {
   if (threads > MAXT) return BSP_ERR_UNSUPPORTED;
   switch (PT) {
-    case 1: return launch_inst<1, CW4, D, MAXT>(a, grid, threads, ldsb, st);
-    case 2: return launch_inst<2, CW4, D, MAXT>(a, grid, threads, ldsb, st);
-    case 4: return launch_inst<4, CW4, D, MAXT>(a, grid, threads, ldsb, st);
-    case 8: return launch_inst<8, CW4, D, (D >= 8 ? 512 : MAXT)>(a, grid, threads, ldsb, st);  // 8 lane tiles and a ring of 8 need more than 128 registers
+    case 1: return launch_inst<1, KIND, D, MAXT>(a, grid, threads, ldsb, st);
+    case 2: return launch_inst<2, KIND, D, MAXT>(a, grid, threads, ldsb, st);
+    case 4: return launch_inst<4, KIND, D, MAXT>(a, grid, threads, ldsb, st);
+    case 8: return launch_inst<8, KIND, D, (D >= 8 ? 512 : MAXT)>(a, grid, threads, ldsb, st);  // 8 lane tiles and a ring of 8 need more than 128 registers
   }
   return BSP_ERR_UNSUPPORTED;
 }
 
-template <bool CW4>
+template <int KIND>
 int launch_pt(const PwArgs& a, int PT, int depth, dim3 grid, int threads, size_t ldsb, hipStream_t st) {
   if (PT == 8 && depth >= 8 && threads > 512) return BSP_ERR_UNSUPPORTED;
   switch (depth) {
-    case 2: return launch_d<CW4, 2, 1024>(a, PT, grid, threads, ldsb, st);
-    case 4: return launch_d<CW4, 4, 1024>(a, PT, grid, threads, ldsb, st);
-    case 8: return launch_d<CW4, 8, 1024>(a, PT, grid, threads, ldsb, st);
-    case 16: return launch_d<CW4, 16, 512>(a, PT, grid, threads, ldsb, st);
+    case 2: return launch_d<KIND, 2, 1024>(a, PT, grid, threads, ldsb, st);
+    case 4: return launch_d<KIND, 4, 1024>(a, PT, grid, threads, ldsb, st);
+    case 8: return launch_d<KIND, 8, 1024>(a, PT, grid, threads, ldsb, st);
+    case 16: return launch_d<KIND, 16, 512>(a, PT, grid, threads, ldsb, st);
   }
   return BSP_ERR_UNSUPPORTED;
 }
@@ -436,8 +478,11 @@ PwChoice pw_choose(int P, int I, int O, int nstrips, int pitch, bool windowed) {
 
 }  // namespace
 
-int bsp_launch_pw(const ConvParams& p, int dtype, const void* plan_host, hipStream_t st) {
-  if (dtype != BSP_BF16 || !plan_host) return BSP_ERR_UNSUPPORTED;
+namespace {
+
+int launch_pw(const ConvParams& p, int dtype, const void* plan_host, int shift, hipStream_t st) {
+  const bool i8 = dtype == BSP_I8;
+  if (!plan_host) return BSP_ERR_UNSUPPORTED;
   const int32_t* hdr = (const int32_t*)plan_host;
   if (hdr[BSP_PLAN_MAGIC_W] != BSP_PLAN_MAGIC || hdr[BSP_PLAN_VERSION_W] != BSP_PLAN_VERSION ||
       hdr[BSP_PLAN_O_W] != p.O || hdr[BSP_PLAN_I_W] != p.I || hdr[BSP_PLAN_H_W] != p.H ||
@@ -449,14 +494,14 @@ int bsp_launch_pw(const ConvParams& p, int dtype, const void* plan_host, hipStre
   if ((int64_t)p.B * p.L * p.J * p.I * 2 >= (1ll << 31) || (int64_t)p.P * p.O * 2 >= (1ll << 31))
     return BSP_ERR_UNSUPPORTED;
   const int nstrips = rs[BSP_ROWS_NSTRIPS_W];
-  const int raw = p.I * 2;
+  const int raw = p.I * (i8 ? 1 : 2);
   const int pitch = raw <= 128 ? 128 : (raw + 255) & ~255;
 #ifdef BSP_ROWS_TUNE
   long long* a_trace = nullptr;
 #endif
   const int maxsteps = rs[BSP_ROWS_MAXSTRIPSTEPS_W];
   const int depth0 = maxsteps <= 2 ? 2 : maxsteps <= 4 ? 4 : 8;
-  PwChoice ch = pw_choose(p.P, p.I, p.O, nstrips, pitch, rs[BSP_ROWS_WINDOW_W] == 4);
+  PwChoice ch = pw_choose(p.P, raw / 2, i8 ? (1 << 30) : p.O, nstrips, pitch, rs[BSP_ROWS_WINDOW_W] == 4);
 #ifdef BSP_ROWS_TUNE  // experiments only: never defined in the product build
   if (const char* e = std::getenv("BSP_PWK_TUNE")) {
     int q[5] = {0, 0, 0, 0, 0};
@@ -480,14 +525,14 @@ int bsp_launch_pw(const ConvParams& p, int dtype, const void* plan_host, hipStre
   a.Y = (unsigned char*)p.Y;
   a.bias = p.bias;
   a.residual = (const unsigned char*)p.residual;
-  a.relu = p.relu;
+  a.relu = i8 ? shift : p.relu;
   a.rstrip = sec + rs[BSP_ROWS_OFF_STRIP_W];
   a.rslab = sec + rs[BSP_ROWS_OFF_SLAB_W];
   a.rdesc = (const unsigned char*)(sec + rs[BSP_ROWS_OFF_DESC_W]);
   a.rfrag = (const unsigned char*)(sec + rs[BSP_ROWS_OFF_FRAG_W]);
   a.nstrips = nstrips;
   a.P = p.P;
-  a.I = p.I;
+  a.I = raw / 2;  // int8: pairs of codes
   a.O = p.O;
   a.S = p.sh;
   a.L = p.L;
@@ -512,11 +557,12 @@ int bsp_launch_pw(const ConvParams& p, int dtype, const void* plan_host, hipStre
   // workgroup takes whole windows (or every strip there is)
   a.win_out = ch.wout && rs[BSP_ROWS_WINDOW_W] == 4 && (ch.NS % 4 == 0 || ch.NS >= nstrips);
   a.out_off = (int32_t)xbytes;
-  a.opitch = ch.NS * 32 + 16;
+  a.opitch = ch.NS * (i8 ? 16 : 32) + 16;
+  if (i8 && !a.win_out) return BSP_ERR_UNSUPPORTED;
   const int64_t ldsb = xbytes + (a.win_out ? (int64_t)a.MT * a.opitch : 0);
   if (ldsb > kLdsLimit || ch.PG * ch.NS > 16 || ch.PG * ch.NS < 1) return BSP_ERR_UNSUPPORTED;
   a.nreq = (int32_t)(xbytes / 1024);
-  a.d_cpp = make_fastdiv((uint32_t)(ch.NS * 2));
+  a.d_cpp = make_fastdiv((uint32_t)(ch.NS * (i8 ? 1 : 2)));
   a.mtiles = cdiv(p.P, a.MT);
   a.nsplit = cdiv(nstrips, ch.NS);
   const int64_t wgs = (int64_t)a.mtiles * a.nsplit;
@@ -536,6 +582,20 @@ int bsp_launch_pw(const ConvParams& p, int dtype, const void* plan_host, hipStre
   a.adv_rem = (threads * 16) % pitch;
   dim3 grid((unsigned)(a.per_xcd * 8));
   const int depth = ch.deep ? ch.deep : depth0;
-  return rs[BSP_ROWS_CW_W] == 4 ? launch_pt<true>(a, ch.PT, depth, grid, threads, (size_t)ldsb, st)
-                                 : launch_pt<false>(a, ch.PT, depth, grid, threads, (size_t)ldsb, st);
+  switch (rs[BSP_ROWS_CW_W]) {
+    case 4: return launch_pt<4>(a, ch.PT, depth, grid, threads, (size_t)ldsb, st);
+    case 8: return launch_pt<8>(a, ch.PT, depth, grid, threads, (size_t)ldsb, st);
+    case 16: return launch_pt<16>(a, ch.PT, depth, grid, threads, (size_t)ldsb, st);
+  }
+  return BSP_ERR_UNSUPPORTED;
+}
+
+}  // namespace
+
+int bsp_launch_pw(const ConvParams& p, int dtype, const void* plan_host, hipStream_t st) {
+  return dtype == BSP_BF16 ? launch_pw(p, dtype, plan_host, 0, st) : BSP_ERR_UNSUPPORTED;
+}
+
+int bsp_launch_pw_i8(const ConvParams& p, const void* plan_host, int shift, hipStream_t st) {
+  return p.residual || p.relu ? BSP_ERR_UNSUPPORTED : launch_pw(p, BSP_I8, plan_host, shift, st);
 }

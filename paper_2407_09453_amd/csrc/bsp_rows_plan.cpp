@@ -110,12 +110,28 @@ std::vector<std::vector<int>> group_rows(const Bits& bits, int nbr, int rps, int
   return groups;
 }
 
+// `rows` pieces of 4, 8 or 16 bytes, `pitch` bytes apart, to every sixteenth byte of dst.
+template <int N>
+inline void copy_rows_n(unsigned char* dst, const unsigned char* src, int rows, int64_t pitch) {
+  for (int r = 0; r < rows; ++r) std::memcpy(dst + r * 16, src + r * pitch, N);
+}
+inline void copy_rows(unsigned char* dst, const unsigned char* src, int rows, int64_t pitch, int bytes) {
+  if (bytes == 16)
+    copy_rows_n<16>(dst, src, rows, pitch);
+  else if (bytes == 8)
+    copy_rows_n<8>(dst, src, rows, pitch);
+  else
+    copy_rows_n<4>(dst, src, rows, pitch);
+}
+
 }  // namespace
 
 bool bsp_rows_wanted(int32_t O, int32_t H, int32_t K, int32_t I, int32_t bo, int32_t bi,
                      int32_t dtype) {
   (void)bo;
   (void)bi;
+  // int8: pointwise layers whose pixels are whole 16-code pieces
+  if (dtype == BSP_I8) return H == 1 && K == 1 && I % 16 == 0 && O % 16 == 0 && (int64_t)O * I <= (int64_t)48 << 20;
   if (dtype != BSP_BF16) return false;
   if ((I % 8) != 0 || (O % 8) != 0) return false;
   if (H > BSP_ROWS_MAXH || K > 15) return false;
@@ -124,15 +140,19 @@ bool bsp_rows_wanted(int32_t O, int32_t H, int32_t K, int32_t I, int32_t bo, int
   return true;
 }
 
-// Fills `sec` (words) with the section; with payload == nullptr the weights are left zero
+// Fills `sec` (words) with the section for bf16 or int8 payloads; with payload == nullptr the weights are left zero
 // (the size is the same).  `base_words` is the section's offset in the plan, a multiple of 4.
-int bsp_rows_section(const int32_t* row_ptr, const int32_t* col_idx, const uint16_t* payload,
+int bsp_rows_section(const int32_t* row_ptr, const int32_t* col_idx, const void* payload_v, int32_t dtype,
                      int32_t O, int32_t H, int32_t K, int32_t I, int32_t bo, int32_t bi,
                      std::vector<int32_t>* sec) {
   const int nbr = (int)cdiv(O, bo);
   const int rps = BSP_STRIP / bo;              // block rows per strip: 2, 4, 1
-  const int cw = bi == 4 ? 4 : 8;              // channels per contraction item
-  const int ips = 32 / cw;                     // items per column step: 4 or 8
+  const bool i8 = dtype == BSP_I8;
+  const int es = i8 ? 1 : 2;                   // bytes per weight
+  const unsigned char* payload = (const unsigned char*)payload_v;
+  const int cw = i8 ? 16 : bi == 4 ? 4 : 8;    // channels per contraction item
+  const int ips = 64 / es / cw;                // items per column step: 4 or 8
+  const int bw = std::min(cw, bi);             // an item's channels of one block
   const int nunits = (int)cdiv(I, cw);         // contraction units (channel groups) of the layer
   const int slab = bsp_rows_slab(I, H, K, cw);
   const int upslab = slab / cw;                // units per slab
@@ -147,7 +167,7 @@ int bsp_rows_section(const int32_t* row_ptr, const int32_t* col_idx, const uint1
   for (int r = 0; r < nbr; ++r)
     for (int64_t n = row_ptr[r]; n < row_ptr[r + 1]; ++n) {
       const int c = col_idx[n];
-      const int u0 = c * bi / cw, u1 = std::min<int>(nunits, (c + 1) * bi / cw);
+      const int u0 = c * bi / cw, u1 = std::min<int>(nunits, (int)cdiv((int64_t)(c + 1) * bi, cw));
       for (int u = u0; u < u1; ++u) bits.row(r)[u >> 6] |= 1ull << (u & 63);
     }
   // Pointwise layers: rows are grouped within windows of 64 output channels, and the strips
@@ -216,7 +236,7 @@ int bsp_rows_section(const int32_t* row_ptr, const int32_t* col_idx, const uint1
   int32_t* rstrip = s + off_rstrip;
   int32_t* rslab = s + off_rslab;
   int32_t* rdesc = s + off_rdesc;
-  uint16_t* rfrag = (uint16_t*)(s + off_rfrag);
+  unsigned char* rfrag = (unsigned char*)(s + off_rfrag);
 
   // block (row, column) -> position in the payload, for the rows of one strip
   std::vector<int32_t> pos;
@@ -242,7 +262,7 @@ int bsp_rows_section(const int32_t* row_ptr, const int32_t* col_idx, const uint1
       for (int64_t n = row_ptr[g[m]]; n < row_ptr[g[m] + 1]; ++n) {
         const int cn = col_idx[n];
         pos[m * nbc + cn] = (int32_t)n;
-        kept_items += std::min<int64_t>(nunits, (int64_t)(cn + 1) * bi / cw) - (int64_t)cn * bi / cw;
+        kept_items += std::min<int64_t>(nunits, cdiv((int64_t)(cn + 1) * bi, cw)) - (int64_t)cn * bi / cw;
       }
     union_items += (int64_t)units[t].size();
     size_t e = 0;
@@ -270,26 +290,26 @@ int bsp_rows_section(const int32_t* row_ptr, const int32_t* col_idx, const uint1
           rdesc[(cs + st) * 4 + q] = d;
         }
         if (!payload) continue;
-        for (int dy = 0; dy < H; ++dy)
-          for (int lane = 0; lane < 64; ++lane) {
-            const int j = lane & 15, q = lane >> 4;
-            uint16_t* dst = rfrag + (((cs + st) * H + dy) * 64 + lane) * 8;
-            const int member = j / bo, r = j % bo;
-            if (member >= (int)g.size()) continue;
-            for (int h = 0; h < ips / 4; ++h) {
-              const int64_t it = st * ips + q * (ips / 4) + h;
-              if (it >= items) continue;
-              const int unit = units[t][e0 + (size_t)(it / K)];
-              const int dx = (int)(it % K);
-              const int ch = unit * cw;          // first input channel of the item
-              const int bc = ch / bi;
-              const int32_t n = pos[(size_t)member * nbc + bc];
+        for (int item = 0; item < ips; ++item) {
+          const int64_t it = st * ips + item;
+          if (it >= items) break;
+          const int q = item / (ips / 4), h = item % (ips / 4);  // lane group, place in its 16 bytes
+          const int unit = units[t][e0 + (size_t)(it / K)];
+          const int dx = (int)(it % K);
+          for (int o = 0; o < cw; o += bw) {
+            const int ch = unit * cw + o;  // first input channel of the item's part in one block
+            const int bc = ch / bi;
+            for (size_t m = 0; m < g.size() && bc < nbc; ++m) {
+              const int32_t n = pos[m * nbc + bc];
               if (n < 0) continue;
-              const uint16_t* src = payload + (int64_t)n * blk_elems +
-                                    ((int64_t)r * HK + (int64_t)dy * K + dx) * bi + ch % bi;
-              std::memcpy(dst + h * cw, src, (size_t)cw * 2);
+              for (int dy = 0; dy < H; ++dy) {
+                const unsigned char* src = payload + ((int64_t)n * blk_elems + ((int64_t)dy * K + dx) * bi + ch % bi) * es;
+                unsigned char* dst = rfrag + ((((cs + st) * H + dy) * 64) + q * 16 + (int64_t)m * bo) * 16 + (h * cw + o) * es;
+                copy_rows(dst, src, bo, HK * bi * es, bw * es);
+              }
             }
           }
+        }
       }
       cs += nst;
     }
