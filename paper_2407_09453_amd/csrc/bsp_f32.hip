@@ -323,6 +323,15 @@ __global__ __launch_bounds__(1024) void fc_f32(F32Args a) {
   f32x4_t acc[NQ];
 #pragma unroll
   for (int k = 0; k < NQ; ++k) acc[k] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  // the bias of the channels this wave will store, asked for now: nothing waits for it at the end
+  f32x4_t bv[NQ];
+#pragma unroll
+  for (int k = 0; k < NQ; ++k)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int ch = br * BO + 4 * (a.ks > 1 ? min(wave, NQ - 1) : k) + r;
+      bv[k][r] = a.bias && ch < a.O ? a.bias[ch] : 0.f;
+    }
   float w[D], x[D][BI];
   int jb = 0, cols = 0;  // the columns of this wave's next 64 blocks, one per lane
   auto fetch = [&](int d, int s) {
@@ -351,7 +360,8 @@ __global__ __launch_bounds__(1024) void fc_f32(F32Args a) {
     cols = a.col_idx[n0 + min(jb + lane, nblk - 1) * a.ks];
     const int steps = min(nblk - jb, 64);
 #pragma unroll
-    for (int d = 0; d < D; ++d) fetch(d, d);
+    for (int d = 0; d < D; ++d)
+      if (d < steps) fetch(d, d);
     int s = 0;
     for (; s + D < steps; s += D) {
 #pragma unroll
@@ -388,7 +398,7 @@ __global__ __launch_bounds__(1024) void fc_f32(F32Args a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       if (ch + r >= a.O) continue;
-      float s = acc[k][r] + (a.bias ? a.bias[ch + r] : 0.f);
+      float s = acc[k][r] + bv[k][r];
       if (a.residual) s += a.residual[o + r];
       a.Y[o + r] = a.relu ? fmaxf(s, 0.f) : s;
     }
