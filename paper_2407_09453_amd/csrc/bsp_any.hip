@@ -24,6 +24,7 @@
 #include <cstdlib>
 #include <map>
 #include <mutex>
+#include <type_traits>
 
 namespace {
 
@@ -44,7 +45,7 @@ struct AnyArgs {
   int32_t CW, nchunk, tpc;         // output columns per chunk of columns, such chunks per row, tiles per chunk
   int32_t TPW, pitch, ppp;         // staged pixels per row, bytes per staged pixel, 16-byte pieces staged of each
   int32_t nslabs, spst, nstages, slab_bytes;   // the plan's slabs, how many are staged at a time
-  int32_t nstrips, NS, PG, ks, nset;           // strips per workgroup, pixel groups, waves that share a strip's steps
+  int32_t nstrips, NS, PG, ks, lpg, lks, nset; // strips per workgroup, pixel groups, waves that share a strip's steps; log2
   int32_t total, per_xcd;
   int32_t opitch, stream;          // bytes per pixel of the output image; its pieces are whole output lines
   FastDiv d_nset, d_tpc, d_nchunk, d_cw, d_tpw, d_ppp, d_opp;
@@ -176,7 +177,7 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
   const int plast = min(p0 + px, a.M * a.CW) - 1;
   const int rows = ((int)fdiv((uint32_t)plast, a.d_cw) - m0) * a.lsh + a.H;  // staged rows
 
-  const int k = wave % a.ks, sp = wave / a.ks, pg = sp % a.PG, si = sp / a.PG;
+  const int k = wave & (a.ks - 1), sp = wave >> a.lks, pg = sp & (a.PG - 1), si = sp >> a.lpg;
   const int strip = set * a.NS + si;
   const bool active = si < a.NS && strip < a.nstrips;
   // the strip's step ranges, one slab boundary per lane
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
   for (int stg = 0; stg < a.nstages; ++stg) {
     const int sl0 = stg * a.spst, sl1 = min(sl0 + a.spst, a.nslabs);
     const int slo = __builtin_amdgcn_readlane(tab, sl0), shi = __builtin_amdgcn_readlane(tab, sl1);
-    const int n = active && shi - slo > k ? (shi - slo - k + a.ks - 1) / a.ks : 0;  // this wave's steps
+    const int n = active && shi - slo > k ? (shi - slo - k + a.ks - 1) >> a.lks : 0;  // this wave's steps
 
     // ---- weights: a ring of D steps
     u32x4_t wr[D];
@@ -305,32 +306,47 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
     }
   }
 
-  // ---- waves that share a strip: partial sums through LDS
+  // ---- waves that share a strip: partial sums through LDS.  The strip's matrix tiles are dealt out to
+  // its waves, each adds up its tiles' sums in the order of the waves.
   if (a.ks > 1) {
     __syncthreads();
     f32x4_t* red = (f32x4_t*)lds;  // [wave][PT][64]
-    if (k > 0) {
 #pragma unroll
-      for (int t = 0; t < PT; ++t) red[(wave * PT + t) * 64 + lane] = acc[t];
-    }
+    for (int t = 0; t < PT; ++t) red[(wave * PT + t) * 64 + lane] = acc[t];
     __syncthreads();
-    if (k == 0) {
-      for (int s = 1; s < a.ks; ++s) {
+    const f32x4_t* first = red + (wave - k) * (PT * 64) + lane;
+    // (all of a tile's sums are asked for at once: one after the other they took most of a
+    // microsecond of a small layer's five)
+    auto add_up = [&](auto n) {
 #pragma unroll
-        for (int t = 0; t < PT; ++t) acc[t] = add4<KIND>(acc[t], red[((wave + s) * PT + t) * 64 + lane]);
+      for (int t = 0; t < PT; ++t) {
+        if ((t & (decltype(n)::value - 1)) != k) continue;
+        f32x4_t v[decltype(n)::value];
+#pragma unroll
+        for (int s = 0; s < decltype(n)::value; ++s) v[s] = first[(s * PT + t) * 64];
+#pragma unroll
+        for (int s = 1; s < decltype(n)::value; ++s) v[0] = add4<KIND>(v[0], v[s]);
+        acc[t] = v[0];
       }
-    }
+    };
+    if (a.ks == 8)
+      add_up(std::integral_constant<int, 8>{});
+    else if (a.ks == 4)
+      add_up(std::integral_constant<int, 4>{});
+    else
+      add_up(std::integral_constant<int, 2>{});
   }
   __syncthreads();  // everybody is done with the patch (the partial sums)
 
   // ---- results: bias and the one rounding (or the rescale), into an LDS image of the tile's
   // output; then all waves copy that out, 16 contiguous bytes per lane, with the residual and ReLU
   const int opitch = a.opitch;
-  if (active && k == 0) {
+  if (active) {
     const f32x4_t bv = bias4<KIND>(a, strip * BSP_STRIP + 4 * g);
     unsigned char* ot = lds + (pg * PT * 16 + jn) * opitch;
 #pragma unroll
     for (int t = 0; t < PT; ++t, ot += 16 * opitch) {
+      if ((t & (a.ks - 1)) != k) continue;
       const f32x4_t v = add4<KIND>(acc[t], bv);  // (int32 results)
       const int c = si * BSP_STRIP + 4 * g;
       if constexpr (KIND == kBf16) {
@@ -542,6 +558,8 @@ int launch_kind(const ConvParams& p, const int32_t* hdr, int y32, int shift, hip
   a.NS = best.NS;
   a.PG = best.PG;
   a.ks = best.ks;
+  a.lpg = __builtin_ctz(best.PG);
+  a.lks = __builtin_ctz(best.ks);
   a.nset = cdiv(a.nstrips, best.NS);
   const int px = best.PT * 16 * best.PG;
   const int64_t tiles = (int64_t)B * a.nchunk * a.tpc, total = tiles * a.nset;
