@@ -105,6 +105,8 @@ int dispatch(const bsp_weights* w, const ConvParams& p, void* stream, const Fixe
     // 24 to 32 with 8x8 blocks, whose streaming kernel takes 6.0 against 6.5 at 17 and 7.2 against 6.5
     // at 32; where the weights are the bulk the streaming kernels stay ahead)
     const bool few = p.P > (w->bo == 8 ? 28 : 16) && p.P <= 64 && p.I <= 2048;
+    // (a fixed scratch array refuses the layers it is too small for, whichever kernel takes them)
+    if (fixed && (allow & BSP_KERNEL_FC) && bsp_fc_xlds_scratch(p, w->dtype, w->bo, w->bi) > fixed->bytes) return BSP_ERR_CAPACITY;
     if (!w->kernels && chunked && (few || bsp_any_preferred(p, w->plan_host, w->dtype)))
       rc = bsp_launch_any(p, w->plan_host, st);
     if (rc != BSP_ERR_UNSUPPORTED) return rc;

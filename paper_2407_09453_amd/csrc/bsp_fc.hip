@@ -467,30 +467,52 @@ constexpr int kFcxLds = 150 * 1024;
 
 }  // namespace
 
+namespace {
+
+inline int fcx_tiles(int P) { return (P + 15) / 16 == 3 ? 4 : (P + 15) / 16; }
+inline int fcx_red_bytes(int NT) { return 8 * NT * 32 * 16; }
+// Channel ranges: all of X when [NT * 16][I] bf16 (plus padding and the summing area) fits LDS.
+// False where no range of useful length does.
+bool fcx_ranges(const ConvParams& p, int32_t* nseg, int32_t* segc) {
+  const int NT = fcx_tiles(p.P);
+  const int cap = ((kFcxLds - fcx_red_bytes(NT)) / (NT * 16) - 32) / 2 / 8 * 8;  // channels per range at most
+  if (cap < 64) return false;
+  *nseg = (p.I + cap - 1) / cap;
+  if (*nseg > 1) *nseg = (*nseg + 7) / 8 * 8;  // one range per XCD, or a multiple
+#ifdef BSP_ROWS_TUNE
+  if (const char* e = std::getenv("BSP_FCX_NSEG")) *nseg = std::max(*nseg, std::atoi(e));
+#endif
+  *segc = ((p.I + *nseg - 1) / *nseg + 7) / 8 * 8;
+  *nseg = (p.I + *segc - 1) / *segc;
+  return true;
+}
+bool fcx_takes(const ConvParams& p, int dtype, int bo, int bi) {
+  return dtype == BSP_BF16 && bo == 8 && bi == 8 && p.H == 1 && p.K == 1 && p.sh == 1 && p.sw == 1 && p.ph == 0 &&
+         p.pw == 0 && p.P <= 64 && p.P >= 1 && (p.I % 8) == 0 && (int64_t)p.P * p.I * 2 < (1ll << 31) && p.row_ptr &&
+         p.col_idx;
+}
+
+}  // namespace
+
+int64_t bsp_fc_xlds_scratch(const ConvParams& p, int dtype, int bo, int bi) {
+  int32_t nseg = 0, segc = 0;
+  if (!fcx_takes(p, dtype, bo, bi) || !fcx_ranges(p, &nseg, &segc) || nseg == 1) return 0;
+  return (int64_t)nseg * p.P * p.O * 4;
+}
+
+
 // 8x8 blocks, 1x1, stride 1, no padding, bf16, at most 64 output pixels, I a multiple of 8.
 // `scratch` holds scratch_bytes for the partial sums of layers whose X does not fit LDS in one
 // piece; BSP_ERR_CAPACITY (nothing launched) says how much is needed through *need.
 int bsp_launch_fc_xlds(const ConvParams& p, int dtype, int bo, int bi, float* scratch, int64_t scratch_bytes,
                        int64_t* need, hipStream_t st) {
   if (need) *need = 0;
-  if (dtype != BSP_BF16 || bo != 8 || bi != 8 || p.H != 1 || p.K != 1 || p.sh != 1 || p.sw != 1 ||
-      p.ph != 0 || p.pw != 0 || p.P > 64 || p.P < 1 || (p.I % 8) != 0 || (int64_t)p.P * p.I * 2 >= (1ll << 31) ||
-      !p.row_ptr || !p.col_idx)
-    return BSP_ERR_UNSUPPORTED;
-  const int NT = (p.P + 15) / 16 == 3 ? 4 : (p.P + 15) / 16;
+  if (!fcx_takes(p, dtype, bo, bi)) return BSP_ERR_UNSUPPORTED;
+  const int NT = fcx_tiles(p.P);
   const int nbr = (p.O + 7) / 8;
   FcXArgs q{};
-  // channel ranges: all of X when [NT * 16][I] bf16 (plus padding and the summing area) fits
-  const int red_bytes = 8 * NT * 32 * 16;
-  const int cap = ((kFcxLds - red_bytes) / (NT * 16) - 32) / 2 / 8 * 8;  // channels per range at most
-  if (cap < 64) return BSP_ERR_UNSUPPORTED;
-  q.nseg = (p.I + cap - 1) / cap;
-  if (q.nseg > 1) q.nseg = (q.nseg + 7) / 8 * 8;  // one range per XCD, or a multiple
-#ifdef BSP_ROWS_TUNE
-  if (const char* e = std::getenv("BSP_FCX_NSEG")) q.nseg = std::max(q.nseg, std::atoi(e));
-#endif
-  q.segc = ((p.I + q.nseg - 1) / q.nseg + 7) / 8 * 8;
-  q.nseg = (p.I + q.segc - 1) / q.segc;
+  const int red_bytes = fcx_red_bytes(NT);
+  if (!fcx_ranges(p, &q.nseg, &q.segc)) return BSP_ERR_UNSUPPORTED;
   q.pitch = q.segc * 2 + ((q.segc / 8) % 2 == 0 ? 16 : 32);
   q.red_off = NT * 16 * q.pitch;
   q.rng_off = q.red_off + red_bytes;

@@ -33,6 +33,8 @@ int bsp_launch_fc_stream(const ConvParams& p, int dtype, int bo, int bi, hipStre
 // BSP_ERR_CAPACITY, with nothing launched and the bytes needed in *need, when it is too small.
 int bsp_launch_fc_xlds(const ConvParams& p, int dtype, int bo, int bi, float* scratch, int64_t scratch_bytes,
                        int64_t* need, hipStream_t st);
+// the bytes of scratch memory that layer takes there (0: none, or not a layer of that kernel)
+int64_t bsp_fc_xlds_scratch(const ConvParams& p, int dtype, int bo, int bi);
 
 // LDS-resident kernel (weights and activations of a slab both in LDS); needs the host copy
 // of the plan to size LDS.  BSP_ERR_UNSUPPORTED = not applicable, nothing launched.

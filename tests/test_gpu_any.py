@@ -107,3 +107,24 @@ def test_calls_go_to_the_current_stream():
             assert _current_stream(t) == torch.cuda.current_stream().cuda_stream == s.cuda_stream
     with pytest.raises(ValueError):
         _current_stream(torch.zeros(8))
+
+
+def test_fixed_scratch_refuses_what_it_refused():
+    """The FC entry point with the fixed array: as many bits as the other, and CAPACITY by the
+    documented size of the partial sums, also where a kernel without partial sums takes the layer."""
+    import torch
+    rng = np.random.default_rng(0)
+    for O, refused in ((1000, False), (4096, True)):
+        W = (rng.standard_normal((O, 1, 1, 2048)) * 0.05).astype(np.float32)
+        layer = bsp.BspLayer(W, (rng.random((O // 8, 256)) < 0.5).astype(np.uint8), 8, 8, "bf16")
+        X = torch.randn(64, 2048, device="cuda").bfloat16()
+        Y = torch.empty(64, O, device="cuda", dtype=torch.bfloat16)
+        st = torch.cuda.current_stream().cuda_stream
+        call = lambda: bsp.binding.bsp_fc_fused_static(layer.struct, X.data_ptr(), None, None, False, Y.data_ptr(), 64, st)
+        if refused:
+            with pytest.raises(bsp.BspError) as e:
+                call()
+            assert e.value.code == -7
+        else:
+            call()
+            assert torch.equal(Y, layer.fc(X))
