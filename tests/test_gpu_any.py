@@ -98,6 +98,39 @@ def test_infinities_in_dropped_channels_stay_out():
         assert_close(y, oracle.conv2d(X, c.W, c.bias, c.gamma, 8, 8, c.stride, c.pad), "bf16", f"{I} channels")
 
 
+@pytest.mark.parametrize("bo,bi", [(8, 8), (4, 16), (16, 4)])
+def test_infinities_reach_the_rows_that_keep_their_channel_and_no_others(bo, bi):
+    """An output is infinite or NaN where a kept weight meets such an input, and finite everywhere
+    else: in all block rows of a strip, whatever their neighbours in it keep."""
+    import torch
+    for n, (B, L, J, I, O, H, K, s, p) in enumerate([
+            (33, 1, 1, 64, 256, 1, 1, 1, 0), (64, 1, 1, 2048, 72, 1, 1, 1, 0), (40, 1, 1, 520, 44, 1, 1, 1, 0),
+            (1, 9, 9, 41, 24, 3, 3, 1, 1), (3, 10, 15, 304, 16, 7, 1, 1, 3), (1, 8, 8, 128, 48, 3, 3, 1, 1),
+            (1, 6, 6, 352, 40, 5, 5, 1, 2), (2, 14, 15, 70, 20, 5, 5, 2, 2)]):
+        pad = _pad(H, K, p)
+        c = draw_layer("t", B=B, L=L, J=J, I=I, O=O, H=H, K=K, stride=(s, s), pad=pad, bo=bo, bi=bi, dtype="bf16",
+                       mask_kind="bernoulli", density=0.5, seed=9700 + n, b_std=0.5)
+        print("case", n, (B, L, J, I, O, H, K), bo, bi, flush=True)
+        conv = lambda X: oracle.conv2d(X, c.W, None, c.gamma, bo, bi, c.stride, c.pad)
+        rng = np.random.default_rng(n)
+        hit, X0 = {}, c.X.copy()
+        for v in (np.inf, -np.inf, np.nan):
+            one = np.zeros_like(c.X)
+            at = rng.integers(B), rng.integers(L), rng.integers(J), rng.integers(I)
+            one[at], X0[at], c.X[at] = 1.0, 0.0, v
+            hit[str(v)] = conv(one)      # at most one product per output: its sign is the weight's
+        up = (hit["inf"] > 0) | (hit["-inf"] < 0)
+        down = (hit["inf"] < 0) | (hit["-inf"] > 0)
+        nan = (hit["nan"] != 0) | (up & down)
+        y = to_host(make_layer(c).conv2d(to_device(c), c.stride, c.pad))
+        torch.cuda.synchronize()
+        assert (np.isnan(y) == nan).all(), n
+        assert (np.isposinf(y) == (up & ~nan)).all() and (np.isneginf(y) == (down & ~nan)).all(), n
+        want = oracle.conv2d(X0, c.W, c.bias, c.gamma, bo, bi, c.stride, c.pad)
+        ok = ~(up | down | nan)
+        assert_close(np.where(ok, y, 0.0), np.where(ok, want, 0.0), "bf16", f"case {n}")
+
+
 def test_calls_go_to_the_current_stream():
     import torch
     from paper_2407_09453_amd.binding import _current_stream
