@@ -14,8 +14,8 @@
 // 16x16x32 takes four of them; columns kept on one side only are never multiplied.
 #include "bsp_device.h"
 #include "bsp_launch.h"
+#include "bsp_spgemm_pick.h"
 #include <algorithm>
-#include <cmath>
 #ifdef BSP_ROWS_TUNE
 #include <cstdlib>
 #endif
@@ -570,11 +570,12 @@ int launch_u(const SpParams& q, unsigned grid, hipStream_t st) {
   return hipGetLastError() == hipSuccess ? BSP_OK : BSP_ERR_HIP;
 }
 
-template <int MI, int NI, int GM, int GN, int MV, int NBUF>
+template <int TILE, int MI, int NI, int GM, int GN, int MV>
 int launch_dense(DnParams q, hipStream_t st) {
-  constexpr int RA = GM * MI * 2, RB = GN * NI * 2;
-  const int64_t ldsb = (int64_t)NBUF * (RA + RB) * 1024 + (int64_t)q.nsteps * (RA + RB) * 4;
-  if (ldsb > 160 * 1024) return BSP_ERR_UNSUPPORTED;
+  constexpr int RA = GM * MI * 2, RB = GN * NI * 2, NBUF = kSpTile[TILE].nbuf;
+  static_assert(RA == kSpTile[TILE].ra && RB == kSpTile[TILE].rb, "the instance is the tile that was chosen");
+  const int64_t ldsb = sp_tile_lds(kSpTile[TILE], q.nsteps);
+  if (ldsb > kSpLds) return BSP_ERR_UNSUPPORTED;
   q.tiles_i = (q.ra + RA - 1) / RA;
   q.tiles_j = (q.rb + RB - 1) / RB;
   const int64_t total = (int64_t)q.tiles_i * q.tiles_j;
@@ -585,7 +586,7 @@ int launch_dense(DnParams q, hipStream_t st) {
   static bool raised = false;  // dynamic LDS above 64 KB has to be allowed once per kernel
   if (!raised) {
     if (hipFuncSetAttribute((const void*)spgemm_dense_bf16<MI, NI, GM, GN, MV, NBUF>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSpLds) != hipSuccess)
       return BSP_ERR_HIP;
     raised = true;
   }
@@ -636,34 +637,15 @@ extern "C" int bsp_spgemm_nt(const bsp_bcsr* A, const bsp_bcsr* B, float* C, voi
   if (nsb * 64 > 0x7FFFFFFF) return BSP_ERR_SHAPE;
   q.nsb = (int32_t)nsb;
   DnParams d{q.sa, q.sb, q.ca, q.cb, q.pa, q.pb, C, q.ra, q.rb, q.nsub, (A->cols + 7) / 8, q.nnzb_a, q.nnzb_b, 0, 0, 0, 0, 0};
-  // Which kernel and tile: the fastest by a model in us, rounds of workgroups times (fixed part +
-  // time per eight block columns), from timings at 512 to 4096 and ragged sizes.  For the kernel that
-  // selects columns the time grows with the share of columns that both sides of a tile keep.
   {
-    const double n = d.nsteps;
-    auto rounds = [&](int ra, int rb, int slots) {
-      const double t = (double)((d.ra + ra - 1) / ra) * ((d.rb + rb - 1) / rb);
-      return std::ceil(t / slots);
-    };
-    const double da = (double)A->nnzb / ((double)A->rows * A->cols), db = (double)B->nnzb / ((double)B->rows * B->cols);
-    const double both = (1 - (1 - da) * (1 - da)) * (1 - (1 - db) * (1 - db));
-    const double sparse = rounds(16, 16, 512) * (2 + n * (0.6 + 3.6 * both));
-    const double t256 = rounds(32, 32, 256) * (6 + n * 1.8);
-    const double t128w = rounds(16, 32, 256) * (5 + n * 0.98);
-    const double t128 = rounds(16, 16, 256) * (4 + n * 0.62);
-    const double t64 = rounds(8, 8, 256) <= 1 ? 3.5 + n * 0.38 : rounds(8, 8, 512) * (3 + n * 0.48);
-    const double best = std::min({sparse, t256, t128w, t128, t64});
     hipStream_t st = (hipStream_t)stream;
     int rc = BSP_ERR_UNSUPPORTED;
-    if (best == t64)
-      rc = launch_dense<2, 2, 2, 2, 4, 4>(d, st);
-    else if (best == t128)
-      rc = launch_dense<2, 4, 4, 2, 8, 3>(d, st);
-    else if (best == t128w)
-      rc = launch_dense<4, 4, 2, 4, 6, 3>(d, st);
-    else if (best == t256)
-      rc = launch_dense<8, 4, 2, 4, 4, 2>(d, st);
-    if (best != sparse && rc == BSP_ERR_UNSUPPORTED) rc = launch_dense<2, 2, 2, 2, 4, 4>(d, st);  // (the smallest table)
+    switch (sp_pick(d.ra, d.rb, d.nsteps, (double)A->nnzb / ((double)A->rows * A->cols), (double)B->nnzb / ((double)B->rows * B->cols))) {
+      case SP_TILE_64: rc = launch_dense<SP_TILE_64, 2, 2, 2, 2, 4>(d, st); break;
+      case SP_TILE_128: rc = launch_dense<SP_TILE_128, 2, 4, 4, 2, 8>(d, st); break;
+      case SP_TILE_128W: rc = launch_dense<SP_TILE_128W, 4, 4, 2, 4, 6>(d, st); break;
+      case SP_TILE_256: rc = launch_dense<SP_TILE_256, 8, 4, 2, 4, 4>(d, st); break;
+    }
     if (rc != BSP_ERR_UNSUPPORTED) return rc;
   }
 #ifdef BSP_ROWS_TUNE

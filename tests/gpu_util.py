@@ -56,3 +56,20 @@ def assert_close(y, ref, dtype, what=""):
     tight = err > TIGHT[dtype] * scale + 1e-30
     assert not tight.any(), f"{what}: within the stated tolerance but {tight.sum()} elements " \
         f"beyond the derived bound {TIGHT[dtype]}; worst {(err / np.maximum(scale, 1e-300)).max():.3e}"
+
+
+def kernels_of(call):
+    """Names of the kernels that call() runs, templates included: which of the dispatcher's kernels
+    a test has reached.  (Skips the test where the profiler records no kernels at all.)"""
+    import pytest
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    call()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    names = [e.key for e in p.key_averages() if "(" in e.key]
+    if not names:
+        pytest.skip("the profiler records no kernels here")
+    return names

@@ -1,10 +1,15 @@
 """Block-sparse x block-sparse product: host segment pointers (CPU) and the HIP kernel against
 the oracle (GPU)."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 
 import oracle
 import paper_2407_09453_amd as bsp
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def _draw(Ra, Rb, N, seed, da=0.5, db=0.5):
@@ -106,3 +111,65 @@ def test_spgemm_tiles_and_infinities(Ra, Rb, N):
         assert (np.isnan(got) == np.isnan(want)).all() and (got[~ok & ~np.isnan(want)] == want[~ok & ~np.isnan(want)]).all()
         scale = np.maximum(np.abs(want[ok]), np.sqrt(np.mean(want[ok] ** 2)) + 1e-30)
         assert (np.abs(got[ok] - want[ok]) <= 1e-5 * scale + 1e-30).all()
+
+
+PICK = r"""
+#include <cstdio>
+#include "bsp_spgemm_pick.h"
+int main() {
+  long checked = 0, wrong = 0, chosen[SP_TILES + 1] = {};
+  const double shares[] = {0.02, 0.05, 0.1, 0.2, 0.25, 0.5, 1.0};
+  for (long r = 1; r <= 1024; r += r / 3 + 1)
+    for (long c = 1; c <= 1024; c += c / 3 + 1)
+      for (long n = 1; n <= 4096; n += n / 7 + 1)
+        for (double da : shares)
+          for (double db : shares) {
+            const int t = sp_pick(r, c, n, da, db);
+            const double time = sp_time(t, r, c, n, da, db);
+            ++checked;
+            ++chosen[t];
+            // fits, is no slower than the kernel that needs no table, nor than any other tile that fits
+            if (t < SP_TILES && (kSpTile[t].ra + kSpTile[t].rb) * (kSpTile[t].nbuf * 1024 + n * 4) > 160 * 1024) ++wrong;
+            if (time > sp_time(SP_SELECT, r, c, n, da, db)) ++wrong;
+            for (int o = 0; o < SP_TILES; ++o)
+              if ((kSpTile[o].ra + kSpTile[o].rb) * (kSpTile[o].nbuf * 1024 + n * 4) <= 160 * 1024 && time > sp_time(o, r, c, n, da, db)) ++wrong;
+          }
+  for (long n : chosen)
+    if (!n) ++wrong;
+  // 4096 x 4096 with an inner dimension past the large tiles' tables
+  if (sp_pick(512, 512, 1024 / 8 + 2, 0.2, 0.2) != SP_SELECT || sp_pick(512, 512, 2048 / 8, 0.5, 0.5) != SP_TILE_128) ++wrong;
+  std::printf("%ld %ld\n", checked, wrong);
+}
+"""
+
+
+def test_chosen_tile_fits_and_is_the_fastest_that_does(tmp_path):
+    src = tmp_path / "pick.cpp"
+    src.write_text(PICK)
+    exe = str(tmp_path / "pick")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-I", os.path.join(ROOT, "paper_2407_09453_amd", "csrc"), str(src), "-o", exe], check=True)
+    checked, wrong = map(int, subprocess.run([exe], capture_output=True, text=True, check=True).stdout.split())
+    assert checked > 10 ** 5 and wrong == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Ra,Rb,N,d,kernel", [
+    (250, 250, 40, 0.5, "dense_bf16<2, 4, 4, 2, 8, 3>"), (200, 260, 130, 0.5, "dense_bf16<2, 4, 4, 2, 8, 3>"),
+    (300, 260, 81, 1.0, "dense_bf16<4, 4, 2, 4, 6, 3>"), (512, 505, 70, 0.5, "dense_bf16<8, 4, 2, 4, 4, 2>"),
+    (40, 150, 200, 0.5, "dense_bf16<2, 2, 2, 2, 4, 4>"), (300, 300, 60, 0.1, "nt_bf16"), (199, 261, 130, 0.1, "nt_bf16"),
+    (512, 512, 1040, 0.2, "nt_bf16"), (512, 512, 1040, 0.5, "dense_bf16<2, 4, 4, 2, 8, 3>")])
+def test_every_kernel_of_the_product(Ra, Rb, N, d, kernel):
+    """Each tile of the staged product and the column-selecting kernel over several of its segments,
+    also where the table of the tile that the model likes best does not fit; against fp64."""
+    import torch
+    from gpu_util import kernels_of
+    A, gamma, B, omega = _draw(Ra, Rb, N, Ra + N, d, d)
+    gamma[1], omega[2] = 0, 1                      # an empty block row and a full one
+    Am, Bm = bsp.BspMatrix(A, gamma), bsp.BspMatrix(B, omega)
+    out = torch.full((Ra * 8, Rb * 8), float("nan"), device="cuda")
+    ran = kernels_of(lambda: Am.matmul_nt(Bm, out=out))
+    assert any(kernel in k for k in ran), ran
+    mask = lambda M, g: torch.from_numpy(M).cuda().double() * torch.from_numpy(np.kron(g, np.ones((8, 8), np.uint8))).cuda()
+    want = mask(A, gamma) @ mask(B, omega).t().contiguous()
+    scale = torch.maximum(want.abs(), want.pow(2).mean().sqrt())
+    assert bool(((out.double() - want).abs() <= 1e-5 * scale).all())
