@@ -326,7 +326,8 @@ __global__ __launch_bounds__(512) void spgemm_nt_bf16(SpParams q) {
 //
 // Zero times infinity: a product of an absent block with an infinity or NaN is no part of the
 // result.  It leaves a non-finite sum, so a 16 x 16 tile with one is computed once more from
-// the columns that both of its sides keep (redo_tile), the kernel above's rule.
+// the columns that both of its sides keep (redo_tile), the kernel above's rule, and what was
+// not finite is replaced.
 __device__ const u32x4_t g_zeros[1] = {};
 
 struct DnParams {
@@ -343,41 +344,37 @@ struct DnParams {
   int32_t band;                   // tile rows that consecutive workgroups share operand columns over
 };
 
-// One 16 x 16 tile (block rows r0, r0 + 1 of A against c0, c0 + 1 of B) from the columns that one of
-// the two rows of each side keeps; one column at a time, seldom called.
-template <typename Q>
-__device__ __forceinline__ f32x4_t redo_tile(const Q& q, int r0, int c0, int lane) {
+// One 16 x 16 tile once more (block rows la, la + 1 of the workgroup's A against lb, lb + 1 of its B, from
+// the step table in LDS) from the columns that one of the two rows of each side keeps.  Four steps of
+// loads are out at a time; bound by their latency.  4096^3, half kept, with one NaN in A 187 us, with all
+// of A infinite 726, where finite operands take 124 (one column at a time from col_idx: 1248 and 8517).
+template <int R>
+__device__ __forceinline__ f32x4_t redo_tile(const DnParams& q, const uint32_t* tab, int la, int lb, const unsigned char* pa,
+                                             const unsigned char* pb, int lane) {
+  constexpr int U = 4;
   const int jn = lane & 15, g = lane >> 4, h = jn >> 3;
+  pa += (jn & 7) * 16;
+  pb += (jn & 7) * 16;
   f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-  // next and end of the four rows' blocks (rows past the matrix have none)
-  int pos[4], end[4];
+  for (int s0 = 0; s0 < q.nsteps; s0 += U) {
+    u32x4_t a[U][2], b[U][2];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int row = (k < 2 ? r0 : c0) + (k & 1);
-    const bool ok = row < (k < 2 ? q.ra : q.rb);
-    const int32_t* sp = (k < 2 ? q.sa : q.sb) + (int64_t)(ok ? row : 0) * (q.nsub + 1);
-    pos[k] = ok ? sp[0] : 0;
-    end[k] = ok ? sp[q.nsub] : 0;
-  }
-  const int kNone = 0x7FFFFFFF;
-  for (;;) {
-    int c[4], next = kNone;
+    for (int u = 0; u < U; ++u) {
+      const uint32_t* t = tab + min(s0 + u, q.nsteps - 1) * R;
+      const uint32_t a0 = t[la], a1 = t[la + 1], b0 = t[lb], b1 = t[lb + 1];
+      const uint32_t both = s0 + u < q.nsteps ? (a0 | a1) & (b0 | b1) & 0xFFu : 0u, wa = h ? a1 : a0, wb = h ? b1 : b0;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      c[k] = pos[k] < end[k] ? (k < 2 ? q.ca : q.cb)[pos[k]] : kNone;
-      next = min(next, c[k]);
-    }
-    if (next == kNone) break;
-    if ((c[0] == next || c[1] == next) && (c[2] == next || c[3] == next)) {
-      u32x4_t a = {0u, 0u, 0u, 0u}, b = {0u, 0u, 0u, 0u};
-      if (g == 0) {  // eight of the instruction's 32 products, the others are zeros
-        if ((h ? c[1] : c[0]) == next) a = *(const u32x4_t*)(q.pa + (int64_t)(h ? pos[1] : pos[0]) * 128 + (jn & 7) * 16);
-        if ((h ? c[3] : c[2]) == next) b = *(const u32x4_t*)(q.pb + (int64_t)(h ? pos[3] : pos[2]) * 128 + (jn & 7) * 16);
+      for (int k = 0; k < 2; ++k) {
+        const uint32_t c = 4u * k + g, before = (1u << c) - 1u, on = both >> c & 1u;
+        a[u][k] = b[u][k] = u32x4_t{0u, 0u, 0u, 0u};
+        if (on & wa >> c) a[u][k] = *(const u32x4_t*)(pa + (int64_t)((wa >> 8) + __popc(wa & before)) * 128);
+        if (on & wb >> c) b[u][k] = *(const u32x4_t*)(pb + (int64_t)((wb >> 8) + __popc(wb & before)) * 128);
       }
-      acc = mfma_bf16_16x16x32(b, a, acc);
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) pos[k] += c[k] == next;
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int k = 0; k < 2; ++k) acc = mfma_bf16_16x16x32(b[u][k], a[u][k], acc);
   }
   return acc;
 }
@@ -485,6 +482,7 @@ __global__ __launch_bounds__((GM * GN + MV) * 64) void spgemm_dense_bf16(DnParam
       asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kAhead) : "memory");
     else
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile(".p2align 6");  // (the loop's instructions start on a line: 2 % of 256 x 256 x 32768)
     for (int s = 0; s < q.nsteps; ++s) {
       __builtin_amdgcn_s_barrier();  // step s is there; everyone is done with step s - 1
       if (s + NBUF - 1 < q.nsteps) {
@@ -534,24 +532,33 @@ __global__ __launch_bounds__((GM * GN + MV) * 64) void spgemm_dense_bf16(DnParam
       __builtin_memcpy(q.C + (int64_t)(r0 * 8 + jn) * ncol + c0 * 8 + 4 * g, &v, 16);
   };
   const int ar0 = ti * RA + wm * MI * 2, bc0 = tj * RB + wn * NI * 2;  // the wave's first block rows
-  uint32_t redo = 0;
+  uint32_t redo = 0, bad[4] = {0, 0, 0, 0};  // tiles with a sum that is not finite; the lane's own of these
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
       const f32x4_t v = acc[i][j];
-      // (x - x is not zero for an infinity or NaN)
-      const bool bad = !(v.x - v.x == 0.f) || !(v.y - v.y == 0.f) || !(v.z - v.z == 0.f) || !(v.w - v.w == 0.f);
-      if (__ballot(bad))
+      put(ar0 + 2 * i, bc0 + 2 * j, v);
+      // (the difference is not zero for an infinity or NaN)
+      if (__ballot((v.x - v.x) + (v.y - v.y) + (v.z - v.z) + (v.w - v.w) != 0.f)) {
         redo |= 1u << (i * NI + j);
-      else
-        put(ar0 + 2 * i, bc0 + 2 * j, v);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) bad[r] |= v[r] - v[r] == 0.f ? 0u : 1u << (i * NI + j);
+      }
     }
-  while (redo) {
-    const int t = __ffs((int)redo) - 1;
-    redo &= redo - 1;
-    const int r0 = ar0 + 2 * (t / NI), c0 = bc0 + 2 * (t % NI);
-    put(r0, c0, redo_tile(q, r0, c0, lane));
+  for (; redo; redo &= redo - 1) {
+    const int t = __ffs((int)redo) - 1, i = t / NI, j = t % NI;
+    const int r0 = ar0 + 2 * i, c0 = bc0 + 2 * j, h = jn >> 3;
+    // the lane's block rows; their first blocks (past the matrix: no blocks, any place)
+    const unsigned char* pa = q.pa + (int64_t)q.sa[(int64_t)min(r0 + h, q.ra - 1) * (q.nsub + 1)] * 128;
+    const unsigned char* pb = q.pb + (int64_t)q.sb[(int64_t)min(c0 + h, q.rb - 1) * (q.nsub + 1)] * 128;
+    const f32x4_t v = redo_tile<R>(q, tab, wm * MI * 2 + 2 * i, RA + wn * NI * 2 + 2 * j, pa, pb, lane);
+    if (r0 + h < q.ra && c0 + (g >> 1) < q.rb) {
+      float* at = q.C + (int64_t)(r0 * 8 + jn) * ncol + c0 * 8 + 4 * g;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (bad[r] >> t & 1u) at[r] = v[r];
+    }
   }
 }
 

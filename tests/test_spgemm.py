@@ -173,3 +173,31 @@ def test_every_kernel_of_the_product(Ra, Rb, N, d, kernel):
     want = mask(A, gamma) @ mask(B, omega).t().contiguous()
     scale = torch.maximum(want.abs(), want.pow(2).mean().sqrt())
     assert bool(((out.double() - want).abs() <= 1e-5 * scale).all())
+
+
+@pytest.mark.gpu
+def test_one_nan_costs_little_and_leaves_the_other_rows_alone():
+    """What is not finite is computed once more, from a table that is in LDS anyway: the rows without
+    it keep their bits, and the product stays within a few times its own time (about 1.5)."""
+    import torch
+    A, gamma, B, omega = _draw(256, 256, 256, 77)
+    gamma[3, 5] = 1
+    def product(A):
+        Am, Bm = bsp.BspMatrix(A, gamma), bsp.BspMatrix(B, omega)
+        C = Am.matmul_nt(Bm)
+        best = float("inf")
+        for _ in range(5):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            for _ in range(10):
+                Am.matmul_nt(Bm, out=C)
+            t1.record()
+            torch.cuda.synchronize()
+            best = min(best, t0.elapsed_time(t1))
+        return C, best
+    clean, t_clean = product(A)
+    A[3 * 8 + 2, 5 * 8 + 1] = np.nan
+    got, t_nan = product(A)
+    others = torch.arange(2048, device="cuda") != 26
+    assert torch.equal(got[others], clean[others]) and bool(got[26].isnan().any())
+    assert t_nan < 4 * t_clean, (t_nan, t_clean)
