@@ -1,6 +1,6 @@
 // Layers of any shape on 16x16 matrix tiles, activations staged in LDS: bf16 layers whose channel
 // counts are no multiple of eight, int8 layers (exact 32-bit sums, int8 or int32 results), and bf16
-// layers of any channel count that are too small to fill the chip (bsp_any_preferred).
+// layers of any channel count that are too small to fill the chip (bsp_rules.h).
 //
 // The weights come from the plan's step section (four (chunk, tap) pairs per step, a step's
 // 16 x 64-byte operand contiguous), so only chunks that some block of a strip keeps have steps.  A
@@ -706,32 +706,18 @@ const int32_t* plan_of(const ConvParams& p, int dtype, const void* plan_host) {
 
 }  // namespace
 
-// Where both this kernel and a specialised one take a layer: the specialised ones share a patch or
-// a weight fragment among more products, which pays once the chip is full of work; this one splits
-// small layers finer (pixels, strips, contraction) and has the shorter opening.  The lines were drawn
-// by timing both sides on 220 layers (the networks' layers and random ones), in matrix instructions
-// of a layer.  `best of others / here` in microseconds, on either side of a line:
-//   1x7 17x17x128 batch 16 10.8 / 7.8, 1x7 stride 2 53x53x360 batch 23 63 / 39: windows of five and
-//   more columns in one row have no line, nor have 5x5 windows (15x15x248 batch 4 41 / 12)
-//   1x3 8x8x384 batch 16 (41 K) 11.1 / 7.7; 81x67x288 batch 3 (164 K) 13.7 / 17.5
-//   7x1 18x18x296 batch 5 (199 K) 13.8 / 13.8; 58x81x280 batch 2 (233 K) 12.7 / 19.8; stride 2: no line
-//   3x1 22x26x304 batch 2 (35 K) 9.6 / 7.1; 24x27x184 batch 20 (94 K) 11.5 / 11.6
-//   3x3 14x14x256 batch 1 (10 K) 8.2 / 6.0; 21x21x88 batch 13 (63 K) 7.4 / 10.2
-//   3x3 stride 2 36x23x496 batch 3 (43 K) 21 / 12; 70x70x128 batch 1 (63 K) 8.6 / 9.7
+bool bsp_any_beats(const ConvParams& p, const void* plan_host, BspRival rival) {
+  const int32_t* hdr = plan_of(p, BSP_BF16, plan_host);
+  return hdr && bsp_any_beats_bf16(rival, hdr[BSP_PLAN_BO_W], p.H, p.K, p.sh > 1 || p.sw > 1,
+                                   (int64_t)((p.P + 15) / 16) * hdr[BSP_PLAN_NSTEPS_W], (int64_t)p.P * p.O, p.I, p.O);
+}
+
 // int8 against the LDS-resident kernel, which keeps one slab's weights in LDS: several slabs always
-// (7x7x512 batch 32 15.2 / 11.5), one slab below 20 K (1x1 56x56x64->256 batch 2 6.4 / 5.0, batch 32
-// 21 / 31).
-bool bsp_any_preferred(const ConvParams& p, const void* plan_host, int dtype) {
-  const int32_t* hdr = plan_of(p, dtype, plan_host);
-  if (!hdr) return false;
-  const int64_t mm = (int64_t)((p.P + 15) / 16) * hdr[BSP_PLAN_NSTEPS_W];
-  if (dtype == BSP_I8) return hdr[BSP_PLAN_NSLABS_W] > 1 || mm <= 20000;
-  const bool strided = p.sh > 1 || p.sw > 1;
-  if (p.H == 1 && p.K == 1) return false;
-  if (p.H == 1) return p.K >= 5 || mm <= 100000;
-  if (p.K == 1) return p.H >= 5 ? strided || mm <= 100000 : mm <= 45000;
-  if (p.H >= 5 || p.K >= 5) return true;
-  return mm <= (strided ? 60000 : 30000);
+// (7x7x512 batch 32 15.2 / 11.5), one slab below 20 K matrix instructions (1x1 56x56x64->256 batch 2 6.4 / 5.0,
+// batch 32 21 / 31).
+bool bsp_any_beats_i8(const ConvParams& p, const void* plan_host) {
+  const int32_t* hdr = plan_of(p, BSP_I8, plan_host);
+  return hdr && (hdr[BSP_PLAN_NSLABS_W] > 1 || (int64_t)((p.P + 15) / 16) * hdr[BSP_PLAN_NSTEPS_W] <= 20000);
 }
 
 int bsp_launch_any(const ConvParams& p, const void* plan_host, hipStream_t st) {

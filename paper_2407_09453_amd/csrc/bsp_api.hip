@@ -100,16 +100,17 @@ int dispatch(const bsp_weights* w, const ConvParams& p, void* stream, const Fixe
     const bool chunked = bsp_tile_supported(p, w->dtype);  // whole 8-channel chunks
     hipStream_t st = (hipStream_t)stream;
     int rc = BSP_ERR_UNSUPPORTED;
-    // up to 64 pixels and short rows: staged once and split over strips and contraction (7x7x2048->512
-    // 9.0 -> 6.5 us, FC 64 x 2048 -> 1000 10.1 -> 6.8; from 17 pixels with 4x16 blocks, 7.7 -> 6.7; from
-    // 24 to 32 with 8x8 blocks, whose streaming kernel takes 6.0 against 6.5 at 17 and 7.2 against 6.5
-    // at 32; where the weights are the bulk the streaming kernels stay ahead)
-    const bool few = p.P > (w->bo == 8 ? 28 : 16) && p.P <= 64 && p.I <= 2048;
+    // the any-shape kernel takes what it is the faster one on (it is no part of a caller's mask)
+    bool any = !w->kernels;
+    auto any_beats = [&](BspRival rival) { return any && chunked && bsp_any_beats(p, w->plan_host, rival); };
+    const bool flat = p.H == 1 && p.K == 1 && p.ph == 0 && p.pw == 0 && p.sh == 1 && p.sw == 1;
     // (a fixed scratch array refuses the layers it is too small for, whichever kernel takes them)
     if (fixed && (allow & BSP_KERNEL_FC) && bsp_fc_xlds_scratch(p, w->dtype, w->bo, w->bi) > fixed->bytes) return BSP_ERR_CAPACITY;
-    if (!w->kernels && chunked && (few || bsp_any_preferred(p, w->plan_host, w->dtype)))
+    if (any && chunked && bsp_any_few(w->bo, p.P, p.I, p.O, flat)) {
       rc = bsp_launch_any(p, w->plan_host, st);
-    if (rc != BSP_ERR_UNSUPPORTED) return rc;
+      if (rc != BSP_ERR_UNSUPPORTED) return rc;
+      any = false;
+    }
     if (chunked && (allow & BSP_KERNEL_FC)) {
       int64_t need = 0;
       rc = fixed ? bsp_launch_fc_xlds(p, w->dtype, w->bo, w->bi, fixed->ptr, fixed->bytes, &need, st)
@@ -124,20 +125,31 @@ int dispatch(const bsp_weights* w, const ConvParams& p, void* stream, const Fixe
     // than 100 000 pixels.  A caller's kernel mask overrides the rule.
     if ((allow & BSP_KERNEL_PW) && p.H == 1 && p.K == 1) rc = bsp_launch_pw(p, w->dtype, w->plan_host, st);
     if (rc != BSP_ERR_UNSUPPORTED) return rc;
-    if ((allow & BSP_KERNEL_BAND) && p.H == 3 && p.K == 3) rc = bsp_launch_band(p, w->dtype, w->plan_host, st);
-    if (rc != BSP_ERR_UNSUPPORTED) return rc;
     const bool rows_pick = p.H > 1 ? p.I >= 128
                                    : (p.I >= 128 && p.I <= 512 && p.O >= 128 && p.P < 100000);
-    if ((allow & BSP_KERNEL_ROWS) && (rows_pick || w->kernels)) rc = bsp_launch_rows(p, w->dtype, w->plan_host, st);
-    if (rc != BSP_ERR_UNSUPPORTED) return rc;
-    if ((allow & BSP_KERNEL_FIRST) && p.I <= 4) rc = bsp_launch_first(p, w->dtype, w->plan_host, st);
-    if (rc != BSP_ERR_UNSUPPORTED) return rc;
-    if (allow & BSP_KERNEL_LDS) rc = bsp_launch_lds(p, w->dtype, w->plan_host, st);
-    if (rc != BSP_ERR_UNSUPPORTED) return rc;
-    if (!w->kernels) rc = bsp_launch_any(p, w->plan_host, st);
-    if (rc != BSP_ERR_UNSUPPORTED) return rc;
-    if (chunked && (allow & BSP_KERNEL_TILE)) rc = bsp_launch_tile(p, w->dtype, st);
-    if (rc != BSP_ERR_UNSUPPORTED) return rc;
+    // the row-band kernel takes all windows of one row and nearly all of three: where it is passed over,
+    // so are the kernels after it
+    const bool over_rows = rows_pick && (p.H == 1 ? p.sh == 1 && p.sw == 1 : p.H == 3) && any_beats(BSP_RIVAL_ROWS);
+    for (;;) {
+      if ((allow & BSP_KERNEL_BAND) && p.H == 3 && p.K == 3 && !any_beats(BSP_RIVAL_BAND))
+        rc = bsp_launch_band(p, w->dtype, w->plan_host, st);
+      if (rc != BSP_ERR_UNSUPPORTED) return rc;
+      if ((allow & BSP_KERNEL_ROWS) && (rows_pick || w->kernels) && !any_beats(BSP_RIVAL_ROWS))
+        rc = bsp_launch_rows(p, w->dtype, w->plan_host, st);
+      if (rc != BSP_ERR_UNSUPPORTED) return rc;
+      if ((allow & BSP_KERNEL_FIRST) && p.I <= 4) rc = bsp_launch_first(p, w->dtype, w->plan_host, st);
+      if (rc != BSP_ERR_UNSUPPORTED) return rc;
+      if ((allow & BSP_KERNEL_LDS) && !(any && over_rows) && !any_beats(BSP_RIVAL_LDS))
+        rc = bsp_launch_lds(p, w->dtype, w->plan_host, st);
+      if (rc != BSP_ERR_UNSUPPORTED) return rc;
+      if ((allow & BSP_KERNEL_TILE) && chunked && !(any && over_rows) && !any_beats(BSP_RIVAL_TILE))
+        rc = bsp_launch_tile(p, w->dtype, st);
+      if (rc != BSP_ERR_UNSUPPORTED) return rc;
+      if (!any) break;
+      rc = bsp_launch_any(p, w->plan_host, st);
+      if (rc != BSP_ERR_UNSUPPORTED) return rc;
+      any = false;  // declined: what was passed over for it
+    }
   } else if (!w->kernels) {
     const int rc = bsp_launch_f32(p, w->nnzb, w->bo, w->bi, (hipStream_t)stream);
     if (rc != BSP_ERR_UNSUPPORTED) return rc;
@@ -296,7 +308,7 @@ int bsp_conv2d_i8(const bsp_weights* w, const int8_t* X, const int32_t* bias, vo
     const int rc = bsp_launch_pw_i8(p, w->plan_host, shift, (hipStream_t)stream);
     if (rc != BSP_ERR_UNSUPPORTED) return rc;
   }
-  if (y_dtype == BSP_I8 && (w->kernels ? w->kernels & BSP_KERNEL_LDS : !bsp_any_preferred(p, w->plan_host, BSP_I8)) &&
+  if (y_dtype == BSP_I8 && (w->kernels ? w->kernels & BSP_KERNEL_LDS : !bsp_any_beats_i8(p, w->plan_host)) &&
       aligned16(X)) {
     const int rc = bsp_launch_lds_i8(p, w->plan_host, shift, (hipStream_t)stream);
     if (rc != BSP_ERR_UNSUPPORTED) return rc;

@@ -6,6 +6,7 @@
 
 #include "bsp.h"
 #include "bsp_device.h"
+#include "bsp_rules.h"
 
 int bsp_launch_general(const ConvParams& p, int dtype, int bo, int bi, hipStream_t st);
 
@@ -17,8 +18,9 @@ int bsp_launch_f32(const ConvParams& p, int64_t nnzb, int bo, int bi, hipStream_
 // applicable, nothing launched.
 int bsp_launch_any(const ConvParams& p, const void* plan_host, hipStream_t st);
 int bsp_launch_any_i8(const ConvParams& p, const void* plan_host, int y_i8, int shift, hipStream_t st);
-// whether these are the faster ones on a layer that a specialised kernel takes too
-bool bsp_any_preferred(const ConvParams& p, const void* plan_host, int dtype);
+// whether these are the faster ones on a layer that `rival` (int8: the LDS-resident kernel) may take too
+bool bsp_any_beats(const ConvParams& p, const void* plan_host, BspRival rival);
+bool bsp_any_beats_i8(const ConvParams& p, const void* plan_host);
 
 // LDS-tiled bf16 kernels (need the plan's step section and I % 8 == 0).
 // BSP_ERR_UNSUPPORTED means "use the general kernel", nothing was launched.

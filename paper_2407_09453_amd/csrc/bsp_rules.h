@@ -1,0 +1,70 @@
+// Where the any-shape kernels and a specialised one both take a layer: which of the two runs it
+// (library private; plain C++, also compiled on the host by the tests).
+//
+// A specialised kernel shares a patch or a weight fragment among more products, which pays once the
+// chip is full of work; the any-shape one splits small layers finer (pixels, strips, contraction) and
+// has the shorter opening.  The lines were drawn by timing both sides on 3800 layers (the networks' and
+// random ones), along the matrix instructions of a layer (mm) and its results (po).  The last numbers
+// of each entry are `the other / here` in microseconds, on either side of a line.
+#ifndef BSP_RULES_H
+#define BSP_RULES_H
+
+#include <stdint.h>
+
+enum BspRival { BSP_RIVAL_BAND, BSP_RIVAL_ROWS, BSP_RIVAL_LDS, BSP_RIVAL_TILE };
+
+// bf16 windows: whether the any-shape kernel is to take the layer that `rival` could take (bo: output
+// channels per block).
+//   one row, row-band kernel: 1x7 17x17x160->192 batch 16 (100 861) 10.2 / 9.0, 17x17x192 batch 32 (220 218)
+//     17.5 / 13.9; 29x29x456->168 batch 4 (187 579) 13 % slower here, 57x57x272->192 batch 4 (252 030) 19 %; with
+//     16x4 blocks no line, 36x36x160->184 batch 31 (1.05 M) 66 / 40
+//   one row, LDS kernel: 1x7 31x13x248->80 (32 382) 19.8 / 7.0; 37x37x32->184 batch 28 (201 264)
+//     13.2 / 16.4; 1x3 98x32x8->144 batch 21 (37 044, po 9.5 M) 13.5 / 18.5; strided ones have no line
+//   one column: 7x1 22x22x192->104 batch 8 (62 920) 9.4 / 7.8, 17x17x160->192 batch 16 (97 K) 10.0 / 9.5,
+//     68x6x152->200 batch 11 (91 887) 9.4 / 11.0; 3x1 24x27x184 batch 20 (94 K) 11.5 / 11.6
+//   3x3, band kernel: 56x56x64 batch 1 (14 112, po 201 K) 5.8 / 5.1; 35x35x64->96 batch 4 (28 244, po
+//     470 K) 5.4 / 5.9
+//   3x3, the others: 10x10x112->336 batch 5 (15 904) 8.6 / 5.4; 111x11x40->16 batch 30 (20 610) 5.6 / 6.9;
+//     stride 2 35x35x72->224 batch 7 (58 424) 14.3 / 10.2, 39x39x8->160 batch 21 (59 910, po 5.1 M) 8.4 / 14.0
+//   larger windows, row-band kernel (three or seven rows): 3x5 13x13x184->24 batch 8 (6 860) 8.8 / 5.3,
+//     34x11x168->24 batch 27 (99 856) 7.9 / 14.4; 7x7 11x9x144->8 batch 6 (3 268) 8.0 / 5.8,
+//     18x10x288->112 batch 15 (489 086) 16.5 / 31.5
+//   larger windows, LDS kernel: 5x5 50x26x40->8 batch 7 (18 208) 11.3 / 6.4, with 4x16 blocks
+//     73x73x24->32 batch 5 (63 308) 7.0 / 8.6, 7x7 64x48x8->152 batch 32 (638 976) 23 / 51
+//   larger windows, ring-tile kernel: 5x5 25x25x248->16 batch 3 (po 30 K) 43 / 8.3, 85x85x16->448 batch 3
+//     (po 9.7 M) 15.3 / 21.8; 7x7 32x32x232->32 batch 4 (po 131 K) 66 / 13, 37x8x64->144 batch 27 (po
+//     1.2 M) 18.7 / 24.2
+inline bool bsp_any_beats_bf16(BspRival rival, int bo, int H, int K, bool strided, int64_t mm, int64_t po, int64_t I, int64_t O) {
+  if (H == 1 && K == 1) return rival == BSP_RIVAL_TILE;
+  if (H == 1) {
+    if (rival == BSP_RIVAL_ROWS) return bo == 16 || mm <= (I <= 208 ? 240000 : 120000);
+    return rival == BSP_RIVAL_TILE || strided || (mm <= (bo == 16 ? 1000000 : 120000) && po <= 4000000);
+  }
+  if (K == 1) {
+    if (rival == BSP_RIVAL_TILE) return true;
+    if (H <= 3) return mm <= 45000 && po <= 4000000;
+    if (rival == BSP_RIVAL_ROWS) return strided || mm <= 100000;
+    return (mm <= 100000 && po <= 4000000) || (strided && po <= 10000000);
+  }
+  if (H <= 3 && K <= 3) {
+    if (rival == BSP_RIVAL_TILE) return true;
+    if (rival == BSP_RIVAL_BAND) return mm <= 25000 && po <= 250000;
+    return mm <= (strided ? 60000 : 30000) && po <= 3000000;
+  }
+  if (rival == BSP_RIVAL_ROWS) return H <= 3 ? mm <= 80000 && po <= 300000 : mm <= 30000;
+  if (rival == BSP_RIVAL_LDS) return mm <= (bo == 4 ? 25000 : 80000) && po <= 3000000;
+  return H * K <= 25 ? O < 272 || po <= 1000000 : O < 136 || po <= 800000;
+}
+
+// bf16, up to 64 pixels and short rows: staged once and split over strips and contraction (7x7x2048->512
+// 9.0 -> 6.5 us, FC 64 x 2048 -> 1000 10.1 -> 6.8; from 17 pixels with 4x16 blocks, 7.7 -> 6.7; from
+// 24 to 32 with 8x8 blocks, whose streaming kernel takes 6.0 against 6.5 at 17 and 7.2 against 6.5
+// at 32; where the weights are the bulk the streaming kernels stay ahead: long rows, and with 4x16 and
+// 16x4 blocks as many strips as there are CUs or somewhat fewer, 33 x 2048 -> 4096 8.7 there against
+// 12.8, 52 x 1864 -> 3346 9.4 against 11.5).
+inline bool bsp_any_few(int bo, int64_t P, int64_t I, int64_t O, bool pointwise) {
+  if (P <= (bo == 8 ? 28 : 16) || P > 64 || I > 2048) return false;
+  return !(pointwise && bo != 8 && P > 32 && O <= 4096 && I * O > 4400000);
+}
+
+#endif

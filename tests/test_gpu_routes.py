@@ -1,0 +1,66 @@
+"""Layers on either side of the dispatcher's lines: the kernel that runs, and its results against fp64
+(needs a GPU)."""
+import numpy as np
+import pytest
+
+import paper_2407_09453_amd as bsp
+
+from gpu_util import kernels_of
+
+pytestmark = pytest.mark.gpu
+
+
+def _fp64(X, W, stride, pad):
+    """The layer in fp64, window tap by window tap."""
+    import torch
+    B, L, J, I = X.shape
+    O, H, K, _ = W.shape
+    M, N = (L + 2 * pad[0] - H) // stride + 1, (J + 2 * pad[1] - K) // stride + 1
+    Xp = torch.zeros(B, L + 2 * pad[0], J + 2 * pad[1], I, dtype=torch.float64, device="cuda")
+    Xp[:, pad[0]:pad[0] + L, pad[1]:pad[1] + J] = X.double()
+    Y = torch.zeros(B * M * N, O, dtype=torch.float64, device="cuda")
+    for h in range(H):
+        for k in range(K):
+            x = Xp[:, h:h + (M - 1) * stride + 1:stride, k:k + (N - 1) * stride + 1:stride].reshape(-1, I).contiguous()
+            Y += x @ W[:, h, k].double().t().contiguous()
+    return Y.view(B, M, N, O)
+
+
+def _draw(n, B, L, J, I, O, H, K, bo, bi):
+    import torch
+    gen = torch.Generator("cuda").manual_seed(n)
+    gamma = (np.random.default_rng(n).random((-(-O // bo), -(-I // bi))) < 0.5).astype(np.uint8)
+    gamma[0, 0] = 1
+    keep = torch.from_numpy(np.kron(gamma, np.ones((bo, bi), np.uint8))[:O, :I].copy()).cuda()
+    X = torch.randn(B, L, J, I, generator=gen, device="cuda")
+    W = torch.randn(O, H, K, I, generator=gen, device="cuda") * (2.0 / (I * H * K)) ** 0.5
+    return X, W, gamma, keep[:, None, None, :]
+
+
+BF16 = [
+    # B, L, J, I, O, H, K, stride, blocks, kernel
+    (16, 17, 17, 160, 192, 1, 7, 1, (8, 8), "conv_any"), (4, 57, 57, 272, 192, 1, 7, 1, (8, 8), "conv_rows"),
+    (28, 37, 37, 32, 184, 1, 7, 1, (4, 16), "conv_lds"), (8, 22, 22, 192, 104, 7, 1, 1, (4, 16), "conv_any"),
+    (1, 56, 56, 64, 64, 3, 3, 1, (8, 8), "conv_any"), (4, 35, 35, 64, 96, 3, 3, 1, (8, 8), "conv_band"),
+    (21, 77, 77, 8, 160, 3, 3, 2, (4, 16), "conv_lds"), (40, 34, 11, 168, 24, 3, 5, 1, (4, 16), "conv_rows"),
+    (15, 18, 10, 288, 112, 7, 7, 1, (4, 16), "conv_rows"), (5, 73, 73, 24, 32, 5, 5, 1, (4, 16), "conv_lds"),
+    (27, 37, 8, 64, 144, 7, 7, 1, (8, 8), "conv_tile"), (3, 25, 25, 248, 16, 5, 5, 1, (4, 16), "conv_any"),
+    (33, 1, 1, 2048, 4096, 1, 1, 1, (4, 16), "fc_stream"), (64, 1, 1, 2048, 1000, 1, 1, 1, (8, 8), "conv_any"),
+]
+
+
+@pytest.mark.parametrize("n", range(len(BF16)))
+def test_bf16_layers(n):
+    import torch
+    B, L, J, I, O, H, K, s, (bo, bi), kernel = BF16[n]
+    X, W, gamma, keep = _draw(n, B, L, J, I, O, H, K, bo, bi)
+    X, W = X.bfloat16(), W.bfloat16()
+    bias = np.random.default_rng(n).standard_normal(O).astype(np.float32)
+    layer = bsp.BspLayer(W.float().cpu().numpy(), gamma, bo, bi, "bf16", bias=bias)
+    pad = (H // 2, K // 2)
+    out = torch.full(layer.out_shape(B, L, J, (s, s), pad), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ran = kernels_of(lambda: layer.conv2d(X, (s, s), pad, out=out))
+    assert any(kernel in k for k in ran), ran
+    want = _fp64(X, W * keep, s, pad) + torch.from_numpy(bias).cuda()
+    scale = torch.maximum(want.abs(), want.pow(2).mean().sqrt())
+    assert bool(((out.double() - want).abs() <= 6e-3 * scale).all())   # one rounding to bf16 is 3.9e-3 at most

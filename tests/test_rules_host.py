@@ -1,0 +1,76 @@
+"""Which kernel takes a layer where several can (csrc/bsp_rules.h), compiled for the host: layers that
+were timed on both sides of every line go to the side that was faster."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include "bsp_rules.h"
+static int wrong = 0;
+static void is(bool got, bool want, const char* what) {
+  if (got != want) {
+    std::printf("%s\n", what);
+    ++wrong;
+  }
+}
+#define BEATS(want, ...) is(bsp_any_beats_bf16(__VA_ARGS__), want, #__VA_ARGS__)
+#define FEW(want, ...) is(bsp_any_few(__VA_ARGS__), want, #__VA_ARGS__)
+int main() {
+  // rival, bo, H, K, strided, matrix instructions, results, channels in and out        the other / any-shape, us
+  BEATS(true, BSP_RIVAL_ROWS, 8, 1, 7, false, 100861, 887808, 160, 192);      // 10.2 / 9.0
+  BEATS(true, BSP_RIVAL_ROWS, 8, 1, 7, false, 220218, 1775616, 192, 192);      // 17.5 / 13.9
+  BEATS(false, BSP_RIVAL_ROWS, 8, 1, 7, false, 252030, 2495232, 272, 192);     // 19 % slower
+  BEATS(true, BSP_RIVAL_ROWS, 16, 1, 7, false, 1054620, 7392384, 160, 184);   // 66 / 40
+  BEATS(true, BSP_RIVAL_LDS, 8, 1, 7, false, 32382, 161200, 248, 80);         // 19.8 / 7.0
+  BEATS(false, BSP_RIVAL_LDS, 4, 1, 7, false, 201264, 7053088, 32, 184);      // 13.2 / 16.4
+  BEATS(false, BSP_RIVAL_LDS, 16, 1, 3, false, 37044, 9483264, 8, 144);       // 13.5 / 18.5
+  BEATS(true, BSP_RIVAL_LDS, 8, 1, 7, true, 53694, 4519800, 24, 200);         // 10.8 / 11.0: no line
+  BEATS(true, BSP_RIVAL_LDS, 4, 7, 1, false, 62920, 402688, 192, 104);        // 9.4 / 7.8
+  BEATS(true, BSP_RIVAL_ROWS, 8, 7, 1, false, 97104, 887808, 160, 192);       // 10.0 / 9.5
+  BEATS(false, BSP_RIVAL_LDS, 8, 3, 1, false, 94000, 2384640, 184, 184);      // 11.5 / 11.6
+  BEATS(true, BSP_RIVAL_ROWS, 4, 7, 1, true, 174202, 659456, 328, 128);       // 19.0 / 15.2
+  BEATS(true, BSP_RIVAL_BAND, 8, 3, 3, false, 14112, 200704, 64, 64);         // 5.8 / 5.1
+  BEATS(false, BSP_RIVAL_BAND, 8, 3, 3, false, 28244, 470400, 64, 96);        // 5.4 / 5.9
+  BEATS(true, BSP_RIVAL_LDS, 8, 3, 3, false, 15904, 168000, 112, 336);        // 8.6 / 5.4
+  BEATS(true, BSP_RIVAL_LDS, 16, 3, 3, true, 58424, 1920800, 72, 224);        // 14.3 / 10.2
+  BEATS(false, BSP_RIVAL_LDS, 4, 3, 3, true, 59910, 5110560, 8, 160);         // 8.4 / 14.0
+  BEATS(true, BSP_RIVAL_ROWS, 8, 3, 5, false, 6860, 37632, 184, 24);          // 8.8 / 5.3
+  BEATS(false, BSP_RIVAL_ROWS, 4, 3, 5, false, 99856, 242352, 168, 24);       // 7.9 / 14.4
+  BEATS(true, BSP_RIVAL_ROWS, 8, 7, 7, false, 3268, 4752, 144, 8);            // 8.0 / 5.8
+  BEATS(false, BSP_RIVAL_ROWS, 4, 7, 7, false, 489086, 302400, 288, 112);     // 16.5 / 31.5
+  BEATS(true, BSP_RIVAL_LDS, 8, 5, 5, false, 18208, 72800, 40, 8);            // 11.3 / 6.4
+  BEATS(false, BSP_RIVAL_LDS, 4, 5, 5, false, 63308, 852640, 24, 32);         // 7.0 / 8.6
+  BEATS(false, BSP_RIVAL_LDS, 4, 7, 7, false, 638976, 14942208, 8, 152);      // 23 / 51
+  BEATS(true, BSP_RIVAL_TILE, 4, 5, 5, false, 21476, 30000, 248, 16);         // 43 / 8.3
+  BEATS(false, BSP_RIVAL_TILE, 16, 5, 5, false, 230350, 9710400, 16, 448);    // 15.3 / 21.8
+  BEATS(true, BSP_RIVAL_TILE, 8, 7, 7, false, 182272, 131072, 232, 32);       // 66 / 13
+  BEATS(false, BSP_RIVAL_TILE, 8, 7, 7, false, 326500, 1150848, 64, 144);     // 18.7 / 24.2
+  // pointwise layers: never before the specialised kernels, before the ring-tile kernel always
+  BEATS(false, BSP_RIVAL_ROWS, 8, 1, 1, false, 100, 1000, 64, 64);
+  BEATS(false, BSP_RIVAL_LDS, 8, 1, 1, false, 100, 1000, 64, 64);
+  BEATS(true, BSP_RIVAL_TILE, 8, 1, 1, true, 1000000, 100000000, 64, 64);
+  // block rows, pixels, channels in and out, 1x1
+  FEW(true, 8, 64, 2048, 1000, true);                                     // 10.1 / 6.8
+  FEW(false, 8, 28, 2048, 1000, true);
+  FEW(false, 8, 65, 2048, 1000, true);
+  FEW(false, 8, 64, 2056, 1000, true);
+  FEW(true, 4, 17, 2048, 1000, true);                                     // 7.7 / 6.7
+  FEW(false, 4, 33, 2048, 4096, true);                                    // 8.7 / 12.8
+  FEW(false, 16, 52, 1864, 3346, true);                                   // 9.4 / 11.5
+  FEW(true, 16, 61, 1656, 4406, true);                                    // 16.7 / 10.2
+  FEW(true, 8, 64, 2048, 4096, true);                                     // 14.3 / 13.2
+  FEW(true, 4, 49, 2048, 4096, false);                                    // a window
+  std::printf("%d\n", wrong);
+}
+"""
+
+
+def test_timed_layers_go_to_the_faster_kernel(tmp_path):
+    src = tmp_path / "rules.cpp"
+    src.write_text(PROGRAM)
+    exe = str(tmp_path / "rules")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-I", os.path.join(ROOT, "paper_2407_09453_amd", "csrc"), str(src), "-o", exe], check=True)
+    out = subprocess.run([exe], capture_output=True, text=True, check=True).stdout
+    assert out.strip() == "0", out
