@@ -48,7 +48,7 @@ struct AnyArgs {
   int32_t nstrips, NS, PG, ks, lpg, lks, nset; // strips per workgroup, pixel groups, waves that share a strip's steps; log2
   int32_t total, per_xcd;
   int32_t opitch, stream;          // bytes per pixel of the output image; its pieces are whole output lines
-  int32_t K, bo;                   // (these and the two pointers: kept_only)
+  int32_t K, lbo;                  // log2 of the block rows' height (these and the two pointers: kept_only)
   const int32_t* plan;
   const unsigned char* payload;
   FastDiv d_nset, d_tpc, d_nchunk, d_cw, d_tpw, d_ppp, d_opp;
@@ -155,11 +155,11 @@ __device__ __forceinline__ f32x4_t bias4(const AnyArgs& a, int ch) {
 // The sums of one 16 x 16 tile (a strip, and one output pixel per lane column, whose window starts at
 // iy0, ix0) from kept blocks alone.  A step of the plan multiplies a channel that one block row of the
 // strip keeps with zeros for those that drop it, which an infinity or NaN turns into NaN; here every
-// block row is summed by itself, with zeros on both sides where it drops a channel.  Straight from
-// memory, and bound by its chain of two loads per two steps: with a NaN in every image FC
-// 64 x 2048 -> 1000 takes 36 us instead of 6.3, 3x3 14x14x256 batch 1 39 instead of 5.3, 3x3
-// 47x33x100->76 batch 3 25 instead of 6.4.  Tiles of finite sums never come here; looking for the
-// others costs 0.06 us a layer.
+// block row is summed by itself, with zeros for the channels that it drops.  Straight from
+// memory, and bound by its chain of two loads per two steps: with a NaN in one image FC
+// 64 x 2048 -> 1000 takes 33 us instead of 6.3, 3x3 14x14x256 batch 1 34 instead of 5.4, 3x3
+// 47x33x100->76 batch 3 22 instead of 6.4.  Tiles of finite sums never come here; looking for the
+// others costs at most 0.05 us a layer.
 template <bool VEC>
 __device__ __forceinline__ f32x4_t kept_only(const AnyArgs& a, const unsigned char* xim, int strip, int iy0, int ix0, int lane) {
   constexpr int U = 2;
@@ -171,7 +171,7 @@ __device__ __forceinline__ f32x4_t kept_only(const AnyArgs& a, const unsigned ch
   asm volatile("" : "+v"(plan), "+v"(payload), "+v"(xim), "+v"(HK), "+v"(K), "+v"(rowb), "+v"(strip));
   const PlanView pv = plan_view(plan);
   const int c0 = pv.strip_ptr[strip], npairs = (pv.strip_ptr[strip + 1] - c0) * HK;
-  const int nrows = BSP_STRIP / a.bo, bi = 64 / a.bo, mine = jn / a.bo, at0 = (jn & (a.bo - 1)) * HK;
+  const int bi = 64 >> a.lbo, mine = jn >> a.lbo, at0 = (jn & ((1 << a.lbo) - 1)) * HK;
   f32x4_t acc[BSP_MAXSUB] = {};
   for (int q = g; q < npairs + g; q += 4 * U) {
     u32x4_t w[U], x[U];
@@ -201,19 +201,18 @@ __device__ __forceinline__ f32x4_t kept_only(const AnyArgs& a, const unsigned ch
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const u32x4_t none = {0u, 0u, 0u, 0u};
       if (bi == 4) {
         if (src[u].x < 0) x[u].x = x[u].y = 0u;
         if (src[u].y < 0) x[u].z = x[u].w = 0u;
-        acc[0] = mfma_bf16_16x16x32(w[u], x[u], acc[0]);
-      } else {
-#pragma unroll
-        for (int s = 0; s < BSP_MAXSUB; ++s)
-          if (s < nrows) acc[s] = mfma_bf16_16x16x32(mine == s ? w[u] : none, src[u][s] >= 0 ? x[u] : none, acc[s]);
+        src[u].x = 0;
       }
+      // (a block row's sums are taken from its own instruction, whatever the others made of them)
+#pragma unroll
+      for (int s = 0; s < BSP_MAXSUB; ++s)
+        acc[s] = mfma_bf16_16x16x32(w[u], src[u][s] >= 0 ? x[u] : u32x4_t{0u, 0u, 0u, 0u}, acc[s]);
     }
   }
-  const int row = 4 * g / a.bo;  // the lane's four channels lie in one block row
+  const int row = 4 * g >> a.lbo;  // the lane's four channels lie in one block row
   return row == 0 ? acc[0] : row == 1 ? acc[1] : row == 2 ? acc[2] : acc[3];
 }
 
@@ -415,17 +414,17 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
     const int lane = id & 63, g = lane >> 4, jn = lane & 15;
     const f32x4_t bv = bias4<KIND>(a, strip * BSP_STRIP + 4 * g);
     unsigned char* ot = lds + (pg * PT * 16 + jn) * opitch;
-    uint32_t bad = 0;  // tiles with a sum that is not finite
+    uint32_t bad = 0;  // bit 15 or 31: a result that is not finite (an exponent of ones carries over)
+    auto not_finite = [](uint32_t pair) { return (pair & 0x7F807F80u) + 0x00800080u; };
 #pragma unroll
     for (int t = 0; t < PT; ++t, ot += 16 * opitch) {
       if ((t & (a.ks - 1)) != k) continue;
       const f32x4_t v = add4<KIND>(acc[t], bv);  // (int32 results)
       const int c = si * BSP_STRIP + 4 * g;
       if constexpr (KIND == kBf16) {
-        *(u32x2_t*)(ot + c * 2) = u32x2_t{pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)};
-        // (the difference is not zero for an infinity or NaN)
-        const float d = (v.x - v.x) + (v.y - v.y) + (v.z - v.z) + (v.w - v.w);
-        if (__ballot(d != 0.f)) bad |= 1u << t;
+        const u32x2_t b = {pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)};
+        *(u32x2_t*)(ot + c * 2) = b;
+        bad |= not_finite(b.x) | not_finite(b.y);
       } else if (a.y32) {
         *(f32x4_t*)(ot + c * 4) = v;
       } else {
@@ -433,24 +432,26 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
       }
     }
     if constexpr (KIND == kBf16) {
-      if (bad) {
+      if (__ballot(bad & 0x80008000u)) {
         // (the arguments once more: what only this needs takes no scalar registers before)
         auto* again = (const __attribute__((address_space(4))) AnyArgs*)__builtin_amdgcn_kernarg_segment_ptr();
         asm volatile("" : "+s"(again));
         const AnyArgs& b = *(const AnyArgs*)again;
-        for (; bad; bad &= bad - 1) {
-          const int tile = pg * PT + __ffs((int)bad) - 1;
+#pragma unroll 1
+        for (int t = k; t < PT; t += b.ks) {
+          const int tile = pg * PT + t;
+          auto place = [&] { return (u32x2_t*)(lds + (tile * 16 + jn) * opitch + (si * BSP_STRIP + 4 * g) * 2); };
+          if (!__ballot((not_finite(place()->x) | not_finite(place()->y)) & 0x80008000u)) continue;
           const int p = min(p0 + tile * 16 + jn, plast);
           const int y = (int)fdiv((uint32_t)p, b.d_cw), x = col0 + p - y * b.CW;
           const f32x4_t v = kept_only<VEC>(b, b.X + (int64_t)img * b.L * b.J * b.I * 2, strip, y * b.sh - b.ph, x * b.sw - b.pw, lane) +
                             bias4<KIND>(b, strip * BSP_STRIP + 4 * g);
-          u32x2_t* const at = (u32x2_t*)(lds + (tile * 16 + jn) * opitch + (si * BSP_STRIP + 4 * g) * 2);
-          const u32x2_t was = *at, now = {pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)};
-          auto take = [](uint32_t o, uint32_t n) {  // those of the results that are not finite
-            const uint32_t m = ((o & 0x7F80u) == 0x7F80u ? 0xFFFFu : 0u) | ((o & 0x7F800000u) == 0x7F800000u ? 0xFFFF0000u : 0u);
-            return (o & ~m) | (n & m);
+          asm volatile("" ::: "memory");  // (read again, not kept)
+          auto take = [&](uint32_t was, uint32_t now) {  // those of the results that are not finite
+            const uint32_t m = (not_finite(was) >> 15 & 0x00010001u) * 0xFFFFu;
+            return (was & ~m) | (now & m);
           };
-          *at = u32x2_t{take(was.x, now.x), take(was.y, now.y)};
+          *place() = u32x2_t{take(place()->x, pack_bf16x2(v.x, v.y)), take(place()->y, pack_bf16x2(v.z, v.w))};
         }
       }
     }
@@ -571,7 +572,7 @@ int launch_kind(const ConvParams& p, const int32_t* hdr, int y32, int shift, hip
   a.wfrag = (const unsigned char*)(p.plan + hdr[BSP_PLAN_OFF_WFRAG_W]);
   a.plan = p.plan;
   a.payload = (const unsigned char*)p.payload;
-  a.bo = hdr[BSP_PLAN_BO_W];
+  a.lbo = __builtin_ctz(hdr[BSP_PLAN_BO_W]);
   a.K = p.K;
   a.relu = p.relu;
   a.shift = shift;
