@@ -585,8 +585,14 @@ int launch_gran(const ConvParams& p, int64_t nnzb, hipStream_t st) {
 
 }  // namespace
 
-int bsp_launch_f32(const ConvParams& p, int64_t nnzb, int bo, int bi, hipStream_t st) {
+int bsp_launch_f32(const ConvParams& p, int64_t nnzb, int bo, int bi, const void* plan_host, hipStream_t st) {
   if (nnzb < 1 || nnzb > 0x7FFFFFFF || !p.row_ptr || !p.col_idx) return BSP_ERR_UNSUPPORTED;
+  const int32_t* hdr = (const int32_t*)plan_host;
+  const bool flat = p.H == 1 && p.K == 1 && p.ph == 0 && p.pw == 0 && p.sh == 1 && p.sw == 1;
+  const int64_t HK = (int64_t)p.H * p.K;
+  if (bsp_f32_general(bo, p.I, p.O, HK, hdr[BSP_PLAN_NCHUNKS_W] * HK, hdr[BSP_PLAN_NSTRIPS_W], (int64_t)p.P * p.O,
+                      flat && p.P <= 256))
+    return BSP_ERR_UNSUPPORTED;
   if (bo == 8 && bi == 8) return launch_gran<8, 8>(p, nnzb, st);
   if (bo == 4 && bi == 16) return launch_gran<4, 16>(p, nnzb, st);
   if (bo == 16 && bi == 4) return launch_gran<16, 4>(p, nnzb, st);

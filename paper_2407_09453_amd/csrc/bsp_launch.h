@@ -10,8 +10,9 @@
 
 int bsp_launch_general(const ConvParams& p, int dtype, int bo, int bi, hipStream_t st);
 
-// Single-precision layers of any shape (4x4x1 matrix tiles on the compressed block rows).
-int bsp_launch_f32(const ConvParams& p, int64_t nnzb, int bo, int bi, hipStream_t st);
+// Single-precision layers of any shape (4x4x1 matrix tiles on the compressed block rows), but those that
+// the general kernel is the faster one on.
+int bsp_launch_f32(const ConvParams& p, int64_t nnzb, int bo, int bi, const void* plan_host, hipStream_t st);
 
 // Layers of any shape with at least 16 bytes of channels per pixel, from the plan's step section
 // and its host copy.  int8: y_i8 and shift as in bsp_launch_i8.  BSP_ERR_UNSUPPORTED = not

@@ -67,4 +67,24 @@ inline bool bsp_any_few(int bo, int64_t P, int64_t I, int64_t O, bool pointwise)
   return !(pointwise && bo != 8 && P > 32 && O <= 4096 && I * O > 4400000);
 }
 
+// fp32: whether the general kernel is to take the layer.  It sums a strip of sixteen channels chunk by
+// chunk and tap by tap (`pairs` of them over all strips), straight from memory: few of those are over
+// before the other kernel has staged its first patch, and its results leave in longer runs.  Timed on
+// 4100 layers, general / matrix tiles in us, pairs per strip in brackets: one chunk of input channels 1x1
+// 15x5x5->125 batch 34 with 16x4 blocks 3.9 / 9.5, 3x3 50x12x3->323 batch 50 31 / 60, 5x5 43x43x1->496
+// batch 8 [14] 51 / 23; 8x8 1x1 14x14x11->118 batch 6 [1.5] 4.3 / 6.7, 1x3 21x21x27 [7] and up the tiles, 1x3
+// 111x111x20 batch 47 [6, 7 M results] 73 / 39; 16x4 1x1 49x49x79->180 batch 25 [10, 11 M] 165 / 51.
+// The tiles' results leave as vectors where the channels out are a multiple of four, one by one where
+// they are not, which moves the line down there and up here: 4x16 1x1 58x58x25->108 batch 37 [3.7] 59 / 37,
+// 44x44x21->85 batch 33 [3] 25 / 37.  FC layers of up to 256 rows (`few`) are
+// not staged: only a single chunk is left to the general kernel, 12x4x4x5->110 3.2 / 6.2.
+inline bool bsp_f32_general(int bo, int64_t I, int64_t O, int64_t HK, int64_t pairs, int64_t strips, int64_t po, bool few) {
+  if (few) return I <= 8;
+  const bool streams = O % 4 == 0 && po > 1000000;
+  if (I <= 8 && (HK == 1 || (HK <= 9 && !streams))) return true;
+  int most = streams ? 2 : bo == 8 ? 5 : bo == 4 ? 3 : 6;
+  if (O % 4) most = bo == 8 ? 7 : bo == 4 ? 5 : 10;
+  return pairs <= most * strips;
+}
+
 #endif

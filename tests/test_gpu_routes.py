@@ -64,3 +64,28 @@ def test_bf16_layers(n):
     want = _fp64(X, W * keep, s, pad) + torch.from_numpy(bias).cuda()
     scale = torch.maximum(want.abs(), want.pow(2).mean().sqrt())
     assert bool(((out.double() - want).abs() <= 6e-3 * scale).all())   # one rounding to bf16 is 3.9e-3 at most
+
+
+F32 = [
+    (34, 15, 15, 5, 125, 1, 1, 1, (16, 4), "conv_general"), (25, 49, 49, 79, 180, 1, 1, 1, (16, 4), "conv_f32"),
+    (6, 14, 14, 11, 118, 1, 1, 1, (8, 8), "conv_general"), (4, 13, 21, 64, 102, 1, 3, 1, (8, 8), "conv_f32"),
+    (50, 50, 12, 3, 323, 3, 3, 1, (16, 4), "conv_general"), (8, 43, 43, 1, 496, 5, 5, 1, (16, 4), "conv_f32"),
+    (192, 1, 1, 5, 110, 1, 1, 1, (16, 4), "conv_general"), (192, 1, 1, 9, 110, 1, 1, 1, (16, 4), "fc_f32"),
+    (5, 20, 20, 30, 33, 1, 1, 2, (4, 16), "conv_general"), (5, 20, 20, 130, 33, 1, 1, 2, (4, 16), "conv_f32"),
+]
+
+
+@pytest.mark.parametrize("n", range(len(F32)))
+def test_f32_layers(n):
+    import torch
+    B, L, J, I, O, H, K, s, (bo, bi), kernel = F32[n]
+    X, W, gamma, keep = _draw(100 + n, B, L, J, I, O, H, K, bo, bi)
+    bias = np.random.default_rng(n).standard_normal(O).astype(np.float32)
+    layer = bsp.BspLayer(W.cpu().numpy(), gamma, bo, bi, "f32", bias=bias)
+    pad = (H // 2, K // 2)
+    out = torch.full(layer.out_shape(B, L, J, (s, s), pad), float("nan"), device="cuda")
+    ran = kernels_of(lambda: layer.conv2d(X, (s, s), pad, out=out))
+    assert any(kernel in k for k in ran), ran
+    want = _fp64(X, W * keep, s, pad) + torch.from_numpy(bias).cuda()
+    scale = torch.maximum(want.abs(), want.pow(2).mean().sqrt())
+    assert bool(((out.double() - want).abs() <= 1e-5 * scale).all())   # at most 300 terms

@@ -17,6 +17,7 @@ static void is(bool got, bool want, const char* what) {
 }
 #define BEATS(want, ...) is(bsp_any_beats_bf16(__VA_ARGS__), want, #__VA_ARGS__)
 #define FEW(want, ...) is(bsp_any_few(__VA_ARGS__), want, #__VA_ARGS__)
+#define F32(want, ...) is(bsp_f32_general(__VA_ARGS__), want, #__VA_ARGS__)
 int main() {
   // rival, bo, H, K, strided, matrix instructions, results, channels in and out        the other / any-shape, us
   BEATS(true, BSP_RIVAL_ROWS, 8, 1, 7, false, 100861, 887808, 160, 192);      // 10.2 / 9.0
@@ -62,6 +63,30 @@ int main() {
   FEW(true, 16, 61, 1656, 4406, true);                                    // 16.7 / 10.2
   FEW(true, 8, 64, 2048, 4096, true);                                     // 14.3 / 13.2
   FEW(true, 4, 49, 2048, 4096, false);                                    // a window
+  // block rows, channels in and out, window, (chunk, tap) pairs, strips, results, FC of up to 256 rows: general / tiles, us
+  F32(true, 16, 5, 125, 1, 8, 8, 318750, false);                          // 3.9 / 9.5
+  F32(true, 16, 3, 323, 9, 21 * 9, 21, 9690000, false);                   // 31 / 60
+  F32(false, 16, 1, 496, 25, 31 * 14, 31, 7336832, false);                // 51 / 23
+  F32(false, 8, 8, 64, 9, 4 * 9, 4, 6400000, false);                      // many results, by vectors
+  F32(true, 8, 8, 64, 9, 4 * 9, 4, 640000, false);
+  F32(true, 8, 8, 64, 1, 4, 4, 6400000, false);
+  F32(true, 8, 11, 118, 1, 12, 8, 138768, false);                         // 4.3 / 6.7
+  F32(false, 8, 40, 84, 3, 58, 7, 111384, false);                         // 6.7 / 5.6
+  F32(true, 8, 18, 11, 3, 11, 2, 77128, false);
+  F32(false, 8, 20, 20, 3, 12, 2, 11581740, false);                       // 73 / 39
+  F32(false, 16, 79, 180, 1, 120, 12, 10804500, false);                   // 165 / 51
+  F32(false, 4, 43, 100, 1, 6 * 27, 27, 64600, false);                    // 5.6 / 5.3
+  for (int odd = 0; odd < 2; ++odd) {                                     // the line itself, results by vectors and one by one
+    F32(true, 8, 64, 64 + odd, 1, odd ? 28 : 20, 4, 500000, false);
+    F32(false, 8, 64, 64 + odd, 1, odd ? 29 : 21, 4, 500000, false);
+    F32(true, 4, 64, 64 + odd, 1, odd ? 20 : 12, 4, 500000, false);
+    F32(false, 4, 64, 64 + odd, 1, odd ? 21 : 13, 4, 500000, false);
+    F32(true, 16, 64, 64 + odd, 1, odd ? 40 : 24, 4, 500000, false);
+    F32(false, 16, 64, 64 + odd, 1, odd ? 41 : 25, 4, 500000, false);
+    F32(odd, 8, 64, 64 + odd, 1, 9, 4, 5000000, false);
+  }
+  F32(true, 8, 5, 110, 1, 7, 7, 21120, true);                             // 3.2 / 6.2
+  F32(false, 8, 64, 64, 1, 8, 4, 4096, true);
   std::printf("%d\n", wrong);
 }
 """
