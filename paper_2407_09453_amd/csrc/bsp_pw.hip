@@ -449,7 +449,7 @@ inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 // plentiful or the tile is thin (many small workgroups hide each other's latencies), many when they are not
 // (every strip group re-reads the tile from L2, which is what bounds deep layers); whole-line
 // output for layers that widen (their output is the bulk of the traffic).
-PwChoice pw_choose(int P, int I, int O, int nstrips, int pitch, bool windowed) {
+PwChoice pw_choose(int P, int I, int O, int nstrips, int pitch, bool windowed, bool i8) {
   PwChoice c{4, 1, 1, 0};
   while (c.PT > 1 && 16 * c.PT * pitch > 128 * 1024) c.PT /= 2;
   int ns = (P >= 50000 || (I <= 128 && P >= 20000)) ? 4 : (I >= 512 ? 16 : 8);
@@ -471,6 +471,7 @@ PwChoice pw_choose(int P, int I, int O, int nstrips, int pitch, bool windowed) {
     c.PT = 2;
     c.NS = nstrips <= 8 ? nstrips : 4;
   }
+  if (i8 && nstrips < 4) c.PT = bsp_pw_thin(c.PT, pitch, c.NS);
   const int64_t xb = (int64_t)16 * c.PT * pitch, ob = (int64_t)16 * c.PT * (c.NS * 32 + 16);
   c.wout = windowed && (c.NS % 4 == 0 || c.NS >= nstrips) && O >= I && xb + ob <= kLdsLimit;
   return c;
@@ -501,7 +502,7 @@ int launch_pw(const ConvParams& p, int dtype, const void* plan_host, int shift, 
 #endif
   const int maxsteps = rs[BSP_ROWS_MAXSTRIPSTEPS_W];
   const int depth0 = maxsteps <= 2 ? 2 : maxsteps <= 4 ? 4 : 8;
-  PwChoice ch = pw_choose(p.P, raw / 2, i8 ? (1 << 30) : p.O, nstrips, pitch, rs[BSP_ROWS_WINDOW_W] == 4);
+  PwChoice ch = pw_choose(p.P, raw / 2, i8 ? (1 << 30) : p.O, nstrips, pitch, rs[BSP_ROWS_WINDOW_W] == 4, i8);
 #ifdef BSP_ROWS_TUNE  // experiments only: never defined in the product build
   if (const char* e = std::getenv("BSP_PWK_TUNE")) {
     int q[5] = {0, 0, 0, 0, 0};

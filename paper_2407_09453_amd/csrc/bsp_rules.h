@@ -67,6 +67,19 @@ inline bool bsp_any_few(int bo, int64_t P, int64_t I, int64_t O, bool pointwise)
   return !(pointwise && bo != 8 && P > 32 && O <= 4096 && I * O > 4400000);
 }
 
+// Pointwise kernel, int8 layers of one to three strips: lane tiles per wave.  A workgroup is as few waves
+// as strips and keeps its pixels in LDS, so that a wide tile leaves a CU with hardly a wave to ask for the
+// next one: tiles of 64 pixels stay while a CU holds 13 waves with them, of 32 while it holds 12 (64, 32
+// and 16 pixels, in brackets the LDS-resident kernel: 112x112x288->16 batch 16 21.0 / 15.1 / 14.4 (15.6),
+// 1008->16 58 / 44 / 36 (38), 1008->32 48 / 40 / 34 (39), 512->32 24.1 / 20.8 / 19.4 (20.1), 512->48 22.5 /
+// 20.2 / 21.8 (20.6), 144->32 9.1 / 8.4 / 12.0 (12.8), 144->48 9.7 / 10.8 / 16.4 (13.7)).
+inline int bsp_pw_thin(int PT, int64_t pitch, int NS) {
+  auto waves = [&](int pt) { return 160 * 1024 / (16 * pt * (pitch + NS * 16 + 16)) * NS; };
+  if (PT == 4 && waves(4) < 13) PT = 2;
+  if (PT == 2 && waves(2) < 12) PT = 1;
+  return PT;
+}
+
 // fp32: whether the general kernel is to take the layer.  It sums a strip of sixteen channels chunk by
 // chunk and tap by tap (`pairs` of them over all strips), straight from memory: few of those are over
 // before the other kernel has staged its first patch, and its results leave in longer runs.  Timed on

@@ -89,3 +89,33 @@ def test_f32_layers(n):
     want = _fp64(X, W * keep, s, pad) + torch.from_numpy(bias).cuda()
     scale = torch.maximum(want.abs(), want.pow(2).mean().sqrt())
     assert bool(((out.double() - want).abs() <= 1e-5 * scale).all())   # at most 300 terms
+
+
+def _i8_layer(n, B, L, J, I, O, H, K, bo, bi):
+    """A layer of codes and its exact sums (fp64 holds them)."""
+    import torch
+    gen = torch.Generator("cuda").manual_seed(n)
+    X, _, gamma, keep = _draw(n, 1, 1, 1, I, O, 1, 1, bo, bi)
+    X = torch.randint(-128, 128, (B, L, J, I), generator=gen, device="cuda", dtype=torch.int8)
+    W = torch.randint(-128, 128, (O, H, K, I), generator=gen, device="cuda", dtype=torch.int8)
+    bias = np.random.default_rng(n).integers(-40000, 40000, O, dtype=np.int32)
+    return bsp.BspLayerI8(W.cpu().numpy(), gamma, bo, bi, bias=bias), X, W * keep, torch.from_numpy(bias).cuda()
+
+
+def _rescale(acc, shift):
+    import torch
+    return ((acc + ((1 << shift) >> 1)) >> shift).clamp(-128, 127).to(torch.int8)
+
+
+@pytest.mark.parametrize("O", (16, 32, 48, 64))
+@pytest.mark.parametrize("I", (144, 272, 640, 1008))
+@pytest.mark.parametrize("B,L", ((2, 57), (29, 56)))
+def test_i8_pointwise_layers_of_few_strips(B, L, I, O):
+    """Every lane tile that the pointwise kernel's choice ends at, pixels that do not fill the last one."""
+    import torch
+    bo, bi = ((8, 8), (4, 16), (16, 4))[(O // 16 + I) % 3]
+    layer, X, W, bias = _i8_layer(O + I, B, L, L - 1, I, O, 1, 1, bo, bi)
+    out = torch.full((B, L, L - 1, O), 77, dtype=torch.int8, device="cuda")
+    ran = kernels_of(lambda: layer.conv2d(X, shift=9, out=out))
+    assert any("conv_pw" in k for k in ran), ran
+    assert torch.equal(out, _rescale(_fp64(X, W, 1, (0, 0)).to(torch.int64) + bias, 9))

@@ -17,6 +17,7 @@ static void is(bool got, bool want, const char* what) {
 }
 #define BEATS(want, ...) is(bsp_any_beats_bf16(__VA_ARGS__), want, #__VA_ARGS__)
 #define FEW(want, ...) is(bsp_any_few(__VA_ARGS__), want, #__VA_ARGS__)
+#define THIN(want, ...) is(bsp_pw_thin(__VA_ARGS__) == want, true, #__VA_ARGS__)
 #define F32(want, ...) is(bsp_f32_general(__VA_ARGS__), want, #__VA_ARGS__)
 int main() {
   // rival, bo, H, K, strided, matrix instructions, results, channels in and out        the other / any-shape, us
@@ -63,6 +64,21 @@ int main() {
   FEW(true, 16, 61, 1656, 4406, true);                                    // 16.7 / 10.2
   FEW(true, 8, 64, 2048, 4096, true);                                     // 14.3 / 13.2
   FEW(true, 4, 49, 2048, 4096, false);                                    // a window
+  // lane tiles, bytes of a pixel, strips
+  THIN(2, 4, 256, 1);
+  THIN(1, 4, 512, 1);
+  THIN(1, 4, 1024, 1);
+  THIN(4, 4, 128, 1);
+  THIN(4, 4, 256, 2);
+  THIN(2, 4, 512, 2);
+  THIN(2, 4, 768, 2);
+  THIN(1, 4, 1024, 2);
+  THIN(4, 4, 256, 3);
+  THIN(2, 4, 512, 3);
+  THIN(2, 4, 1024, 3);
+  THIN(2, 2, 256, 1);
+  THIN(1, 2, 512, 1);
+  THIN(1, 1, 128, 1);
   // block rows, channels in and out, window, (chunk, tap) pairs, strips, results, FC of up to 256 rows: general / tiles, us
   F32(true, 16, 5, 125, 1, 8, 8, 318750, false);                          // 3.9 / 9.5
   F32(true, 16, 3, 323, 9, 21 * 9, 21, 9690000, false);                   // 31 / 60
