@@ -308,13 +308,15 @@ int bsp_conv2d_i8(const bsp_weights* w, const int8_t* X, const int32_t* bias, vo
     const int rc = bsp_launch_pw_i8(p, w->plan_host, shift, (hipStream_t)stream);
     if (rc != BSP_ERR_UNSUPPORTED) return rc;
   }
-  if (y_dtype == BSP_I8 && (w->kernels ? w->kernels & BSP_KERNEL_LDS : !bsp_any_beats_i8(p, w->plan_host)) &&
-      aligned16(X)) {
+  const bool lds = y_dtype == BSP_I8 && aligned16(X) && (!w->kernels || (w->kernels & BSP_KERNEL_LDS));
+  const bool any = !w->kernels;
+  if (lds && !(any && bsp_any_beats_i8(p, w->plan_host))) {
     const int rc = bsp_launch_lds_i8(p, w->plan_host, shift, (hipStream_t)stream);
     if (rc != BSP_ERR_UNSUPPORTED) return rc;
   }
-  if (!w->kernels) {
-    const int rc = bsp_launch_any_i8(p, w->plan_host, y_dtype == BSP_I8, shift, (hipStream_t)stream);
+  if (any) {
+    int rc = bsp_launch_any_i8(p, w->plan_host, y_dtype == BSP_I8, shift, (hipStream_t)stream);
+    if (rc == BSP_ERR_UNSUPPORTED && lds) rc = bsp_launch_lds_i8(p, w->plan_host, shift, (hipStream_t)stream);
     if (rc != BSP_ERR_UNSUPPORTED) return rc;
   }
   return bsp_launch_i8(p, y_dtype == BSP_I8, y_dtype == BSP_I8 ? shift : 0, w->bo, w->bi,

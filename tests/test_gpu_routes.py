@@ -107,6 +107,18 @@ def _rescale(acc, shift):
     return ((acc + ((1 << shift) >> 1)) >> shift).clamp(-128, 127).to(torch.int8)
 
 
+def test_i8_activations_beyond_the_any_shape_kernels_reach():
+    """Between 2 and 4 GiB of a pointwise layer's codes, several slabs: the LDS-resident kernel takes them."""
+    import torch
+    B, L, I, O = 53, 252, 640, 48
+    layer, X, W, bias = _i8_layer(300, B, L, L, I, O, 1, 1, 8, 8)
+    out = torch.full((B, L, L, O), 77, dtype=torch.int8, device="cuda")
+    ran = kernels_of(lambda: layer.conv2d(X, shift=9, out=out))
+    assert X.numel() >= 1 << 31 and any("conv_lds" in k for k in ran), ran
+    for b in (0, B // 2, B - 1):
+        assert torch.equal(out[b:b + 1], _rescale(_fp64(X[b:b + 1], W, 1, (0, 0)).to(torch.int64) + bias, 9))
+
+
 @pytest.mark.parametrize("O", (16, 32, 48, 64))
 @pytest.mark.parametrize("I", (144, 272, 640, 1008))
 @pytest.mark.parametrize("B,L", ((2, 57), (29, 56)))
