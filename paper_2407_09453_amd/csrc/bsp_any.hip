@@ -713,12 +713,10 @@ bool bsp_any_beats(const ConvParams& p, const void* plan_host, BspRival rival) {
                                    (int64_t)((p.P + 15) / 16) * hdr[BSP_PLAN_NSTEPS_W], (int64_t)p.P * p.O, p.I, p.O);
 }
 
-// int8 against the LDS-resident kernel, which keeps one slab's weights in LDS: several slabs always
-// (7x7x512 batch 32 15.2 / 11.5), one slab below 20 K matrix instructions (1x1 56x56x64->256 batch 2 6.4 / 5.0,
-// batch 32 21 / 31).
 bool bsp_any_beats_i8(const ConvParams& p, const void* plan_host) {
   const int32_t* hdr = plan_of(p, BSP_I8, plan_host);
-  return hdr && (hdr[BSP_PLAN_NSLABS_W] > 1 || (int64_t)((p.P + 15) / 16) * hdr[BSP_PLAN_NSTEPS_W] <= 20000);
+  return hdr && bsp_any_beats_lds_i8(hdr[BSP_PLAN_NSLABS_W], (int64_t)p.H * p.K, p.P, p.O,
+                                     (int64_t)((p.P + 15) / 16) * hdr[BSP_PLAN_NSTEPS_W]);
 }
 
 int bsp_launch_any(const ConvParams& p, const void* plan_host, hipStream_t st) {

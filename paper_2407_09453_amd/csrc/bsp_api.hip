@@ -309,7 +309,8 @@ int bsp_conv2d_i8(const bsp_weights* w, const int8_t* X, const int32_t* bias, vo
     if (rc != BSP_ERR_UNSUPPORTED) return rc;
   }
   const bool lds = y_dtype == BSP_I8 && aligned16(X) && (!w->kernels || (w->kernels & BSP_KERNEL_LDS));
-  const bool any = !w->kernels;
+  const bool alone = y_dtype != BSP_I8 || p.I % 16 || p.O % 16;  // no other kernel but the any-shape one takes it
+  const bool any = !w->kernels && !(alone && bsp_i8_general(p.I, p.O, (int64_t)p.H * p.K, (int64_t)p.P * p.O));
   if (lds && !(any && bsp_any_beats_i8(p, w->plan_host))) {
     const int rc = bsp_launch_lds_i8(p, w->plan_host, shift, (hipStream_t)stream);
     if (rc != BSP_ERR_UNSUPPORTED) return rc;

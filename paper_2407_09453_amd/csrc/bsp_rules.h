@@ -67,6 +67,30 @@ inline bool bsp_any_few(int bo, int64_t P, int64_t I, int64_t O, bool pointwise)
   return !(pointwise && bo != 8 && P > 32 && O <= 4096 && I * O > 4400000);
 }
 
+// int8 against the LDS-resident kernel, which keeps one slab's weights in LDS.  One slab (other us /
+// any-shape us): below 20 K matrix instructions, 1x1 56x56x64->256 batch 2 6.4 / 5.0, batch 32 21 / 31.
+// Several slabs: always for a window, 7x7x512 batch 32 15.2 / 11.5, 2x2 47x47x208->32 batch 61 21 / 14, 25x25x624->192
+// batch 29 41 / 35 (a few of many channels out go the other way, 28x28x512 batch 16 49 / 52, 3x1 73x73x192->160
+// batch 59 99 / 121, but their neighbours do not, 23x23x624->416 batch 37 102 / 73, 62x62x208->176 batch 45 57 /
+// 53).  Not narrow 1x1 layers of large images (65536 pixels and more, the pointwise kernel has the others):
+// 600x600x640->16 57 / 95, ->32 58 / 69, ->48 62 / 62, 300x300x640->16 23 / 17.
+inline bool bsp_any_beats_lds_i8(int nslabs, int64_t HK, int64_t P, int64_t O, int64_t mm) {
+  if (nslabs == 1) return mm <= 20000;
+  return HK > 1 || O >= 48 || P <= 100000;
+}
+
+// int8, layers of no other kernel (32-bit results, or channels that are not whole pieces): one or two
+// products per pixel tile are over before a patch is staged (general / any-shape us: 16->16 on 6840 pixels
+// 3.2 / 4.0, 24->40 on 6647 3.3 / 4.0; three products, 40->504 on 246, are 3.4 / 4.0 at the worst and even
+// on the whole).  Many results leave better through the any-shape kernel's LDS image (16->32 on 114308
+// 9.4 / 7.8) but for very many of whole rows (16->592 on 113535 62 / 82, 32->432 on 83810 32 / 41, 32->384 on
+// 31000 16.8 / 16.2).  Channels in that are not whole eights are loaded one by one in the general kernel:
+// two products 0.88 times its time, three 0.75.
+inline bool bsp_i8_general(int64_t I, int64_t O, int64_t HK, int64_t po) {
+  if (HK != 1 || I > 32 || I % 8) return false;
+  return po <= 1000000 || (O % 16 == 0 && po > (I <= 16 ? 5000000 : 20000000));
+}
+
 // Pointwise kernel, int8 layers of one to three strips: lane tiles per wave.  A workgroup is as few waves
 // as strips and keeps its pixels in LDS, so that a wide tile leaves a CU with hardly a wave to ask for the
 // next one: tiles of 64 pixels stay while a CU holds 13 waves with them, of 32 while it holds 12 (64, 32

@@ -107,6 +107,32 @@ def _rescale(acc, shift):
     return ((acc + ((1 << shift) >> 1)) >> shift).clamp(-128, 127).to(torch.int8)
 
 
+I8 = [
+    # B, L, J, I, O, H, K, stride, blocks, 8-bit results, kernel
+    (11, 23, 26, 24, 40, 1, 1, 1, (16, 4), True, "conv_general"), (11, 23, 26, 22, 40, 1, 1, 1, (16, 4), True, "conv_any"),
+    (9, 28, 30, 16, 16, 1, 1, 1, (4, 16), False, "conv_general"), (9, 28, 30, 40, 16, 1, 1, 1, (8, 8), False, "conv_any"),
+    (25, 39, 41, 32, 32, 1, 1, 1, (8, 8), False, "conv_any"), (25, 39, 41, 16, 80, 1, 1, 2, (16, 4), False, "conv_general"),
+    (25, 79, 41, 16, 112, 1, 1, 1, (8, 8), False, "conv_general"), (25, 79, 41, 24, 112, 1, 1, 1, (8, 8), False, "conv_any"),
+    (1, 330, 331, 640, 32, 1, 1, 1, (8, 8), True, "conv_lds"), (1, 330, 331, 640, 48, 1, 1, 1, (8, 8), True, "conv_any"),
+    (16, 37, 38, 144, 80, 1, 3, 1, (4, 16), True, "conv_any"), (35, 37, 37, 176, 160, 1, 5, 1, (4, 16), True, "conv_any"),
+    (32, 7, 7, 512, 512, 3, 3, 1, (8, 8), True, "conv_any"), (50, 32, 32, 192, 64, 3, 3, 1, (8, 8), True, "conv_any"),
+]
+
+
+@pytest.mark.parametrize("n", range(len(I8)))
+def test_i8_layers(n):
+    import torch
+    B, L, J, I, O, H, K, s, (bo, bi), y8, kernel = I8[n]
+    layer, X, W, bias = _i8_layer(200 + n, B, L, J, I, O, H, K, bo, bi)
+    pad = (H // 2, K // 2)
+    dt = torch.int8 if y8 else torch.int32
+    out = torch.full(layer.out_shape(B, L, J, (s, s), pad), 77, dtype=dt, device="cuda")
+    ran = kernels_of(lambda: layer.conv2d(X, (s, s), pad, shift=9 if y8 else None, out=out))
+    assert any(kernel in k for k in ran), ran
+    acc = _fp64(X, W, s, pad).to(torch.int64) + bias
+    assert torch.equal(out, _rescale(acc, 9) if y8 else acc.int())
+
+
 def test_i8_activations_beyond_the_any_shape_kernels_reach():
     """Between 2 and 4 GiB of a pointwise layer's codes, several slabs: the LDS-resident kernel takes them."""
     import torch

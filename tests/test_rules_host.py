@@ -17,6 +17,8 @@ static void is(bool got, bool want, const char* what) {
 }
 #define BEATS(want, ...) is(bsp_any_beats_bf16(__VA_ARGS__), want, #__VA_ARGS__)
 #define FEW(want, ...) is(bsp_any_few(__VA_ARGS__), want, #__VA_ARGS__)
+#define LDS8(want, ...) is(bsp_any_beats_lds_i8(__VA_ARGS__), want, #__VA_ARGS__)
+#define GEN8(want, ...) is(bsp_i8_general(__VA_ARGS__), want, #__VA_ARGS__)
 #define THIN(want, ...) is(bsp_pw_thin(__VA_ARGS__) == want, true, #__VA_ARGS__)
 #define F32(want, ...) is(bsp_f32_general(__VA_ARGS__), want, #__VA_ARGS__)
 int main() {
@@ -64,6 +66,30 @@ int main() {
   FEW(true, 16, 61, 1656, 4406, true);                                    // 16.7 / 10.2
   FEW(true, 8, 64, 2048, 4096, true);                                     // 14.3 / 13.2
   FEW(true, 4, 49, 2048, 4096, false);                                    // a window
+  // int8: slabs, window, pixels, channels out, matrix instructions: LDS-resident / any-shape, us
+  LDS8(true, 1, 1, 6272, 256, 6272);                                      // 6.4 / 5.0
+  LDS8(false, 1, 1, 100352, 256, 100352);                                 // 21 / 31
+  LDS8(true, 4, 9, 1568, 512, 216000);                                    // 15.2 / 11.5
+  LDS8(false, 2, 1, 360000, 16, 225000);                                  // 57 / 95
+  LDS8(false, 2, 1, 360000, 32, 450000);                                  // 58 / 69
+  LDS8(true, 2, 1, 360000, 48, 675000);                                   // 62 / 62
+  LDS8(true, 2, 1, 90000, 16, 56250);                                     // 23 / 17
+  LDS8(true, 2, 4, 134749, 32, 210550);                                   // 21 / 14
+  LDS8(true, 5, 9, 18125, 192, 1120537);                                  // 41 / 35
+  // int8: channels in and out, window, results: general / any-shape, us
+  GEN8(true, 16, 16, 1, 109440);                                          // 3.2 / 4.0
+  GEN8(true, 24, 40, 1, 265880);                                          // 3.3 / 4.0
+  GEN8(true, 32, 16, 1, 1000000);
+  GEN8(false, 32, 16, 1, 1000016);
+  GEN8(true, 16, 592, 1, 67212720);                                       // 62 / 82
+  GEN8(false, 16, 352, 1, 4066304);                                       // 10.1 / 7.8
+  GEN8(false, 16, 24, 1, 6000000);
+  GEN8(false, 24, 16, 1, 8000000);
+  GEN8(true, 32, 432, 1, 36205920);                                       // 32 / 41
+  GEN8(false, 32, 384, 1, 12000000);                                      // 16.8 / 16.2
+  GEN8(false, 40, 16, 1, 1000);
+  GEN8(false, 17, 16, 1, 1000);
+  GEN8(false, 16, 16, 3, 1000);
   // lane tiles, bytes of a pixel, strips
   THIN(2, 4, 256, 1);
   THIN(1, 4, 512, 1);
