@@ -499,9 +499,7 @@ Pick choose(int B, int M, int N, int os, int nstrips, int steps, int nslabs, int
   for (int PT : {1, 2, 4})
     for (int PG : {1, 2, 4, 8}) {
       const int px = PT * 16 * PG;
-      for (int nc = 1; nc <= (flat ? 1 : cdiv(N, 8)); ++nc) {
-        const int cw = flat ? px : cdiv(N, nc);
-        if (!flat && cw > 64) continue;
+      const auto width = [&](int cw) {
         const int64_t nchunk = cdiv(N, cw), tpc = cdiv((int64_t)M * cw, px), tiles = (int64_t)B * nchunk * tpc;
         const int orows = std::min(M, px % cw == 0 ? px / cw : (px - 2) / cw + 2);
         const int trows = (orows - 1) * lsh + H, tpw = (cw - 1) * lsw + K;
@@ -533,7 +531,11 @@ Pick choose(int B, int M, int N, int os, int nstrips, int steps, int nslabs, int
             }
           if (spst == 1) break;
         }
-      }
+      };
+      if (flat)
+        width(px);
+      else
+        bsp_widths(N, 8, width);
     }
   return best;
 }
@@ -615,14 +617,17 @@ int launch_kind(const ConvParams& p, const int32_t* hdr, int y32, int shift, hip
     static std::map<std::array<int32_t, 12>, Pick> memo;
     const int steps = cdiv(hdr[BSP_PLAN_NSTEPS_W], a.nstrips);
     const std::array<int32_t, 12> key = {B, a.M, a.N, p.I, p.O, p.H, p.K, p.sh * 2 + flat, p.sw, steps, a.nslabs, os};
-    std::lock_guard<std::mutex> lock(mu);
-    auto it = memo.find(key);
-    if (it == memo.end()) {
+    std::unique_lock<std::mutex> lock(mu);
+    const auto it = memo.find(key);
+    if (it != memo.end()) {
+      best = it->second;
+    } else {
+      lock.unlock();  // other layers' launches do not wait for this one's search
+      best = choose(B, a.M, a.N, os, a.nstrips, steps, a.nslabs, slab_pieces, pieces, p.H, p.K, a.lsh, a.lsw, flat);
+      lock.lock();
       if (memo.size() > 4096) memo.clear();
-      it = memo.emplace(key, choose(B, a.M, a.N, os, a.nstrips, steps, a.nslabs, slab_pieces, pieces, p.H, p.K, a.lsh, a.lsw, flat))
-               .first;
+      memo.emplace(key, best);
     }
-    best = it->second;
   }
 #ifdef BSP_ROWS_TUNE  // experiments only: never defined in the product build
   if (const char* e = std::getenv("BSP_ANY_TUNE")) {

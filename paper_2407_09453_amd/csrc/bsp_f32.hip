@@ -422,9 +422,7 @@ Pick choose(int B, int M, int N, int I, int nbr, int H, int K, int lsh, int lsw,
   for (int PT : {1, 2, 4}) {
     if (PT * NQ > 8) continue;  // (accumulator registers)
     const int px = PT * 64;
-    for (int nc = 1; nc <= (flat ? 1 : cdiv(N, 4)); ++nc) {
-      const int cw = flat ? px : cdiv(N, nc);
-      if (cw > 64 && !flat) continue;
+    const auto width = [&](int cw) {
       const int64_t nchunk = cdiv(N, cw), tpc = cdiv((int64_t)M * cw, px), tiles = (int64_t)B * nchunk * tpc;
       const int orows = std::min(M, px % cw == 0 ? px / cw : (px - 2) / cw + 2);
       const int trows = (orows - 1) * lsh + H, tpw = (cw - 1) * lsw + K;
@@ -458,7 +456,11 @@ Pick choose(int B, int M, int N, int I, int nbr, int H, int K, int lsh, int lsw,
           }
         }
       }
-    }
+    };
+    if (flat)
+      width(px);
+    else
+      bsp_widths(N, 4, width);
   }
   return best;
 }
@@ -535,13 +537,17 @@ int launch_gran(const ConvParams& p, int64_t nnzb, hipStream_t st) {
     static std::mutex mu;
     static std::map<std::array<int32_t, 9>, Pick> memo;
     const std::array<int32_t, 9> key = {B, a.M, a.N, p.I, p.O, p.H, p.K, p.sh * 2 + flat, p.sw};
-    std::lock_guard<std::mutex> lock(mu);
-    auto it = memo.find(key);
-    if (it == memo.end()) {
+    std::unique_lock<std::mutex> lock(mu);
+    const auto it = memo.find(key);
+    if (it != memo.end()) {
+      best = it->second;
+    } else {
+      lock.unlock();  // other layers' launches do not wait for this one's search
+      best = choose(B, a.M, a.N, p.I, a.nbr, p.H, p.K, a.lsh, a.lsw, flat, BO / 4, BI);
+      lock.lock();
       if (memo.size() > 4096) memo.clear();
-      it = memo.emplace(key, choose(B, a.M, a.N, p.I, a.nbr, p.H, p.K, a.lsh, a.lsw, flat, BO / 4, BI)).first;
+      memo.emplace(key, best);
     }
-    best = it->second;
   }
   if (best.PT == 0) return BSP_ERR_UNSUPPORTED;
   a.CW = best.CW;

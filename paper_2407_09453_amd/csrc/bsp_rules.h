@@ -124,4 +124,16 @@ inline bool bsp_f32_general(int bo, int64_t I, int64_t O, int64_t HK, int64_t pa
   return pairs <= most * strips;
 }
 
+// The widths of at most 64 columns that up to ceil(N / least) even chunks of N columns have, each once, the
+// widest first: 64 of them at the most, however wide the image is.
+template <typename F>
+inline void bsp_widths(int64_t N, int least, F&& each) {
+  for (int64_t nc = (N + 63) / 64; nc <= (N + least - 1) / least;) {
+    const int cw = (int)((N + nc - 1) / nc);
+    each(cw);
+    if (cw == 1) return;
+    nc = (N + cw - 2) / (cw - 1);  // the fewest chunks that are narrower
+  }
+}
+
 #endif

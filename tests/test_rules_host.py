@@ -7,6 +7,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 PROGRAM = r"""
 #include <cstdio>
+#include <vector>
 #include "bsp_rules.h"
 static int wrong = 0;
 static void is(bool got, bool want, const char* what) {
@@ -129,6 +130,20 @@ int main() {
   }
   F32(true, 8, 5, 110, 1, 7, 7, 21120, true);                             // 3.2 / 6.2
   F32(false, 8, 64, 64, 1, 8, 4, 4096, true);
+  // the widths that a tile's search tries: those of every even cut, and few of them on the widest image
+  for (int least : {4, 8})
+    for (int64_t N = 1; N <= 3000; ++N) {
+      std::vector<int> got, want;
+      bsp_widths(N, least, [&](int cw) { got.push_back(cw); });
+      for (int64_t nc = 1; nc <= (N + least - 1) / least; ++nc) {
+        const int cw = (int)((N + nc - 1) / nc);
+        if (cw <= 64 && (want.empty() || want.back() != cw)) want.push_back(cw);
+      }
+      is(got == want, true, "bsp_widths");
+    }
+  int tried = 0;
+  bsp_widths(0x7FFFFFFF, 4, [&](int) { ++tried; });
+  is(tried <= 61, true, "bsp_widths on the widest image");
   std::printf("%d\n", wrong);
 }
 """
