@@ -73,3 +73,19 @@ def kernels_of(call):
     if not names:
         pytest.skip("the profiler records no kernels here")
     return names
+
+
+def conv_fp64(X, W, stride, pad):
+    """The layer in fp64 on the GPU, window tap by window tap (for layers that the oracle takes long over)."""
+    import torch
+    B, L, J, I = X.shape
+    O, H, K, _ = W.shape
+    M, N = (L + 2 * pad[0] - H) // stride + 1, (J + 2 * pad[1] - K) // stride + 1
+    Xp = torch.zeros(B, L + 2 * pad[0], J + 2 * pad[1], I, dtype=torch.float64, device="cuda")
+    Xp[:, pad[0]:pad[0] + L, pad[1]:pad[1] + J] = X.double()
+    Y = torch.zeros(B * M * N, O, dtype=torch.float64, device="cuda")
+    for h in range(H):
+        for k in range(K):
+            x = Xp[:, h:h + (M - 1) * stride + 1:stride, k:k + (N - 1) * stride + 1:stride].reshape(-1, I).contiguous()
+            Y += x @ W[:, h, k].double().t().contiguous()
+    return Y.view(B, M, N, O)

@@ -4,9 +4,10 @@ import numpy as np
 import pytest
 
 import oracle
+import paper_2407_09453_amd as bsp
 from synthetic import draw_layer
 
-from gpu_util import TOL, make_layer, to_device, to_host
+from gpu_util import TOL, conv_fp64, kernels_of, make_layer, to_device, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -62,3 +63,61 @@ def test_f32_shapes(bo, bi, fused):
             ref = oracle.conv2d(c.X, c.W, c.bias, c.gamma, bo, bi, c.stride, c.pad)
         torch.cuda.synchronize()
         _assert_close(to_host(Y), ref, I * H * K, f"shape {n}")
+
+
+def _check_on_gpu(kernel, gran, B, L, J, I, O, H, K, s, density):
+    """One layer against fp64, its kept blocks drawn block row by block row with the given densities in
+    turn; `kernel` is what has to run it."""
+    import torch
+    bo, bi = gran
+    gen = torch.Generator("cuda").manual_seed(I + O)
+    rng = np.random.default_rng(I + O)
+    nbr, nbc = -(-O // bo), -(-I // bi)
+    gamma = (rng.random((nbr, nbc)) < np.resize(density, nbr)[:, None]).astype(np.uint8)
+    keep = torch.from_numpy(np.kron(gamma, np.ones(gran, np.uint8))[:O, :I].copy()).cuda()[:, None, None, :]
+    X = torch.randn(B, L, J, I, generator=gen, device="cuda")
+    W = torch.randn(O, H, K, I, generator=gen, device="cuda")
+    R = torch.randn((B, (L - 1) // s + 1, (J - 1) // s + 1, O), generator=gen, device="cuda")
+    bias = rng.standard_normal(O).astype(np.float32)
+    layer = bsp.BspLayer(W.cpu().numpy(), gamma, bo, bi, "f32", bias=bias)
+    ref = conv_fp64(X, W * keep, s, (H // 2, K // 2)) + torch.from_numpy(bias).cuda()
+    rms = ref.pow(2).mean().sqrt()
+    terms = max(float(max(density)) * I * H * K, 24)
+    sigma = (terms / 6) ** 0.5 * 2.0 ** -24     # of a sum of so many terms, as above
+    for fused in (False, True):
+        Y = torch.full(tuple(R.shape), float("nan"), device="cuda")
+        args = dict(residual=R, relu=True) if fused else {}
+        ran = kernels_of(lambda: layer.conv2d(X, (s, s), (H // 2, K // 2), out=Y, **args))
+        assert any(kernel in k for k in ran), ran
+        want = (ref + R).clamp_min(0) if fused else ref
+        err = (Y - want).abs()
+        assert bool((err <= max(TOL["f32"], 8 * sigma) * torch.maximum(ref.abs(), rms)).all()), (gran, fused)
+        assert float(err.pow(2).mean().sqrt() / rms) <= 2 * sigma, (gran, fused)
+
+
+GRANS = [(8, 8), (4, 16), (16, 4)]
+UNEVEN = (1.0, 0.83, 0.0, 0.6, 0.97)
+
+
+@pytest.mark.parametrize("gran", GRANS)
+@pytest.mark.parametrize("shape", [(16, 28, 28, 61, 1, 1, 1), (8, 57, 57, 109, 1, 1, 2), (12, 57, 57, 109, 1, 3, 1)])
+def test_rows_of_more_than_64_blocks(gran, shape):
+    """Many pixels, so that no two waves share a row of up to 138 blocks: a wave asks for the row's next 64
+    columns in the middle of a slab, at another place in every row; one row is empty."""
+    B, L, J, O, H, K, s = shape
+    _check_on_gpu("conv_f32<%d, %d" % gran, gran, B, L, J, gran[1] * 138 - 3, O, H, K, s, UNEVEN)
+
+
+@pytest.mark.parametrize("gran", GRANS)
+@pytest.mark.parametrize("shape", [(63, 55, 57, 93, 205, 1, 1, 1), (63, 55, 57, 93, 204, 1, 1, 2), (32, 56, 57, 29, 205, 3, 3, 1)])
+def test_widest_pixel_tiles(gran, shape):
+    """Four lane tiles a wave (two with 16x4 blocks), ragged channels and pixels that do not fill the last tile."""
+    tiles = 2 if gran[0] == 16 else 4
+    _check_on_gpu("conv_f32<%d, %d, %d>" % (*gran, tiles), gran, *shape, (1.0, 0.9, 0.7))
+
+
+@pytest.mark.parametrize("gran", GRANS)
+@pytest.mark.parametrize("rows", [1, 65])
+def test_fc_rows_of_more_than_64_blocks_a_wave(gran, rows):
+    """Long rows without staging: sixteen waves share them, 128 blocks each and a few more."""
+    _check_on_gpu("fc_f32<%d, %d>" % gran, gran, rows, 1, 1, gran[1] * (16 * 128 + 3) - 1, 37, 1, 1, 1, (1.0, 0.96, 0.0))

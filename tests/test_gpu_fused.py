@@ -1,9 +1,11 @@
-"""Fused residual / ReLU epilogue: every kernel of the dispatcher against the oracle, and
-against the unfused HIP layer followed by torch's element-wise ops (needs a GPU)."""
+"""Fused residual / ReLU epilogue: the dispatcher's choice, and the LDS-resident and the ring-tile
+kernel alone, against the oracle, and against the unfused HIP layer followed by torch's element-wise
+ops (needs a GPU)."""
 import numpy as np
 import pytest
 
 import oracle
+import paper_2407_09453_amd as bsp
 from synthetic import draw_layer
 
 from gpu_util import assert_close, make_layer, to_device, to_host
@@ -11,13 +13,13 @@ from gpu_util import assert_close, make_layer, to_device, to_host
 pytestmark = pytest.mark.gpu
 
 SHAPES = [
-    # B, L, J, I, O, H, K, stride, pad                       (kernel the dispatcher picks)
+    # B, L, J, I, O, H, K, stride, pad               (what takes the bf16 layer alone, or has it)
     (2, 20, 20, 64, 64, 3, 3, (1, 1), (1, 1)),       # LDS-resident, one slab
     (1, 14, 14, 192, 128, 3, 3, (1, 1), (1, 1)),     # LDS-resident, three slabs
     (3, 13, 13, 128, 96, 1, 1, (1, 1), (0, 0)),      # LDS-resident, pointwise
     (1, 12, 12, 16, 16, 5, 5, (1, 1), (2, 2)),       # ring-tile kernel (5x5 window)
     (8, 1, 1, 512, 48, 1, 1, (1, 1), (0, 0)),        # weight-streaming FC
-    (1, 3, 3, 20, 12, 3, 3, (1, 1), (1, 1)),         # general kernel, ragged O and I
+    (1, 3, 3, 20, 12, 3, 3, (1, 1), (1, 1)),         # ragged O and I: any-shape kernel
     (2, 15, 13, 3, 64, 7, 7, (2, 2), (3, 3)),        # first layer (narrow input)
 ]
 
@@ -53,6 +55,24 @@ def test_fused_epilogue_vs_oracle(dtype, residual, relu):
         scale = np.maximum(np.abs(pre) + (np.abs(R) if residual else 0), np.sqrt(np.mean(pre * pre)))
         tol = {"bf16": 2e-2, "f32": 1e-5}[dtype]
         assert (np.abs(y - ref) <= tol * scale).all(), (shape, float((np.abs(y - ref) / scale).max()))
+
+
+@pytest.mark.parametrize("residual,relu", [(True, True), (True, False), (False, True)])
+def test_fused_epilogue_of_the_lds_and_ring_tile_kernels(residual, relu):
+    import torch
+    for n, family in [(0, bsp.BSP_KERNEL_LDS), (1, bsp.BSP_KERNEL_LDS), (2, bsp.BSP_KERNEL_LDS),
+                      (0, bsp.BSP_KERNEL_TILE), (1, bsp.BSP_KERNEL_TILE), (3, bsp.BSP_KERNEL_TILE)]:
+        c, R = _case(SHAPES[n], 700 + n, "bf16")
+        Y = torch.full((c.B, c.M, c.N, c.O), float("nan"), dtype=torch.bfloat16, device="cuda")
+        print("case", n, SHAPES[n], family, flush=True)
+        make_layer(c).conv2d(to_device(c), c.stride, c.pad, out=Y, residual=to_device(c, R) if residual else None,
+                             relu=relu, family=family)
+        y = to_host(Y)
+        ref = oracle.conv2d_fused(c.X, c.W, c.bias, c.gamma, c.bo, c.bi, c.stride, c.pad,
+                                  residual=R if residual else None, relu=relu, dtype="bf16")
+        pre = oracle.conv2d(c.X, c.W, c.bias, c.gamma, c.bo, c.bi, c.stride, c.pad)
+        scale = np.maximum(np.abs(pre) + (np.abs(R) if residual else 0), np.sqrt(np.mean(pre * pre)))
+        assert (np.abs(y - ref) <= 2e-2 * scale).all(), (SHAPES[n], family)
 
 
 def test_fused_equals_unfused_layer_plus_torch_ops():

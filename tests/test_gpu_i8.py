@@ -5,6 +5,8 @@ import pytest
 import oracle
 import paper_2407_09453_amd as bsp
 
+from gpu_util import kernels_of
+
 pytestmark = pytest.mark.gpu
 
 GRANS = [(8, 8), (4, 16), (16, 4)]
@@ -69,7 +71,8 @@ def test_shifted_int8_output_bit_exact(shift):
 
 
 LDS_SHAPES = [
-    # channel counts in whole 16-code chunks: these take the LDS-resident int8 kernel
+    # channel counts in whole 16-code chunks: what the LDS-resident int8 kernel takes (the dispatcher gives
+    # most of them to the any-shape and the pointwise kernel)
     (2, 20, 20, 64, 64, 3, 3, (1, 1), (1, 1)),       # one slab
     (1, 14, 14, 192, 128, 3, 3, (1, 1), (1, 1)),     # two slabs, two strip groups
     (3, 13, 13, 128, 96, 1, 1, (1, 1), (0, 0)),      # pointwise, ragged strip group
@@ -84,6 +87,7 @@ LDS_SHAPES = [
 
 @pytest.mark.parametrize("bo,bi", GRANS)
 def test_lds_int8_kernel_bit_exact(bo, bi):
+    """Through the dispatcher."""
     import torch
     for n, shape in enumerate(LDS_SHAPES):
         X, W, bias, gamma, s, p = _draw(shape, 300 + n, bo, bi, extreme=(n % 4 == 0))
@@ -95,9 +99,29 @@ def test_lds_int8_kernel_bit_exact(bo, bi):
             torch.cuda.synchronize()
             want = oracle.conv2d_i8(X, W, bias, gamma, bo, bi, s, p, shift=shift)
             assert (Y.cpu().numpy() == want).all(), (shape, bo, bi, shift)
-        # the int32 sums (general kernel) shifted on the host give the same bytes
+        # the int32 sums (another kernel) shifted on the host give the same bytes
         Y32 = layer.conv2d(Xd, s, p).cpu().numpy().astype(np.int64)
         assert (oracle.requant_shift(Y32, 6) == oracle.conv2d_i8(X, W, bias, gamma, bo, bi, s, p, shift=6)).all()
+
+
+@pytest.mark.parametrize("bo,bi", GRANS)
+def test_lds_int8_kernel_alone_bit_exact(bo, bi):
+    """The same layers with no other kernel allowed; shifts at which the rescale changes its form."""
+    import torch
+    for n, shape in enumerate(LDS_SHAPES):
+        X, W, bias, gamma, s, p = _draw(shape, 300 + n, bo, bi, extreme=(n % 4 == 0))
+        print("case", n, shape, bo, bi, flush=True)
+        layer = bsp.BspLayerI8(W, gamma, bo, bi, bias=bias)
+        layer.struct.kernels = bsp.BSP_KERNEL_LDS
+        Xd = torch.from_numpy(X).cuda()
+        Y = torch.full(layer.out_shape(*shape[:3], s, p), 77, dtype=torch.int8, device="cuda")
+        ran = kernels_of(lambda: layer.conv2d(Xd, s, p, shift=9, out=Y))
+        assert any("conv_lds" in k for k in ran), (shape, ran)
+        acc = oracle.conv2d_i8(X, W, bias, gamma, bo, bi, s, p)
+        for shift in (0, 9, 24, 25, 31):
+            Y.fill_(77)
+            layer.conv2d(Xd, s, p, shift=shift, out=Y)
+            assert (Y.cpu().numpy() == oracle.requant_shift(acc, shift)).all(), (shape, bo, bi, shift)
 
 
 def test_int8_config1_full_size():

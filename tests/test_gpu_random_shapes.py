@@ -7,7 +7,7 @@ import oracle
 import paper_2407_09453_amd as bsp
 from synthetic import draw_layer
 
-from gpu_util import assert_close, gpu_conv, oracle_conv
+from gpu_util import assert_close, gpu_conv, kernels_of, make_layer, oracle_conv, to_device, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -87,8 +87,8 @@ def test_random_shapes_int8():
 
 
 def _tiled_shapes(seed, count):
-    """Shapes with whole 16-channel chunks and more pixels: these land in the LDS-resident
-    kernels (bf16 and int8), with several tiles, slabs and strip groups."""
+    """Shapes with whole 16-channel chunks and more pixels, with several tiles, slabs and strip groups for
+    the LDS-resident kernels (bf16 and int8)."""
     rng = np.random.default_rng(seed)
     out = []
     while len(out) < count:
@@ -123,3 +123,38 @@ def test_random_tiled_shapes_bf16_and_int8():
         torch.cuda.synchronize()
         want = oracle.conv2d_i8(X, W, bias, c.gamma, bo, bi, s, p, shift=shift)
         assert (Y8.cpu().numpy() == want).all(), (n, shift)
+
+
+def test_random_tiled_shapes_on_the_lds_and_ring_tile_kernels():
+    """The same shapes and windows of 5x5 and 7x7, each kernel alone: the dispatcher gives most of them to others."""
+    import torch
+    rng = np.random.default_rng(16)
+    ran = {"lds": 0, "tile": 0, "lds_i8": 0}
+    big = [(2, 20, 21, 64, 48, 5, 5, (1, 1), (2, 2), 4, 16), (1, 26, 13, 40, 32, 7, 7, (2, 2), (3, 3), 8, 8),
+           (1, 15, 30, 32, 128, 5, 5, (1, 1), (0, 0), 16, 4)]
+    for n, (B, L, J, I, O, H, K, s, p, bo, bi) in enumerate(_tiled_shapes(79, 24) + big):
+        print("case", n, (B, L, J, I, O, H, K, s, p, bo, bi), flush=True)
+        c = draw_layer("t", B=B, L=L, J=J, I=I, O=O, H=H, K=K, stride=s, pad=p, bo=bo, bi=bi,
+                       dtype="bf16", mask_kind="exact", density=0.5, seed=7000 + n, b_std=0.5)
+        layer, X, ref = make_layer(c), to_device(c), oracle_conv(c)
+        for name, family in (("lds", bsp.BSP_KERNEL_LDS), ("tile", bsp.BSP_KERNEL_TILE)):
+            Y = torch.full((c.B, c.M, c.N, c.O), float("nan"), dtype=torch.bfloat16, device="cuda")
+            try:
+                layer.conv2d(X, s, p, out=Y, family=family)
+            except bsp.BspError:
+                continue
+            ran[name] += 1
+            assert_close(to_host(Y), ref, "bf16", f"{name} {n}")
+        Xq = rng.integers(-128, 128, (B, L, J, I), dtype=np.int8)
+        W = rng.integers(-128, 128, (O, H, K, I), dtype=np.int8)
+        bias = rng.integers(-2 ** 16, 2 ** 16, O).astype(np.int32)
+        layer = bsp.BspLayerI8(W, c.gamma, bo, bi, bias=bias)
+        layer.struct.kernels = bsp.BSP_KERNEL_LDS
+        shift = int(rng.integers(4, 14))
+        Xd = torch.from_numpy(Xq).cuda()
+        Y8 = torch.full(layer.out_shape(B, L, J, s, p), 77, dtype=torch.int8, device="cuda")
+        ran["lds_i8"] += any("conv_lds" in k for k in kernels_of(lambda: layer.conv2d(Xd, s, p, shift=shift, out=Y8)))
+        want = oracle.conv2d_i8(Xq, W, bias, c.gamma, bo, bi, s, p, shift=shift)
+        assert (Y8.cpu().numpy() == want).all(), (n, shift)
+    print(ran)
+    assert ran["lds"] >= 24 and ran["tile"] >= 20 and ran["lds_i8"] >= 24, ran

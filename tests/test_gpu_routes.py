@@ -5,25 +5,9 @@ import pytest
 
 import paper_2407_09453_amd as bsp
 
-from gpu_util import kernels_of
+from gpu_util import conv_fp64, kernels_of
 
 pytestmark = pytest.mark.gpu
-
-
-def _fp64(X, W, stride, pad):
-    """The layer in fp64, window tap by window tap."""
-    import torch
-    B, L, J, I = X.shape
-    O, H, K, _ = W.shape
-    M, N = (L + 2 * pad[0] - H) // stride + 1, (J + 2 * pad[1] - K) // stride + 1
-    Xp = torch.zeros(B, L + 2 * pad[0], J + 2 * pad[1], I, dtype=torch.float64, device="cuda")
-    Xp[:, pad[0]:pad[0] + L, pad[1]:pad[1] + J] = X.double()
-    Y = torch.zeros(B * M * N, O, dtype=torch.float64, device="cuda")
-    for h in range(H):
-        for k in range(K):
-            x = Xp[:, h:h + (M - 1) * stride + 1:stride, k:k + (N - 1) * stride + 1:stride].reshape(-1, I).contiguous()
-            Y += x @ W[:, h, k].double().t().contiguous()
-    return Y.view(B, M, N, O)
 
 
 def _draw(n, B, L, J, I, O, H, K, bo, bi):
@@ -61,7 +45,7 @@ def test_bf16_layers(n):
     out = torch.full(layer.out_shape(B, L, J, (s, s), pad), float("nan"), dtype=torch.bfloat16, device="cuda")
     ran = kernels_of(lambda: layer.conv2d(X, (s, s), pad, out=out))
     assert any(kernel in k for k in ran), ran
-    want = _fp64(X, W * keep, s, pad) + torch.from_numpy(bias).cuda()
+    want = conv_fp64(X, W * keep, s, pad) + torch.from_numpy(bias).cuda()
     scale = torch.maximum(want.abs(), want.pow(2).mean().sqrt())
     assert bool(((out.double() - want).abs() <= 6e-3 * scale).all())   # one rounding to bf16 is 3.9e-3 at most
 
@@ -86,7 +70,7 @@ def test_f32_layers(n):
     out = torch.full(layer.out_shape(B, L, J, (s, s), pad), float("nan"), device="cuda")
     ran = kernels_of(lambda: layer.conv2d(X, (s, s), pad, out=out))
     assert any(kernel in k for k in ran), ran
-    want = _fp64(X, W * keep, s, pad) + torch.from_numpy(bias).cuda()
+    want = conv_fp64(X, W * keep, s, pad) + torch.from_numpy(bias).cuda()
     scale = torch.maximum(want.abs(), want.pow(2).mean().sqrt())
     assert bool(((out.double() - want).abs() <= 1e-5 * scale).all())   # at most 300 terms
 
@@ -129,7 +113,7 @@ def test_i8_layers(n):
     out = torch.full(layer.out_shape(B, L, J, (s, s), pad), 77, dtype=dt, device="cuda")
     ran = kernels_of(lambda: layer.conv2d(X, (s, s), pad, shift=9 if y8 else None, out=out))
     assert any(kernel in k for k in ran), ran
-    acc = _fp64(X, W, s, pad).to(torch.int64) + bias
+    acc = conv_fp64(X, W, s, pad).to(torch.int64) + bias
     assert torch.equal(out, _rescale(acc, 9) if y8 else acc.int())
 
 
@@ -142,7 +126,7 @@ def test_i8_activations_beyond_the_any_shape_kernels_reach():
     ran = kernels_of(lambda: layer.conv2d(X, shift=9, out=out))
     assert X.numel() >= 1 << 31 and any("conv_lds" in k for k in ran), ran
     for b in (0, B // 2, B - 1):
-        assert torch.equal(out[b:b + 1], _rescale(_fp64(X[b:b + 1], W, 1, (0, 0)).to(torch.int64) + bias, 9))
+        assert torch.equal(out[b:b + 1], _rescale(conv_fp64(X[b:b + 1], W, 1, (0, 0)).to(torch.int64) + bias, 9))
 
 
 @pytest.mark.parametrize("O", (16, 32, 48, 64))
@@ -156,4 +140,4 @@ def test_i8_pointwise_layers_of_few_strips(B, L, I, O):
     out = torch.full((B, L, L - 1, O), 77, dtype=torch.int8, device="cuda")
     ran = kernels_of(lambda: layer.conv2d(X, shift=9, out=out))
     assert any("conv_pw" in k for k in ran), ran
-    assert torch.equal(out, _rescale(_fp64(X, W, 1, (0, 0)).to(torch.int64) + bias, 9))
+    assert torch.equal(out, _rescale(conv_fp64(X, W, 1, (0, 0)).to(torch.int64) + bias, 9))
