@@ -112,15 +112,27 @@ inline int bsp_pw_thin(int PT, int64_t pitch, int NS) {
 // batch 8 [14] 51 / 23; 8x8 1x1 14x14x11->118 batch 6 [1.5] 4.3 / 6.7, 1x3 21x21x27 [7] and up the tiles, 1x3
 // 111x111x20 batch 47 [6, 7 M results] 73 / 39; 16x4 1x1 49x49x79->180 batch 25 [10, 11 M] 165 / 51.
 // The tiles' results leave as vectors where the channels out are a multiple of four, one by one where
-// they are not, which moves the line down there and up here: 4x16 1x1 58x58x25->108 batch 37 [3.7] 59 / 37,
-// 44x44x21->85 batch 33 [3] 25 / 37.  FC layers of up to 256 rows (`few`) are
-// not staged: only a single chunk is left to the general kernel, 12x4x4x5->110 3.2 / 6.2.
+// they are not, which moves the line down there, the further the more results, and up here: 4x16 1x1
+// 58x58x25->108 batch 37 [3.7] 59 / 37, 44x44x21->85 batch 33 [3] 25 / 37; 8x8 52x52x33->236 batch 29 [2]
+// 63 / 42, 16x4 41x41x80->234 batch 4 [10] 25 / 17 at 1.6 M results, 5x5x14->66 batch 2 3.5 / 3.8.  A block of
+// sixteen channels is multiplied whole, also where the layer has eight: 4x16 3x1 110x110x1->248 batch 48
+// 52 / 80.  One row of 4x16 blocks is one wave, which stages its patch alone: 1x1 35x35x81->4 batch 4 [4]
+// 4.3 / 9.8, 287->4 on 84700 pixels [8] 14 / 32.  FC layers of up to 256 rows (`few`) are not staged: only a single chunk is left to the general
+// kernel, 12x4x4x5->110 3.2 / 6.2.
 inline bool bsp_f32_general(int bo, int64_t I, int64_t O, int64_t HK, int64_t pairs, int64_t strips, int64_t po, bool few) {
   if (few) return I <= 8;
-  const bool streams = O % 4 == 0 && po > 1000000;
-  if (I <= 8 && (HK == 1 || (HK <= 9 && !streams))) return true;
-  int most = streams ? 2 : bo == 8 ? 5 : bo == 4 ? 3 : 6;
-  if (O % 4) most = bo == 8 ? 7 : bo == 4 ? 5 : 10;
+  const bool vectors = O % 4 == 0, many = po > 1000000;
+  if (I <= 8 && (HK == 1 || (HK <= 9 && (!vectors || !many || bo == 4)))) return true;
+  int most;
+  if (!vectors)
+    most = bo == 4 ? 5 : many ? 6 : bo == 8 ? 7 : 12;
+  else if (many)
+    most = bo == 4 ? 2 : 1;
+  else if (po > 300000)
+    most = bo == 8 ? 4 : 2;
+  else
+    most = bo == 8 ? 5 : bo == 4 ? 3 : 7;
+  if (HK == 1 && bo == 4 && O <= 4) most = 8;
   return pairs <= most * strips;
 }
 

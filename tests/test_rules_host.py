@@ -119,15 +119,19 @@ int main() {
   F32(false, 8, 20, 20, 3, 12, 2, 11581740, false);                       // 73 / 39
   F32(false, 16, 79, 180, 1, 120, 12, 10804500, false);                   // 165 / 51
   F32(false, 4, 43, 100, 1, 6 * 27, 27, 64600, false);                    // 5.6 / 5.3
-  for (int odd = 0; odd < 2; ++odd) {                                     // the line itself, results by vectors and one by one
-    F32(true, 8, 64, 64 + odd, 1, odd ? 28 : 20, 4, 500000, false);
-    F32(false, 8, 64, 64 + odd, 1, odd ? 29 : 21, 4, 500000, false);
-    F32(true, 4, 64, 64 + odd, 1, odd ? 20 : 12, 4, 500000, false);
-    F32(false, 4, 64, 64 + odd, 1, odd ? 21 : 13, 4, 500000, false);
-    F32(true, 16, 64, 64 + odd, 1, odd ? 40 : 24, 4, 500000, false);
-    F32(false, 16, 64, 64 + odd, 1, odd ? 41 : 25, 4, 500000, false);
-    F32(odd, 8, 64, 64 + odd, 1, 9, 4, 5000000, false);
-  }
+  F32(true, 4, 1, 248, 3, 16 * 3, 16, 32946000, false);                   // 52 / 80
+  F32(false, 8, 33, 236, 1, 30, 15, 18505568, false);                     // 63 / 42
+  // the line itself: block rows; vectors up to 3e5, up to 1e6 and beyond; one by one up to 1e6 and beyond
+  const int lines[3][6] = {{8, 5, 4, 1, 7, 6}, {4, 3, 2, 2, 5, 5}, {16, 7, 2, 1, 12, 6}};
+  for (auto& l : lines)
+    for (int k = 0; k < 5; ++k) {
+      const int O = k < 3 ? 64 : 63, po = k == 0 ? 300000 : k == 1 || k == 3 ? 1000000 : 1000001;
+      F32(true, l[0], 64, O, 1, 4 * l[1 + k], 4, po, false);
+      F32(false, l[0], 64, O, 1, 4 * l[1 + k] + 1, 4, po, false);
+    }
+  F32(true, 4, 81, 4, 1, 4, 1, 19600, false);                             // 4.3 / 9.8
+  F32(true, 4, 287, 4, 1, 8, 1, 338800, false);                           // 14 / 32
+  F32(false, 4, 287, 4, 1, 9, 1, 338800, false);
   F32(true, 8, 5, 110, 1, 7, 7, 21120, true);                             // 3.2 / 6.2
   F32(false, 8, 64, 64, 1, 8, 4, 4096, true);
   // the widths that a tile's search tries: those of every even cut, and few of them on the widest image
