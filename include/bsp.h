@@ -141,12 +141,14 @@ typedef struct bsp_weights {
   int32_t dtype;            /* element type of payload, X and Y: BSP_F32 or BSP_BF16 */
   int32_t kernels;          /* 0: the library picks the kernel.  Otherwise a mask of
                                bsp_kernel_family bits the dispatcher may use (the
-                               general-shape kernel is always allowed); for tests and timing */
+                               general-shape kernel is always allowed, kernels without a bit
+                               are not); for tests and timing */
   int64_t nnzb;             /* kept blocks */
   const int32_t* row_ptr;   /* device copies of bsp_pack's arrays that match `payload`, or both */
-  const int32_t* col_idx;   /* null.  The kernel that streams compressed block rows (FC layers
-                               with 8x8 blocks) reads them on the device when they are given;
-                               with null pointers it is not used. */
+  const int32_t* col_idx;   /* null.  The kernels that walk compressed block rows (FC layers
+                               with 8x8 blocks; fp32 layers) read them on the device when they
+                               are given, columns ascending in each row as bsp_pack writes
+                               them; with null pointers they are not used. */
   const void* payload;      /* device [nnzb][bo][H][K][bi] */
   const void* plan;         /* device copy of bsp_plan_build's output */
   int64_t plan_bytes;

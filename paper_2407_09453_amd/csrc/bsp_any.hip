@@ -13,8 +13,8 @@
 // every instance keeps to 128 registers (144 in the four-tile one: 1x1 28x28x128->512 int8 28 us
 // instead of 19).  Measured (general kernel / here): bf16 3x3 47x33x100->76 batch 3 36.9 / 7.1 us;
 // 3x3 14x14x300->300 batch 16 150 / 22; 5x5 100x90x37->50 batch 2 52 / 9.4; 1x1 14x14x1001->333 batch 8
-// 51 / 10.4; FC 32 x 1001 -> 999 28.6 / 5.4; int8 3x3 28x28x136->200 batch 8 28 / 8.2; 1x1
-// 56x56x40->200 batch 16 15.9 / 17.0, the one of 27 shapes that gained nothing.
+// 51 / 10.4; FC 32 x 1001 -> 999 28.6 / 5.4; int8 3x3 28x28x136->200 batch 8 28 / 8.2.  Which layers go
+// to the other kernels instead: bsp_rules.h.
 #include "bsp_launch.h"
 #include "bsp_tile.h"
 
@@ -219,8 +219,9 @@ __device__ __forceinline__ f32x4_t kept_only(const AnyArgs& a, const unsigned ch
 // One (tile of PT * 16 * PG output pixels) x (NS strips) per workgroup.  A tile is consecutive
 // pixels of a chunk of image columns; its input patch, halo included, is staged as whole pixels
 // (zeros outside the image and past the last channel), as many of the plan's slabs at a time as
-// LDS takes.  A staged pixel is an odd number of 16-byte pieces, so the sixteen pixels of a matrix
-// tile read different banks.  Wave = (strip, pixel group, share of the strip's steps): a step's
+// LDS takes.  A staged pixel is an odd number of 16-byte pieces, so pixels of a matrix tile that lie in
+// one patch row read different banks; those of two rows can collide (bf16 3x3 47x33x100->76: 0.19 M of
+// 0.51 M LDS cycles).  Wave = (strip, pixel group, share of the strip's steps): a step's
 // weights come from the plan through a register ring of D, its activations from LDS one step ahead.
 template <int KIND, int PT, bool VEC>
 __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {

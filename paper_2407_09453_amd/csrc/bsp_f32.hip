@@ -11,10 +11,14 @@
 // of which the union would leave about 100.
 //
 // Measured (this file / the general kernel it took these layers from): 3x3 64->64 at 56x56, batch
-// 32, half of the 8x8 blocks kept: 55 / 188 us = 67 TFLOP/s, bound by the matrix instructions'
-// issue (45 us with staging and stores taken out; without LDS reads no faster); 3x3 128->416 at
-// 28x28, batch 16, 4x16: 38 / 247 us; 5x5 48->64 at 35x35, batch 8: 21 / 93 us; 1x1 256->1024 at
-// 14x14, batch 8: 15 / 49 us; FC 64 x 256 -> 256: 7.5 / 14.2 us, 1 x 4096 -> 4096: 21 / 197 us.
+// 32, half of the 8x8 blocks kept: 55 / 188 us = 67 TFLOP/s; 3x3 128->416 at 28x28, batch 16, 4x16:
+// 38 / 247 us; 5x5 48->64 at 35x35, batch 8: 21 / 93 us; 1x1 256->1024 at 14x14, batch 8: 15 / 49 us;
+// FC 64 x 256 -> 256: 5.9 / 13.9 us, 1 x 4096 -> 4096: 21 / 197 us.  Layers with little to sum per strip
+// stay with the general kernel (bsp_f32_general).
+//
+// What bounds the first of them: the matrix cores are busy 54 % of its time (30 us), staging and
+// stores that nothing hides are 10 us (45 without them), the rest lies between the products.  Not
+// in the LDS reads, of whose 11.5 M active cycles 7.4 M are conflicts: without them it is no faster.
 #include "bsp_launch.h"
 #include "bsp_tile.h"
 
@@ -66,8 +70,10 @@ struct F32Args {
 // pixels of a chunk of image columns (whole rows where they are at most 64 wide), so every lane
 // has a pixel whatever the sizes; its input patch, halo included, is staged slab by slab of
 // channels (zero outside the image and past the last channel).  A staged pixel takes
-// slab * 4 + 16 bytes: an odd number of 16-byte pieces, so lanes on neighbouring pixels read
-// different banks.  Wave = (block row, share of its blocks): it walks its kept blocks tap by tap;
+// slab * 4 + 16 bytes: an odd number of 16-byte pieces, so lanes on neighbouring pixels of a patch
+// row read different banks; where a tile's pixels go on in the next row (chunks of eight columns,
+// rows of ten staged pixels) some of them collide.
+// Wave = (block row, share of its blocks): it walks its kept blocks tap by tap;
 // the block's weights come straight from the compressed row, four taps ahead in a register ring,
 // the pixels' channels from LDS one lane tile ahead.
 template <int BO, int BI, int PT>

@@ -1,5 +1,6 @@
 // General-shape block-sparse implicit-GEMM kernel: any H x K window, stride,
 // padding, ragged channel counts, all three block granularities, fp32 or bf16.
+// fp32 layers with little to sum per strip (bsp_f32_general) and whatever no other kernel takes.
 // Operands go straight from global memory (through L1/L2) into MFMA registers;
 // the shape-specialised kernels stage activations through LDS instead.
 //

@@ -1,6 +1,9 @@
 // LDS-resident tiled kernel: weights AND activations of the current slab of input channels
 // live in LDS, the hot loop touches nothing else.  bf16 layers (fp32 accumulation), first
-// layers with at most four input channels, and int8 layers (exact int32 sums).
+// layers with at most four input channels, and int8 layers (exact int32 sums) of channels in whole
+// sixteens.  The band, row-band, pointwise and any-shape kernels have the layers that they are faster
+// on (bsp_rules.h); left here are windows of fewer than 128 input channels on images too wide or
+// strides too large for the band kernel, and int8 windows of one slab on many pixels.
 //
 // A persistent workgroup of twelve waves owns a group of four strips (64 output channels)
 // and walks units = (pixel tile of an image, slab of input channels).  Eight waves compute

@@ -107,7 +107,7 @@ inline int bsp_pw_thin(int PT, int64_t pitch, int NS) {
 // fp32: whether the general kernel is to take the layer.  It sums a strip of sixteen channels chunk by
 // chunk and tap by tap (`pairs` of them over all strips), straight from memory: few of those are over
 // before the other kernel has staged its first patch, and its results leave in longer runs.  Timed on
-// 4100 layers, general / matrix tiles in us, pairs per strip in brackets: one chunk of input channels 1x1
+// 5500 layers, general / matrix tiles in us, pairs per strip in brackets: one chunk of input channels 1x1
 // 15x5x5->125 batch 34 with 16x4 blocks 3.9 / 9.5, 3x3 50x12x3->323 batch 50 31 / 60, 5x5 43x43x1->496
 // batch 8 [14] 51 / 23; 8x8 1x1 14x14x11->118 batch 6 [1.5] 4.3 / 6.7, 1x3 21x21x27 [7] and up the tiles, 1x3
 // 111x111x20 batch 47 [6, 7 M results] 73 / 39; 16x4 1x1 49x49x79->180 batch 25 [10, 11 M] 165 / 51.
@@ -117,8 +117,8 @@ inline int bsp_pw_thin(int PT, int64_t pitch, int NS) {
 // 63 / 42, 16x4 41x41x80->234 batch 4 [10] 25 / 17 at 1.6 M results, 5x5x14->66 batch 2 3.5 / 3.8.  A block of
 // sixteen channels is multiplied whole, also where the layer has eight: 4x16 3x1 110x110x1->248 batch 48
 // 52 / 80.  One row of 4x16 blocks is one wave, which stages its patch alone: 1x1 35x35x81->4 batch 4 [4]
-// 4.3 / 9.8, 287->4 on 84700 pixels [8] 14 / 32.  FC layers of up to 256 rows (`few`) are not staged: only a single chunk is left to the general
-// kernel, 12x4x4x5->110 3.2 / 6.2.
+// 4.3 / 9.8, 287->4 on 84700 pixels [8] 14 / 32.  FC layers of up to 256 rows (`few`) are not staged: only a
+// single chunk is left to the general kernel, 12x4x4x5->110 3.2 / 6.2.
 inline bool bsp_f32_general(int bo, int64_t I, int64_t O, int64_t HK, int64_t pairs, int64_t strips, int64_t po, bool few) {
   if (few) return I <= 8;
   const bool vectors = O % 4 == 0, many = po > 1000000;

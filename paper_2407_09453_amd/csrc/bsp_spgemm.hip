@@ -307,7 +307,7 @@ __global__ __launch_bounds__(512) void spgemm_nt_bf16(SpParams q) {
 // The same product as a tiled dense one, absent blocks staged as zeros.  A 16 x 16 tile of the
 // kernel above can skip a column only if both rows of a side drop it, (1 - d)^2 of them, and its
 // operands serve no other tile, so LDS gives it a quarter of the matrix rate; here a fragment
-// serves a whole wave tile.  4096^3, half of the blocks kept on both sides: 355 -> 123 us (1.1 PFLOP/s
+// serves a whole wave tile.  4096^3, half of the blocks kept on both sides: 344 -> 112 us (1.2 PFLOP/s
 // of multiply-adds issued), all kept 533 -> 128, a quarter 159 -> 113, a tenth 98 / 111 (the kernel
 // above stays); 1024^3 52 -> 9.9, 512^3 19.9 -> 7.0.
 //

@@ -1,4 +1,5 @@
-// LDS-tiled block-sparse implicit-GEMM convolution, bf16 in / fp32 accumulate.
+// LDS-tiled block-sparse implicit-GEMM convolution, bf16 in / fp32 accumulate: large windows (5x5, 7x7)
+// with many results, where the any-shape kernel is slower (bsp_rules.h), and what that one declines.
 //
 // One workgroup (4 waves) owns a TH x TW tile of output pixels of one image and
 // a group of strips (16 output channels each).  The input patch the tile needs
