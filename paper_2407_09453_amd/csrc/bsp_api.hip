@@ -130,17 +130,24 @@ int dispatch(const bsp_weights* w, const ConvParams& p, void* stream, const Fixe
     // the row-band kernel takes all windows of one row and nearly all of three: where it is passed over,
     // so are the kernels after it
     const bool over_rows = rows_pick && (p.H == 1 ? p.sh == 1 && p.sw == 1 : p.H == 3) && any_beats(BSP_RIVAL_ROWS);
+    // three rows and plenty of work: the persistent kernel (no part of a caller's mask either), in the
+    // place of the kernel that would run next
+    auto tall = [&](BspRival rival) { return !w->kernels && chunked && p.H == 3 ? bsp_launch_tall(p, w->plan_host, rival, st) : BSP_ERR_UNSUPPORTED; };
     for (;;) {
       if ((allow & BSP_KERNEL_BAND) && p.H == 3 && p.K == 3 && !any_beats(BSP_RIVAL_BAND))
         rc = bsp_launch_band(p, w->dtype, w->plan_host, st);
       if (rc != BSP_ERR_UNSUPPORTED) return rc;
-      if ((allow & BSP_KERNEL_ROWS) && (rows_pick || w->kernels) && !any_beats(BSP_RIVAL_ROWS))
-        rc = bsp_launch_rows(p, w->dtype, w->plan_host, st);
+      if ((allow & BSP_KERNEL_ROWS) && (rows_pick || w->kernels) && !any_beats(BSP_RIVAL_ROWS)) {
+        rc = tall(BSP_RIVAL_ROWS);
+        if (rc == BSP_ERR_UNSUPPORTED) rc = bsp_launch_rows(p, w->dtype, w->plan_host, st);
+      }
       if (rc != BSP_ERR_UNSUPPORTED) return rc;
       if ((allow & BSP_KERNEL_FIRST) && p.I <= 4) rc = bsp_launch_first(p, w->dtype, w->plan_host, st);
       if (rc != BSP_ERR_UNSUPPORTED) return rc;
-      if ((allow & BSP_KERNEL_LDS) && !(any && over_rows) && !any_beats(BSP_RIVAL_LDS))
-        rc = bsp_launch_lds(p, w->dtype, w->plan_host, st);
+      if ((allow & BSP_KERNEL_LDS) && !(any && over_rows) && !any_beats(BSP_RIVAL_LDS)) {
+        rc = tall(BSP_RIVAL_LDS);
+        if (rc == BSP_ERR_UNSUPPORTED) rc = bsp_launch_lds(p, w->dtype, w->plan_host, st);
+      }
       if (rc != BSP_ERR_UNSUPPORTED) return rc;
       if ((allow & BSP_KERNEL_TILE) && chunked && !(any && over_rows) && !any_beats(BSP_RIVAL_TILE))
         rc = bsp_launch_tile(p, w->dtype, st);

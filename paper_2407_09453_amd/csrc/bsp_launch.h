@@ -49,6 +49,14 @@ int bsp_launch_lds_i8(const ConvParams& p, const void* plan_host, int shift, hip
 // section and its host copy).  BSP_ERR_UNSUPPORTED = not applicable, nothing launched.
 int bsp_launch_rows(const ConvParams& p, int dtype, const void* plan_host, hipStream_t st);
 
+// the row-band kernel's own estimate for a layer, in rough ns (rs: the row-band section of the host plan)
+double bsp_rows_cost(const ConvParams& p, const int32_t* rs);
+
+// Persistent kernel for three-row windows at stride 1 (bf16; needs the plan's row-band section and its
+// host copy), for the layers on which it is faster than the kernel `rival` that could take them too.
+// BSP_ERR_UNSUPPORTED = not applicable or not faster, nothing launched.
+int bsp_launch_tall(const ConvParams& p, const void* plan_host, BspRival rival, hipStream_t st);
+
 // Band kernel (bf16, 3x3 stride 1 padding 1, at most 128 input channels, rows of at most 64
 // pixels, strips x column tiles <= 16).  BSP_ERR_UNSUPPORTED = not applicable, nothing launched.
 int bsp_launch_band(const ConvParams& p, int dtype, const void* plan_host, hipStream_t st);

@@ -883,6 +883,11 @@ static int rows_fill_common(const ConvParams& p, const ConvParams& v, const int3
   return BSP_OK;
 }
 
+double bsp_rows_cost(const ConvParams& p, const int32_t* rs) {
+  Choice c;
+  return rows_choose(p, rs, p.sh, &c) ? c.cost : 1e300;
+}
+
 int bsp_launch_rows(const ConvParams& p, int dtype, const void* plan_host, hipStream_t st) {
   if (dtype != BSP_BF16 || !plan_host) return BSP_ERR_UNSUPPORTED;
   const int32_t* hdr = (const int32_t*)plan_host;

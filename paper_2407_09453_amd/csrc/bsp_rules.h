@@ -56,6 +56,24 @@ inline bool bsp_any_beats_bf16(BspRival rival, int bo, int H, int K, bool stride
   return H * K <= 25 ? O < 272 || po <= 1000000 : O < 136 || po <= 800000;
 }
 
+// bf16 windows of three rows at stride 1: whether the persistent kernel takes a layer from `rival`.  mr: matrix
+// instructions of the row-band section's steps; cost: the two kernels' own models of a layer, which put
+// the persistent one at 0.95 (0.85 to 1.10) of what it takes and the row-band kernel at 1.47 times (1.12 to 2.0)
+// (rival / here in us, from 550 random layers):
+//   row-band kernel, more than 128 channels in: 58x76x544->336 batch 3 71 / 29, 56x56x256 batch 16 47 / 42,
+//     28x28x512 batch 16 52 / 40, 28x28x256->512 batch 16 27 / 24; 17x17x256->296 batch 4 10.4 / 12.7, 34x34x520->64
+//     batch 6 14.3 / 18.2.  At this line 1 of 120 taken layers is more than a tenth slower (0.85), and the
+//     geometric mean of the taken ones is 1.29 times faster.
+//   band kernel: never; its workgroups stage whole lines, 73x73x80->192 batch 16 26 / 36, 56x56x128->256 batch 16
+//     26.9 / 27.9 (76x76x112->208 batch 3 30 / 17 is an exception)
+//   LDS kernel (more strips than the band kernel has waves, 4-channel blocks, other widths): 104x104x72->344
+//     16x4 blocks batch 9 98 / 61, 52x52x72->432 batch 10 39 / 29; 33x33x64->448 16x4 batch 10 14.6 / 15.7 (thinner
+//     pixels or fewer strips: 149x149x32 batch 16 stays)
+inline bool bsp_tall_beats(BspRival rival, int64_t mr, int64_t I, int64_t O, double cost, double rows_cost) {
+  if (rival == BSP_RIVAL_ROWS) return I > 128 && cost < 1.35 * rows_cost;
+  return rival == BSP_RIVAL_LDS && I >= 64 && I <= 128 && O > 64 && mr > 120000;
+}
+
 // bf16, up to 64 pixels and short rows: staged once and split over strips and contraction (7x7x2048->512
 // 9.0 -> 6.5 us, FC 64 x 2048 -> 1000 10.1 -> 6.8; from 17 pixels with 4x16 blocks, 7.7 -> 6.7; from
 // 24 to 32 with 8x8 blocks, whose streaming kernel takes 6.0 against 6.5 at 17 and 7.2 against 6.5
