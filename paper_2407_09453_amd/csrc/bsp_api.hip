@@ -158,7 +158,9 @@ int dispatch(const bsp_weights* w, const ConvParams& p, void* stream, const Fixe
       any = false;  // declined: what was passed over for it
     }
   } else if (!w->kernels) {
-    const int rc = bsp_launch_f32(p, w->nnzb, w->bo, w->bi, w->plan_host, (hipStream_t)stream);
+    int rc = bsp_launch_f32x3(p, w->plan_host, (hipStream_t)stream);
+    if (rc != BSP_ERR_UNSUPPORTED) return rc;
+    rc = bsp_launch_f32(p, w->nnzb, w->bo, w->bi, w->plan_host, (hipStream_t)stream);
     if (rc != BSP_ERR_UNSUPPORTED) return rc;
   }
   return bsp_launch_general(p, w->dtype, w->bo, w->bi, (hipStream_t)stream);

@@ -370,6 +370,29 @@ int bsp_quantize(const float* W, int64_t n, int32_t bits, int8_t* codes, double*
   return BSP_OK;
 }
 
+// Whether an fp32 layer's plan has the three-part section: whole chunks, and not so many weights that the
+// section (six bytes a weight of the strips' unions) outweighs what it gives: layers of more are bound by
+// their weights.
+static bool bsp_x3_wanted(int32_t O, int32_t H, int32_t K, int32_t I, int32_t dtype) {
+  return dtype == BSP_F32 && I % 8 == 0 && (int64_t)O * I * H * K <= (int64_t)8 << 20;
+}
+
+// Four weights into the three parts of a step's fragment (each part's fragments are 64 x 8 apart).
+static void split_parts(const float* w, uint16_t* d) {
+  for (int i = 0; i < 4; ++i) {
+    float rest = w[i];
+    for (int q = 0; q < 3; ++q) {
+      uint32_t u;
+      std::memcpy(&u, &rest, 4);
+      u = (u + 0x7FFFu + ((u >> 16) & 1u)) & 0xFFFF0000u;  // to nearest even (finite values)
+      d[q * 64 * 8 + i] = (uint16_t)(u >> 16);
+      float part;
+      std::memcpy(&part, &u, 4);
+      rest -= part;
+    }
+  }
+}
+
 // ---------------------------------------------------------------- launch plan
 // One pass serves both entry points: with out == nullptr it only counts.
 static int plan_walk(const int32_t* row_ptr, const int32_t* col_idx, const void* payload,
@@ -457,6 +480,7 @@ static int plan_walk(const int32_t* row_ptr, const int32_t* col_idx, const void*
     if (count > max_chunks) max_chunks = count;
     if (nsteps - strip_first_step > max_steps) max_steps = (int32_t)(nsteps - strip_first_step);
   }
+  const int64_t all_steps = nsteps;
   if (!steps_wanted) nsteps = 0;
   const int64_t nchunks = (int64_t)xc_list.size();
   auto pad4 = [](int64_t w) { return (w + 3) & ~int64_t(3); };
@@ -479,7 +503,13 @@ static int plan_walk(const int32_t* row_ptr, const int32_t* col_idx, const void*
     if (int rc = bsp_first_section(row_ptr, col_idx, out ? (const uint16_t*)payload : nullptr, O, H,
                                    K, I, bo, bi, &first))
       return rc;
-  const int64_t total = first.empty() ? off_rows + (int64_t)rows.size() : off_first + (int64_t)first.size();
+  // the three-part section of an fp32 layer comes last as well (such a layer has neither of the two above)
+  const bool x3 = bsp_x3_wanted(O, H, K, I, dtype) && all_steps > 0;
+  const int64_t off_x3 = off_rows;
+  const int64_t x3_desc = BSP_X3_HEADER_WORDS + pad4((int64_t)nstrips * (nslabs + 1)), x3_frag = x3_desc + all_steps * 4;
+  const int64_t total = x3              ? off_x3 + x3_frag + all_steps * 3 * 64 * 4
+                        : first.empty() ? off_rows + (int64_t)rows.size()
+                                        : off_first + (int64_t)first.size();
   if (total > std::numeric_limits<int32_t>::max()) return BSP_ERR_SHAPE;
   if (words_needed) *words_needed = total;
   if (!out) return BSP_OK;
@@ -518,6 +548,49 @@ static int plan_walk(const int32_t* row_ptr, const int32_t* col_idx, const void*
   if (nchunks) {
     std::memcpy(out + off_xc, xc_list.data(), sizeof(int32_t) * xc_list.size());
     std::memcpy(out + off_src, src_list.data(), sizeof(int32_t) * src_list.size());
+  }
+  if (x3 && payload) {
+    out[BSP_PLAN_OFF_X3_W] = (int32_t)off_x3;
+    int32_t* sec = out + off_x3;
+    sec[BSP_X3_NSTEPS_W] = (int32_t)all_steps;
+    sec[BSP_X3_NSLABS_W] = nslabs;
+    sec[BSP_X3_SLAB_W] = slab;
+    sec[BSP_X3_OFF_SLAB_W] = BSP_X3_HEADER_WORDS;
+    sec[BSP_X3_OFF_DESC_W] = (int32_t)x3_desc;
+    sec[BSP_X3_OFF_FRAG_W] = (int32_t)x3_frag;
+    sec[BSP_X3_USABLE_W] = 1;
+    std::memcpy(sec + BSP_X3_HEADER_WORDS, slab_ptr.data(), sizeof(int32_t) * slab_ptr.size());
+    const float* plf = (const float*)payload;
+    for (int64_t i = 0; i < nnzb * blk_elems; ++i) {
+      const float m = std::fabs(plf[i]);
+      if (!(m == 0.0f || (m >= 0x1p-100f && m < 0x1p127f))) sec[BSP_X3_USABLE_W] = 0;
+    }
+    int32_t* xdesc = sec + x3_desc;
+    uint16_t* wfrag = (uint16_t*)(sec + x3_frag);
+    for (int32_t t = 0; sec[BSP_X3_USABLE_W] && t < nstrips; ++t) {
+      int32_t e = strip_ptr[t];
+      for (int32_t sl = 0; sl < nslabs; ++sl) {
+        const int32_t e0 = e;
+        while (e < strip_ptr[(size_t)t + 1] && xc_list[e] / slab_chunks == sl) ++e;
+        const int64_t pairs = (int64_t)(e - e0) * HK;
+        const int64_t s0 = slab_ptr[(size_t)t * (nslabs + 1) + sl];
+        for (int64_t q = 0; q < pairs; ++q) {
+          const int64_t step = s0 + q / 4;
+          const int32_t g = (int32_t)(q % 4);
+          const int32_t ce = e0 + (int32_t)(q / HK);
+          const int32_t tap = (int32_t)(q % HK);
+          xdesc[step * 4 + g] = (xc_list[ce] - sl * slab_chunks) | ((tap / K) << 16) | ((tap % K) << 24);
+          const int32_t* sr = &src_list[(size_t)ce * BSP_MAXSUB];
+          for (int32_t j = 0; j < BSP_STRIP; ++j) {
+            uint16_t* d = wfrag + (step * 3 * 64 + g * 16 + j) * 8;
+            for (int32_t h = 0; h < 2; ++h) {  // four channels; 4-wide blocks: one block each
+              const int32_t so = bi >= 8 ? sr[j / bo] : sr[h];
+              if (so >= 0) split_parts(plf + so + ((int64_t)(j % bo) * HK + tap) * bi + (bi >= 8 ? 4 * h : 0), d + 4 * h);
+            }
+          }
+        }
+      }
+    }
   }
   if (!steps_wanted) return BSP_OK;
 

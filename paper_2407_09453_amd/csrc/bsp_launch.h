@@ -14,6 +14,10 @@ int bsp_launch_general(const ConvParams& p, int dtype, int bo, int bi, hipStream
 // the general kernel is the faster one on.
 int bsp_launch_f32(const ConvParams& p, int64_t nnzb, int bo, int bi, const void* plan_host, hipStream_t st);
 
+// Single-precision layers in whole chunks of eight input channels on the bf16 matrix cores (three parts a
+// value), from the plan's three-part section.  BSP_ERR_UNSUPPORTED = not applicable, nothing launched.
+int bsp_launch_f32x3(const ConvParams& p, const void* plan_host, hipStream_t st);
+
 // Layers of any shape with at least 16 bytes of channels per pixel, from the plan's step section
 // and its host copy.  int8: y_i8 and shift as in bsp_launch_i8.  BSP_ERR_UNSUPPORTED = not
 // applicable, nothing launched.

@@ -76,6 +76,7 @@ enum {
   BSP_PLAN_MAXSLABSTEPS_W = 23,  // most steps in any one (strip, slab)
   BSP_PLAN_OFF_ROWS_W = 24,   // first word of the row-band section, 0 when there is none
   BSP_PLAN_OFF_FIRST_W = 25,  // first word of the thin-input section, 0 when there is none
+  BSP_PLAN_OFF_X3_W = 26,     // first word of the three-part section, 0 when there is none
 };
 
 // Row-band section (bf16 layers with whole 8-channel groups; read by bsp_rows.hip and bsp_pw.hip;
@@ -139,6 +140,24 @@ enum {
   BSP_FIRST_STEPS_W = 1,
   BSP_FIRST_KT_W = 2,        // H * K * I
   BSP_FIRST_OFF_FRAG_W = 3,  // in words from the section start
+};
+
+// Three-part section (fp32 layers in whole chunks of eight input channels, of a size that it is worth the
+// room; read by bsp_f32x3.hip).  Steps as in the step section, in slabs of bsp_slab_channels channels; a
+// weight is the sum of three bf16 parts, each the one nearest to what those before it leave.
+//   [0..7]                        header, see enum
+//   slab_ptr[nstrips][nslabs+1]   first step of each (strip, slab)
+//   xdesc[nsteps][4]              per 16-lane group: chunk in the slab | tap row << 16 | tap column << 24
+//   wfrag[nsteps][3][64][8]       bf16 parts of the weights in MFMA operand order
+enum {
+  BSP_X3_HEADER_WORDS = 8,
+  BSP_X3_NSTEPS_W = 0,
+  BSP_X3_NSLABS_W = 1,
+  BSP_X3_SLAB_W = 2,
+  BSP_X3_OFF_SLAB_W = 3,     // in words from the section start
+  BSP_X3_OFF_DESC_W = 4,
+  BSP_X3_OFF_FRAG_W = 5,
+  BSP_X3_USABLE_W = 6,       // 0: a weight is not finite, below 2^-100 or past bf16's range
 };
 
 // Channels of one slab of the row-band section: windows are staged 128 channels at a time;

@@ -154,6 +154,20 @@ inline bool bsp_f32_general(int bo, int64_t I, int64_t O, int64_t HK, int64_t pa
   return pairs <= most * strips;
 }
 
+// fp32 in whole chunks of eight channels in: whether the three-part kernel takes the layer from the two
+// above (steps: the most of a strip on average; the others / here in us, 500 random layers: 1.31 times faster over
+// all, 1.36 over those this line takes, five of 429 more than a tenth slower).  Strips of 4x16 blocks
+// unite four block rows, which leaves little to skip, and one or two strips do not pay for the splitting of
+// a long pixel: 4x16 3x3 35x35x448->16 batch 2 at stride 2 28 / 45, 12x12x408->8 1x3 11.2 / 14.2, 32x10x400->72 batch 2
+// 18.2 / 22.6 (a loss on this side), 49x49x104->584 and the like 1.5 times faster; 8x8 1x1 18x105x1120->16 17.1 / 24.9.
+// One chunk and tap is over at once in the general kernel: 1x1 70x70x8->768 batch 5 23 / 28.  3x3 56x56x64 batch 32
+// 55 / 37, 1x1 28x28x128->512 batch 8 16.5 / 12.2, 16x4 3x1 68x68x40->326 batch 11 31 / 21.
+inline bool bsp_f32x3_beats(int bo, int64_t strips, int64_t steps, int64_t P, int64_t I, int64_t HK) {
+  if (I * HK <= 8) return false;
+  if (bo == 4) return strips > 1 && (strips > 2 || steps <= 30) && strips * steps * ((P + 15) / 16) >= 6000;
+  return !(strips == 1 && bo == 8 && steps > 30);
+}
+
 // The widths of at most 64 columns that up to ceil(N / least) even chunks of N columns have, each once, the
 // widest first: 64 of them at the most, however wide the image is.
 template <typename F>
