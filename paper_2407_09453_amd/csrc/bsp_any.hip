@@ -414,6 +414,7 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
     asm volatile("" : "+v"(id));  // (lane, column and group once more: no registers for them until here)
     const int lane = id & 63, g = lane >> 4, jn = lane & 15;
     const f32x4_t bv = bias4<KIND>(a, strip * BSP_STRIP + 4 * g);
+    const RescaleI8 rescale(__builtin_bit_cast(i32x4_t, bv), KIND == kI8 ? a.shift : 0);
     unsigned char* ot = lds + (pg * PT * 16 + jn) * opitch;
     uint32_t bad = 0;  // bit 15 or 31: a result that is not finite (an exponent of ones carries over)
     auto not_finite = [](uint32_t pair) { return (pair & 0x7F807F80u) + 0x00800080u; };
@@ -429,7 +430,7 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
       } else if (a.y32) {
         *(f32x4_t*)(ot + c * 4) = v;
       } else {
-        *(uint32_t*)(ot + c) = rescale_i8x4(__builtin_bit_cast(i32x4_t, acc[t]), __builtin_bit_cast(i32x4_t, bv), a.shift);
+        *(uint32_t*)(ot + c) = rescale(__builtin_bit_cast(i32x4_t, acc[t]));
       }
     }
     if constexpr (KIND == kBf16) {

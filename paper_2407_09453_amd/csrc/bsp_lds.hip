@@ -503,11 +503,12 @@ __global__ __launch_bounds__(kThreads, 1) void conv_lds(ConvParams p, TileCfg t,
     if (!reload_w) __syncthreads();  // E (the staging tile has been drained by now)
     if (sl == t.nslabs - 1 && valid) {
       // + bias, one rounding; lane holds channels 4g..4g+3 of pixel jn of every pixel tile
+      const RescaleI8 rescale(__builtin_bit_cast(i32x4_t, acc_t{bv[0], bv[1], bv[2], bv[3]}), I8 ? c.shift : 0);
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
         if constexpr (I8) {
           // exact sum + 32-bit bias, rounding right shift (ties upward), saturation to int8
-          const uint32_t packed = rescale_i8x4(acc[nt], i32x4_t{bv[0], bv[1], bv[2], bv[3]}, c.shift);
+          const uint32_t packed = rescale(acc[nt]);
           *(uint32_t*)(lds + orow + nt * 16 * OUT_ROW) = packed;
         } else {
           u32x2_t v;

@@ -263,9 +263,10 @@ __global__ __launch_bounds__(MAXT) void conv_pw(PwArgs a) {
     // + bias, rounding right shift (ties upward), saturation, into the image of the output lines
     unsigned char* ot = lds + a.out_off;
     const int range0 = ns * a.NS * 16, lpix = pg * (PT * 16) + c;
+    const RescaleI8 rescale(bv, a.relu);
 #pragma unroll
     for (int t = 0; t < PT; ++t) {
-      const uint32_t v = rescale_i8x4(acc[t], bv, a.relu);
+      const uint32_t v = rescale(acc[t]);
       if (chan >= 0) *(uint32_t*)(ot + (lpix + t * 16) * a.opitch + (chan - range0)) = v;
     }
     __syncthreads();

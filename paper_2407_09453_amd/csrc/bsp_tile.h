@@ -64,31 +64,48 @@ __device__ __forceinline__ u32x2_t post_bf16x4_reg(u32x2_t v, u32x2_t r, bool ha
 
 // Four int8 results from four exact sums: + 32-bit bias, rounding right shift (ties upward),
 // saturation to [-128, 127], lowest channel in the lowest byte; nothing wraps.  Up to a shift of 24 a
-// sum that leaves 32 bits saturates either way, so a saturating 32-bit addition and the rounding
-// bit taken by itself give the same bytes as 64-bit arithmetic at a quarter of its instructions (five
-// per result); in the pointwise kernel, whose 1x1 56x56x64->256 layer at batch 32 has one step per
-// strip, 16.5 -> 15.6 us.
+// sum that leaves 32 bits saturates either way, so one saturating addition of the bias and half a unit (put
+// together once for all of a strip's pixels), a shift and a median do, and the bytes are put together by
+// permutes: fifteen instructions for four results.  (A bias within half a unit of the largest integer takes
+// the 64-bit way.)  1x1 56x56x64->256 at batch 32, whose strips have one step, in the pointwise kernel: 16.5
+// us with 64 bits, 15.6 with the rounding bit added by itself (twenty-eight instructions); that form and this one
+// in turn on another box 14.0 and 12.8; all ResNet50-shaped layers 542 -> 524.
 typedef __attribute__((ext_vector_type(4))) int acc_i32x4_t;
-__device__ __forceinline__ uint32_t rescale_i8x4(acc_i32x4_t sum, acc_i32x4_t bias, int shift) {
-  int q[4];
-  if (shift <= 24) {
+struct RescaleI8 {
+  acc_i32x4_t bias, plus;  // plus: the bias and half a unit
+  int shift;
+  bool wide;
+  __device__ __forceinline__ RescaleI8(acc_i32x4_t b, int s) : bias(b), shift(s) {
+    const int half = s && s <= 24 ? 1 << (s - 1) : 0;
+    bool near = false;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int v = __builtin_elementwise_add_sat(sum[r], bias[r]);
-      const int up = shift ? (int)__builtin_amdgcn_ubfe((uint32_t)v, (uint32_t)(shift - 1), 1u) : 0;
-      q[r] = (v >> shift) + up;
-      q[r] = q[r] < -128 ? -128 : (q[r] > 127 ? 127 : q[r]);
+      near |= b[r] > 0x7FFFFFFF - half;
+      plus[r] = (int)((uint32_t)b[r] + (uint32_t)half);
     }
-  } else {
-    const long long half = 1ll << (shift - 1);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const long long w = ((long long)sum[r] + bias[r] + half) >> shift;
-      q[r] = w < -128 ? -128 : (w > 127 ? 127 : (int)w);
-    }
+    wide = s > 24 || __ballot(near) != 0;
   }
-  return (uint32_t)(q[0] & 0xFF) | (uint32_t)(q[1] & 0xFF) << 8 | (uint32_t)(q[2] & 0xFF) << 16 | (uint32_t)q[3] << 24;
-}
+  __device__ __forceinline__ uint32_t operator()(acc_i32x4_t sum) const {
+    int q[4];
+    if (!wide) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int v = __builtin_elementwise_add_sat(sum[r], plus[r]) >> shift;
+        q[r] = min(max(v, -128), 127);
+      }
+    } else {
+      const long long half = shift ? 1ll << (shift - 1) : 0;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const long long w = ((long long)sum[r] + bias[r] + half) >> shift;
+        q[r] = w < -128 ? -128 : (w > 127 ? 127 : (int)w);
+      }
+    }
+    const uint32_t lo = __builtin_amdgcn_perm((uint32_t)q[1], (uint32_t)q[0], 0x0c0c0400u);
+    const uint32_t hi = __builtin_amdgcn_perm((uint32_t)q[3], (uint32_t)q[2], 0x04000c0cu);
+    return lo | hi;
+  }
+};
 
 // The activations one step needs: every pixel tile of the wave reads its 16
 // bytes at the offset the step's descriptor d (chunk, tap) selects.
