@@ -106,6 +106,10 @@ int dispatch(const bsp_weights* w, const ConvParams& p, void* stream, const Fixe
     const bool flat = p.H == 1 && p.K == 1 && p.ph == 0 && p.pw == 0 && p.sh == 1 && p.sw == 1;
     // (a fixed scratch array refuses the layers it is too small for, whichever kernel takes them)
     if (fixed && (allow & BSP_KERNEL_FC) && bsp_fc_xlds_scratch(p, w->dtype, w->bo, w->bi) > fixed->bytes) return BSP_ERR_CAPACITY;
+    if (any && chunked && p.P <= 64 && p.H == 1 && p.K == 1 && bsp_pw_few_beats(w->bo, p.P, p.I, p.O)) {
+      rc = bsp_launch_pw_few(p, w->plan_host, st);
+      if (rc != BSP_ERR_UNSUPPORTED) return rc;
+    }
     if (any && chunked && bsp_any_few(w->bo, p.P, p.I, p.O, flat)) {
       rc = bsp_launch_any(p, w->plan_host, st);
       if (rc != BSP_ERR_UNSUPPORTED) return rc;

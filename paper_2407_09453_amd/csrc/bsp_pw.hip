@@ -21,6 +21,7 @@
 //
 // Staged pixels past the layer's last pixel are never written to LDS and never stored: each
 // MFMA column depends on its own pixel only.
+#include "bsp_kept.h"
 #include "bsp_launch.h"
 #include "bsp_tile.h"
 
@@ -58,6 +59,17 @@ struct PwArgs {
 #endif
 };
 
+// Up to 64 pixels, where the layers run that the streaming FC kernels and the any-shape kernel take otherwise: a
+// sum that is no finite number is formed again from kept blocks alone, as those kernels do (looking for one: a ballot,
+// a flag per wave and a barrier, 0.1 to 0.2 us of 1 x 512 -> 2048's 4.1).  Instances of their own keep the others
+// as they are.
+struct PwFewArgs : PwArgs {
+  const int32_t* plan;
+  const unsigned char* payload;
+  int32_t H, K, lbo;               // 1, 1, log2 of the block rows' height
+  int32_t flag_off;                // LDS offset of a flag per wave
+};
+
 #ifdef BSP_ROWS_TUNE
 #define PW_MARK(k)                                                                                   \
   do {                                                                                               \
@@ -71,10 +83,10 @@ typedef __attribute__((address_space(1))) const void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
 // KIND: 8 or 4, the channels per unit of a bf16 layer; 16, an int8 layer.
-template <int PT, int KIND, int D, int MAXT>
-__global__ __launch_bounds__(MAXT) void conv_pw(PwArgs a) {
-  constexpr bool CW4 = KIND == 4, I8 = KIND == 16;
-  kernarg_touch<PwArgs>();
+template <int PT, int KIND, int D, int MAXT, typename Args>
+__global__ __launch_bounds__(MAXT) void conv_pw(Args a) {
+  constexpr bool CW4 = KIND == 4, I8 = KIND == 16, FEW = std::is_same<Args, PwFewArgs>::value;
+  kernarg_touch<Args>();
   extern __shared__ __align__(16) unsigned char lds[];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -180,7 +192,7 @@ __global__ __launch_bounds__(MAXT) void conv_pw(PwArgs a) {
   PW_MARK(4);
   __syncthreads();                // everybody's have
   PW_MARK(5);
-  if (!active && !a.win_out) return;  // (with win_out every wave helps to store the tile)
+  if (!FEW && !active && !a.win_out) return;  // (with win_out every wave helps to store the tile)
 
   const int lp0 = pg * (PT * 16) + c;  // this lane's pixel of the wave's first lane tile
   const uint32_t swz = ((uint32_t)lp0 >> a.swz_shift) & (uint32_t)a.swz_mask;  // the same in every lane tile
@@ -281,6 +293,40 @@ __global__ __launch_bounds__(MAXT) void conv_pw(PwArgs a) {
     return;
   }
   const int ptile0 = pix0 + pg * (PT * 16);
+  if constexpr (FEW) {
+    uint32_t* flags = (uint32_t*)(lds + a.flag_off);
+    bool bad = false;
+#pragma unroll
+    for (int t = 0; t < PT; ++t)
+      if (chan >= 0 && ptile0 + t * 16 + c < a.P) {  // (the other lanes' pixels were never staged)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) bad |= (__float_as_uint(acc[t][r]) & 0x7F800000u) == 0x7F800000u;
+      }
+    const uint64_t mine = __ballot(bad);
+    if (lane == 0) flags[wave] = mine != 0;
+    __syncthreads();
+    if (__ballot(lane < nwaves && flags[lane < nwaves ? lane : 0])) {
+      // the workgroup's strips (whole windows of four) cover the channels of as many strips in natural order
+      const int nat = ns * a.NS + sidx, ch = nat * BSP_STRIP + 4 * g;
+      if (sidx >= a.NS || nat * BSP_STRIP >= a.O) return;
+      f32x4_t b4 = {0.f, 0.f, 0.f, 0.f};
+      if (a.bias && ch < a.O) b4 = f32x4_t{a.bias[ch], a.bias[ch + 1], a.bias[ch + 2], a.bias[ch + 3]};
+#pragma unroll 1
+      for (int t = 0; t < PT; ++t) {
+        const int pixel = ptile0 + t * 16 + c, p = min(pixel, a.P - 1);
+        const int img = (int)fdiv((uint32_t)p, a.d_mn), r2 = p - img * a.MN;
+        const int oy = (int)fdiv((uint32_t)r2, a.d_n), ox = r2 - oy * a.N;
+        const f32x4_t v = kept_only<true>(a, a.X + (int64_t)img * a.L * a.J * a.I * 2, nat, oy * a.S, ox * a.S, lane) + b4;
+        if (pixel >= a.P || ch >= a.O) continue;
+        u32x2_t o = {pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)};
+        const uint32_t off = ((uint32_t)pixel * (uint32_t)a.O + (uint32_t)ch) * 2u;
+        if (a.residual || a.relu) o = post_bf16x4(o, a.residual ? (const uint16_t*)(a.residual + off) : nullptr, 4, true, a.relu);
+        *(u32x2_t*)(a.Y + off) = o;
+      }
+      return;
+    }
+    if (!active && !a.win_out) return;
+  }
   // lane rows 0/1 (and 2/3) hold the two halves of one 8-channel block row: after an exchange
   // an even row has all eight channels of lane tile t, an odd row those of lane tile t + 1
   const int ch8 = __builtin_amdgcn_ds_bpermute(((lane & 32) + c) << 2, chan);  // the even row's channel
@@ -396,42 +442,44 @@ __global__ __launch_bounds__(MAXT) void conv_pw(PwArgs a) {
 
 constexpr int kLdsLimit = 160 * 1024;
 
-template <int PT, int KIND, int D, int MAXT>
-int launch_inst(const PwArgs& a, dim3 grid, int threads, size_t ldsb, hipStream_t st) {
+template <int PT, int KIND, int D, int MAXT, typename Args>
+int launch_inst(const Args& a, dim3 grid, int threads, size_t ldsb, hipStream_t st) {
   static bool raised = false;  // dynamic LDS above 64 KB has to be allowed once per kernel
   if (!raised) {
-    if (hipFuncSetAttribute((const void*)conv_pw<PT, KIND, D, MAXT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    if (hipFuncSetAttribute((const void*)conv_pw<PT, KIND, D, MAXT, Args>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             kLdsLimit) != hipSuccess)
       return BSP_ERR_HIP;
     raised = true;
   }
-  hipLaunchKernelGGL((conv_pw<PT, KIND, D, MAXT>), grid, dim3(threads), ldsb, st, a);
+  hipLaunchKernelGGL((conv_pw<PT, KIND, D, MAXT, Args>), grid, dim3(threads), ldsb, st, a);
   return hipGetLastError() == hipSuccess ? BSP_OK : BSP_ERR_HIP;
 }
 
 // Ring depth D: strips of at most 2 (4) steps take instances with as many registers for
 // weights, which leaves room for more waves per SIMD; deep asks for 16 (workgroups of at most
 // 512 threads, which may then use 256 registers per lane); otherwise 8.
-template <int KIND, int D, int MAXT>
-int launch_d(const PwArgs& a, int PT, dim3 grid, int threads, size_t ldsb, hipStream_t st) {
+template <int KIND, int D, int MAXT, typename Args>
+int launch_d(const Args& a, int PT, dim3 grid, int threads, size_t ldsb, hipStream_t st) {
   if (threads > MAXT) return BSP_ERR_UNSUPPORTED;
   switch (PT) {
-    case 1: return launch_inst<1, KIND, D, MAXT>(a, grid, threads, ldsb, st);
-    case 2: return launch_inst<2, KIND, D, MAXT>(a, grid, threads, ldsb, st);
-    case 4: return launch_inst<4, KIND, D, MAXT>(a, grid, threads, ldsb, st);
-    case 8: return launch_inst<8, KIND, D, (D >= 8 ? 512 : MAXT)>(a, grid, threads, ldsb, st);  // 8 lane tiles and a ring of 8 need more than 128 registers
+    case 1: return launch_inst<1, KIND, D, MAXT, Args>(a, grid, threads, ldsb, st);
+    case 2: return launch_inst<2, KIND, D, MAXT, Args>(a, grid, threads, ldsb, st);
+    case 4: return launch_inst<4, KIND, D, MAXT, Args>(a, grid, threads, ldsb, st);
+    case 8:
+      if constexpr (std::is_same<Args, PwArgs>::value)
+        return launch_inst<8, KIND, D, (D >= 8 ? 512 : MAXT), Args>(a, grid, threads, ldsb, st);  // 8 lane tiles and a ring of 8 need more than 128 registers
   }
   return BSP_ERR_UNSUPPORTED;
 }
 
-template <int KIND>
-int launch_pt(const PwArgs& a, int PT, int depth, dim3 grid, int threads, size_t ldsb, hipStream_t st) {
+template <int KIND, typename Args>
+int launch_pt(const Args& a, int PT, int depth, dim3 grid, int threads, size_t ldsb, hipStream_t st) {
   if (PT == 8 && depth >= 8 && threads > 512) return BSP_ERR_UNSUPPORTED;
   switch (depth) {
-    case 2: return launch_d<KIND, 2, 1024>(a, PT, grid, threads, ldsb, st);
-    case 4: return launch_d<KIND, 4, 1024>(a, PT, grid, threads, ldsb, st);
-    case 8: return launch_d<KIND, 8, 1024>(a, PT, grid, threads, ldsb, st);
-    case 16: return launch_d<KIND, 16, 512>(a, PT, grid, threads, ldsb, st);
+    case 2: return launch_d<KIND, 2, 1024, Args>(a, PT, grid, threads, ldsb, st);
+    case 4: return launch_d<KIND, 4, 1024, Args>(a, PT, grid, threads, ldsb, st);
+    case 8: return launch_d<KIND, 8, 1024, Args>(a, PT, grid, threads, ldsb, st);
+    case 16: return launch_d<KIND, 16, 512, Args>(a, PT, grid, threads, ldsb, st);
   }
   return BSP_ERR_UNSUPPORTED;
 }
@@ -482,7 +530,7 @@ PwChoice pw_choose(int P, int I, int O, int nstrips, int pitch, bool windowed, b
 
 namespace {
 
-int launch_pw(const ConvParams& p, int dtype, const void* plan_host, int shift, hipStream_t st) {
+int launch_pw(const ConvParams& p, int dtype, const void* plan_host, int shift, bool few, hipStream_t st) {
   const bool i8 = dtype == BSP_I8;
   if (!plan_host) return BSP_ERR_UNSUPPORTED;
   const int32_t* hdr = (const int32_t*)plan_host;
@@ -492,7 +540,7 @@ int launch_pw(const ConvParams& p, int dtype, const void* plan_host, int shift, 
     return BSP_ERR_UNSUPPORTED;
   const int32_t* rs = hdr + hdr[BSP_PLAN_OFF_ROWS_W];
   if (p.H != 1 || p.K != 1 || p.ph != 0 || p.pw != 0 || p.sh != p.sw || p.sh < 1) return BSP_ERR_UNSUPPORTED;
-  if (rs[BSP_ROWS_NSLABS_W] != 1 || p.P <= 64) return BSP_ERR_UNSUPPORTED;  // (FC layers: streaming kernels)
+  if (rs[BSP_ROWS_NSLABS_W] != 1 || few != (p.P <= 64)) return BSP_ERR_UNSUPPORTED;
   if ((int64_t)p.B * p.L * p.J * p.I * 2 >= (1ll << 31) || (int64_t)p.P * p.O * 2 >= (1ll << 31))
     return BSP_ERR_UNSUPPORTED;
   const int nstrips = rs[BSP_ROWS_NSTRIPS_W];
@@ -584,7 +632,22 @@ int launch_pw(const ConvParams& p, int dtype, const void* plan_host, int shift, 
   a.adv_rem = (threads * 16) % pitch;
   dim3 grid((unsigned)(a.per_xcd * 8));
   const int depth = ch.deep ? ch.deep : depth0;
-  switch (rs[BSP_ROWS_CW_W]) {
+  const int cw = rs[BSP_ROWS_CW_W];
+  if (few && !i8) {
+    // (what is formed again is a workgroup's range of channels: the range that its strips cover)
+    if (rs[BSP_ROWS_WINDOW_W] != 4 || (ch.NS % 4 && ch.NS < nstrips)) return BSP_ERR_UNSUPPORTED;
+    PwFewArgs f{};
+    static_cast<PwArgs&>(f) = a;
+    f.plan = p.plan;
+    f.payload = (const unsigned char*)p.payload;
+    f.H = f.K = 1;
+    f.lbo = __builtin_ctz(hdr[BSP_PLAN_BO_W]);
+    f.flag_off = (int32_t)ldsb;
+    if (ldsb + 64 > kLdsLimit) return BSP_ERR_UNSUPPORTED;
+    return cw == 4 ? launch_pt<4>(f, ch.PT, depth, grid, threads, (size_t)ldsb + 64, st)
+                   : launch_pt<8>(f, ch.PT, depth, grid, threads, (size_t)ldsb + 64, st);
+  }
+  switch (cw) {
     case 4: return launch_pt<4>(a, ch.PT, depth, grid, threads, (size_t)ldsb, st);
     case 8: return launch_pt<8>(a, ch.PT, depth, grid, threads, (size_t)ldsb, st);
     case 16: return launch_pt<16>(a, ch.PT, depth, grid, threads, (size_t)ldsb, st);
@@ -595,9 +658,15 @@ int launch_pw(const ConvParams& p, int dtype, const void* plan_host, int shift, 
 }  // namespace
 
 int bsp_launch_pw(const ConvParams& p, int dtype, const void* plan_host, hipStream_t st) {
-  return dtype == BSP_BF16 ? launch_pw(p, dtype, plan_host, 0, st) : BSP_ERR_UNSUPPORTED;
+  return dtype == BSP_BF16 ? launch_pw(p, dtype, plan_host, 0, false, st) : BSP_ERR_UNSUPPORTED;
+}
+
+int bsp_launch_pw_few(const ConvParams& p, const void* plan_host, hipStream_t st) {
+  return launch_pw(p, BSP_BF16, plan_host, 0, true, st);
 }
 
 int bsp_launch_pw_i8(const ConvParams& p, const void* plan_host, int shift, hipStream_t st) {
-  return p.residual || p.relu ? BSP_ERR_UNSUPPORTED : launch_pw(p, BSP_I8, plan_host, shift, st);
+  const bool few = p.P <= 64;
+  if (p.residual || p.relu || (few && !bsp_pw_few_beats_i8(p.I, p.O))) return BSP_ERR_UNSUPPORTED;
+  return launch_pw(p, BSP_I8, plan_host, shift, few, st);
 }

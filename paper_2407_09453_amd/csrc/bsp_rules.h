@@ -85,6 +85,27 @@ inline bool bsp_any_few(int bo, int64_t P, int64_t I, int64_t O, bool pointwise)
   return !(pointwise && bo != 8 && P > 32 && O <= 4096 && I * O > 4400000);
 }
 
+// 1x1 layers of up to 64 pixels, stride 1 or more: the pointwise kernel, which copies a pixel tile's whole rows into LDS
+// and walks each strip's weights behind one wait, against the kernels below it (streaming FC and any-shape in
+// bf16).  The call costs a launch, two memory latencies and the tile's copy; the copy grows with I, and from
+// some length on the streaming kernels' split of it is worth more.  Other us / pointwise us:
+//   8x8   1 x 512 -> 4096 4.4 / 4.1, 16 x 64 -> 1000 4.1 / 3.4, 49 x 512 -> 2048 5.0 / 4.4; past 512 channels
+//         only from 17 pixels: 28 x 1024 -> 1000 1.23x, 64 x 1280 -> 4096 1.43x, 1 x 1024 0.93x, 32 x 2048 -> 256 0.94x
+//   4x16  1 x 512 -> 1000 1.28x, 8 x 1280 -> 1000 1.06x, 1 x 2048 -> 256 0.89x; from 8192 channels out 1.4x to 2.5x
+//         whatever the length; past 16 pixels 512 channels 1.02x to 1.26x, 32 x 1024 -> 256 0.97x, -> 4096 1.09x
+//   16x4  to 16 pixels 1.3x to 3x; past them 512 -> 1000 1.01x, 1024 -> 1000 0.97x, 1024 -> 4096 1.06x
+inline bool bsp_pw_few_beats(int bo, int64_t P, int64_t I, int64_t O) {
+  if (I <= 512) return true;
+  if (I > 2048) return false;
+  if (bo == 8) return P > 16 && I <= 1280;
+  if (bo == 4) return P <= 16 ? I <= 1280 || O >= 8192 : I <= 1280 && O >= 4096;
+  return P <= 16 || O >= 4096;
+}
+
+// The same in int8, against the any-shape kernel: 1.05x to 1.35x for up to 1024 channels (1 x 256 -> 256
+// 1.31x, 49 x 512 -> 2048 1.29x, 64 x 1024 -> 1008 1.07x); 2048 -> 1008 0.92x, 2048 -> 4096 0.99x to 1.31x.
+inline bool bsp_pw_few_beats_i8(int64_t I, int64_t O) { return I <= 1024 || (I <= 2048 && O >= 4096); }
+
 // int8 against the LDS-resident kernel, which keeps one slab's weights in LDS.  One slab (other us /
 // any-shape us): below 20 K matrix instructions, 1x1 56x56x64->256 batch 2 6.4 / 5.0, batch 32 21 / 31.
 // Several slabs: always for a window, 7x7x512 batch 32 15.2 / 11.5, 2x2 47x47x208->32 batch 61 21 / 14, 25x25x624->192
