@@ -8,9 +8,9 @@
 // sixteen rows gives back at most two thirds of that (the union of its block rows' columns).  Bound by
 // LDS and the matrix cores alike: a step (four (chunk, tap) pairs) reads 3 KB of activations for six
 // instructions of 16 cycles.  The weights' parts lie in the plan in operand order; activations are split
-// once, where they are staged.  Measured (conv_f32 -> here): 3x3 56x56x64 batch 32 55 -> 39 us, of which the
-// products are 15 by LDS or by the matrix cores; 28x28x128 batch 8 25.6 -> 15.0, 1x1 28x28x128->512 batch 8
-// 16.5 -> 12.2; relative error of the first against 64 bits 3.1e-7 -> 1.0e-7.
+// once, where they are staged.  Measured (conv_f32 -> here): 3x3 56x56x64 batch 32 54 -> 34 us, of which the
+// products are 15 by LDS or by the matrix cores (36 with seven spilled registers); 28x28x128 batch 8 25.6 -> 15.0,
+// 1x1 28x28x128->512 batch 8 16.5 -> 12.2 (both with those spills); relative error of the first against 64 bits 3.1e-7 -> 1.0e-7.
 //
 // What three parts cannot hold takes another way: a tile that stages a non-zero value below 2^-100, or that
 // ends in an infinity or NaN (a value past bf16's range, an infinity times a zero that fills up a block
@@ -313,18 +313,23 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
 
   // ---- results: bias, into an LDS image of the tile's output; then all waves copy that out, 16 contiguous
   // bytes per lane, with the residual and ReLU
+  // (the lane anew: the rare path's pixels are those of `base`, and kept from there they were seven spilled
+  // registers, whose 13 MB of scratch at 3x3 56x56x64 batch 32 were written by every launch and read by none)
+  int el = lane;
+  asm volatile("" : "+v"(el));
+  const int eg = el >> 4, ejn = el & 15;
   uint32_t small = 0;
   for (int i = 0; i < nthreads >> 6; ++i) small |= flags[i];
   const int opitch = a.opitch;
   if (active) {
-    const int ch = strip * BSP_STRIP + 4 * g;
+    const int ch = strip * BSP_STRIP + 4 * eg;
     f32x4_t bv = {0.f, 0.f, 0.f, 0.f};
     if (a.bias) {
 #pragma unroll
       for (int r = 0; r < 4; ++r)
         if (ch + r < a.O) bv[r] = a.bias[ch + r];
     }
-    unsigned char* ot = lds + (pg * PT * 16 + jn) * opitch + (si * BSP_STRIP + 4 * g) * 4;
+    unsigned char* ot = lds + (pg * PT * 16 + ejn) * opitch + (si * BSP_STRIP + 4 * eg) * 4;
 #pragma unroll
     for (int t = 0; t < PT; ++t) {
       if ((t & (a.ks - 1)) != k) continue;
@@ -332,9 +337,9 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) again |= (__float_as_uint(acc[t][r]) & 0x7F800000u) == 0x7F800000u;
       if (__ballot(again)) {
-        const int p = min(p0 + (pg * PT + t) * 16 + jn, plast);
+        const int p = min(p0 + (pg * PT + t) * 16 + ejn, plast);
         const int y = (int)fdiv((uint32_t)p, a.d_cw), x = col0 + p - y * a.CW;
-        acc[t] = exact_tile(a, xim, strip, y * a.sh - a.ph, x * a.sw - a.pw, lane);
+        acc[t] = exact_tile(a, xim, strip, y * a.sh - a.ph, x * a.sw - a.pw, el);
       }
       *(f32x4_t*)(ot + t * 16 * opitch) = acc[t] + bv;
     }
