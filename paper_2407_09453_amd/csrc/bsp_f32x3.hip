@@ -314,7 +314,7 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
   // ---- results: bias, into an LDS image of the tile's output; then all waves copy that out, 16 contiguous
   // bytes per lane, with the residual and ReLU
   // (the lane anew: the rare path's pixels are those of `base`, and kept from there they were seven spilled
-  // registers, whose 13 MB of scratch at 3x3 56x56x64 batch 32 were written by every launch and read by none)
+  // registers, whose 11 MB of scratch at 3x3 56x56x64 batch 32 were written by every launch and read by none)
   int el = lane;
   asm volatile("" : "+v"(el));
   const int eg = el >> 4, ejn = el & 15;
