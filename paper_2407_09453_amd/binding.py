@@ -148,6 +148,8 @@ def load_library():
 
 # A layer call's arguments as one string of 14 words: ctypes converts an argument at a time, 1.2 of the 5 us
 # that a call of a small layer took on the host (5.2, now 4.4; FC 64 x 256 -> 256 fp32 5.3 -> 4.6 in all).
+# Arguments that are no plain integers, such as a stream given as a torch Stream or a ctypes pointer, go
+# through the entry point itself, where ctypes takes or refuses them.
 _CALL_CONV, _CALL_FC, _CALL_CONV_I8, _CALL_FC_I8 = range(4)
 _pack14 = struct.Struct("=14q").pack
 
@@ -488,10 +490,18 @@ class BspLayer:
         if general:
             bsp_conv2d_general(self.struct, X.data_ptr(), bias, out.data_ptr(), B, L, J, stride, pad, st)
             return out
-        rc = _lib.bsp_call_packed(_CALL_CONV, _pack14(
-            ctypes.addressof(self.struct), X.data_ptr(), bias or 0,
-            0 if residual is None else residual.data_ptr(), 1 if relu else 0, out.data_ptr(),
-            B, L, J, stride[0], stride[1], pad[0], pad[1], st or 0))
+        try:
+            words = _pack14(ctypes.addressof(self.struct), X.data_ptr(), bias or 0,
+                            0 if residual is None else residual.data_ptr(), 1 if relu else 0, out.data_ptr(),
+                            B, L, J, stride[0], stride[1], pad[0], pad[1], st or 0)
+        except struct.error:
+            if fused:
+                bsp_conv2d_fused(self.struct, X.data_ptr(), bias, None if residual is None else residual.data_ptr(),
+                                 relu, out.data_ptr(), B, L, J, stride, pad, st)
+            else:
+                bsp_conv2d(self.struct, X.data_ptr(), bias, out.data_ptr(), B, L, J, stride, pad, st)
+            return out
+        rc = _lib.bsp_call_packed(_CALL_CONV, words)
         if rc:
             raise BspError(rc, "bsp_conv2d_fused" if fused else "bsp_conv2d")
         return out
@@ -504,10 +514,19 @@ class BspLayer:
             import torch
             out = torch.empty((B, self.O), dtype=self.torch_dtype, device=X.device)
         st = _current_stream(X) if stream is None else stream
-        rc = _lib.bsp_call_packed(_CALL_FC, _pack14(
-            ctypes.addressof(self.struct), X.data_ptr(), 0 if self.d_bias is None else self.d_bias.data_ptr(),
-            0 if residual is None else residual.data_ptr(), 1 if relu else 0, out.data_ptr(),
-            B, 1, 1, 1, 1, 0, 0, st or 0))
+        bias = None if self.d_bias is None else self.d_bias.data_ptr()
+        try:
+            words = _pack14(ctypes.addressof(self.struct), X.data_ptr(), bias or 0,
+                            0 if residual is None else residual.data_ptr(), 1 if relu else 0, out.data_ptr(),
+                            B, 1, 1, 1, 1, 0, 0, st or 0)
+        except struct.error:
+            if residual is not None or relu:
+                bsp_fc_fused(self.struct, X.data_ptr(), bias, None if residual is None else residual.data_ptr(),
+                             relu, out.data_ptr(), B, st)
+            else:
+                bsp_fc(self.struct, X.data_ptr(), bias, out.data_ptr(), B, st)
+            return out
+        rc = _lib.bsp_call_packed(_CALL_FC, words)
         if rc:
             raise BspError(rc, "bsp_fc_fused" if residual is not None or relu else "bsp_fc")
         return out
@@ -630,10 +649,16 @@ class BspLayerI8:
             out = torch.empty(self.out_shape(B, L, J, stride, pad), dtype=ydt, device=X.device)
         assert out.dtype == ydt
         st = _current_stream(X) if stream is None else stream
-        rc = _lib.bsp_call_packed(_CALL_CONV_I8, _pack14(
-            ctypes.addressof(self.struct), X.data_ptr(), 0 if self.d_bias is None else self.d_bias.data_ptr(),
-            out.data_ptr(), BSP_I32 if shift is None else BSP_I8, 0 if shift is None else shift,
-            B, L, J, stride[0], stride[1], pad[0], pad[1], st or 0))
+        bias = None if self.d_bias is None else self.d_bias.data_ptr()
+        code = BSP_I32 if shift is None else BSP_I8
+        try:
+            words = _pack14(ctypes.addressof(self.struct), X.data_ptr(), bias or 0, out.data_ptr(), code,
+                            0 if shift is None else shift, B, L, J, stride[0], stride[1], pad[0], pad[1], st or 0)
+        except struct.error:
+            bsp_conv2d_i8(self.struct, X.data_ptr(), bias, out.data_ptr(), code, 0 if shift is None else shift,
+                          B, L, J, stride, pad, st)
+            return out
+        rc = _lib.bsp_call_packed(_CALL_CONV_I8, words)
         if rc:
             raise BspError(rc, "bsp_conv2d_i8")
         return out
@@ -647,10 +672,15 @@ class BspLayerI8:
         if out is None:
             out = torch.empty((B, self.O), dtype=ydt, device=X.device)
         st = _current_stream(X) if stream is None else stream
-        rc = _lib.bsp_call_packed(_CALL_FC_I8, _pack14(
-            ctypes.addressof(self.struct), X.data_ptr(), 0 if self.d_bias is None else self.d_bias.data_ptr(),
-            out.data_ptr(), BSP_I32 if shift is None else BSP_I8, 0 if shift is None else shift,
-            B, 1, 1, 1, 1, 0, 0, st or 0))
+        bias = None if self.d_bias is None else self.d_bias.data_ptr()
+        code = BSP_I32 if shift is None else BSP_I8
+        try:
+            words = _pack14(ctypes.addressof(self.struct), X.data_ptr(), bias or 0, out.data_ptr(), code,
+                            0 if shift is None else shift, B, 1, 1, 1, 1, 0, 0, st or 0)
+        except struct.error:
+            bsp_fc_i8(self.struct, X.data_ptr(), bias, out.data_ptr(), code, 0 if shift is None else shift, B, st)
+            return out
+        rc = _lib.bsp_call_packed(_CALL_FC_I8, words)
         if rc:
             raise BspError(rc, "bsp_fc_i8")
         return out
