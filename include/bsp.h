@@ -179,7 +179,10 @@ enum bsp_kernel_family {
  *   X, Y     device, element type w->dtype; bias device float[O] or null (no bias)
  *   stream   a hipStream_t passed as void* (null = default stream)
  * Accumulation is fp32; bias is added in fp32; the result is rounded once
- * (nearest-even) to w->dtype.  Asynchronous: returns after the launch.
+ * (nearest-even) to w->dtype.  An fp32 layer whose channels are whole groups of eight may be
+ * multiplied as three bf16 parts a value: its sums of two terms and more lie nearer to the exact
+ * ones than those of fp32 multiply-adds, a sum with a single non-zero term may be one unit in the
+ * last place from the nearest float.  Asynchronous: returns after the launch.
  * B = 0 is valid and does nothing (X and Y may then be null).
  * Device memory the library owns: a bf16 layer with 8x8 blocks, 1x1 window and at most 64
  * output pixels whose activations do not fit the 150 KB of LDS in one piece (I * 32 *

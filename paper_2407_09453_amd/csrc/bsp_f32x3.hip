@@ -1,8 +1,14 @@
 // Single-precision layers in whole chunks of eight input channels on the bf16 matrix cores: every value is
 // the sum of three bf16 parts (8 + 8 + 8 bits: exact for 2^-100 <= |v| < 2^127), and of the nine products of
-// two values' parts the six largest are summed in fp32, the leading one by itself.  What is left out is
-// below 2^-25 of a product; a sum of n terms is rounded n / 32 times per part instead of n times, so results
-// lie nearer to 64 bits than those of fp32 multiply-adds.
+// two values' parts the six largest are summed in fp32, the leading one by itself.  (Splitting a number into
+// pieces whose products are exact is Dekker's, Numer. Math. 18, 1971.)  What is left out is below 2^-24 of
+// a product, as much as one rounding; a sum of n terms is rounded n / 32 times per part instead of n times, so
+// sums of two terms and more lie nearer to 64 bits than those of fp32 multiply-adds (2-norm of the error of 1x1
+// sums of 1, 2, 8 and 64 terms, multiply-adds / here: 2.54e-8 / 2.61e-8, 3.10e-8 / 2.62e-8, 5.37e-8 / 2.89e-8, 1.44e-7 /
+// 4.87e-8).  A sum of one term is the nearest float with a multiply-add and was not in 4 % of cases here; layers
+// whose strips have at most kShort steps, those that scale or permute channels among them, sum eight of the
+// nine: 2.54e-8, not the nearest in 0.2 %, by 0.506 of a last place at the most.  (Everywhere those two would cost
+// 3x3 56x56x64 batch 32 37 -> 42 us.)
 //
 // Why: the fp32 matrix instructions reach 117 to 150 TFLOP/s, six bf16 ones per product 380, and a strip of
 // sixteen rows gives back at most two thirds of that (the union of its block rows' columns).  Bound by
@@ -113,8 +119,8 @@ __device__ f32x4_t exact_tile(const X3Args& a, const float* xim, int strip, int 
 // One (tile of PT * 16 * PG output pixels) x (NS strips) per workgroup, as in conv_any: consecutive pixels of a
 // chunk of image columns, the input patch staged with its halo, as many slabs at a time as LDS takes.  A staged
 // pixel holds per chunk its three parts side by side, in an odd number of 16-byte pieces (no bank
-// conflicts within a patch row).  Wave = (strip, pixel group, share of the strip's steps).
-template <int PT>
+// conflicts within a patch row).  Wave = (strip, pixel group, share of the strip's steps).  SHORT: eight products.
+template <int PT, bool SHORT>
 __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
   kernarg_touch<X3Args>();
   extern __shared__ __align__(16) unsigned char lds[];
@@ -148,7 +154,7 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
     const int y = (int)fdiv((uint32_t)p, a.d_cw), x = p - y * a.CW;
     base[t] = ((y - m0) * a.lsh * a.TPW + x * a.lsw) * a.pitch;
   }
-  f32x4_t hi[PT], lo[PT];  // the leading products' sums, the other five's
+  f32x4_t hi[PT], lo[PT];  // the leading products' sums, the others'
 #pragma unroll
   for (int t = 0; t < PT; ++t) hi[t] = lo[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
@@ -240,14 +246,16 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
         for (int r = 0; r < 3; ++r) f[t][r] = *(const u32x4_t*)(lds + base[t0 + t] + at + r * 16);
     };
     auto mma = [&](int t0, const u32x4_t (&f)[2][3]) {
-      constexpr int wi[6] = {0, 0, 1, 1, 2, 0}, xi[6] = {0, 2, 1, 0, 0, 1};
+      constexpr int wi[8] = {0, 1, 2, 0, 1, 1, 2, 0}, xi[8] = {0, 2, 1, 2, 1, 0, 0, 1};
 #pragma unroll
-      for (int m = 0; m < 6; ++m)
+      for (int m = 0; m < 8; ++m) {
+        if (!SHORT && (m == 1 || m == 2)) continue;
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
           f32x4_t& acc = m == 0 ? hi[t0 + t] : lo[t0 + t];
           acc = mfma_bf16_16x16x32(w[wi[m]], f[t][xi[m]], acc);
         }
+      }
     };
     u32x4_t fa[2][3], fb[2][3];
     uint32_t at = 0;
@@ -375,6 +383,10 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
 }
 
 constexpr int kLdsLimit = 160 * 1024, kFlags = 32;
+// Steps of a strip up to which eight products of nine are summed: sixteen rows with one weight each meet at most
+// sixteen chunks of channels (4x16 blocks: thirty-two).  1x1 28x28x128->512 batch 8 10.8 -> 11.4 us, 56x56x64->64
+// batch 32 15.1 -> 15.4, ->256 40.1 -> 42.0, 3x3 40x40x24->200 batch 16 the same.
+constexpr int kShort = 4;
 
 inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
@@ -430,15 +442,15 @@ Pick choose(int B, int M, int N, int nstrips, int steps, int nslabs, int slab_ch
   return best;
 }
 
-template <int PT>
+template <int PT, bool SHORT>
 int launch_inst(const X3Args& a, int threads, size_t ldsb, hipStream_t st) {
   static bool raised = false;  // dynamic LDS above 64 KB has to be allowed once per kernel
   if (!raised) {
-    if (hipFuncSetAttribute((const void*)conv_f32x3<PT>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit) != hipSuccess)
+    if (hipFuncSetAttribute((const void*)conv_f32x3<PT, SHORT>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit) != hipSuccess)
       return BSP_ERR_HIP;
     raised = true;
   }
-  hipLaunchKernelGGL((conv_f32x3<PT>), dim3((unsigned)(a.per_xcd * 8)), dim3(threads), ldsb, st, a);
+  hipLaunchKernelGGL((conv_f32x3<PT, SHORT>), dim3((unsigned)(a.per_xcd * 8)), dim3(threads), ldsb, st, a);
   return hipGetLastError() == hipSuccess ? BSP_OK : BSP_ERR_HIP;
 }
 
@@ -566,5 +578,7 @@ int bsp_launch_f32x3(const ConvParams& p, const void* plan_host, hipStream_t st)
   // whole 128-byte lines leave as streaming stores (nothing dirty is left for the kernel's end)
   a.stream = best.NS >= a.nstrips ? flat || p.O >= 32 : p.O % 32 == 0 && best.NS % 2 == 0;
   const int threads = 64 * best.NS * best.PG * best.ks;
-  return best.PT == 4 ? launch_inst<4>(a, threads, (size_t)best.lds, st) : launch_inst<2>(a, threads, (size_t)best.lds, st);
+  const size_t ldsb = (size_t)best.lds;
+  if (steps <= kShort) return best.PT == 4 ? launch_inst<4, true>(a, threads, ldsb, st) : launch_inst<2, true>(a, threads, ldsb, st);
+  return best.PT == 4 ? launch_inst<4, false>(a, threads, ldsb, st) : launch_inst<2, false>(a, threads, ldsb, st);
 }

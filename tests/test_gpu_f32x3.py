@@ -104,3 +104,26 @@ def test_weights_beyond_three_parts_stay_on_the_fp32_kernel():
     W[0, 0, 0, 0] = 1e-35
     ran = kernels_of(lambda: bsp.BspLayer(W, gamma, 8, 8, "f32", bias=bias).conv2d(X, (1, 1), pad))
     assert any("conv_f32<" in k for k in ran), ran
+
+
+@pytest.mark.parametrize("I", [64, 128, 136])
+def test_sums_of_one_product(I):
+    """One-hot inputs.  Up to sixteen chunks eight of the nine products of parts are summed: what is left out is
+    2^-34 of the product, and the minor ones' sum, at most 2^-6 of it, is rounded twice after the small ones, together
+    less than 2^-7 of a unit in the last place.  Beyond them six: 2^-24 of the product is left out at the most."""
+    import torch
+    gen = torch.Generator("cuda").manual_seed(7)
+    B, L, O = 8, 40, 64
+    W = torch.randn(O, 1, 1, I, generator=gen, device="cuda")
+    x = torch.randn(B, L, L, generator=gen, device="cuda")
+    x[0, 0] = W[:, 0, 0, 0] = 1 + 2.0 ** -8 - 2.0 ** -17  # the parts with the largest minor products
+    at = torch.randint(0, I, (B, L, L, 1), generator=gen, device="cuda")
+    at[0, 0] = 0
+    X = torch.zeros(B, L, L, I, device="cuda").scatter_(3, at, x[..., None])
+    layer = bsp.BspLayer(W.cpu().numpy(), np.ones((8, I // 8), np.uint8), 8, 8, "f32")
+    ran = kernels_of(lambda: layer.conv2d(X))
+    assert any("conv_f32x3" in k for k in ran), ran
+    want = x.double()[..., None] * W.view(O, I).t()[at[..., 0]].double()
+    ulp = torch.pow(2.0, torch.floor(torch.log2(want.abs())) - 23)
+    out = 0.0 if I <= 128 else 2.0 ** -24 * want.abs()
+    assert bool(((layer.conv2d(X).double() - want).abs() <= out + (0.5 + 2.0 ** -7) * ulp).all())
