@@ -1,5 +1,5 @@
 // Single-precision layers in whole chunks of eight input channels on the bf16 matrix cores: every value is
-// the sum of three bf16 parts (8 + 8 + 8 bits: exact for 2^-100 <= |v| < 2^127), and of the nine products of
+// the sum of three bf16 parts (8 + 8 + 8 bits, exact: see kScale), and of the nine products of
 // two values' parts the six largest are summed in fp32, the leading one by itself.  (Splitting a number into
 // pieces whose products are exact is Dekker's, Numer. Math. 18, 1971.)  What is left out is below 2^-24 of
 // a product, as much as one rounding; a sum of n terms is rounded n / 32 times per part instead of n times, so
@@ -18,10 +18,10 @@
 // products are 15 by LDS or by the matrix cores (36 with seven spilled registers); 28x28x128 batch 8 25.6 -> 15.0,
 // 1x1 28x28x128->512 batch 8 16.5 -> 12.2 (both with those spills); relative error of the first against 64 bits 3.1e-7 -> 1.0e-7.
 //
-// What three parts cannot hold takes another way: a tile that stages a non-zero value below 2^-100, or that
-// ends in an infinity or NaN (a value past bf16's range, an infinity times a zero that fills up a block
-// row), is summed again in fp32, block row by block row, straight from memory (exact_tile); layers with such
-// weights stay with conv_f32.
+// What three parts cannot hold takes another way: a lane tile that ends in an infinity or NaN (a value or sum past
+// 2^111, an infinity times a zero that fills up a block row) is summed again in fp32, block row by block row,
+// straight from memory (exact_tile); layers with weights that are not finite, below 2^-100 or from 2^127
+// upwards stay with conv_f32.
 #include "bsp_launch.h"
 #include "bsp_tile.h"
 
@@ -52,12 +52,18 @@ struct X3Args {
   int32_t nslabs, spst, nstages, slab_chunks;  // the plan's slabs, how many are staged at a time, chunks of one
   int32_t nstrips, NS, PG, ks, lpg, lks, nset; // strips per workgroup, pixel groups, waves that share a strip's steps; log2
   int32_t total, per_xcd;
-  int32_t opitch, flag_off, stream;
+  int32_t opitch, stream;
   int32_t lbo;
   const int32_t* plan;
   const float* payload;
   FastDiv d_nset, d_tpc, d_nchunk, d_cw, d_tpw, d_ppp, d_opp;
 };
+
+// Activations are multiplied by this where they are staged, and the sums divided by it: the smallest floats'
+// last bits then lie at 2^-133, where bf16's end, so that no value below 2^111 loses any, and a product of 2^-126 keeps
+// its last 39.  (Without it each tile that staged a value below 2^-100 was summed twice, the second time straight from
+// memory: 3x3 56x56x64 batch 32 with one such value 213 us, with one in a hundred 656, now 37 as without any.)
+constexpr float kScale = 65536.f;
 
 // eight floats -> three times eight bf16
 struct Parts {
@@ -162,7 +168,6 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
   const int pieces = rows * a.TPW * a.ppp;
   const float* xim = a.X + (int64_t)img * a.L * a.J * a.I;
   const int rowpitch = a.TPW * a.pitch;
-  uint32_t least = 0xFFFFFFFFu;  // the smallest non-zero magnitude staged, as twice its bits less one
 
   for (int stg = 0; stg < a.nstages; ++stg) {
     const int sl0 = stg * a.spst, sl1 = min(sl0 + a.spst, a.nslabs);
@@ -223,9 +228,7 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         if (dst[u] < 0) continue;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) least = min(least, (__float_as_uint(v[u][i >> 2][i & 3]) << 1) - 1u);
-        const Parts s = split8(v[u][0], v[u][1]);
+        const Parts s = split8(v[u][0] * kScale, v[u][1] * kScale);
 #pragma unroll
         for (int r = 0; r < 3; ++r) *(u32x4_t*)(lds + dst[u] + r * 16) = s.p[r];
       }
@@ -311,12 +314,8 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
       acc[t] = v;
     }
   }
-  // does the tile hold a value that three parts do not? (a flag per wave)
-  uint32_t* flags = (uint32_t*)(lds + a.flag_off);
-  {
-    const bool small = __ballot(least < (27u << 24) - 1u) != 0;  // below 2^-100
-    if (lane == 0) flags[wave] = small;
-  }
+#pragma unroll
+  for (int t = 0; t < PT; ++t) acc[t] *= 1.f / kScale;
   __syncthreads();  // everybody is done with the patch (the partial sums)
 
   // ---- results: bias, into an LDS image of the tile's output; then all waves copy that out, 16 contiguous
@@ -326,8 +325,6 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
   int el = lane;
   asm volatile("" : "+v"(el));
   const int eg = el >> 4, ejn = el & 15;
-  uint32_t small = 0;
-  for (int i = 0; i < nthreads >> 6; ++i) small |= flags[i];
   const int opitch = a.opitch;
   if (active) {
     const int ch = strip * BSP_STRIP + 4 * eg;
@@ -341,7 +338,7 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
 #pragma unroll
     for (int t = 0; t < PT; ++t) {
       if ((t & (a.ks - 1)) != k) continue;
-      bool again = small != 0;
+      bool again = false;
 #pragma unroll
       for (int r = 0; r < 4; ++r) again |= (__float_as_uint(acc[t][r]) & 0x7F800000u) == 0x7F800000u;
       if (__ballot(again)) {
@@ -382,7 +379,7 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
   }
 }
 
-constexpr int kLdsLimit = 160 * 1024, kFlags = 32;
+constexpr int kLdsLimit = 160 * 1024;
 // Steps of a strip up to which eight products of nine are summed: sixteen rows with one weight each meet at most
 // sixteen chunks of channels (4x16 blocks: thirty-two).  1x1 28x28x128->512 batch 8 10.8 -> 11.4 us, 56x56x64->64
 // batch 32 15.1 -> 15.4, ->256 40.1 -> 42.0, 3x3 40x40x24->200 batch 16 the same.
@@ -412,12 +409,12 @@ Pick choose(int B, int M, int N, int nstrips, int steps, int nslabs, int slab_ch
         for (int spst = nslabs;; spst = (spst + 1) / 2) {
           const int ppp = std::min(spst * slab_chunks, chunks), nstages = cdiv(nslabs, spst);
           const int64_t patch = pix * ((ppp * 3 | 1) * 16);
-          if (patch <= kLdsLimit - kFlags)
+          if (patch <= kLdsLimit)
             for (int ks : {1, 2, 4}) {
               if (PG * ks > 8 || ks > PT) continue;
               const int nsmax = std::min(nstrips, 8 / (PG * ks));
               const int NS = cdiv(nstrips, cdiv(nstrips, nsmax)), waves = NS * PG * ks;
-              const int64_t ldsb = std::max({patch, ks > 1 ? (int64_t)waves * PT * 1024 : 0, (int64_t)px * (NS * 64 + 16)}) + kFlags;
+              const int64_t ldsb = std::max({patch, ks > 1 ? (int64_t)waves * PT * 1024 : 0, (int64_t)px * (NS * 64 + 16)});
               if (ldsb > kLdsLimit) continue;
               const int64_t wgs = tiles * cdiv(nstrips, NS);
               const int resident = std::max(1, std::min((int)(kLdsLimit / ldsb), 16 / waves));
@@ -574,7 +571,6 @@ int bsp_launch_f32x3(const ConvParams& p, const void* plan_host, hipStream_t st)
   a.d_ppp = make_fastdiv((uint32_t)a.ppp);
   a.d_opp = make_fastdiv((uint32_t)(best.NS * 4));
   a.opitch = best.NS * BSP_STRIP * 4 + 16;
-  a.flag_off = best.lds - kFlags;
   // whole 128-byte lines leave as streaming stores (nothing dirty is left for the kernel's end)
   a.stream = best.NS >= a.nstrips ? flat || p.O >= 32 : p.O % 32 == 0 && best.NS % 2 == 0;
   const int threads = 64 * best.NS * best.PG * best.ks;

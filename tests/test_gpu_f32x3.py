@@ -21,7 +21,12 @@ SHAPES = [
     (4, 35, 35, 96, 100, 3, 3, 1, (4, 16), 0.5),     # four block rows a strip
     (2, 14, 14, 256, 256, 3, 3, 1, (8, 8), 1.0),     # waves share a strip's steps
     (300, 7, 5, 24, 136, 2, 2, 1, (8, 8), 0.5),
+    (2, 10, 10, 512, 64, 3, 3, 1, (16, 4), 0.75),    # four lane tiles: four waves share a strip's steps
+    (6, 40, 40, 64, 40, 3, 3, 1, (4, 16), 0.5),      # two of them; five output block rows in a strip and a half
+    (16, 40, 40, 64, 64, 3, 3, 1, (8, 8), 0.5),      # two groups of pixels
+    (8, 28, 28, 128, 512, 1, 1, 1, (8, 8), 0.5),     # a plain matrix product of few steps
 ]
+TILES = [2, 2, 2, 2, 2, 2, 2, 2, 2, 4, 4, 4, 4, 4]  # lane tiles of a wave
 
 
 def _layer(n, scale=1.0):
@@ -47,7 +52,7 @@ def test_against_fp64(n):
     print("three-part case", n, SHAPES[n], flush=True)
     out = torch.full(layer.out_shape(B, L, J, (s, s), pad), float("nan"), device="cuda")
     ran = kernels_of(lambda: layer.conv2d(X, (s, s), pad, out=out))
-    assert any("conv_f32x3" in k for k in ran), ran
+    assert any("conv_f32x3<%d" % TILES[n] in k for k in ran), ran
     want = conv_fp64(X, W * keep, s, pad) + torch.from_numpy(bias).cuda()
     rms = want.pow(2).mean().sqrt()
     # a sum of n products takes n / 32 roundings of 2^-24 at most for the leading parts and the others are
@@ -60,20 +65,21 @@ def test_against_fp64(n):
     assert torch.equal(layer.conv2d(X, (s, s), pad, residual=R, relu=True), torch.relu(out + R))
 
 
-@pytest.mark.parametrize("n", [0, 3, 7, 8])
-@pytest.mark.parametrize("what", ["tiny", "huge", "inf", "nan"])
+@pytest.mark.parametrize("n", [0, 3, 5, 7, 8, 9, 10, 11, 12, 13])
+@pytest.mark.parametrize("what", ["huge", "sums", "inf", "nan"])
 def test_values_beyond_three_parts(n, what):
     """Results are those of an fp32 sum over kept blocks: a dropped channel's infinity reaches nothing, values
-    below 2^-100 keep their bits, values near the largest are no infinities."""
+    and sums near the largest are no infinities."""
     import torch
-    X, W, keep, gamma, bias, layer, pad = _layer(n, 2.0 ** -20 if what == "huge" else 1.0)
+    X, W, keep, gamma, bias, layer, pad = _layer(n, {"huge": 2.0 ** -20, "sums": 2.0 ** 15}.get(what, 1.0))
     B, L, J, I, O, H, K, s, (bo, bi), density = SHAPES[n]
+    print("beyond three parts", n, SHAPES[n], what, flush=True)
     c = int(np.argmin(gamma.sum(0)))  # a block column that some block rows drop
     assert gamma[1].sum() == 0
-    if what == "tiny":
-        X[0] *= 2.0 ** -115
-    elif what == "huge":
+    if what == "huge":
         X[0, 3, 3, c * bi] = 3.4e38
+    elif what == "sums":
+        X[0] *= 2.0 ** 100
     else:
         X[0, 3, 3, c * bi] = float(what)
         X[B - 1, 2, 4, 0] = -float(what)
@@ -89,13 +95,102 @@ def test_values_beyond_three_parts(n, what):
     finite = want.isfinite() & (want.abs() < 3.4e38)
     assert torch.equal(got.isfinite(), finite)
     assert torch.equal(got.isnan(), want.isnan())
-    if what == "tiny":  # (without the bias, which hides them)
-        bare = bsp.BspLayer(W.cpu().numpy(), gamma, bo, bi, "f32")
-        got, want = bare.conv2d(X, (s, s), pad)[0].double(), (want - torch.from_numpy(bias).cuda())[0]
-        want = conv_fp64(X[:1], W * keep, s, pad)[0]
-        finite = torch.ones_like(want, dtype=torch.bool)
+    if what == "sums":  # (the first image's sums are of another size than the others')
+        got, want, finite = got[0], want[0], finite[0]
     err, ref = (got - want).abs()[finite], want[finite]
-    assert bool((err <= 1e-5 * torch.maximum(ref.abs(), ref[ref.abs() < 1e30].pow(2).mean().sqrt())).all())
+    rms = ref[ref.abs() < (1e37 if what == "sums" else 1e30)].pow(2).mean().sqrt()
+    assert bool((err <= 1e-5 * torch.maximum(ref.abs(), rms)).all())
+
+
+def _three_parts(x):
+    """x as far as three bf16 parts hold it."""
+    parts, rest = 0.0, x.cpu()
+    for _ in range(3):
+        part = rest.bfloat16().float()
+        parts, rest = parts + part.double(), rest - part
+    return parts.cuda()
+
+
+@pytest.mark.parametrize("n", [0, 3, 5, 7, 8, 9, 10, 11, 12, 13])
+@pytest.mark.parametrize("rows", ["all", "half"])
+def test_small_values_keep_their_bits(n, rows):
+    """Values near the smallest float, of which three bf16 parts hold ten bits unless they are scaled: the results that
+    they alone make keep the accuracy of an fp32 sum, beside others in the same tile that no bit of theirs reaches."""
+    import torch
+    X, W, keep, gamma, bias, layer, pad = _layer(n)
+    B, L, J, I, O, H, K, s, (bo, bi), density = SHAPES[n]
+    print("small values", n, SHAPES[n], rows, flush=True)
+    top = L if rows == "all" else L // 2
+    X[0, :top] *= 2.0 ** -125
+    X[0, 0] = 0.0
+    bare = bsp.BspLayer(W.cpu().numpy(), gamma, bo, bi, "f32")  # (a bias would hide them)
+    got, want = bare.conv2d(X, (s, s), pad)[0].double(), conv_fp64(X[:1], W * keep, s, pad)[0]
+    parts = conv_fp64(_three_parts(X[:1]), W * keep, s, pad)[0]
+    last = (top - 1 + pad[0] - (H - 1)) // s if rows == "half" else want.shape[0] - 1  # output rows of small values alone
+    sigma = (max(density * I * H * K, 24) / 6) ** 0.5 * 2.0 ** -24  # as above
+    bound = max(1e-6, 16 * sigma)
+    for a, b, alone in ((0, last + 1, True), (last + H, want.shape[0], False)):
+        if a >= b:
+            continue
+        g, v = got[a:b], want[a:b]
+        scale = torch.maximum(v.abs(), v.pow(2).mean().sqrt())
+        assert bool(((g - v).abs() <= bound * scale).all()), (a, b)
+        if alone:  # (the bound sees what the parts of unscaled values lose)
+            assert bool(((parts[a:b] - v).abs() > 4 * bound * scale).any())
+
+
+@pytest.mark.parametrize("x,w", [(-55, -55), (-62, -62), (-90, -36), (-130, 0), (-64, -66)])
+def test_small_products_keep_their_bits(x, w):
+    """Products down to the smallest floats, one to a sum: within what test_sums_of_one_product allows, and, where the
+    result has fewer than 24 bits, the rounding to those (a quarter of a place at the most) and then to its own."""
+    import torch
+    gen = torch.Generator("cuda").manual_seed(x * 1000 + w)
+    B, L, I, O = 8, 40, 64, 64
+    W = torch.randn(O, 1, 1, I, generator=gen, device="cuda") * 2.0 ** w
+    v = torch.randn(B, L, L, generator=gen, device="cuda") * 2.0 ** x
+    at = torch.randint(0, I, (B, L, L, 1), generator=gen, device="cuda")
+    X = torch.zeros(B, L, L, I, device="cuda").scatter_(3, at, v[..., None])
+    layer = bsp.BspLayer(W.cpu().numpy(), np.ones((8, 8), np.uint8), 8, 8, "f32")
+    ran = kernels_of(lambda: layer.conv2d(X))
+    assert any("conv_f32x3" in k for k in ran), ran
+    want = v.double()[..., None] * W.view(O, I).t()[at[..., 0]].double()
+    place = torch.pow(2.0, torch.floor(torch.log2(want.abs())).clamp_min(-126) - 23)
+    most = 0.5 + 2.0 ** -7 + 0.25 * (want.abs() < 2.0 ** -126)
+    assert bool(((layer.conv2d(X).double() - want).abs() <= most * place).all())
+
+
+def _fastest(call, n=20):
+    import torch
+    call()
+    best = 1e9
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(n):
+            call()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) / n)
+    return best
+
+
+def test_small_values_cost_nothing():
+    """One activation near the smallest float, one in a hundred, or all of them: within 1.5 times the time without any
+    (6, 18 and 18 times while the tiles that held one were summed a second time)."""
+    import torch
+    gen = torch.Generator("cuda").manual_seed(3)
+    gamma = (np.random.default_rng(3).random((8, 8)) < 0.5).astype(np.uint8)
+    layer = bsp.BspLayer(torch.randn(64, 3, 3, 64, generator=gen, device="cuda").cpu().numpy(), gamma, 8, 8, "f32")
+    X = torch.randn(32, 56, 56, 64, generator=gen, device="cuda")
+    out = torch.empty(32, 56, 56, 64, device="cuda")
+    timed = lambda x: _fastest(lambda: layer.conv2d(x, (1, 1), (1, 1), out=out))
+    base = timed(X)
+    one, many = X.clone(), X.clone()
+    one[0, 3, 3, 5] = 1e-36
+    many[torch.rand(X.shape, generator=gen, device="cuda") < 0.01] = 1e-36
+    times = [timed(x) / base for x in (one, many, X * 1e-36)]
+    print("times of the time without small values:", times, flush=True)
+    assert max(times) <= 1.5, times
 
 
 def test_weights_beyond_three_parts_stay_on_the_fp32_kernel():
