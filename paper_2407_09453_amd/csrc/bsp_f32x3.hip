@@ -89,37 +89,70 @@ __device__ __forceinline__ Parts split8(const f32x4_t lo, const f32x4_t hi) {
 }
 
 // The sums of one 16 x 16 tile (a strip, and one output pixel per lane column, whose window starts at
-// iy0, ix0) in fp32 from kept blocks alone, every block row by itself with zeros for the channels that it
-// drops.  Rare, and bound by its chain of loads.
-__device__ f32x4_t exact_tile(const X3Args& a, const float* xim, int strip, int iy0, int ix0, int lane) {
+// iy0, ix0) in fp32 from kept blocks alone: every block row by itself, with zeros for the channels that it drops,
+// where a value is an infinity or NaN, all of them in one where none is (a dropped channel then meets a zero weight).
+// Straight from memory; four (chunk, tap) pairs to an instruction and twice those in flight, bound by two loads after
+// each other: with one NaN 3x3 56x56x64 batch 32 takes 46 us (121 with one pair in flight), 28x28x128 batch 8 37 (113),
+// 14x14x256 batch 2 with 16x4 blocks 59 (187).
+__device__ __forceinline__ f32x4_t exact_tile(const X3Args& a, const float* xim, int strip, int iy0, int ix0, int lane) {
+  constexpr int U = 2;
   const int g = lane >> 4, jn = lane & 15, HK = a.H * a.K;
   const PlanView pv = plan_view(a.plan);
   const int c0 = pv.strip_ptr[strip], npairs = (pv.strip_ptr[strip + 1] - c0) * HK;
   const int bi = 64 >> a.lbo, mine = jn >> a.lbo, at0 = (jn & ((1 << a.lbo) - 1)) * HK;
-  f32x4_t acc[BSP_MAXSUB] = {};
+  const int nrows = BSP_STRIP >> a.lbo;  // block rows of a strip
+  f32x4_t all = {0.f, 0.f, 0.f, 0.f}, acc[BSP_MAXSUB] = {};
 #pragma unroll 1
-  for (int pair = 0; pair < npairs; ++pair) {
-    const int chunk = pair / HK, tap = pair - chunk * HK, th = tap / a.K, tw = tap - th * a.K;
-    const int iy = iy0 + th, ix = ix0 + tw;
-    const int xc = pv.chunk_xc[c0 + chunk];
-    const i32x4_t src = *(const i32x4_t*)(pv.chunk_src + (c0 + chunk) * BSP_MAXSUB);
-    const int at = (at0 + tap) * bi;
+  for (int q = 0; q < npairs; q += 4 * U) {
+    int xc[U], at[U];
+    i32x4_t src[U];
+    bool in[U];
+    const float* px[U];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {  // four channels at a time, lane group g holds the g-th of them
-      float w = 0.f, x = 0.f;
-      const int s = bi == 4 ? (h == 0 ? src.x : src.y) : mine == 0 ? src.x : mine == 1 ? src.y : mine == 2 ? src.z : src.w;
-      if (s >= 0) w = a.payload[(int64_t)s + at + (bi == 4 ? 0 : 4 * h) + g];
-      if ((unsigned)iy < (unsigned)a.L && (unsigned)ix < (unsigned)a.J)
-        x = xim[(int64_t)(iy * a.J + ix) * a.I + xc * 8 + 4 * h + g];
+    for (int u = 0; u < U; ++u) {
+      const int pair = min(q + 4 * u + g, npairs - 1), chunk = pair / HK, tap = pair - chunk * HK, th = tap / a.K;
+      const int iy = iy0 + th, ix = ix0 + tap - th * a.K;
+      xc[u] = pv.chunk_xc[c0 + chunk];
+      src[u] = *(const i32x4_t*)(pv.chunk_src + (c0 + chunk) * BSP_MAXSUB);
+      if (q + 4 * u + g >= npairs) src[u] = i32x4_t{-1, -1, -1, -1};  // (past the end: no weights, so no product)
+      in[u] = src[u].x >= 0 || src[u].y >= 0 || src[u].z >= 0 || src[u].w >= 0;
+      in[u] = in[u] && (unsigned)iy < (unsigned)a.L && (unsigned)ix < (unsigned)a.J;
+      px[u] = xim + (int64_t)(iy * a.J + ix) * a.I;
+      at[u] = (at0 + tap) * bi;
+    }
+    f32x4_t w[U][2], x[U][2];
 #pragma unroll
-      for (int q = 0; q < BSP_MAXSUB; ++q) {
-        const bool kept = bi == 4 ? q == 0 && s >= 0 : src[q] >= 0;
-        acc[q] = mfma_f32_16x16x4(w, kept ? x : 0.f, acc[q]);
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {  // four channels at a time; 4-wide blocks: each from its own
+        const int s = bi == 4 ? (h == 0 ? src[u].x : src[u].y) : mine == 0 ? src[u].x : mine == 1 ? src[u].y : mine == 2 ? src[u].z : src[u].w;
+        w[u][h] = x[u][h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        if (s >= 0) w[u][h] = *(const f32x4_t*)(a.payload + (int64_t)s + at[u] + (bi == 4 ? 0 : 4 * h));
+        if (in[u]) x[u][h] = *(const f32x4_t*)(px[u] + xc[u] * 8 + 4 * h);
+      }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      bool odd = false;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) odd |= (__float_as_uint(x[u][i >> 2][i & 3]) & 0x7F800000u) == 0x7F800000u;
+      if (__ballot(odd) == 0) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) all = mfma_f32_16x16x4(w[u][i >> 2][i & 3], x[u][i >> 2][i & 3], all);
+      } else {
+#pragma unroll
+        for (int s = 0; s < BSP_MAXSUB; ++s) {
+          if (s >= nrows) break;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const bool kept = (bi == 4 && i >= 4 ? src[u].y : src[u][s]) >= 0;
+            acc[s] = mfma_f32_16x16x4(w[u][i >> 2][i & 3], kept ? x[u][i >> 2][i & 3] : 0.f, acc[s]);
+          }
+        }
       }
     }
   }
   const int row = 4 * g >> a.lbo;  // the lane's four channels lie in one block row
-  return row == 0 ? acc[0] : row == 1 ? acc[1] : row == 2 ? acc[2] : acc[3];
+  return all + (row == 0 ? acc[0] : row == 1 ? acc[1] : row == 2 ? acc[2] : acc[3]);
 }
 
 // One (tile of PT * 16 * PG output pixels) x (NS strips) per workgroup, as in conv_any: consecutive pixels of a
@@ -335,18 +368,21 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
         if (ch + r < a.O) bv[r] = a.bias[ch + r];
     }
     unsigned char* ot = lds + (pg * PT * 16 + ejn) * opitch + (si * BSP_STRIP + 4 * eg) * 4;
+    uint32_t redo = 0;  // lane tiles with an infinity or NaN
 #pragma unroll
     for (int t = 0; t < PT; ++t) {
       if ((t & (a.ks - 1)) != k) continue;
       bool again = false;
 #pragma unroll
       for (int r = 0; r < 4; ++r) again |= (__float_as_uint(acc[t][r]) & 0x7F800000u) == 0x7F800000u;
-      if (__ballot(again)) {
-        const int p = min(p0 + (pg * PT + t) * 16 + ejn, plast);
-        const int y = (int)fdiv((uint32_t)p, a.d_cw), x = col0 + p - y * a.CW;
-        acc[t] = exact_tile(a, xim, strip, y * a.sh - a.ph, x * a.sw - a.pw, el);
-      }
+      if (__ballot(again)) redo |= 1u << t;
       *(f32x4_t*)(ot + t * 16 * opitch) = acc[t] + bv;
+    }
+#pragma unroll 1
+    for (; redo; redo &= redo - 1) {
+      const int t = __builtin_ctz(redo), p = min(p0 + (pg * PT + t) * 16 + ejn, plast);
+      const int y = (int)fdiv((uint32_t)p, a.d_cw), x = col0 + p - y * a.CW;
+      *(f32x4_t*)(ot + t * 16 * opitch) = exact_tile(a, xim, strip, y * a.sh - a.ph, x * a.sw - a.pw, el) + bv;
     }
   }
   __syncthreads();
