@@ -261,6 +261,7 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         if (dst[u] < 0) continue;
+        asm volatile("" : "+v"(v[u][0]), "+v"(v[u][1]));  // (scaled here: where they are loaded, each would be waited for by itself)
         const Parts s = split8(v[u][0] * kScale, v[u][1] * kScale);
 #pragma unroll
         for (int r = 0; r < 3; ++r) *(u32x4_t*)(lds + dst[u] + r * 16) = s.p[r];
