@@ -31,6 +31,7 @@
 #include <cstdlib>
 #include <map>
 #include <mutex>
+#include <type_traits>
 
 namespace {
 
@@ -43,7 +44,7 @@ struct X3Args {
   const float* residual;
   const int32_t* slab_ptr;
   const unsigned char* xdesc;
-  const unsigned char* wfrag;
+  const unsigned char* wfrag;      // DIRECT: where the weights lie in the payload
   int32_t relu;
   int32_t L, J, I, O, H, K, M, N;
   int32_t sh, sw, ph, pw, gsh, gsw, lsh, lsw;  // input pixels per staged pixel, staged pixels per output pixel
@@ -159,7 +160,8 @@ __device__ __forceinline__ f32x4_t exact_tile(const X3Args& a, const float* xim,
 // chunk of image columns, the input patch staged with its halo, as many slabs at a time as LDS takes.  A staged
 // pixel holds per chunk its three parts side by side, in an odd number of 16-byte pieces (no bank
 // conflicts within a patch row).  Wave = (strip, pixel group, share of the strip's steps).  SHORT: eight products.
-template <int PT, bool SHORT>
+// DIRECT: the plan holds the weights' places in the payload and they are split here, step by step.
+template <int PT, bool SHORT, bool DIRECT>
 __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
   kernarg_touch<X3Args>();
   extern __shared__ __align__(16) unsigned char lds[];
@@ -200,6 +202,7 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
   const int iy0 = m0 * a.sh - a.ph, ix0 = col0 * a.sw - a.pw;
   const int pieces = rows * a.TPW * a.ppp;
   const float* xim = a.X + (int64_t)img * a.L * a.J * a.I;
+  const uint32_t wrow = (uint32_t)(jn & ((1 << a.lbo) - 1)) * (256u >> a.lbo);  // bytes of a block's rows before this lane's
   const int rowpitch = a.TPW * a.pitch;
 
   for (int stg = 0; stg < a.nstages; ++stg) {
@@ -209,6 +212,8 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
 
     // ---- weights: one step ahead; descriptors: two
     u32x4_t w[3], wn[3];
+    f32x4_t wl, wh;        // DIRECT: the next step's weights, and where they and those after them lie
+    int lo0 = -1, hi0 = -1, lo1 = -1, hi1 = -1;
     int dn, an, dnn, ann;  // descriptor and place of the slab in a staged pixel, of the next step and the one after
     int fcs = slo + k, fsl = sl0, fadd = 0, fend = __builtin_amdgcn_readlane(tab, sl0 + 1), wcs = 0;
     auto ask_desc = [&]() {
@@ -222,11 +227,34 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
       dnn = *(const int*)(a.xdesc + ((uint32_t)cs * 16u + (uint32_t)g * 4u));
       ann = fadd;
       wcs = cs;
+      if constexpr (DIRECT) {
+        const u32x2_t at = *(const u32x2_t*)(a.wfrag + ((uint32_t)cs * 128u + (uint32_t)(g * 4 + (jn >> a.lbo)) * 8u));
+        lo1 = (int)at.x;
+        hi1 = (int)at.y;
+      }
     };
     auto ask_weights = [&]() {
-      const unsigned char* p = a.wfrag + ((uint32_t)wcs * 3072u + (uint32_t)lane * 16u);
+      if constexpr (DIRECT) {
+        lo0 = lo1;
+        hi0 = hi1;
+        wl = *(const f32x4_t*)((const unsigned char*)a.payload + ((uint32_t)max(lo0, 0) * 4u + wrow));
+        wh = *(const f32x4_t*)((const unsigned char*)a.payload + ((uint32_t)max(hi0, 0) * 4u + wrow));
+      } else {
+        const unsigned char* p = a.wfrag + ((uint32_t)wcs * 3072u + (uint32_t)lane * 16u);
 #pragma unroll
-      for (int r = 0; r < 3; ++r) wn[r] = *(const u32x4_t*)(p + r * 1024);
+        for (int r = 0; r < 3; ++r) wn[r] = *(const u32x4_t*)(p + r * 1024);
+      }
+    };
+    auto take_weights = [&]() {
+      if constexpr (DIRECT) {
+        const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+        const Parts s = split8(lo0 < 0 ? zero : wl, hi0 < 0 ? zero : wh);
+#pragma unroll
+        for (int r = 0; r < 3; ++r) w[r] = s.p[r];
+      } else {
+#pragma unroll
+        for (int r = 0; r < 3; ++r) w[r] = wn[r];
+      }
     };
     dn = dnn = an = ann = 0;
     if (n > 0) {  // their latency passes while the patch is staged
@@ -302,8 +330,7 @@ __global__ __launch_bounds__(512, 4) void conv_f32x3(X3Args a) {
     }
 #pragma unroll 1
     for (int i = 0; i < n; ++i) {
-#pragma unroll
-      for (int r = 0; r < 3; ++r) w[r] = wn[r];
+      take_weights();
       dn = dnn;
       an = ann;
       ask_weights();
@@ -476,15 +503,15 @@ Pick choose(int B, int M, int N, int nstrips, int steps, int nslabs, int slab_ch
   return best;
 }
 
-template <int PT, bool SHORT>
+template <int PT, bool SHORT, bool DIRECT>
 int launch_inst(const X3Args& a, int threads, size_t ldsb, hipStream_t st) {
   static bool raised = false;  // dynamic LDS above 64 KB has to be allowed once per kernel
   if (!raised) {
-    if (hipFuncSetAttribute((const void*)conv_f32x3<PT, SHORT>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit) != hipSuccess)
+    if (hipFuncSetAttribute((const void*)conv_f32x3<PT, SHORT, DIRECT>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit) != hipSuccess)
       return BSP_ERR_HIP;
     raised = true;
   }
-  hipLaunchKernelGGL((conv_f32x3<PT, SHORT>), dim3((unsigned)(a.per_xcd * 8)), dim3(threads), ldsb, st, a);
+  hipLaunchKernelGGL((conv_f32x3<PT, SHORT, DIRECT>), dim3((unsigned)(a.per_xcd * 8)), dim3(threads), ldsb, st, a);
   return hipGetLastError() == hipSuccess ? BSP_OK : BSP_ERR_HIP;
 }
 
@@ -516,7 +543,7 @@ int bsp_launch_f32x3(const ConvParams& p, const void* plan_host, hipStream_t st)
   a.residual = (const float*)p.residual;
   a.slab_ptr = sec + x3[BSP_X3_OFF_SLAB_W];
   a.xdesc = (const unsigned char*)(sec + x3[BSP_X3_OFF_DESC_W]);
-  a.wfrag = (const unsigned char*)(sec + x3[BSP_X3_OFF_FRAG_W]);
+  a.wfrag = (const unsigned char*)(sec + x3[x3[BSP_X3_OFF_SRC_W] ? BSP_X3_OFF_SRC_W : BSP_X3_OFF_FRAG_W]);
   a.relu = p.relu;
   a.plan = p.plan;
   a.payload = (const float*)p.payload;
@@ -612,6 +639,10 @@ int bsp_launch_f32x3(const ConvParams& p, const void* plan_host, hipStream_t st)
   a.stream = best.NS >= a.nstrips ? flat || p.O >= 32 : p.O % 32 == 0 && best.NS % 2 == 0;
   const int threads = 64 * best.NS * best.PG * best.ks;
   const size_t ldsb = (size_t)best.lds;
-  if (steps <= kShort) return best.PT == 4 ? launch_inst<4, true>(a, threads, ldsb, st) : launch_inst<2, true>(a, threads, ldsb, st);
-  return best.PT == 4 ? launch_inst<4, false>(a, threads, ldsb, st) : launch_inst<2, false>(a, threads, ldsb, st);
+  auto launch = [&](auto direct) {
+    constexpr bool D = decltype(direct)::value;
+    if (steps <= kShort) return best.PT == 4 ? launch_inst<4, true, D>(a, threads, ldsb, st) : launch_inst<2, true, D>(a, threads, ldsb, st);
+    return best.PT == 4 ? launch_inst<4, false, D>(a, threads, ldsb, st) : launch_inst<2, false, D>(a, threads, ldsb, st);
+  };
+  return x3[BSP_X3_OFF_SRC_W] ? launch(std::true_type{}) : launch(std::false_type{});
 }

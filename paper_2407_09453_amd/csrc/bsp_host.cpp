@@ -378,9 +378,18 @@ static bool bsp_x3_wanted(int32_t O, int32_t H, int32_t K, int32_t I, int32_t dt
   return dtype == BSP_F32 && I % 8 == 0 && (int64_t)O * I * H * K <= (int64_t)8 << 20;
 }
 
+// Whether that section only says where the weights lie in the payload, and the kernel splits them.  Rows of a 1x1
+// layer's blocks lie side by side there; a window's do not, and reading them sixteen lines at a time would bound
+// the kernel.  Splitting them anew for every tile costs it a seventh: 1x1 20x20x1024->1056 batch 16 97 -> 111 us (121 on
+// conv_f32), 2048->1000 batch 2 32.6 -> 36.4 (61), 28x28x1024->1056 with 16x4 blocks 171 -> 196 (192).  So it is for
+// the largest ones, most of which are FC layers, never have more than the 256 rows from which that kernel runs, and
+// would be packed for nothing: 1000 x 2048 2.6 -> 1.0 ms and 9.8 -> 0.7 MB, 4096 x 2048 16 -> 5.4 ms and 40 -> 2.8 MB.
+static bool bsp_x3_direct(int32_t O, int64_t HK, int32_t I) { return HK == 1 && (int64_t)O * I > (int64_t)1 << 20; }
+
 // Eight weights into the three parts of a step's fragment (each part's fragments are 64 x 8 apart).  The
-// lanes of the inner loops are independent and go through vector registers (a plan of 1000 x 2048, half
-// kept, 5.2 -> 2.7 ms with this and the look at the weights below, most of the rest for its 10 MB of memory).
+// lanes of the inner loops are independent and go through vector registers.  What the parts cost when a layer is
+// packed, half of its 8x8 blocks kept (before there were any / now, a quarter of it memory's first touch):
+// 3x3 64->64 15 / 37 us and 0.2 MB of plan, 512->512 0.1 / 2.2 ms and 11 MB, 256 x 256 27 / 71 us.
 static void split_parts(const float* w, uint16_t* d) {
   uint32_t u[8];
   float rest[8], part[8];
@@ -509,7 +518,8 @@ static int plan_walk(const int32_t* row_ptr, const int32_t* col_idx, const void*
   const bool x3 = bsp_x3_wanted(O, H, K, I, dtype) && all_steps > 0 && bsp_f32x3_beats(bo, nstrips, cdiv(all_steps, nstrips), 1ll << 31, I, HK);
   const int64_t off_x3 = off_rows;
   const int64_t x3_desc = BSP_X3_HEADER_WORDS + pad4((int64_t)nstrips * (nslabs + 1)), x3_frag = x3_desc + all_steps * 4;
-  const int64_t total = x3              ? off_x3 + x3_frag + all_steps * 3 * 64 * 4
+  const bool x3_direct = bsp_x3_direct(O, HK, I);
+  const int64_t total = x3              ? off_x3 + x3_frag + all_steps * (x3_direct ? 32 : 3 * 64 * 4)
                         : first.empty() ? off_rows + (int64_t)rows.size()
                                         : off_first + (int64_t)first.size();
   if (total > std::numeric_limits<int32_t>::max()) return BSP_ERR_SHAPE;
@@ -559,7 +569,7 @@ static int plan_walk(const int32_t* row_ptr, const int32_t* col_idx, const void*
     sec[BSP_X3_SLAB_W] = slab;
     sec[BSP_X3_OFF_SLAB_W] = BSP_X3_HEADER_WORDS;
     sec[BSP_X3_OFF_DESC_W] = (int32_t)x3_desc;
-    sec[BSP_X3_OFF_FRAG_W] = (int32_t)x3_frag;
+    sec[x3_direct ? BSP_X3_OFF_SRC_W : BSP_X3_OFF_FRAG_W] = (int32_t)x3_frag;
     std::memcpy(sec + BSP_X3_HEADER_WORDS, slab_ptr.data(), sizeof(int32_t) * slab_ptr.size());
     const float* plf = (const float*)payload;
     const int32_t least = 0x0D800000, past = 0x7F000000;  // 2^-100 and 2^127 as bits
@@ -573,6 +583,7 @@ static int plan_walk(const int32_t* row_ptr, const int32_t* col_idx, const void*
     sec[BSP_X3_USABLE_W] = other == 0;
     int32_t* xdesc = sec + x3_desc;
     uint16_t* wfrag = (uint16_t*)(sec + x3_frag);
+    if (x3_direct) std::memset(sec + x3_frag, 0xFF, sizeof(int32_t) * (size_t)all_steps * 32);
     for (int32_t t = 0; sec[BSP_X3_USABLE_W] && t < nstrips; ++t) {
       int32_t e = strip_ptr[t];
       for (int32_t sl = 0; sl < nslabs; ++sl) {
@@ -584,6 +595,14 @@ static int plan_walk(const int32_t* row_ptr, const int32_t* col_idx, const void*
           for (int32_t th = 0, tap = 0; th < H; ++th)
             for (int32_t tw = 0; tw < K; ++tw, ++tap, ++at4) {
               xdesc[at4] = (xc_list[ce] - sl * slab_chunks) | (th << 16) | (tw << 24);
+              if (x3_direct) {
+                int32_t* d = sec + x3_frag + at4 * 8;
+                for (int32_t r = 0; r < rows_per_strip; ++r) {
+                  d[2 * r] = sr[r];
+                  d[2 * r + 1] = bi == 4 ? sr[1] : sr[r] < 0 ? -1 : sr[r] + 4;
+                }
+                continue;
+              }
               uint16_t* d = wfrag + ((at4 >> 2) * 3 * 64 + (at4 & 3) * 16) * 8;
               if (bi >= 8) {
                 for (int32_t r = 0; r < rows_per_strip; ++r)

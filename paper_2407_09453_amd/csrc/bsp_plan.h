@@ -148,7 +148,9 @@ enum {
 //   [0..7]                        header, see enum
 //   slab_ptr[nstrips][nslabs+1]   first step of each (strip, slab)
 //   xdesc[nsteps][4]              per 16-lane group: chunk in the slab | tap row << 16 | tap column << 24
-//   wfrag[nsteps][3][64][8]       bf16 parts of the weights in MFMA operand order
+//   wfrag[nsteps][3][64][8]       windows: bf16 parts of the weights in MFMA operand order
+//   src[nsteps][4][4][2]          1x1 layers instead, whose blocks lie row after row in the payload: the first element of
+//                                 the chunk's first and last four channels, per 16-lane group and block row, or -1
 enum {
   BSP_X3_HEADER_WORDS = 8,
   BSP_X3_NSTEPS_W = 0,
@@ -158,6 +160,7 @@ enum {
   BSP_X3_OFF_DESC_W = 4,
   BSP_X3_OFF_FRAG_W = 5,
   BSP_X3_USABLE_W = 6,       // 0: a weight is not finite, below 2^-100 or past bf16's range
+  BSP_X3_OFF_SRC_W = 7,      // 0: there are fragments
 };
 
 // Channels of one slab of the row-band section: windows are staged 128 channels at a time;

@@ -25,8 +25,14 @@ SHAPES = [
     (6, 40, 40, 64, 40, 3, 3, 1, (4, 16), 0.5),      # two of them; five output block rows in a strip and a half
     (16, 40, 40, 64, 64, 3, 3, 1, (8, 8), 0.5),      # two groups of pixels
     (8, 28, 28, 128, 512, 1, 1, 1, (8, 8), 0.5),     # a plain matrix product of few steps
+    (1, 23, 19, 1032, 1034, 1, 1, 1, (8, 8), 0.5),   # weights from the payload, a strip that is not full
+    (2, 25, 27, 2048, 520, 1, 1, 2, (16, 4), 0.5),
+    (4, 30, 31, 1024, 1040, 1, 1, 1, (4, 16), 0.25),
+    (8, 31, 28, 1032, 1034, 1, 1, 1, (16, 4), 0.1),
+    (1, 23, 19, 1032, 1032, 1, 1, 1, (8, 8), 0.03),  # few steps
+    (8, 30, 30, 1032, 1032, 1, 1, 1, (8, 8), 0.03),
 ]
-TILES = [2, 2, 2, 2, 2, 2, 2, 2, 2, 4, 4, 4, 4, 4]  # lane tiles of a wave
+TILES = [2, 2, 2, 2, 2, 2, 2, 2, 2, 4, 4, 4, 4, 4, 2, 2, 2, 4, 2, 4]  # lane tiles of a wave
 
 
 def _layer(n, scale=1.0):
@@ -65,7 +71,7 @@ def test_against_fp64(n):
     assert torch.equal(layer.conv2d(X, (s, s), pad, residual=R, relu=True), torch.relu(out + R))
 
 
-@pytest.mark.parametrize("n", [0, 3, 5, 7, 8, 9, 10, 11, 12, 13])
+@pytest.mark.parametrize("n", [0, 3, 5, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 18, 19])
 @pytest.mark.parametrize("what", ["huge", "sums", "inf", "nan"])
 def test_values_beyond_three_parts(n, what):
     """Results are those of an fp32 sum over kept blocks: a dropped channel's infinity reaches nothing, values
@@ -111,7 +117,7 @@ def _three_parts(x):
     return parts.cuda()
 
 
-@pytest.mark.parametrize("n", [0, 3, 5, 7, 8, 9, 10, 11, 12, 13])
+@pytest.mark.parametrize("n", [0, 3, 5, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17, 18, 19])
 @pytest.mark.parametrize("rows", ["all", "half"])
 def test_small_values_keep_their_bits(n, rows):
     """Values near the smallest float, of which three bf16 parts hold ten bits unless they are scaled: the results that
