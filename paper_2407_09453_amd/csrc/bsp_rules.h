@@ -176,17 +176,22 @@ inline bool bsp_f32_general(int bo, int64_t I, int64_t O, int64_t HK, int64_t pa
 }
 
 // fp32 in whole chunks of eight channels in: whether the three-part kernel takes the layer from the two
-// above (steps: the most of a strip on average; the others / here in us, 500 random layers: 1.31 times faster over
-// all, 1.36 over those this line takes, five of 429 more than a tenth slower).  Strips of 4x16 blocks
-// unite four block rows, which leaves little to skip, and one or two strips do not pay for the splitting of
-// a long pixel: 4x16 3x3 35x35x448->16 batch 2 at stride 2 28 / 45, 12x12x408->8 1x3 11.2 / 14.2, 32x10x400->72 batch 2
-// 18.2 / 22.6 (a loss on this side), 49x49x104->584 and the like 1.5 times faster; 8x8 1x1 18x105x1120->16 17.1 / 24.9.
-// One chunk and tap is over at once in the general kernel: 1x1 70x70x8->768 batch 5 23 / 28.  3x3 56x56x64 batch 32
-// 55 / 37, 1x1 28x28x128->512 batch 8 16.5 / 12.2, 16x4 3x1 68x68x40->326 batch 11 31 / 21.
+// above (steps: a strip's, on average).  6000 random layers, the others / here: 1.36 times faster over the 5237
+// that this line takes, 104 of them (most with a tenth of their blocks kept, or one strip) more than a tenth slower, down
+// to 3.9 / 9.5 us for 1x1 27x27x296->8 batch 5; 0.95 over the 137 that the one step of one strip and the few tiles send back.
+//   One chunk and tap is over at once in the general kernel: 1x1 70x70x8->768 batch 5 23 / 28; so is one step of one
+//   strip, 3x1 95x100x88->4 batch 24 6.8 / 24.3.
+//   Strips of 4x16 blocks unite four block rows, which leaves little to skip, and one or two strips do not pay for the
+//   splitting of a long pixel: 3x3 35x35x448->16 batch 2 at stride 2 28 / 45, 12x12x408->8 1x3 11.2 / 14.2; 8x8 1x1
+//   18x105x1120->16 17.1 / 24.9.
+//   Few tiles (of sixteen pixels and a strip) of many steps leave most of the chip idle for one long chain: 4x16 5x5
+//   5x5x344->48 batch 6 23 / 42, 3x3 32x10x400->72 batch 2 18.2 / 22.6, 8x8 5x5 15x15x504->109 batch 6 at stride 2 48 / 82.
+// 3x3 56x56x64 batch 32 55 / 36, 1x1 28x28x128->512 batch 8 15.2 / 11.3, 16x4 3x1 68x68x40->326 batch 11 31 / 21.
 inline bool bsp_f32x3_beats(int bo, int64_t strips, int64_t steps, int64_t P, int64_t I, int64_t HK) {
-  if (I * HK <= 8) return false;
-  if (bo == 4) return strips > 1 && (strips > 2 || steps <= 30) && strips * steps * ((P + 15) / 16) >= 6000;
-  return !(strips == 1 && bo == 8 && steps > 30);
+  if (I * HK <= 8 || strips * steps == 1) return false;
+  const int64_t tiles = strips * ((P + 15) / 16);
+  if (bo == 4) return strips > 1 && (strips > 2 || steps <= 30) && steps * tiles >= 6000 && (steps <= 25 || tiles >= 256);
+  return bo != 8 || ((strips > 1 || steps <= 30) && (steps <= 100 || tiles >= 400));
 }
 
 // The widths of at most 64 columns that up to ceil(N / least) even chunks of N columns have, each once, the

@@ -21,6 +21,7 @@ static void is(bool got, bool want, const char* what) {
 #define LDS8(want, ...) is(bsp_any_beats_lds_i8(__VA_ARGS__), want, #__VA_ARGS__)
 #define GEN8(want, ...) is(bsp_i8_general(__VA_ARGS__), want, #__VA_ARGS__)
 #define THIN(want, ...) is(bsp_pw_thin(__VA_ARGS__) == want, true, #__VA_ARGS__)
+#define X3(want, ...) is(bsp_f32x3_beats(__VA_ARGS__), want, #__VA_ARGS__)
 #define F32(want, ...) is(bsp_f32_general(__VA_ARGS__), want, #__VA_ARGS__)
 int main() {
   // rival, bo, H, K, strided, matrix instructions, results, channels in and out        the other / any-shape, us
@@ -134,6 +135,35 @@ int main() {
   F32(false, 4, 287, 4, 1, 9, 1, 338800, false);
   F32(true, 8, 5, 110, 1, 7, 7, 21120, true);                             // 3.2 / 6.2
   F32(false, 8, 64, 64, 1, 8, 4, 4096, true);
+  // block rows, strips, steps, pixels, channels in, window: the others / three parts, us
+  X3(true, 8, 4, 15, 100352, 64, 9);                                      // 55 / 36
+  X3(true, 8, 32, 4, 6272, 128, 1);                                       // 15.2 / 11.3
+  X3(true, 16, 21, 2, 50864, 40, 3);                                      // 31 / 21
+  X3(false, 8, 48, 1, 24500, 8, 1);                                       // 23 / 28
+  X3(true, 16, 41, 1, 100000, 24, 1);
+  X3(false, 16, 1, 1, 57600, 88, 3);                                      // 6.8 / 24.3
+  X3(true, 16, 1, 2, 57600, 88, 3);
+  X3(true, 16, 1, 57, 1600, 256, 9);                                      // one strip, 16x4
+  X3(false, 8, 1, 35, 1890, 1120, 1);                                     // 17.1 / 24.9
+  X3(true, 8, 1, 30, 1890, 960, 1);
+  X3(false, 4, 1, 26, 1152, 408, 3);                                      // 11.2 / 14.2
+  X3(false, 4, 1, 126, 648, 448, 9);                                      // 28 / 45
+  X3(false, 4, 2, 31, 100000, 136, 9);
+  X3(true, 4, 2, 30, 100000, 136, 9);
+  X3(false, 4, 4, 5, 4224, 32, 9);                                        // few products
+  X3(false, 4, 3, 269, 150, 344, 25);                                     // 23 / 42
+  X3(false, 4, 5, 105, 640, 400, 9);                                      // 18.2 / 22.6
+  X3(true, 4, 37, 24, 7203, 104, 9);                                      // 1.5 times faster
+  X3(false, 4, 16, 26, 240, 104, 9);
+  X3(true, 4, 16, 26, 256, 104, 9);
+  X3(false, 8, 7, 303, 384, 504, 25);                                     // 48 / 82
+  X3(true, 8, 25, 101, 256, 504, 9);
+  X3(false, 8, 25, 101, 240, 504, 9);
+  X3(true, 8, 25, 100, 240, 504, 9);
+  X3(true, 16, 7, 303, 384, 504, 25);                                     // 16x4 blocks unite nothing
+  // what no number of pixels brings to that kernel gets no weights for it in its plan
+  X3(false, 4, 1, 20, (int64_t)1 << 31, 64, 9);
+  X3(true, 4, 3, 300, (int64_t)1 << 31, 64, 9);
   // the widths that a tile's search tries: those of every even cut, and few of them on the widest image
   for (int least : {4, 8})
     for (int64_t N = 1; N <= 3000; ++N) {
