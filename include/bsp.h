@@ -377,6 +377,22 @@ int bsp_conv2d_i8(const bsp_weights* w, const int8_t* X, const int32_t* bias, vo
 int bsp_fc_i8(const bsp_weights* w, const int8_t* X, const int32_t* bias, void* Y,
               int32_t y_dtype, int32_t shift, int32_t B, void* stream);
 
+/* -------------------------------------------- the layer calls in packed form
+ * The same four calls with their arguments in one array of BSP_CALL_WORDS words, for callers that
+ * pay for every argument (ctypes converts each by itself, a quarter of a small layer's call):
+ * pointers as addresses, other arguments as signed integers, in the order of the call's own
+ * arguments, the batch in the same place for both kinds of layer.
+ *   words 0, 1, 2       w, X, bias
+ *   words 3, 4, 5       BSP_CALL_CONV2D, BSP_CALL_FC: residual, relu, Y (bsp_conv2d_fused, bsp_fc_fused)
+ *                       BSP_CALL_CONV2D_I8, BSP_CALL_FC_I8: Y, y_dtype, shift (bsp_conv2d_i8, bsp_fc_i8)
+ *   words 6 .. 12       B, L, J, stride_h, stride_w, pad_h, pad_w; an FC layer's are B alone, the
+ *                       other six are not read
+ *   word 13             stream
+ * Errors: NULL (words), SHAPE (unknown call), otherwise those of the call. */
+enum bsp_call { BSP_CALL_CONV2D = 0, BSP_CALL_FC = 1, BSP_CALL_CONV2D_I8 = 2, BSP_CALL_FC_I8 = 3 };
+enum { BSP_CALL_WORDS = 14 };
+int bsp_call_packed(int32_t call, const int64_t* words);
+
 #ifdef __cplusplus
 }
 #endif

@@ -32,7 +32,7 @@ EXPORTS = ("bsp_strerror", "bsp_version", "bsp_pack_count", "bsp_pack", "bsp_unp
            "bsp_conv2d_general", "bsp_quantize", "bsp_conv2d_i8", "bsp_fc_i8",
            "bsp_block_importance", "bsp_select_mask", "bsp_mask_step", "bsp_conv2d_fused",
            "bsp_fc_fused", "bsp_fc_fused_static", "bsp_bcsr_segments", "bsp_spgemm_nt",
-           "bsp_conv2d_only", "bsp_bottleneck", "bsp_bench_copy", "bsp_bench_mfma_bf16", "bsp_bench_lds_read")
+           "bsp_conv2d_only", "bsp_bottleneck", "bsp_call_packed", "bsp_bench_copy", "bsp_bench_mfma_bf16", "bsp_bench_lds_read")
 
 
 class BspError(RuntimeError):
@@ -146,11 +146,11 @@ def load_library():
     return lib
 
 
-# A layer call's arguments as one string of 14 words: ctypes converts an argument at a time, 1.2 of the 5 us
+# A layer call's arguments as one string of 14 words (bsp_call_packed): ctypes converts an argument at a time, 1.2 of the 5 us
 # that a call of a small layer took on the host (5.2, now 4.4; FC 64 x 256 -> 256 fp32 5.3 -> 4.6 in all).
 # Arguments that are no plain integers, such as a stream given as a torch Stream or a ctypes pointer, go
 # through the entry point itself, where ctypes takes or refuses them.
-_CALL_CONV, _CALL_FC, _CALL_CONV_I8, _CALL_FC_I8 = range(4)
+BSP_CALL_CONV2D, BSP_CALL_FC, BSP_CALL_CONV2D_I8, BSP_CALL_FC_I8 = range(4)
 _pack14 = struct.Struct("=14q").pack
 
 
@@ -501,7 +501,7 @@ class BspLayer:
             else:
                 bsp_conv2d(self.struct, X.data_ptr(), bias, out.data_ptr(), B, L, J, stride, pad, st)
             return out
-        rc = _lib.bsp_call_packed(_CALL_CONV, words)
+        rc = _lib.bsp_call_packed(BSP_CALL_CONV2D, words)
         if rc:
             raise BspError(rc, "bsp_conv2d_fused" if fused else "bsp_conv2d")
         return out
@@ -526,7 +526,7 @@ class BspLayer:
             else:
                 bsp_fc(self.struct, X.data_ptr(), bias, out.data_ptr(), B, st)
             return out
-        rc = _lib.bsp_call_packed(_CALL_FC, words)
+        rc = _lib.bsp_call_packed(BSP_CALL_FC, words)
         if rc:
             raise BspError(rc, "bsp_fc_fused" if residual is not None or relu else "bsp_fc")
         return out
@@ -658,7 +658,7 @@ class BspLayerI8:
             bsp_conv2d_i8(self.struct, X.data_ptr(), bias, out.data_ptr(), code, 0 if shift is None else shift,
                           B, L, J, stride, pad, st)
             return out
-        rc = _lib.bsp_call_packed(_CALL_CONV_I8, words)
+        rc = _lib.bsp_call_packed(BSP_CALL_CONV2D_I8, words)
         if rc:
             raise BspError(rc, "bsp_conv2d_i8")
         return out
@@ -680,7 +680,7 @@ class BspLayerI8:
         except struct.error:
             bsp_fc_i8(self.struct, X.data_ptr(), bias, out.data_ptr(), code, 0 if shift is None else shift, B, st)
             return out
-        rc = _lib.bsp_call_packed(_CALL_FC_I8, words)
+        rc = _lib.bsp_call_packed(BSP_CALL_FC_I8, words)
         if rc:
             raise BspError(rc, "bsp_fc_i8")
         return out

@@ -344,31 +344,27 @@ int bsp_fc_i8(const bsp_weights* w, const int8_t* X, const int32_t* bias, void* 
   return bsp_conv2d_i8(w, X, bias, Y, y_dtype, shift, B, 1, 1, 1, 1, 0, 0, stream);
 }
 
-// The four layer calls with their arguments in one array of 14 words, for callers that pay per argument (a
-// ctypes call converts each by itself: 1.2 of the 5 us that a small layer takes on the host).
-// what: 0 bsp_conv2d_fused, 1 bsp_fc_fused (L .. pad_w unused): w, X, bias, residual, relu, Y, B, L, J, stride_h,
-// stride_w, pad_h, pad_w, stream; 2 bsp_conv2d_i8, 3 bsp_fc_i8: w, X, bias, Y, y_dtype, shift, B, L, ...
-int bsp_call_packed(int32_t what, const int64_t* words) {
+int bsp_call_packed(int32_t call, const int64_t* words) {
   if (!words) return BSP_ERR_NULL;
-  int64_t a[14];
-  for (int i = 0; i < 14; ++i) a[i] = words[i];
+  int64_t a[BSP_CALL_WORDS];
+  for (int i = 0; i < BSP_CALL_WORDS; ++i) a[i] = words[i];
   const bsp_weights* w = (const bsp_weights*)(uintptr_t)a[0];
   const void* X = (const void*)(uintptr_t)a[1];
   void* stream = (void*)(uintptr_t)a[13];
   auto n = [&](int i) { return (int32_t)a[i]; };
-  switch (what) {
-    case 0:
+  switch (call) {
+    case BSP_CALL_CONV2D:
       return bsp_conv2d_fused(w, X, (const float*)(uintptr_t)a[2], (const void*)(uintptr_t)a[3], n(4), (void*)(uintptr_t)a[5], n(6), n(7), n(8),
                               n(9), n(10), n(11), n(12), stream);
-    case 1:
+    case BSP_CALL_FC:
       return bsp_fc_fused(w, X, (const float*)(uintptr_t)a[2], (const void*)(uintptr_t)a[3], n(4), (void*)(uintptr_t)a[5], n(6), stream);
-    case 2:
+    case BSP_CALL_CONV2D_I8:
       return bsp_conv2d_i8(w, (const int8_t*)X, (const int32_t*)(uintptr_t)a[2], (void*)(uintptr_t)a[3], n(4), n(5), n(6), n(7), n(8), n(9),
                            n(10), n(11), n(12), stream);
-    case 3:
+    case BSP_CALL_FC_I8:
       return bsp_fc_i8(w, (const int8_t*)X, (const int32_t*)(uintptr_t)a[2], (void*)(uintptr_t)a[3], n(4), n(5), n(6), stream);
   }
-  return BSP_ERR_UNSUPPORTED;
+  return BSP_ERR_SHAPE;
 }
 
 }  // extern "C"

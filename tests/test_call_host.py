@@ -41,3 +41,12 @@ def test_streams_that_ctypes_refuses(stream):
     for call in _calls(stream):
         with pytest.raises(ctypes.ArgumentError):
             call()
+
+
+def test_packed_calls_that_are_none():
+    packed = bsp.binding.load_library().bsp_call_packed
+    assert packed(0, None) == -1
+    for call in (-1, 4):
+        assert packed(call, bytes(14 * 8)) == -2
+    for call in range(4):
+        assert packed(call, bytes(14 * 8)) == -1  # no weights
