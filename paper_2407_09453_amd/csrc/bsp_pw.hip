@@ -456,10 +456,10 @@ int launch_inst(const Args& a, dim3 grid, int threads, size_t ldsb, hipStream_t 
 }
 
 // Ring depth D: strips of at most 2 (4) steps take instances with as many registers for
-// weights, which leaves room for more waves per SIMD; deep asks for 16 (workgroups of at most
-// 512 threads, which may then use 256 registers per lane); otherwise 8.
-template <int KIND, int D, int MAXT, typename Args>
+// weights, which leaves room for more waves per SIMD; otherwise 8.
+template <int KIND, int D, typename Args>
 int launch_d(const Args& a, int PT, dim3 grid, int threads, size_t ldsb, hipStream_t st) {
+  constexpr int MAXT = 1024;
   if (threads > MAXT) return BSP_ERR_UNSUPPORTED;
   switch (PT) {
     case 1: return launch_inst<1, KIND, D, MAXT, Args>(a, grid, threads, ldsb, st);
@@ -476,10 +476,9 @@ template <int KIND, typename Args>
 int launch_pt(const Args& a, int PT, int depth, dim3 grid, int threads, size_t ldsb, hipStream_t st) {
   if (PT == 8 && depth >= 8 && threads > 512) return BSP_ERR_UNSUPPORTED;
   switch (depth) {
-    case 2: return launch_d<KIND, 2, 1024, Args>(a, PT, grid, threads, ldsb, st);
-    case 4: return launch_d<KIND, 4, 1024, Args>(a, PT, grid, threads, ldsb, st);
-    case 8: return launch_d<KIND, 8, 1024, Args>(a, PT, grid, threads, ldsb, st);
-    case 16: return launch_d<KIND, 16, 512, Args>(a, PT, grid, threads, ldsb, st);
+    case 2: return launch_d<KIND, 2, Args>(a, PT, grid, threads, ldsb, st);
+    case 4: return launch_d<KIND, 4, Args>(a, PT, grid, threads, ldsb, st);
+    case 8: return launch_d<KIND, 8, Args>(a, PT, grid, threads, ldsb, st);
   }
   return BSP_ERR_UNSUPPORTED;
 }
@@ -487,7 +486,6 @@ int launch_pt(const Args& a, int PT, int depth, dim3 grid, int threads, size_t l
 struct PwChoice {
   int PT, PG, NS;
   int wout;      // results leave through an LDS image of whole output lines
-  int deep = 0;  // ring depth override (0: from the plan's longest strip)
 };
 
 inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
@@ -550,15 +548,12 @@ int launch_pw(const ConvParams& p, int dtype, const void* plan_host, int shift, 
   long long* a_trace = nullptr;
 #endif
   const int maxsteps = rs[BSP_ROWS_MAXSTRIPSTEPS_W];
-  const int depth0 = maxsteps <= 2 ? 2 : maxsteps <= 4 ? 4 : 8;
+  const int depth = maxsteps <= 2 ? 2 : maxsteps <= 4 ? 4 : 8;
   PwChoice ch = pw_choose(p.P, raw / 2, i8 ? (1 << 30) : p.O, nstrips, pitch, rs[BSP_ROWS_WINDOW_W] == 4, i8);
 #ifdef BSP_ROWS_TUNE  // experiments only: never defined in the product build
   if (const char* e = std::getenv("BSP_PWK_TUNE")) {
-    int q[5] = {0, 0, 0, 0, 0};
-    if (sscanf(e, "%d,%d,%d,%d,%d", q, q + 1, q + 2, q + 3, q + 4) >= 4) {
-      ch = PwChoice{q[0], q[1], q[2], q[3]};
-      ch.deep = q[4];
-    }
+    int q[4];
+    if (sscanf(e, "%d,%d,%d,%d", q, q + 1, q + 2, q + 3) == 4) ch = PwChoice{q[0], q[1], q[2], q[3]};
   }
   if (const char* e = std::getenv("BSP_PW_TRACE_PTR")) a_trace = (long long*)std::strtoull(e, nullptr, 16);
   if (std::getenv("BSP_ROWS_VERBOSE"))
@@ -631,7 +626,6 @@ int launch_pw(const ConvParams& p, int dtype, const void* plan_host, int shift, 
   a.adv_pix = (threads * 16) / pitch;
   a.adv_rem = (threads * 16) % pitch;
   dim3 grid((unsigned)(a.per_xcd * 8));
-  const int depth = ch.deep ? ch.deep : depth0;
   const int cw = rs[BSP_ROWS_CW_W];
   if (few && !i8) {
     // (what is formed again is a workgroup's range of channels: the range that its strips cover)
