@@ -69,7 +69,9 @@ inline bool bsp_any_beats_bf16(BspRival rival, int bo, int H, int K, bool stride
 //   LDS kernel (more strips than the band kernel has waves, 4-channel blocks, other widths): 104x104x72->344
 //     16x4 blocks batch 9 98 / 61, 52x52x72->432 batch 10 39 / 29; 33x33x64->448 16x4 batch 10 14.6 / 15.7 (thinner
 //     pixels or fewer strips: 149x149x32 batch 16 stays)
+//   Below 20 K matrix instructions a full chip's opening is longer than the layer.
 inline bool bsp_tall_beats(BspRival rival, int64_t mr, int64_t I, int64_t O, double cost, double rows_cost) {
+  if (mr < 20000) return false;
   if (rival == BSP_RIVAL_ROWS) return I > 128 && cost < 1.35 * rows_cost;
   return rival == BSP_RIVAL_LDS && I >= 64 && I <= 128 && O > 64 && mr > 120000;
 }

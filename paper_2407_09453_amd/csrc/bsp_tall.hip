@@ -582,8 +582,8 @@ int bsp_launch_tall(const ConvParams& p, const void* plan_host, BspRival rival, 
   if ((int64_t)p.B * p.L * p.J * p.I * 2 >= (1ll << 31) || (int64_t)p.P * p.O * 2 >= (1ll << 31)) return BSP_ERR_UNSUPPORTED;
   const int64_t mr = (int64_t)((p.P + 15) / 16) * rs[BSP_ROWS_NCS_W] * p.H;
 #ifndef BSP_ROWS_TUNE
-  // (no search where no cost would decide, nor for small layers: a full chip's opening is longer than those)
-  if (mr < 20000 || !bsp_tall_beats(rival, mr, p.I, p.O, 0.0, 1.0)) return BSP_ERR_UNSUPPORTED;
+  // (no search where no cost would decide)
+  if (!bsp_tall_beats(rival, mr, p.I, p.O, 0.0, 1.0)) return BSP_ERR_UNSUPPORTED;
 #endif
   const int cus = device_cus();
   Choice ch;

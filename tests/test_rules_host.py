@@ -21,6 +21,9 @@ static void is(bool got, bool want, const char* what) {
 #define LDS8(want, ...) is(bsp_any_beats_lds_i8(__VA_ARGS__), want, #__VA_ARGS__)
 #define GEN8(want, ...) is(bsp_i8_general(__VA_ARGS__), want, #__VA_ARGS__)
 #define THIN(want, ...) is(bsp_pw_thin(__VA_ARGS__) == want, true, #__VA_ARGS__)
+#define TALL(want, ...) is(bsp_tall_beats(__VA_ARGS__), want, #__VA_ARGS__)
+#define PWFEW(want, ...) is(bsp_pw_few_beats(__VA_ARGS__), want, #__VA_ARGS__)
+#define PWFEW8(want, ...) is(bsp_pw_few_beats_i8(__VA_ARGS__), want, #__VA_ARGS__)
 #define X3(want, ...) is(bsp_f32x3_beats(__VA_ARGS__), want, #__VA_ARGS__)
 #define F32(want, ...) is(bsp_f32_general(__VA_ARGS__), want, #__VA_ARGS__)
 int main() {
@@ -68,6 +71,52 @@ int main() {
   FEW(true, 16, 61, 1656, 4406, true);                                    // 16.7 / 10.2
   FEW(true, 8, 64, 2048, 4096, true);                                     // 14.3 / 13.2
   FEW(true, 4, 49, 2048, 4096, false);                                    // a window
+  // rival, matrix instructions, channels in and out, both models: the other / persistent, us
+  TALL(true, BSP_RIVAL_ROWS, 1964952, 544, 336, 44422, 53418);            // 71 / 29
+  TALL(true, BSP_RIVAL_ROWS, 2474304, 256, 256, 41416, 47991);            // 47 / 42
+  TALL(true, BSP_RIVAL_ROWS, 2631888, 512, 512, 40516, 48351);            // 52 / 40
+  TALL(true, BSP_RIVAL_ROWS, 1265376, 256, 512, 23586, 24452);            // 27 / 24
+  TALL(false, BSP_RIVAL_ROWS, 66576, 256, 296, 11353, 5246);              // 10.4 / 12.7
+  TALL(false, BSP_RIVAL_ROWS, 175770, 520, 64, 17696, 10246);             // 14.3 / 18.2
+  TALL(false, BSP_RIVAL_ROWS, 2474304, 128, 256, 41416, 47991);
+  TALL(true, BSP_RIVAL_ROWS, 20000, 136, 256, 1349, 1000);
+  TALL(false, BSP_RIVAL_ROWS, 20000, 136, 256, 1350, 1000);
+  TALL(false, BSP_RIVAL_ROWS, 19999, 136, 256, 1, 1000);                  // a full chip's opening is longer
+  TALL(true, BSP_RIVAL_LDS, 1405404, 72, 344, 39535, 0);                  // 98 / 61
+  TALL(true, BSP_RIVAL_LDS, 542490, 72, 432, 20220, 0);                   // 39 / 29
+  TALL(false, BSP_RIVAL_LDS, 532824, 32, 64, 17086, 0);
+  TALL(false, BSP_RIVAL_LDS, 542490, 72, 64, 20220, 0);
+  TALL(false, BSP_RIVAL_LDS, 120000, 72, 432, 20220, 0);
+  TALL(false, BSP_RIVAL_LDS, 542490, 136, 432, 20220, 0);
+  TALL(false, BSP_RIVAL_BAND, 879285, 80, 192, 1, 1000);                  // 26 / 36
+  TALL(false, BSP_RIVAL_TILE, 879285, 256, 192, 1, 1000);
+  // 1x1 of up to 64 pixels, block rows, pixels, channels in and out: the others / pointwise
+  PWFEW(true, 8, 1, 512, 4096);                                           // 4.4 / 4.1
+  PWFEW(true, 8, 16, 64, 1000);                                           // 4.1 / 3.4
+  PWFEW(true, 8, 49, 512, 2048);                                          // 5.0 / 4.4
+  PWFEW(true, 8, 28, 1024, 1000);                                         // 1.23 times faster, and so on
+  PWFEW(true, 8, 64, 1280, 4096);                                         // 1.43
+  PWFEW(false, 8, 1, 1024, 1000);                                         // 0.93
+  PWFEW(false, 8, 16, 1024, 1000);
+  PWFEW(false, 8, 32, 2048, 256);                                         // 0.94
+  PWFEW(true, 4, 1, 512, 1000);                                           // 1.28
+  PWFEW(true, 4, 8, 1280, 1000);                                          // 1.06
+  PWFEW(false, 4, 1, 2048, 256);                                          // 0.89
+  PWFEW(true, 4, 1, 2048, 8192);                                          // 1.4 and up
+  PWFEW(false, 4, 32, 1024, 256);                                         // 0.97
+  PWFEW(true, 4, 32, 1024, 4096);                                         // 1.09
+  PWFEW(false, 4, 32, 1288, 4096);
+  PWFEW(true, 16, 8, 2048, 1000);                                         // 1.3 and up
+  PWFEW(true, 16, 32, 512, 1000);                                         // 1.01
+  PWFEW(false, 16, 32, 1024, 1000);                                       // 0.97
+  PWFEW(true, 16, 32, 1024, 4096);                                        // 1.06
+  PWFEW(false, 16, 8, 2056, 8192);
+  PWFEW8(true, 256, 256);                                                 // 1.31
+  PWFEW8(true, 512, 2048);                                                // 1.29
+  PWFEW8(true, 1024, 1008);                                               // 1.07
+  PWFEW8(false, 2048, 1008);                                              // 0.92
+  PWFEW8(true, 2048, 4096);                                               // 0.99 to 1.31
+  PWFEW8(false, 2064, 4096);
   // int8: slabs, window, pixels, channels out, matrix instructions: LDS-resident / any-shape, us
   LDS8(true, 1, 1, 6272, 256, 6272);                                      // 6.4 / 5.0
   LDS8(false, 1, 1, 100352, 256, 100352);                                 // 21 / 31
