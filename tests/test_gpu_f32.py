@@ -43,16 +43,27 @@ def _assert_close(y, ref, terms, what):
     assert rel <= 2 * np.sqrt(max(terms, 24) / 6) * 2.0 ** -24, (what, rel)
 
 
+OFF_X3 = 26  # the plan's header word that says where its three-part section is (csrc/bsp_plan.h)
+
+
 @pytest.mark.parametrize("bo,bi", [(8, 8), (4, 16), (16, 4)])
 @pytest.mark.parametrize("fused", [False, True], ids=["plain", "fused"])
-def test_f32_shapes(bo, bi, fused):
+@pytest.mark.parametrize("parts", [True, False], ids=["as packed", "without parts"])
+def test_f32_shapes(bo, bi, fused, parts):
+    """As the dispatcher sends them, and the whole chunks of channels among them with a plan that has no three-part
+    section, as plans of layers past its limits: on the kernels before that one."""
     import torch
     for n, (B, L, J, I, O, H, K, s, p) in enumerate(SHAPES):
+        if I % 8 and not parts:
+            continue
         pad = (p if H > 1 or K == 1 else 0, p if K > 1 or H == 1 else 0)
         c = draw_layer("t", B=B, L=L, J=J, I=I, O=O, H=H, K=K, stride=(s, s), pad=pad, bo=bo, bi=bi, dtype="f32",
                        mask_kind="bernoulli", density=0.5, seed=9100 + n, b_std=0.5)
         print("case", n, SHAPES[n], bo, bi, fused, flush=True)
         layer = make_layer(c)
+        if not parts:
+            layer.plan[OFF_X3] = 0
+            assert not any("conv_f32x3" in k for k in kernels_of(lambda: layer.conv2d(to_device(c), c.stride, c.pad)))
         Y = torch.full((c.B, c.M, c.N, c.O), float("nan"), device="cuda")
         if fused:
             r = np.random.default_rng(n).standard_normal(tuple(Y.shape)).astype(np.float32)

@@ -201,12 +201,25 @@ def test_rare_values_cost_little():
     assert max(times[:3]) <= 1.5 and times[3] <= 2, times
 
 
-def test_weights_beyond_three_parts_stay_on_the_fp32_kernel():
-    X, W, keep, gamma, bias, layer, pad = _layer(2)
-    W = W.cpu().numpy()
-    W[0, 0, 0, 0] = 1e-35
-    ran = kernels_of(lambda: bsp.BspLayer(W, gamma, 8, 8, "f32", bias=bias).conv2d(X, (1, 1), pad))
+@pytest.mark.parametrize("value", [1e-35, 3e38, float("inf"), float("nan")])
+def test_weights_beyond_three_parts_stay_on_the_fp32_kernel(value):
+    """A layer with such a weight in a kept block, and what becomes of its results."""
+    import torch
+    n = 2
+    X, W, keep, gamma, bias, _, pad = _layer(n)
+    X *= 0.25  # (the largest weight's products stay below the largest float)
+    W[0, 0, 0, 0] = value
+    layer = bsp.BspLayer(W.cpu().numpy(), gamma, 8, 8, "f32", bias=bias)
+    got = layer.conv2d(X, (1, 1), pad).double()
+    ran = kernels_of(lambda: layer.conv2d(X, (1, 1), pad))
     assert any("conv_f32<" in k for k in ran), ran
+    assert keep[0, 0, 0, 0] == 1
+    want = conv_fp64(X, torch.where(keep.bool(), W, 0.0), 1, pad) + torch.from_numpy(bias).cuda()
+    assert torch.equal(got.isnan(), want.isnan())
+    finite = want.isfinite() & (want.abs() < 3.4e38)
+    assert torch.equal(got.isfinite(), finite)
+    err, ref = (got - want).abs()[finite], want[finite]
+    assert bool((err <= 1e-5 * torch.maximum(ref.abs(), ref[ref.abs() < 1e30].pow(2).mean().sqrt())).all())
 
 
 @pytest.mark.parametrize("I", [64, 128, 136])

@@ -39,34 +39,53 @@ def _infinities(c, n):
     return up & ~nan, down & ~nan, nan, X0
 
 
+def _check(n, c, kernel):
+    import torch
+    bo, bi = c.bo, c.bi
+    layer, X = make_layer(c), to_device(c)
+    Y = torch.full((c.B, c.M, c.N, c.O), float("nan"), device="cuda", dtype=torch.bfloat16)
+    ran = kernels_of(lambda: layer.conv2d(X, c.stride, c.pad, out=Y))
+    assert any(kernel in k for k in ran), ran
+    want = oracle.conv2d(c.X, c.W, c.bias, c.gamma, bo, bi, c.stride, c.pad)
+    assert_close(to_host(Y), want, "bf16", f"shape {n}")
+    # bit for bit the plain call followed by torch's add and relu, each rounding once
+    R = torch.randn(Y.shape, device="cuda", generator=torch.Generator("cuda").manual_seed(n)).bfloat16()
+    post = lambda y: torch.relu(y.float() + R.float()).bfloat16()
+    assert torch.equal(layer.conv2d(X, c.stride, c.pad, residual=R, relu=True), post(Y)), n
+    # an infinity reaches the rows that keep its channel and no others
+    up, down, nan, X0 = _infinities(c, n)
+    Y1 = layer.conv2d(to_device(c), c.stride, c.pad)
+    y, ok = to_host(Y1), ~(up | down | nan)
+    assert (np.isnan(y) == nan).all() and (np.isposinf(y) == up).all() and (np.isneginf(y) == down).all(), n
+    want = oracle.conv2d(X0, c.W, c.bias, c.gamma, bo, bi, c.stride, c.pad)
+    assert_close(np.where(ok, y, 0.0), np.where(ok, want, 0.0), "bf16", f"shape {n}, infinities")
+    Y2 = layer.conv2d(to_device(c), c.stride, c.pad, residual=R, relu=True)
+    same = torch.from_numpy(~nan).cuda()
+    assert torch.equal(Y2[same], post(Y1)[same]), n
+
+
+def _case(n, shape, bo, bi, density):
+    B, L, J, I, O, s = shape
+    print("case", n, shape, bo, bi, density, flush=True)
+    return draw_layer("t", B=B, L=L, J=J, I=I, O=O, H=1, K=1, stride=(s, s), pad=(0, 0), bo=bo, bi=bi, dtype="bf16",
+                      mask_kind="bernoulli", density=density, seed=9900 + n, b_std=0.5)
+
+
 @pytest.mark.parametrize("bo,bi", [(8, 8), (4, 16), (16, 4)])
 @pytest.mark.parametrize("density", [0.0, 0.5, 1.0])
 def test_few_pixels(bo, bi, density):
-    import torch
-    for n, (B, L, J, I, O, s) in enumerate(SHAPES):
-        c = draw_layer("t", B=B, L=L, J=J, I=I, O=O, H=1, K=1, stride=(s, s), pad=(0, 0), bo=bo, bi=bi, dtype="bf16",
-                       mask_kind="bernoulli", density=density, seed=9900 + n, b_std=0.5)
-        print("case", n, SHAPES[n], bo, bi, density, flush=True)
-        layer, X = make_layer(c), to_device(c)
-        Y = torch.full((c.B, c.M, c.N, c.O), float("nan"), device="cuda", dtype=torch.bfloat16)
-        ran = kernels_of(lambda: layer.conv2d(X, c.stride, c.pad, out=Y))
-        assert any("conv_pw" in k for k in ran), ran
-        want = oracle.conv2d(c.X, c.W, c.bias, c.gamma, bo, bi, c.stride, c.pad)
-        assert_close(to_host(Y), want, "bf16", f"shape {n}")
-        # bit for bit the plain call followed by torch's add and relu, each rounding once
-        R = torch.randn(Y.shape, device="cuda", generator=torch.Generator("cuda").manual_seed(n)).bfloat16()
-        post = lambda y: torch.relu(y.float() + R.float()).bfloat16()
-        assert torch.equal(layer.conv2d(X, c.stride, c.pad, residual=R, relu=True), post(Y)), n
-        # an infinity reaches the rows that keep its channel and no others
-        up, down, nan, X0 = _infinities(c, n)
-        Y1 = layer.conv2d(to_device(c), c.stride, c.pad)
-        y, ok = to_host(Y1), ~(up | down | nan)
-        assert (np.isnan(y) == nan).all() and (np.isposinf(y) == up).all() and (np.isneginf(y) == down).all(), n
-        want = oracle.conv2d(X0, c.W, c.bias, c.gamma, bo, bi, c.stride, c.pad)
-        assert_close(np.where(ok, y, 0.0), np.where(ok, want, 0.0), "bf16", f"shape {n}, infinities")
-        Y2 = layer.conv2d(to_device(c), c.stride, c.pad, residual=R, relu=True)
-        same = torch.from_numpy(~nan).cuda()
-        assert torch.equal(Y2[same], post(Y1)[same]), n
+    for n, shape in enumerate(SHAPES):
+        _check(n, _case(n, shape, bo, bi, density), "conv_pw")
+
+
+@pytest.mark.parametrize("bo,bi", [(8, 8), (4, 16), (16, 4)])
+@pytest.mark.parametrize("n,tiles,steps", [(0, 2, 2), (1, 2, 4), (2, 2, 8), (3, 4, 2), (4, 4, 4), (5, 4, 8)])
+def test_lane_tiles_and_steps(bo, bi, n, tiles, steps):
+    """Layers of many channels out, whose workgroups have several lane tiles a wave, with as many registers for weights
+    as a strip's steps need."""
+    shape = [(33, 1, 1, 40, 5200, 1), (6, 3, 9, 112, 5208, 2), (64, 1, 1, 512, 6000, 1), (5, 1, 1, 40, 10400, 1), (33, 1, 1, 112, 10408, 1),
+             (1, 7, 7, 256, 12000, 1)][n]
+    _check(n, _case(20 + n, shape, bo, bi, 0.5), "conv_pw<%d, %d, %d," % (tiles, 4 if bi == 4 else 8, steps))
 
 
 @pytest.mark.parametrize("bo,bi", [(8, 8), (4, 16), (16, 4)])

@@ -23,6 +23,20 @@ SHAPES = [
     (29, 21, 21, 88, 264, 3, (1, 1), (16, 4), 0.75),    # two column groups
     (17, 19, 19, 80, 376, 3, (1, 1), (8, 8), 1.0),      # two of each
     (6, 103, 41, 192, 400, 1, (1, 0), (4, 16), 0.5),    # 3x1
+    # several items to a workgroup, one after the other, and several images to a tile
+    (160, 10, 6, 224, 608, 3, (1, 1), (8, 8), 1.0),     # both
+    (200, 9, 8, 256, 608, 1, (1, 0), (16, 4), 1.0),
+    (200, 10, 6, 96, 296, 3, (1, 1), (4, 16), 0.25),    # and two shares of the contraction
+    (200, 8, 6, 512, 344, 3, (1, 1), (16, 4), 0.25),
+    (160, 8, 9, 288, 200, 5, (1, 2), (4, 16), 0.75),    # items and shares, fourteen rows
+    (33, 20, 25, 384, 296, 3, (1, 1), (8, 8), 0.5),     # seven rows
+    (5, 42, 48, 384, 608, 3, (1, 1), (16, 4), 1.0),
+    (160, 7, 8, 512, 200, 1, (1, 0), (4, 16), 0.75),    # images and shares
+    (160, 9, 6, 136, 72, 3, (1, 1), (8, 8), 0.5),       # four shares
+    (100, 10, 8, 96, 152, 5, (1, 2), (16, 4), 1.0),
+    (2, 56, 66, 384, 152, 3, (1, 1), (8, 8), 1.0),
+    (200, 7, 5, 72, 512, 3, (1, 1), (4, 16), 0.5),      # six images
+    (100, 10, 9, 104, 296, 3, (1, 1), (8, 8), 0.75),    # three images, two column groups
 ]
 
 
