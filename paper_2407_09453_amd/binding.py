@@ -514,12 +514,12 @@ class BspLayer:
             import torch
             out = torch.empty((B, self.O), dtype=self.torch_dtype, device=X.device)
         st = _current_stream(X) if stream is None else stream
-        bias = None if self.d_bias is None else self.d_bias.data_ptr()
         try:
-            words = _pack14(ctypes.addressof(self.struct), X.data_ptr(), bias or 0,
+            words = _pack14(ctypes.addressof(self.struct), X.data_ptr(), 0 if self.d_bias is None else self.d_bias.data_ptr(),
                             0 if residual is None else residual.data_ptr(), 1 if relu else 0, out.data_ptr(),
                             B, 1, 1, 1, 1, 0, 0, st or 0)
         except struct.error:
+            bias = None if self.d_bias is None else self.d_bias.data_ptr()
             if residual is not None or relu:
                 bsp_fc_fused(self.struct, X.data_ptr(), bias, None if residual is None else residual.data_ptr(),
                              relu, out.data_ptr(), B, st)
@@ -649,14 +649,13 @@ class BspLayerI8:
             out = torch.empty(self.out_shape(B, L, J, stride, pad), dtype=ydt, device=X.device)
         assert out.dtype == ydt
         st = _current_stream(X) if stream is None else stream
-        bias = None if self.d_bias is None else self.d_bias.data_ptr()
-        code = BSP_I32 if shift is None else BSP_I8
         try:
-            words = _pack14(ctypes.addressof(self.struct), X.data_ptr(), bias or 0, out.data_ptr(), code,
-                            0 if shift is None else shift, B, L, J, stride[0], stride[1], pad[0], pad[1], st or 0)
+            words = _pack14(ctypes.addressof(self.struct), X.data_ptr(), 0 if self.d_bias is None else self.d_bias.data_ptr(),
+                            out.data_ptr(), BSP_I32 if shift is None else BSP_I8, 0 if shift is None else shift,
+                            B, L, J, stride[0], stride[1], pad[0], pad[1], st or 0)
         except struct.error:
-            bsp_conv2d_i8(self.struct, X.data_ptr(), bias, out.data_ptr(), code, 0 if shift is None else shift,
-                          B, L, J, stride, pad, st)
+            bsp_conv2d_i8(self.struct, X.data_ptr(), None if self.d_bias is None else self.d_bias.data_ptr(), out.data_ptr(),
+                          BSP_I32 if shift is None else BSP_I8, 0 if shift is None else shift, B, L, J, stride, pad, st)
             return out
         rc = _lib.bsp_call_packed(BSP_CALL_CONV2D_I8, words)
         if rc:
@@ -672,13 +671,13 @@ class BspLayerI8:
         if out is None:
             out = torch.empty((B, self.O), dtype=ydt, device=X.device)
         st = _current_stream(X) if stream is None else stream
-        bias = None if self.d_bias is None else self.d_bias.data_ptr()
-        code = BSP_I32 if shift is None else BSP_I8
         try:
-            words = _pack14(ctypes.addressof(self.struct), X.data_ptr(), bias or 0, out.data_ptr(), code,
-                            0 if shift is None else shift, B, 1, 1, 1, 1, 0, 0, st or 0)
+            words = _pack14(ctypes.addressof(self.struct), X.data_ptr(), 0 if self.d_bias is None else self.d_bias.data_ptr(),
+                            out.data_ptr(), BSP_I32 if shift is None else BSP_I8, 0 if shift is None else shift,
+                            B, 1, 1, 1, 1, 0, 0, st or 0)
         except struct.error:
-            bsp_fc_i8(self.struct, X.data_ptr(), bias, out.data_ptr(), code, 0 if shift is None else shift, B, st)
+            bsp_fc_i8(self.struct, X.data_ptr(), None if self.d_bias is None else self.d_bias.data_ptr(), out.data_ptr(),
+                      BSP_I32 if shift is None else BSP_I8, 0 if shift is None else shift, B, st)
             return out
         rc = _lib.bsp_call_packed(BSP_CALL_FC_I8, words)
         if rc:
