@@ -111,11 +111,15 @@ int bsp_validate(const int32_t* row_ptr, const int32_t* col_idx,
 
 /* Launch plan.  The kernels walk strips of 16 output channels; for each strip
  * the plan lists which 8-wide groups of input channels carry at least one kept
- * block and where in `payload` each kept block of the strip starts.  For bf16
- * it also holds a copy of the kept weights re-ordered into the exact order in
+ * block and where in `payload` each kept block of the strip starts.  For bf16 and
+ * int8 it also holds a copy of the kept weights re-ordered into the exact order in
  * which the matrix-core kernels consume them (the paper's compiler likewise
  * lays weights out per sub-volume ahead of time, Sections III and V-B), so
- * that every weight read on the device is one contiguous, aligned run.  The
+ * that every weight read on the device is one contiguous, aligned run.  For fp32
+ * layers in whole groups of eight input channels with up to 8 M weights it holds them
+ * as three bf16 parts each, in that order (1x1 layers of more than 2^20: where they
+ * lie in payload): one and a half to six times the payload in size, and about a
+ * nanosecond a weight to build.  The
  * plan is derived from row_ptr / col_idx / payload alone (weights are prepared
  * once, ahead of inference), holds offsets only (position independent), and is
  * private to this library version: build it on the host, copy the bytes to

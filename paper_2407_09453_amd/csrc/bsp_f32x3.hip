@@ -14,9 +14,9 @@
 // sixteen rows gives back at most two thirds of that (the union of its block rows' columns).  Bound by
 // LDS and the matrix cores alike: a step (four (chunk, tap) pairs) reads 3 KB of activations for six
 // instructions of 16 cycles.  The weights' parts lie in the plan in operand order; activations are split
-// once, where they are staged.  Measured (conv_f32 -> here): 3x3 56x56x64 batch 32 54 -> 34 us, of which the
-// products are 15 by LDS or by the matrix cores (36 with seven spilled registers); 28x28x128 batch 8 25.6 -> 15.0,
-// 1x1 28x28x128->512 batch 8 16.5 -> 12.2 (both with those spills); relative error of the first against 64 bits 3.1e-7 -> 1.0e-7.
+// once, where they are staged.  Measured (conv_f32 -> here, in a replayed graph): 3x3 56x56x64 batch 32 52 -> 35 us, of
+// which the products are 15 by LDS or by the matrix cores; 28x28x128 batch 8 21.9 -> 12.0, 1x1 28x28x128->512 batch 8
+// 15.2 -> 11.3; relative error of the first against 64 bits 3.1e-7 -> 1.0e-7.
 //
 // What three parts cannot hold takes another way: a lane tile that ends in an infinity or NaN (a value or sum past
 // 2^111, an infinity times a zero that fills up a block row) is summed again in fp32, block row by block row,

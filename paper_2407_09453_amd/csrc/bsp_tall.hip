@@ -24,9 +24,9 @@
 // A step's fragments are read R patch rows ahead of the matrix instructions that use them; the weights
 // of the next step are asked for when a step begins, on through slabs and items.
 // Measured (row-band kernel -> here, in a replayed graph): 3x3 28x28x512 batch 16 52 -> 40.5 us, 56x56x256
-// 47 -> 42, 28x28x256->512 27 -> 24, 58x76x544->336 batch 3 71 -> 29.  Bound by the matrix cores as far as the
-// clock allows: of 56x56x256's 42 us the products are 45.5 thousand cycles of a SIMD, 24 us at the 1.87 GHz
-// that the chip keeps under this load; without the reads and the weights' loads it is 39 us.
+// 47 -> 42, 28x28x256->512 27 -> 24, 58x76x544->336 batch 3 71 -> 29.  Of 56x56x256's 42 us the products are 45.5
+// thousand cycles of a SIMD, 24 us at the 1.87 GHz that the chip keeps under this load.  Without the reads and
+// the weights' loads it is 39 us, so the rest is not those; what it is has not been timed.
 #include "bsp_launch.h"
 #include "bsp_tile.h"
 
