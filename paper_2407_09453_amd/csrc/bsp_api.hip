@@ -127,6 +127,8 @@ int dispatch(const bsp_weights* w, const ConvParams& p, void* stream, const Fixe
     // timings of the ResNet50-shaped layers): windows with at least 128 input channels, and
     // pointwise layers with 128..512 input channels, at least 128 output channels and fewer
     // than 100 000 pixels.  A caller's kernel mask overrides the rule.
+    if (!w->kernels && p.H == 1 && p.K == 1) rc = bsp_launch_pws(p, w->dtype, w->plan_host, 0, st);
+    if (rc != BSP_ERR_UNSUPPORTED) return rc;
     if ((allow & BSP_KERNEL_PW) && p.H == 1 && p.K == 1) rc = bsp_launch_pw(p, w->dtype, w->plan_host, st);
     if (rc != BSP_ERR_UNSUPPORTED) return rc;
     const bool rows_pick = p.H > 1 ? p.I >= 128
@@ -318,7 +320,8 @@ int bsp_conv2d_i8(const bsp_weights* w, const int8_t* X, const int32_t* bias, vo
   if (y_dtype == BSP_I8 && (shift < 0 || shift > 31)) return BSP_ERR_SHAPE;
   if (p.P == 0) return BSP_OK;
   if (y_dtype == BSP_I8 && (!w->kernels || (w->kernels & BSP_KERNEL_PW)) && aligned16(X)) {
-    const int rc = bsp_launch_pw_i8(p, w->plan_host, shift, (hipStream_t)stream);
+    int rc = w->kernels ? BSP_ERR_UNSUPPORTED : bsp_launch_pws(p, w->dtype, w->plan_host, shift, (hipStream_t)stream);
+    if (rc == BSP_ERR_UNSUPPORTED) rc = bsp_launch_pw_i8(p, w->plan_host, shift, (hipStream_t)stream);
     if (rc != BSP_ERR_UNSUPPORTED) return rc;
   }
   const bool lds = y_dtype == BSP_I8 && aligned16(X) && (!w->kernels || (w->kernels & BSP_KERNEL_LDS));

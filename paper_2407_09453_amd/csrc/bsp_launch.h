@@ -73,6 +73,8 @@ int bsp_launch_first(const ConvParams& p, int dtype, const void* plan_host, hipS
 // Pointwise kernel (bf16, 1x1 windows without padding, any stride, all input channels in one
 // slab of the row-band section).  BSP_ERR_UNSUPPORTED = not applicable, nothing launched.
 int bsp_launch_pw(const ConvParams& p, int dtype, const void* plan_host, hipStream_t st);
+// The same layers with the weights in registers and the pixels streamed past them (int8: shift as below).
+int bsp_launch_pws(const ConvParams& p, int dtype, const void* plan_host, int shift, hipStream_t st);
 // the same for layers of up to 64 pixels (the entry above declines them, this one all others)
 int bsp_launch_pw_few(const ConvParams& p, const void* plan_host, hipStream_t st);
 // the same for int8 codes with int8 results (channels in whole sixteens)

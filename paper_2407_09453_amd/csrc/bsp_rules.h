@@ -108,6 +108,25 @@ inline bool bsp_pw_few_beats(int bo, int64_t P, int64_t I, int64_t O) {
 // 1.31x, 49 x 512 -> 2048 1.29x, 64 x 1024 -> 1008 1.07x); 2048 -> 1008 0.92x, 2048 -> 4096 0.99x to 1.31x.
 inline bool bsp_pw_few_beats_i8(int64_t I, int64_t O) { return I <= 1024 || (I <= 2048 && O >= 4096); }
 
+// 1x1 layers: whether the kernel that streams the pixels past weights in registers takes the layer from the pointwise one.
+// rounds: tiles of 32 pixels (16 where a strip has more than eight steps), times groups of strips, for each workgroup
+// the chip holds.  Its opening brings every weight into registers before the first product, which two rounds pay for;
+// below that a workgroup for each tile is over sooner.  8900 random layers with cold data, the geometric mean of
+// pointwise / here in each class:
+//   bf16, more than 8 strips: up to 2 steps 0.95 to 1 round, 0.98 to 1.02 to 2, 1.03 to 3, 1.10 past that, 3 or 4 steps 0.92, 0.96
+//     to 0.99, 1.18, 1.15 to 1.30, 5 to 8 steps 0.93, 0.97 to 1.02, 1.21, 1.17 to 1.36; 9 to 16 steps 0.91, 0.92, 1.08, 1.02 to
+//     4 (a third of them slower), 1.26 past that; 5 to 8 strips alike, but 9 to 16 steps 1.21 from 2 rounds on
+//   up to 4 strips: up to 2 steps 0.97 to 1.02 however many rounds (64->64 on 100352 pixels 7.1 / 7.8), longer ones 1.03 to
+//     1.20 from 2 rounds on, 9 to 16 steps 0.93 to 4 rounds, 1.08 to 1.15 past that
+//   int8, more than 4 strips: up to 2 steps 0.93, 1.03 to 1.5 rounds, 1.06 to 2, 1.08 to 1.27 past that, 3 to 8 steps 0.87 to 1.04
+//     to 2 rounds, 1.01 to 1.38 past that; up to 4 strips 0.84 to 0.95; 9 to 16 steps 0.84 to 1.1, left where they are
+// 256->128 on 100352 pixels 25.7 / 18.0 us, 64->256 with a residual 26.0 / 24.2, in int8 13.4 / 9.2.
+inline bool bsp_pws_beats(bool i8, int64_t strips, int64_t steps, double rounds) {
+  if (i8) return strips > 4 && steps <= 8 && rounds > (steps <= 2 ? 1.5 : 2);
+  if (strips <= 4 && steps <= 2) return false;
+  return rounds > (steps <= 8 || (strips > 4 && strips <= 8) ? 2 : 4);
+}
+
 // int8 against the LDS-resident kernel, which keeps one slab's weights in LDS.  One slab (other us /
 // any-shape us): below 20 K matrix instructions, 1x1 56x56x64->256 batch 2 6.4 / 5.0, batch 32 21 / 31.
 // Several slabs: always for a window, 7x7x512 batch 32 15.2 / 11.5, 2x2 47x47x208->32 batch 61 21 / 14, 25x25x624->192
