@@ -64,6 +64,9 @@ int bsp_launch_tall(const ConvParams& p, const void* plan_host, BspRival rival, 
 // Band kernel (bf16, 3x3 stride 1 padding 1, at most 128 input channels, rows of at most 64
 // pixels, strips x column tiles <= 16).  BSP_ERR_UNSUPPORTED = not applicable, nothing launched.
 int bsp_launch_band(const ConvParams& p, int dtype, const void* plan_host, hipStream_t st);
+// 3x3 layers with the weights in registers and the bands streamed past them, for the layers on which that is faster.
+// BSP_ERR_UNSUPPORTED = not applicable or not faster, nothing launched.
+int bsp_launch_bands(const ConvParams& p, const void* plan_host, hipStream_t st);
 
 // Thin-input kernel (bf16, at most four input channels, windows up to 7x7, 32 or 64 output
 // channels; needs the plan's thin-input section and its host copy).  BSP_ERR_UNSUPPORTED = not

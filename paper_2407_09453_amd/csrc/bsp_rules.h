@@ -127,6 +127,25 @@ inline bool bsp_pws_beats(bool i8, int64_t strips, int64_t steps, double rounds)
   return rounds > (steps <= 8 || (strips > 4 && strips <= 8) ? 2 : 4);
 }
 
+// 3x3 layers at stride 1 of at most 128 channels in: whether the kernel that streams bands past weights in registers takes
+// the layer from the band and LDS-resident kernels.  rounds: tiles for each workgroup the chip holds.  650 random layers
+// with cold data, the other / here: 1.43 times faster over the 251 of at least 4000 pixels that it can run, 0.95 at the
+// worst; below that 0.98 (long strips 0.64 to 0.9: every workgroup waits for all its weights before its first product).
+//   LDS kernel: 149x149x32 batch 16 27.2 / 14.4, 147x147x32->64 29.6 / 19.1, 97x83x72->104 batch 5 15.4 / 10.7
+//   band kernel, more than 8 strips: 73x73x80->192 batch 16 28.2 / 23.2, 83x83x64->144 batch 28 81 / 53
+//   up to 8 strips of more than three steps: the same time below four rounds (56x56x64 batch 32 11.7 / 11.0, but with its
+//     data in the caches 9.3 / 9.7; 35x35x64->96 batch 16 7.4 / 7.6, 53x53x72->88 15.6 / 16.5, 70x85x64->112 batch 6
+//     11.1 / 11.0), past them 224x224x64 batch 16 66.7 / 51.0, 112x112x64->128 31.2 / 29.5, 137x143x88->120 35.4 / 34.7.
+//     8 strips of more than six steps fill half a SIMD's waves: 112x112x128 batch 16 45.2 / 47.5, 28x28x128 10.4 / 11.9
+//   unless the images leave XCDs idle, to which the band kernel deals them: 112x112x128 batch 4 28.8 / 19.7, 164x116x104->112
+//     batch 1 31.7 / 10.3
+inline bool bsp_bands_beats(int64_t strips, int64_t steps, int64_t B, int64_t P, int64_t I, double rounds) {
+  if (P < 4000) return false;
+  const bool even = 5 * B >= 4 * ((B + 7) / 8 * 8);
+  if (even && I >= 64 && strips <= 8 && steps > 3 && rounds < 4) return false;
+  return steps <= 6 || strips < 8 || !even;
+}
+
 // int8 against the LDS-resident kernel, which keeps one slab's weights in LDS.  One slab (other us /
 // any-shape us): below 20 K matrix instructions, 1x1 56x56x64->256 batch 2 6.4 / 5.0, batch 32 21 / 31.
 // Several slabs: always for a window, 7x7x512 batch 32 15.2 / 11.5, 2x2 47x47x208->32 batch 61 21 / 14, 25x25x624->192
