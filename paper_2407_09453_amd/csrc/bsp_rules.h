@@ -117,14 +117,17 @@ inline bool bsp_pw_few_beats_i8(int64_t I, int64_t O) { return I <= 1024 || (I <
 //     to 0.99, 1.18, 1.15 to 1.30, 5 to 8 steps 0.93, 0.97 to 1.02, 1.21, 1.17 to 1.36; 9 to 16 steps 0.91, 0.92, 1.08, 1.02 to
 //     4 (a third of them slower), 1.26 past that; 5 to 8 strips alike, but 9 to 16 steps 1.21 from 2 rounds on
 //   up to 4 strips: up to 2 steps 0.97 to 1.02 however many rounds (64->64 on 100352 pixels 7.1 / 7.8), longer ones 1.03 to
-//     1.20 from 2 rounds on, 9 to 16 steps 0.93 to 4 rounds, 1.08 to 1.15 past that
+//     1.20 from 2 rounds on, 9 to 16 steps 0.93 to 4 rounds, 1.08 to 1.15 past that; with their data in the caches, as a
+//     layer has it from the one before, 0.92 to 0.96 from 2 to 3 rounds (256->64 on 19881 pixels 5.2 / 5.8), 0.84 to 1.17 to 4,
+//     1.07 to 1.34 past that (the other classes gain alike both ways, but more than 8 strips of up to 2 steps: 64->256 in a
+//     network on 24576 and 25600 pixels, three rounds, about 0.9 us slower each)
 //   int8, more than 4 strips: up to 2 steps 0.93, 1.03 to 1.5 rounds, 1.06 to 2, 1.08 to 1.27 past that, 3 to 8 steps 0.87 to 1.04
 //     to 2 rounds, 1.01 to 1.38 past that; up to 4 strips 0.84 to 0.95; 9 to 16 steps 0.84 to 1.1, left where they are
 // 256->128 on 100352 pixels 25.7 / 18.0 us, 64->256 with a residual 26.0 / 24.2, in int8 13.4 / 9.2.
 inline bool bsp_pws_beats(bool i8, int64_t strips, int64_t steps, double rounds) {
   if (i8) return strips > 4 && steps <= 8 && rounds > (steps <= 2 ? 1.5 : 2);
   if (strips <= 4 && steps <= 2) return false;
-  return rounds > (steps <= 8 || (strips > 4 && strips <= 8) ? 2 : 4);
+  return rounds > (strips <= 4 || (strips > 8 && steps > 8) ? 4 : strips > 8 && steps <= 2 ? 3.2 : 2);
 }
 
 // 3x3 layers at stride 1 of at most 128 channels in: whether the kernel that streams bands past weights in registers takes
@@ -136,14 +139,15 @@ inline bool bsp_pws_beats(bool i8, int64_t strips, int64_t steps, double rounds)
 //   up to 8 strips of more than three steps: the same time below four rounds (56x56x64 batch 32 11.7 / 11.0, but with its
 //     data in the caches 9.3 / 9.7; 35x35x64->96 batch 16 7.4 / 7.6, 53x53x72->88 15.6 / 16.5, 70x85x64->112 batch 6
 //     11.1 / 11.0), past them 224x224x64 batch 16 66.7 / 51.0, 112x112x64->128 31.2 / 29.5, 137x143x88->120 35.4 / 34.7.
-//     8 strips of more than six steps fill half a SIMD's waves: 112x112x128 batch 16 45.2 / 47.5, 28x28x128 10.4 / 11.9
-//   unless the images leave XCDs idle, to which the band kernel deals them: 112x112x128 batch 4 28.8 / 19.7, 164x116x104->112
-//     batch 1 31.7 / 10.3
+//     more than 8 strips below one round 0.91 to 1.0 (37x37x48->184 batch 3 7.0 / 7.7)
+//   more than six steps (two waves a SIMD): 112x112x128 batch 16 45.2 / 47.5, 28x28x128 10.4 / 11.9, 56x56x128 batch 6 11.1 / 11.9,
+//     unless the images leave XCDs idle, to which the band kernel deals them: 112x112x128 batch 4 28.8 / 19.7, 164x116x104->112
+//     batch 1 31.7 / 10.3, but 28x28x128 batch 3 7.6 / 8.1
 inline bool bsp_bands_beats(int64_t strips, int64_t steps, int64_t B, int64_t P, int64_t I, double rounds) {
-  if (P < 4000) return false;
-  const bool even = 5 * B >= 4 * ((B + 7) / 8 * 8);
-  if (even && I >= 64 && strips <= 8 && steps > 3 && rounds < 4) return false;
-  return steps <= 6 || strips < 8 || !even;
+  if (P < 4000 || (strips > 8 && steps > 3 && rounds < 1)) return false;
+  const double fill = (double)B / (double)((B + 7) / 8 * 8);  // the part of the XCDs' time that whole images fill
+  if (steps > 6) return fill <= 0.5 && rounds >= 4 * fill;
+  return !(fill >= 0.8 && I >= 64 && strips <= 8 && steps > 3 && rounds < 4);
 }
 
 // int8 against the LDS-resident kernel, which keeps one slab's weights in LDS.  One slab (other us /

@@ -21,10 +21,10 @@ CASES = [
     (11, 90, 91, 64, 72, 1, (8, 8), 0.5, True, True, True),      # five strips, the last one half
     (20, 80, 82, 64, 128, 0, (8, 8), 0.5, False, True, True),    # eight strips
     (5, 97, 83, 72, 104, 1, (8, 8), 0.25, True, True, True),
-    (3, 70, 71, 128, 128, 1, (8, 8), 0.5, True, False, True),    # steps by weights: eight to twelve
-    (2, 66, 64, 128, 112, 0, (8, 8), 1.0, False, True, True),
+    (2, 90, 121, 128, 128, 1, (8, 8), 0.5, True, False, True),    # steps by weights: eight to twelve
+    (2, 86, 104, 128, 112, 0, (8, 8), 1.0, False, True, True),
     (1, 121, 156, 80, 120, 1, (4, 16), 0.75, True, True, True),
-    (2, 75, 73, 104, 96, 1, (8, 8), 0.75, False, False, True),
+    (1, 95, 93, 104, 96, 1, (8, 8), 0.75, False, False, True),
     (16, 73, 73, 80, 192, 0, (8, 8), 0.5, True, True, True),     # twelve strips
     (28, 29, 27, 32, 256, 1, (8, 8), 0.5, False, True, False),   # sixteen
 ]

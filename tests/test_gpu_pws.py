@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 BF16 = [
     # B, L, J, I, O, stride, blocks, density, residual, relu
     (33, 33, 31, 64, 128, 1, (8, 8), 1.0, True, True),       # two steps, eight strips, a last tile of 31 pixels
-    (9, 61, 63, 64, 256, 1, (8, 8), 0.5, False, True),       # sixteen strips, two workgroups a pixel
+    (19, 61, 63, 64, 256, 1, (8, 8), 0.5, False, True),      # sixteen strips, two workgroups a pixel
     (7, 131, 41, 24, 72, 1, (8, 8), 0.75, True, False),      # one step, five strips, an odd number of pieces a pixel
     (5, 101, 77, 72, 280, 1, (4, 16), 0.5, True, True),      # strips of four block rows; 18 of them, four at a time
     (6, 141, 139, 112, 232, 2, (8, 8), 0.5, False, False),   # every second pixel
@@ -21,13 +21,13 @@ BF16 = [
     (3, 113, 111, 192, 104, 1, (8, 8), 1.0, False, True),    # six steps, two loads a lane
     (3, 113, 111, 192, 104, 1, (16, 4), 1.0, True, False),
     (2, 150, 149, 256, 192, 1, (8, 8), 1.0, True, True),     # eight steps
-    (4, 95, 93, 512, 64, 1, (16, 4), 0.25, False, False),    # four loads a lane
+    (9, 95, 93, 512, 64, 1, (16, 4), 0.25, False, False),    # four loads a lane
     (3, 120, 118, 440, 120, 1, (8, 8), 0.25, True, True),
     (2, 99, 97, 384, 128, 1, (8, 8), 1.0, True, True),       # twelve steps: tiles of 16 pixels
     (2, 99, 97, 360, 256, 1, (4, 16), 1.0, False, True),     # sixteen waves
     (3, 89, 87, 512, 128, 1, (16, 4), 1.0, False, True),     # sixteen steps
     (2, 101, 99, 504, 264, 1, (8, 8), 1.0, True, False),
-    (9, 64, 64, 256, 32, 1, (8, 8), 0.75, False, False),     # two strips on eight waves
+    (17, 64, 64, 256, 32, 1, (8, 8), 0.75, False, False),     # two strips on eight waves
 ]
 
 
