@@ -37,6 +37,7 @@ struct BandArgs {
   int32_t B, L, J, I, O;
   int32_t M, N, pad;  // output rows and columns; padding 1 (M = L, N = J) or 0 (M = L - 2, N = J - 2)
   int32_t nbands, ctiles;
+  int32_t share, nx, nq;  // bands of an XCD, 0 where it has whole images; image: nx for each XCD, nq for each nbands items
   int32_t cw, nchunks;  // columns per chunk (a multiple of 16 when there are several chunks), chunks per row
   int32_t Jp, pitch, swz_shift, swz_mask;
   int32_t ppr;      // pixels per KiB request
@@ -68,11 +69,13 @@ __global__ __launch_bounds__(1024) void conv_band3(BandArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nwaves = (int)(blockDim.x >> 6);
-  // consecutive workgroups go to different XCDs: all bands of an image are given to one XCD, so
-  // that the halo rows two neighbouring bands share are fetched from HBM once
-  const int xcd = blockIdx.x & 7, slot_wg = blockIdx.x >> 3;
-  const int grp8 = (int)fdiv((uint32_t)slot_wg, a.d_nbands), bc = slot_wg - grp8 * a.nbands;  // nbands counts (band, chunk) pairs
-  const int n = xcd + 8 * grp8;
+  // consecutive workgroups go to different XCDs: all bands of an image are given to one XCD, so that the halo rows two
+  // neighbouring bands share are fetched from HBM once; where the images are no multiple of eight, an XCD is given an
+  // eighth of all bands, one after the other (with whole images to some XCDs and none to the others 56x56x128->256 took
+  // 18.5 us instead of 9.7 at batch 1, 112x112x128 24.3 instead of 8.2, 41 instead of 30 at batch 9)
+  const int xcd = blockIdx.x & 7, item = xcd * a.share + (int)(blockIdx.x >> 3);
+  const int q = (int)fdiv((uint32_t)item, a.d_nbands), bc = item - q * a.nbands;  // nbands counts (band, chunk) pairs
+  const int n = xcd * a.nx + q * a.nq;
   if (n >= a.B) return;
   const int band = (int)fdiv((uint32_t)bc, a.d_nchunks), chunk = bc - band * a.nchunks;
   const int y0 = band * BR, x0 = chunk * a.cw;
@@ -394,10 +397,13 @@ int bsp_launch_band(const ConvParams& p, int dtype, const void* plan_host, hipSt
   a.d_rowp = make_fastdiv((uint32_t)(a.cw * (p.O >> 3)));
   a.llpp = a.pitch == 128 ? 3 : 4;
   // multiply-high divisions are exact while dividend * divisor < 2^32
-  const int64_t nwg = (int64_t)((p.B + 7) / 8) * a.nbands * 8;  // eight images at a time, one per XCD
+  const int64_t nwg = ((int64_t)p.B * a.nbands + 7) / 8 * 8;  // as many bands to every XCD
   if (nwg * a.nbands >= (1ll << 32) || nwg >= (1ll << 31) || (int64_t)(BR + 2) * a.rpr * a.rpr >= (1ll << 32) ||
       (int64_t)(BR * a.cw * (p.O >> 3) + 8192) * a.cw * (p.O >> 3) >= (1ll << 32))
     return BSP_ERR_UNSUPPORTED;
+  a.share = p.B % 8 ? (int)(nwg / 8) : 0;
+  a.nx = p.B % 8 ? 0 : 1;
+  a.nq = p.B % 8 ? 1 : 8;
   const int threads = 64 * nstrips * a.ctiles;
   dim3 grid((unsigned)nwg);
   return BR == 7 ? launch_band<7>(a, grid, threads, (size_t)ldsb, st) : launch_band<4>(a, grid, threads, (size_t)ldsb, st);

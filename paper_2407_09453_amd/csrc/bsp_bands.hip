@@ -3,7 +3,7 @@
 //
 // Work split.  A workgroup is one wave per (strip, column tile of 16) and takes every so many-th tile of four output rows
 // x CT column tiles in its XCD's eighth of them.  A wave reads its strip's weights once and keeps them (three fragments a
-// step, twelve steps at the most).  Per tile: the next tile's input is asked for, into registers, by buffer loads whose
+// step, six steps at the most).  Per tile: the next tile's input is asked for, into registers, by buffer loads whose
 // bounds turn what lies outside the image into zeros; the last tile's results leave as whole output lines; this
 // tile's products from LDS, a step's fragments read three patch rows ahead; results into an LDS image of the output; the
 // next tile's input to the other LDS buffer; one barrier.  Steps and their order are the band kernel's, so the
@@ -212,7 +212,6 @@ __global__ __launch_bounds__(T) void conv_bands(BandsArgs a) {
     break;
     switch (n) {
       BANDS_STEPS(1) BANDS_STEPS(2) BANDS_STEPS(3) BANDS_STEPS(4) BANDS_STEPS(5) BANDS_STEPS(6)
-      BANDS_STEPS(7) BANDS_STEPS(8) BANDS_STEPS(9) BANDS_STEPS(10) BANDS_STEPS(11) BANDS_STEPS(12)
     }
 #undef BANDS_STEPS
   };
@@ -305,9 +304,9 @@ int bsp_launch_bands(const ConvParams& p, const void* plan_host, hipStream_t st)
   const int CT = std::max(1, std::min(4 / nstrips, cdiv(p.N, 16))), waves = nstrips * CT, threads = 64 * waves;
   // waves per SIMD that the registers of the instance for so many steps allow; a workgroup's waves are dealt over the
   // four SIMDs from the first one on
-  const int D = steps <= 3 ? 3 : steps <= 5 ? 5 : steps <= 6 ? 6 : steps <= 8 ? 8 : steps <= 10 ? 10 : 12;
-  const int per_simd = D <= 3 ? 4 : D <= 6 ? 3 : 2, held = per_simd / ((waves + 3) / 4);
-  if (steps > 12 || held < 1) return BSP_ERR_UNSUPPORTED;
+  const int D = steps <= 3 ? 3 : steps <= 5 ? 5 : 6;
+  const int per_simd = D <= 3 ? 4 : 3, held = per_simd / ((waves + 3) / 4);
+  if (steps > 6 || held < 1) return BSP_ERR_UNSUPPORTED;
   a.ctiles = CT;
   a.cw = 16 * CT;
   a.nchunks = cdiv(p.N, a.cw);
@@ -341,7 +340,7 @@ int bsp_launch_bands(const ConvParams& p, const void* plan_host, hipStream_t st)
     if (std::atoi(e) == 0) return BSP_ERR_UNSUPPORTED;
   } else
 #endif
-    if (!bsp_bands_beats(nstrips, steps, p.B, p.P, p.I, rounds)) return BSP_ERR_UNSUPPORTED;
+    if (!bsp_bands_beats(nstrips, steps, p.P, p.I, rounds)) return BSP_ERR_UNSUPPORTED;
   const int32_t* sec = p.plan + hdr[BSP_PLAN_OFF_ROWS_W];
   a.X = (const unsigned char*)p.X;
   a.Y = (unsigned char*)p.Y;
@@ -377,9 +376,6 @@ int bsp_launch_bands(const ConvParams& p, const void* plan_host, hipStream_t st)
   switch (D) {
     case 3: return launch_res<3, 1024>(a, grid, threads, (size_t)ldsb, st);
     case 5: return launch_res<5, 768>(a, grid, threads, (size_t)ldsb, st);
-    case 6: return launch_res<6, 768>(a, grid, threads, (size_t)ldsb, st);
-    case 8: return launch_res<8, 512>(a, grid, threads, (size_t)ldsb, st);
-    case 10: return launch_res<10, 512>(a, grid, threads, (size_t)ldsb, st);
-    default: return launch_res<12, 512>(a, grid, threads, (size_t)ldsb, st);
+    default: return launch_res<6, 768>(a, grid, threads, (size_t)ldsb, st);
   }
 }

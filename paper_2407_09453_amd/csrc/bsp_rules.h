@@ -131,23 +131,20 @@ inline bool bsp_pws_beats(bool i8, int64_t strips, int64_t steps, double rounds)
 }
 
 // 3x3 layers at stride 1 of at most 128 channels in: whether the kernel that streams bands past weights in registers takes
-// the layer from the band and LDS-resident kernels.  rounds: tiles for each workgroup the chip holds.  650 random layers
-// with cold data, the other / here: 1.43 times faster over the 251 of at least 4000 pixels that it can run, 0.95 at the
-// worst; below that 0.98 (long strips 0.64 to 0.9: every workgroup waits for all its weights before its first product).
+// the layer from the band and LDS-resident kernels.  rounds: tiles for each workgroup the chip holds.  900 random layers
+// with cold data and with data in the caches, the other / here in us; below 4000 pixels 0.98 (long strips 0.64 to 0.9:
+// every workgroup waits for all its weights before its first product).
 //   LDS kernel: 149x149x32 batch 16 27.2 / 14.4, 147x147x32->64 29.6 / 19.1, 97x83x72->104 batch 5 15.4 / 10.7
-//   band kernel, more than 8 strips: 73x73x80->192 batch 16 28.2 / 23.2, 83x83x64->144 batch 28 81 / 53
-//   up to 8 strips of more than three steps: the same time below four rounds (56x56x64 batch 32 11.7 / 11.0, but with its
-//     data in the caches 9.3 / 9.7; 35x35x64->96 batch 16 7.4 / 7.6, 53x53x72->88 15.6 / 16.5, 70x85x64->112 batch 6
-//     11.1 / 11.0), past them 224x224x64 batch 16 66.7 / 51.0, 112x112x64->128 31.2 / 29.5, 137x143x88->120 35.4 / 34.7.
-//     more than 8 strips below one round 0.91 to 1.0 (37x37x48->184 batch 3 7.0 / 7.7)
-//   more than six steps (two waves a SIMD): 112x112x128 batch 16 45.2 / 47.5, 28x28x128 10.4 / 11.9, 56x56x128 batch 6 11.1 / 11.9,
-//     unless the images leave XCDs idle, to which the band kernel deals them: 112x112x128 batch 4 28.8 / 19.7, 164x116x104->112
-//     batch 1 31.7 / 10.3, but 28x28x128 batch 3 7.6 / 8.1
-inline bool bsp_bands_beats(int64_t strips, int64_t steps, int64_t B, int64_t P, int64_t I, double rounds) {
-  if (P < 4000 || (strips > 8 && steps > 3 && rounds < 1)) return false;
-  const double fill = (double)B / (double)((B + 7) / 8 * 8);  // the part of the XCDs' time that whole images fill
-  if (steps > 6) return fill <= 0.5 && rounds >= 4 * fill;
-  return !(fill >= 0.8 && I >= 64 && strips <= 8 && steps > 3 && rounds < 4);
+//   band kernel, more than 8 strips: 73x73x80->192 batch 16 28.2 / 23.2, 83x83x64->144 batch 28 81 / 53, but 0.91 to 1.0
+//     below one round (37x37x48->184 batch 3 7.0 / 7.7)
+//   up to 8 strips of more than three steps: past four rounds 224x224x64 batch 16 66.7 / 51.0, 112x112x64->128 31.2 / 29.5,
+//     137x143x88->120 35.4 / 34.7; below them the same time (35x35x64->96 batch 16 7.4 / 7.6, 53x53x72->88 15.6 / 16.5), but
+//     up to 4 strips to one and a half 56x56x64 batch 4 5.9 / 5.2, batch 9 7.8 / 6.2, batch 16 8.5 / 7.7 (batch 24 9.0 / 9.4)
+//   more than six steps leave registers for two waves a SIMD: 56x56x128 batch 6 11.1 / 11.9, 28x28x128 batch 32 10.4 / 11.9
+inline bool bsp_bands_beats(int64_t strips, int64_t steps, int64_t P, int64_t I, double rounds) {
+  if (P < 4000 || steps > 6 || (strips > 8 && steps > 3 && rounds < 1)) return false;
+  if (I >= 64 && strips <= 8 && steps > 3) return rounds >= 4 || (strips <= 4 && rounds <= 1.5);
+  return true;
 }
 
 // int8 against the LDS-resident kernel, which keeps one slab's weights in LDS.  One slab (other us /

@@ -20,11 +20,10 @@ CASES = [
     (18, 61, 60, 24, 48, 1, (4, 16), 0.5, False, False, False),  # three strips; a pixel of three pieces
     (11, 90, 91, 64, 72, 1, (8, 8), 0.5, True, True, True),      # five strips, the last one half
     (20, 80, 82, 64, 128, 0, (8, 8), 0.5, False, True, True),    # eight strips
-    (5, 97, 83, 72, 104, 1, (8, 8), 0.25, True, True, True),
-    (2, 90, 121, 128, 128, 1, (8, 8), 0.5, True, False, True),    # steps by weights: eight to twelve
-    (2, 86, 104, 128, 112, 0, (8, 8), 1.0, False, True, True),
-    (1, 121, 156, 80, 120, 1, (4, 16), 0.75, True, True, True),
-    (1, 95, 93, 104, 96, 1, (8, 8), 0.75, False, False, True),
+    (9, 97, 83, 72, 104, 1, (8, 8), 0.25, True, True, True),
+    (12, 64, 100, 96, 104, 1, (8, 8), 0.25, True, False, True),  # seven
+    (1, 149, 131, 56, 64, 1, (8, 8), 0.75, False, True, False),
+    (9, 47, 53, 64, 64, 1, (8, 8), 0.5, True, True, True),
     (16, 73, 73, 80, 192, 0, (8, 8), 0.5, True, True, True),     # twelve strips
     (28, 29, 27, 32, 256, 1, (8, 8), 0.5, False, True, False),   # sixteen
 ]
@@ -79,3 +78,23 @@ def test_bands(n):
     scale = torch.maximum(want.abs(), want.pow(2).mean().sqrt())
     # one rounding to bf16 is 3.9e-3 at most, the fused epilogue has two and may round a sum the other way in the first
     assert bool(((out.double() - want).abs() <= (1.2e-2 if residual else 6e-3) * scale).all())
+
+
+@pytest.mark.parametrize("B", [1, 3, 7, 9, 13])
+def test_band_kernel_with_images_left_over(B):
+    """Batches that are no multiple of eight: every band is computed by some XCD."""
+    import torch
+    print("band kernel, batch", B, flush=True)
+    gen = torch.Generator("cuda").manual_seed(B)
+    gamma = (np.random.default_rng(B).random((16, 9)) < 0.5).astype(np.uint8)
+    W = (torch.randn(128, 3, 3, 72, generator=gen, device="cuda") * 0.05).bfloat16()
+    layer = bsp.BspLayer(W.float().cpu().numpy(), gamma, 8, 8, "bf16")
+    layer.struct.kernels = bsp.BSP_KERNEL_BAND
+    X = torch.randn(B, 37, 53, 72, generator=gen, device="cuda").bfloat16()
+    out = torch.full(layer.out_shape(B, 37, 53, (1, 1), (1, 1)), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ran = kernels_of(lambda: layer.conv2d(X, (1, 1), (1, 1), out=out))
+    assert any("conv_band3<" in k for k in ran), ran
+    keep = torch.from_numpy(np.kron(gamma, np.ones((8, 8), np.uint8))).cuda()
+    want = conv_fp64(X, W * keep[:, None, None, :], 1, (1, 1))
+    scale = torch.maximum(want.abs(), want.pow(2).mean().sqrt())
+    assert bool(((out.double() - want).abs() <= 6e-3 * scale).all())
