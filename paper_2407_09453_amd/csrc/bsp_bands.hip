@@ -15,6 +15,7 @@
 // one takes 14.4.  Four rows rather than seven: a CU then holds twelve waves instead of eight (51 / 56 us), which is
 // worth more than the halo rows; two tiles asked for ahead made no difference, a fragment read one row or five ahead
 // neither.  With a branch per step the compiler waits for every read, so there is straight code for every number of steps.
+#include "bsp_bands_map.h"
 #include "bsp_launch.h"
 #include "bsp_tile.h"
 
@@ -49,8 +50,7 @@ struct BandsArgs {
 
 typedef __attribute__((ext_vector_type(4))) int i32x4_t;
 
-constexpr int BR = 4;  // output rows of a tile
-constexpr int QL = 4;  // pieces of input a lane brings for a tile
+constexpr int BR = kBandsRows, QL = kBandsPieces;
 
 // D: the most steps of a strip; T: 256 times the waves that a SIMD is to hold.
 template <int D, int T, bool RES>
@@ -71,6 +71,7 @@ __global__ __launch_bounds__(T) void conv_bands(BandsArgs a) {
 
   // ---- the pieces of input this lane brings for every tile
   uint32_t xofs[QL], xrc[QL], xlds[QL];  // offset from the patch's first pixel; row | column << 16; place in LDS
+  const uint32_t mine = (uint32_t)(a.spill + lane * 16);
 #pragma unroll
   for (int j = 0; j < QL; ++j) {
     const uint32_t idx = (uint32_t)(tid + j * nthr);
@@ -79,7 +80,7 @@ __global__ __launch_bounds__(T) void conv_bands(BandsArgs a) {
     const uint32_t row = fdiv(px, a.d_jp), col = px - row * a.d_jp.d;
     xofs[j] = some ? (row * (uint32_t)a.J + col) * (uint32_t)(a.cpx * 16) + piece * 16u : 0u;
     xrc[j] = some ? row | col << 16 : 0x7FFFu;
-    xlds[j] = some ? row * (uint32_t)a.rowpitch + col * (uint32_t)a.pitch + piece * 16u : (uint32_t)(a.spill + lane * 16);
+    xlds[j] = some ? row * (uint32_t)a.rowpitch + col * (uint32_t)a.pitch + piece * 16u : mine;
   }
   struct Tile {
     int n, y0, x0;
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(T) void conv_bands(BandsArgs a) {
   };
   auto write_x = [&](uint32_t off) {
 #pragma unroll
-    for (int j = 0; j < QL; ++j) *(i32x4_t*)(lds + off + xlds[j]) = xr[j];
+    for (int j = 0; j < QL; ++j) *(i32x4_t*)(lds + bsp_bands_place(xlds[j], off, mine)) = xr[j];
   };
   Tile at = locate(first);
   load_x(at, true);
@@ -140,7 +141,7 @@ __global__ __launch_bounds__(T) void conv_bands(BandsArgs a) {
     else
       ad[d / 2] = v;
   }
-  const uint32_t bias_at = (uint32_t)(a.spill + 1024 + (wave * 4 + g) * 16);
+  const uint32_t bias_at = bsp_bands_bias((uint32_t)a.spill, (uint32_t)wave, (uint32_t)g);
   if (c < 4) *(float*)(lds + bias_at + c * 4) = a.bias && chan >= 0 ? a.bias[chan + c] : 0.f;
   const uint32_t img = (uint32_t)(a.out_off + (ct * 16 + c) * a.opitch + (chan >= 0 ? chan * 2 : a.O * 2));
 
@@ -259,15 +260,13 @@ __global__ __launch_bounds__(T) void conv_bands(BandsArgs a) {
   }
 }
 
-constexpr int kLdsLimit = 160 * 1024;
-
 inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 template <int D, int T, bool RES>
 int launch_inst(const BandsArgs& a, dim3 grid, int threads, size_t ldsb, hipStream_t st) {
   static bool raised = false;  // dynamic LDS above 64 KB has to be allowed once per kernel
   if (!raised) {
-    if (hipFuncSetAttribute((const void*)conv_bands<D, T, RES>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit) != hipSuccess)
+    if (hipFuncSetAttribute((const void*)conv_bands<D, T, RES>, hipFuncAttributeMaxDynamicSharedMemorySize, kBandsLds) != hipSuccess)
       return BSP_ERR_HIP;
     raised = true;
   }
@@ -295,37 +294,23 @@ int bsp_launch_bands(const ConvParams& p, const void* plan_host, hipStream_t st)
   if ((int64_t)p.B * p.L * p.J * p.I * 2 >= (1ll << 31) || (int64_t)p.P * p.O * 2 >= (1ll << 31)) return BSP_ERR_UNSUPPORTED;
   if (p.L >= 0x7000 || p.J >= 0x7000) return BSP_ERR_UNSUPPORTED;
   const int nstrips = rs[BSP_ROWS_NSTRIPS_W], steps = rs[BSP_ROWS_MAXSTRIPSTEPS_W];
-  if (nstrips < 1 || nstrips > 16) return BSP_ERR_UNSUPPORTED;
+  BandsMap m{};
+  if (!bsp_bands_map(p.I, p.N, p.O, nstrips, steps, &m)) return BSP_ERR_UNSUPPORTED;
+  const int threads = 64 * m.waves, Jp = m.cw + 2;
   BandsArgs a{};
-  a.cpx = p.I / 8;
-  a.pitch = (a.cpx | 1) * 16;  // an odd number of pieces: no two pixels of a lane tile share banks
-  a.opitch = p.O * 2 + 16;
-  // One column tile, more where fewer than four strips make a workgroup of four waves of them.
-  const int CT = std::max(1, std::min(4 / nstrips, cdiv(p.N, 16))), waves = nstrips * CT, threads = 64 * waves;
-  // waves per SIMD that the registers of the instance for so many steps allow; a workgroup's waves are dealt over the
-  // four SIMDs from the first one on
-  const int D = steps <= 3 ? 3 : steps <= 5 ? 5 : 6;
-  const int per_simd = D <= 3 ? 4 : 3, held = per_simd / ((waves + 3) / 4);
-  if (steps > 6 || held < 1) return BSP_ERR_UNSUPPORTED;
-  a.ctiles = CT;
-  a.cw = 16 * CT;
+  a.cpx = m.cpx;
+  a.pitch = m.pitch;
+  a.rowpitch = m.rowpitch;
+  a.pieces = m.pieces;
+  a.ctiles = m.ctiles;
+  a.cw = m.cw;
   a.nchunks = cdiv(p.N, a.cw);
-  const int Jp = a.cw + 2;
-  a.rowpitch = Jp * a.pitch;
-  a.pieces = (BR + 2) * Jp * a.cpx;
-  if (a.pieces > QL * threads) return BSP_ERR_UNSUPPORTED;
-  // Two patches and two images of the output in turn, so that one barrier ends a tile; one of each, and a second
-  // barrier, where a CU then holds more workgroups.
-  const int patch = (BR + 2) * a.rowpitch, image = BR * a.cw * a.opitch, fixed = 1024 + waves * 64;
-  auto resident = [&](int sets) { return std::min(held, kLdsLimit / (sets * (patch + image) + fixed)); };
-  a.single = resident(1) > resident(2);
-  const int sets = a.single ? 1 : 2;
-  if (resident(sets) < 1) return BSP_ERR_UNSUPPORTED;
-  a.slot = a.single ? 0 : patch;
-  a.out_off = sets * patch;
-  a.oslot = a.single ? 0 : image;
-  a.spill = sets * (patch + image);
-  const int64_t ldsb = a.spill + fixed;
+  a.slot = m.slot;
+  a.out_off = m.out_off;
+  a.oslot = m.oslot;
+  a.opitch = m.opitch;
+  a.single = m.single;
+  a.spill = m.spill;
   a.tpi = cdiv(p.M, BR) * a.nchunks;
   const int64_t tiles = (int64_t)p.B * a.tpi;
   if (tiles >= (1ll << 30) || tiles * std::max(a.tpi, a.nchunks) >= (1ll << 32) || (int64_t)QL * threads * std::max(a.cpx, Jp) >= (1ll << 32) ||
@@ -333,8 +318,8 @@ int bsp_launch_bands(const ConvParams& p, const void* plan_host, hipStream_t st)
     return BSP_ERR_UNSUPPORTED;
   a.tiles = (int)tiles;
   a.per_xcd = cdiv(tiles, 8);
-  a.groups = std::min(a.per_xcd, 32 * resident(sets));
-  const double rounds = (double)tiles / (256 * resident(sets));
+  a.groups = std::min(a.per_xcd, 32 * m.resident);
+  const double rounds = (double)tiles / (256 * m.resident);
 #ifdef BSP_ROWS_TUNE  // experiments only: never defined in the product build
   if (const char* e = std::getenv("BSP_BANDS_TUNE")) {
     if (std::atoi(e) == 0) return BSP_ERR_UNSUPPORTED;
@@ -370,12 +355,12 @@ int bsp_launch_bands(const ConvParams& p, const void* plan_host, hipStream_t st)
 #ifdef BSP_ROWS_TUNE
   if (std::getenv("BSP_ROWS_VERBOSE"))
     fprintf(stderr, "bands: B=%d %dx%d %d->%d strips=%d steps=%d | CT=%d D=%d single=%d resident=%d tiles=%d rounds=%.3f lds=%d\n", p.B, p.L, p.J, p.I, p.O, nstrips,
-            steps, CT, D, a.single, resident(sets), a.tiles, rounds, (int)ldsb);
+            steps, m.ctiles, m.depth, a.single, m.resident, a.tiles, rounds, m.lds);
 #endif
   dim3 grid((unsigned)(a.groups * 8));
-  switch (D) {
-    case 3: return launch_res<3, 1024>(a, grid, threads, (size_t)ldsb, st);
-    case 5: return launch_res<5, 768>(a, grid, threads, (size_t)ldsb, st);
-    default: return launch_res<6, 768>(a, grid, threads, (size_t)ldsb, st);
+  switch (m.depth) {
+    case 3: return launch_res<3, 1024>(a, grid, threads, (size_t)m.lds, st);
+    case 5: return launch_res<5, 768>(a, grid, threads, (size_t)m.lds, st);
+    default: return launch_res<6, 768>(a, grid, threads, (size_t)m.lds, st);
   }
 }

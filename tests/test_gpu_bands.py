@@ -26,6 +26,11 @@ CASES = [
     (9, 47, 53, 64, 64, 1, (8, 8), 0.5, True, True, True),
     (16, 73, 73, 80, 192, 0, (8, 8), 0.5, True, True, True),     # twelve strips
     (28, 29, 27, 32, 256, 1, (8, 8), 0.5, False, True, False),   # sixteen
+    # patches smaller than the spill area and the biases, several tiles a workgroup
+    (8, 56, 56, 8, 256, 1, (8, 8), 1.0, False, True, False),
+    (16, 56, 56, 8, 184, 1, (8, 8), 1.0, True, False, False),
+    (8, 56, 56, 8, 256, 0, (4, 16), 1.0, False, False, False),   # no bias
+    (64, 16, 16, 8, 256, 1, (8, 8), 1.0, False, False, True),
 ]
 
 
