@@ -140,8 +140,7 @@ int dispatch(const bsp_weights* w, const ConvParams& p, void* stream, const Fixe
     // place of the kernel that would run next
     auto tall = [&](BspRival rival) { return !w->kernels && chunked && p.H == 3 ? bsp_launch_tall(p, w->plan_host, rival, st) : BSP_ERR_UNSUPPORTED; };
     for (;;) {
-      // (the any-shape kernel's layers stay there: it forms sums that are no finite number again from kept blocks)
-      if (any && chunked && p.H == 3 && p.K == 3 && !any_beats(BSP_RIVAL_LDS)) rc = bsp_launch_bands(p, w->plan_host, st);
+      if (any && chunked && p.H == 3 && p.K == 3) rc = bsp_launch_bands(p, w->plan_host, st);
       if (rc != BSP_ERR_UNSUPPORTED) return rc;
       if ((allow & BSP_KERNEL_BAND) && p.H == 3 && p.K == 3 && !any_beats(BSP_RIVAL_BAND))
         rc = bsp_launch_band(p, w->dtype, w->plan_host, st);

@@ -326,6 +326,8 @@ int bsp_launch_bands(const ConvParams& p, const void* plan_host, hipStream_t st)
   } else
 #endif
     if (!bsp_bands_beats(nstrips, steps, p.P, p.I, rounds)) return BSP_ERR_UNSUPPORTED;
+  // (the any-shape kernel's layers stay there: it forms sums that are no finite number again from kept blocks)
+  if (bsp_any_beats(p, plan_host, BSP_RIVAL_LDS)) return BSP_ERR_UNSUPPORTED;
   const int32_t* sec = p.plan + hdr[BSP_PLAN_OFF_ROWS_W];
   a.X = (const unsigned char*)p.X;
   a.Y = (unsigned char*)p.Y;

@@ -85,9 +85,9 @@ def test_bands(n):
     assert bool(((out.double() - want).abs() <= (1.2e-2 if residual else 6e-3) * scale).all())
 
 
-@pytest.mark.parametrize("B", [1, 3, 7, 9, 13])
+@pytest.mark.parametrize("B", [1, 3, 7, 8, 9, 13, 16])
 def test_band_kernel_with_images_left_over(B):
-    """Batches that are no multiple of eight: every band is computed by some XCD."""
+    """Batches that are and are no multiple of eight, which take an instance each: every band is computed by some XCD."""
     import torch
     print("band kernel, batch", B, flush=True)
     gen = torch.Generator("cuda").manual_seed(B)
