@@ -456,7 +456,7 @@ int launch_pws(const ConvParams& p, int dtype, const void* plan_host, int shift,
 #ifdef BSP_ROWS_TUNE
   if (!std::getenv("BSP_PWS_TUNE"))
 #endif
-    if (!bsp_pws_beats(i8, nstrips, steps, (double)a.tiles * a.nsplit / wgs)) return BSP_ERR_UNSUPPORTED;
+    if (!bsp_pws_beats(i8, nstrips, steps, p.residual != nullptr, (double)a.tiles * a.nsplit / wgs)) return BSP_ERR_UNSUPPORTED;
   a.slot = MT * a.pitch;
   a.opitch = NS * 16 * eb + 16;
   a.out_off = 2 * a.slot;

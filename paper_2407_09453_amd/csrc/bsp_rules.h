@@ -119,15 +119,21 @@ inline bool bsp_pw_few_beats_i8(int64_t I, int64_t O) { return I <= 1024 || (I <
 //   up to 4 strips: up to 2 steps 0.97 to 1.02 however many rounds (64->64 on 100352 pixels 7.1 / 7.8), longer ones 1.03 to
 //     1.20 from 2 rounds on, 9 to 16 steps 0.93 to 4 rounds, 1.08 to 1.15 past that; with their data in the caches, as a
 //     layer has it from the one before, 0.92 to 0.96 from 2 to 3 rounds (256->64 on 19881 pixels 5.2 / 5.8), 0.84 to 1.17 to 4,
-//     1.07 to 1.34 past that (the other classes gain alike both ways, but more than 8 strips of up to 2 steps: 64->256 in a
-//     network on 24576 and 25600 pixels, three rounds, about 0.9 us slower each)
-//   int8, more than 4 strips: up to 2 steps 0.93, 1.03 to 1.5 rounds, 1.06 to 2, 1.08 to 1.27 past that, 3 to 8 steps 0.87 to 1.04
-//     to 2 rounds, 1.01 to 1.38 past that; up to 4 strips 0.84 to 0.95; 9 to 16 steps 0.84 to 1.1, left where they are
+//     1.07 to 1.34 past that
+//   more than 8 strips of up to 2 steps with their data in the caches: without a residual alike; with one, in the stack of a
+//     ResNet50, 0.87 to 0.95 to 3.5 rounds (64->256 on 28224 pixels 6.4 / 7.6), 0.82 to 1.06 to 7 (on 39168 9.0 / 10.9), 1.00
+//     to 1.07 past that, and with cold data 0.99 to 1.08 to 7 rounds
+//   int8, more than 4 strips: 1 step 0.93 to 0.98 to 1.5 rounds, 1.15 to 1.38 past that in the stack of a ResNet50 (64->256 on
+//     25600 pixels 6.1 / 5.1), 1.06 to 1.39 cold; 2 steps 0.94 to 1.04 to 3 rounds in the stack (128->512 on 11200
+//     pixels 5.0 / 5.3), 0.92 to 1.20 cold, 1.04 to 1.24 and 1.00 to 1.21 past that; 3 or 4 steps and more
+//     than 8 strips 0.94 to 1.05 and 0.94 to 1.06 to 3 rounds, 1.11 to 1.33 past that; up to 8 strips 0.86 to 1.00 and 0.94 to
+//     0.95 to 2 rounds, 1.01 to 1.05 and 0.96 to 1.06 to 3; 5 to 8 steps 0.86 to 1.05 to 2 rounds, 1.13 to 1.32 past that; up to 4
+//     strips 0.84 to 1.00 (0.84 to 0.95 cold); 9 to 16 steps 0.98 to 1.03 (0.84 to 1.1), left where they are
 // 256->128 on 100352 pixels 25.7 / 18.0 us, 64->256 with a residual 26.0 / 24.2, in int8 13.4 / 9.2.
-inline bool bsp_pws_beats(bool i8, int64_t strips, int64_t steps, double rounds) {
-  if (i8) return strips > 4 && steps <= 8 && rounds > (steps <= 2 ? 1.5 : 2);
+inline bool bsp_pws_beats(bool i8, int64_t strips, int64_t steps, bool residual, double rounds) {
+  if (i8) return strips > 4 && steps <= 8 && rounds > (steps <= 1 ? 1.5 : steps == 2 || (steps <= 4 && strips > 8) ? 3 : 2);
   if (strips <= 4 && steps <= 2) return false;
-  return rounds > (strips <= 4 || (strips > 8 && steps > 8) ? 4 : strips > 8 && steps <= 2 ? 3.2 : 2);
+  return rounds > (strips <= 4 || (strips > 8 && steps > 8) ? 4 : strips > 8 && steps <= 2 ? (residual ? 7 : 3.2) : 2);
 }
 
 // 3x3 layers at stride 1 of at most 128 channels in: whether the kernel that streams bands past weights in registers takes

@@ -24,6 +24,7 @@ static void is(bool got, bool want, const char* what) {
 #define TALL(want, ...) is(bsp_tall_beats(__VA_ARGS__), want, #__VA_ARGS__)
 #define PWFEW(want, ...) is(bsp_pw_few_beats(__VA_ARGS__), want, #__VA_ARGS__)
 #define PWFEW8(want, ...) is(bsp_pw_few_beats_i8(__VA_ARGS__), want, #__VA_ARGS__)
+#define PWS(want, ...) is(bsp_pws_beats(__VA_ARGS__), want, #__VA_ARGS__)
 #define X3(want, ...) is(bsp_f32x3_beats(__VA_ARGS__), want, #__VA_ARGS__)
 #define F32(want, ...) is(bsp_f32_general(__VA_ARGS__), want, #__VA_ARGS__)
 int main() {
@@ -117,6 +118,38 @@ int main() {
   PWFEW8(false, 2048, 1008);                                              // 0.92
   PWFEW8(true, 2048, 4096);                                               // 0.99 to 1.31
   PWFEW8(false, 2064, 4096);
+  // 1x1 of more than 64 pixels, int8, strips, steps, residual, rounds of 32 (past 8 steps 16) pixels: pointwise / streamed
+  PWS(true, false, 8, 8, false, 100352 / 32 / 512.);                      // 256->128 on 100352 pixels 25.7 / 18.0
+  PWS(true, false, 16, 2, true, 2 * 100352 / 32 / 512.);                  // 64->256 26.0 / 24.2
+  PWS(true, false, 16, 2, true, 2 * 62720 / 32 / 512.);                   // 15.5 / 15.1
+  PWS(false, false, 16, 2, true, 2 * 39168 / 32 / 512.);                  // 9.0 / 10.9
+  PWS(false, false, 16, 2, true, 2 * 28224 / 32 / 512.);                  // 6.4 / 7.6
+  PWS(true, false, 16, 2, false, 2 * 28224 / 32 / 512.);                  // 5.6 / 5.2
+  PWS(false, false, 16, 2, false, 2 * 21632 / 32 / 512.);                 // 4.9 / 5.1
+  PWS(false, false, 4, 2, false, 100352 / 32 / 512.);                     // 64->64 7.1 / 7.8
+  PWS(false, false, 4, 7, false, 19881 / 32 / 512.);                      // 256->64 5.2 / 5.8
+  PWS(true, false, 4, 7, false, 100352 / 32 / 512.);                      // 17.0 / 15.2
+  PWS(true, false, 8, 7, false, 33000 / 32 / 512.);                       // 256->128 11.8 / 8.7
+  PWS(false, false, 8, 7, false, 32000 / 32 / 512.);
+  PWS(true, false, 32, 4, true, 4 * 8320 / 32 / 512.);                    // 128->512 8.1 / 6.5
+  PWS(false, false, 32, 4, true, 4 * 8000 / 32 / 512.);                   // 0.96 to 0.99
+  PWS(true, false, 16, 14, false, 18816 / 16 / 256.);                     // 512->256 17.9 / 14.1
+  PWS(false, false, 16, 14, false, 16000 / 16 / 256.);                    // a third of them slower
+  PWS(true, true, 16, 1, false, 2 * 25600 / 32 / 1024.);                  // 64->256 6.1 / 5.1
+  PWS(false, true, 16, 1, false, 2 * 23232 / 32 / 1024.);                 // 4.8 / 5.1
+  PWS(true, true, 32, 2, false, 4 * 14112 / 32 / 512.);                   // 128->512 6.9 / 5.6
+  PWS(false, true, 32, 2, false, 4 * 11200 / 32 / 512.);                  // 5.0 / 5.3
+  PWS(false, true, 32, 2, false, 4 * 6272 / 32 / 512.);                   // 4.4 / 4.5
+  PWS(false, true, 8, 2, false, 42496 / 32 / 512.);                       // 128->128 5.6 / 6.0
+  PWS(true, true, 8, 4, false, 100352 / 32 / 512.);                       // 256->128 13.7 / 11.2
+  PWS(true, true, 8, 4, false, 42496 / 32 / 512.);                        // 7.6 / 7.4
+  PWS(false, true, 8, 4, false, 31232 / 32 / 512.);                       // 6.1 / 6.5
+  PWS(false, true, 32, 4, false, 4 * 11776 / 32 / 512.);                  // 256->512 5.9 / 6.2
+  PWS(true, true, 32, 4, false, 4 * 13312 / 32 / 512.);                   // 7.4 / 6.4
+  PWS(true, true, 16, 8, false, 2 * 18816 / 32 / 512.);                   // 512->256 10.1 / 7.7
+  PWS(false, true, 16, 8, false, 2 * 14112 / 32 / 512.);                  // 7.0 / 7.3
+  PWS(false, true, 4, 4, false, 100352 / 32 / 512.);                      // 256->64 8.9 / 9.7
+  PWS(false, true, 16, 15, false, 100352 / 16 / 256.);
   // int8: slabs, window, pixels, channels out, matrix instructions: LDS-resident / any-shape, us
   LDS8(true, 1, 1, 6272, 256, 6272);                                      // 6.4 / 5.0
   LDS8(false, 1, 1, 100352, 256, 100352);                                 // 21 / 31
