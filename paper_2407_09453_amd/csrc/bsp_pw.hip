@@ -614,7 +614,8 @@ int launch_pw(const ConvParams& p, int dtype, const void* plan_host, int shift, 
   a.per_xcd = cdiv(wgs, 8);
   a.pair = hdr[BSP_PLAN_BO_W] != 4 && ch.PT >= 2;
   // multiply-high divisions are exact while dividend * divisor < 2^32
-  const int64_t pmax = (int64_t)a.mtiles * a.MT;  // pixel numbers the staging loop divides
+  // (pixel numbers, which are divided where the stride is not 1; at stride 1 a line: larger layers go on to the kernels after)
+  const int64_t pmax = (int64_t)a.mtiles * a.MT;
   if (pmax * std::max(a.MN, a.N) >= (1ll << 32) || (int64_t)a.per_xcd * 8 * a.nsplit >= (1ll << 32) ||
       xbytes * pitch >= (1ll << 32) || (int64_t)a.per_xcd * 8 >= (1ll << 31))
     return BSP_ERR_UNSUPPORTED;

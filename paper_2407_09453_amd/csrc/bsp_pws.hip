@@ -484,9 +484,9 @@ int launch_pws(const ConvParams& p, int dtype, const void* plan_host, int shift,
   a.N = p.N;
   a.MN = p.M * p.N;
   a.pair = hdr[BSP_PLAN_BO_W] != 4;
-  // multiply-high divisions are exact while dividend * divisor < 2^32
+  // multiply-high divisions are exact while dividend * divisor < 2^32 (at stride 1 no pixel number is divided)
   const int64_t pieces = (int64_t)QL * threads, outs = (int64_t)SW * threads;
-  if ((int64_t)p.P * std::max(a.MN, a.N) >= (1ll << 32) || (int64_t)a.groups * a.nsplit * a.nsplit >= (1ll << 32) || ((int64_t)a.tiles + 2 * a.groups) * MT >= (1ll << 30) ||
+  if ((a.S > 1 && (int64_t)p.P * std::max(a.MN, a.N) >= (1ll << 32)) || (int64_t)a.groups * a.nsplit * a.nsplit >= (1ll << 32) || ((int64_t)a.tiles + 2 * a.groups) * MT >= (1ll << 30) ||
       pieces * a.cpx >= (1ll << 32) || outs * NS * 2 >= (1ll << 32))
     return BSP_ERR_UNSUPPORTED;
   a.d_mn = make_fastdiv((uint32_t)a.MN);

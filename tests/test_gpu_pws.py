@@ -6,7 +6,7 @@ import pytest
 
 import paper_2407_09453_amd as bsp
 
-from gpu_util import kernels_of
+from gpu_util import conv_fp64, kernels_of
 
 pytestmark = pytest.mark.gpu
 
@@ -102,3 +102,35 @@ def test_i8(n):
     X[0, 0, :16] = 127               # the largest sums
     X[0, 1, :16] = -128
     _same(layer, lambda y: layer.conv2d(X, (1, 1), (0, 0), shift=shift, out=y), layer.out_shape(B, L, J, (1, 1), (0, 0)), torch.int8, torch.int8)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "i8"])
+@pytest.mark.parametrize("B,L,J", [(1, 300, 300), (3, 211, 210)])
+def test_pixels_times_an_images_pixels_past_32_bits(dtype, B, L, J):
+    """No pixel number is divided at stride 1: the kernel takes such layers, every pixel right."""
+    import torch
+    I, O = 64, 128
+    print("large images", dtype, B, L, J, flush=True)
+    rng = np.random.default_rng(O)
+    gamma = _mask(O, O, I, 8, 8, 0.5)
+    keep = torch.from_numpy(np.kron(gamma, np.ones((8, 8), np.uint8))).cuda()
+    shape = (B, L, J, O)
+    if dtype == "bf16":
+        W = torch.from_numpy(rng.standard_normal((O, 1, 1, I), dtype=np.float32)).bfloat16().cuda()
+        X = torch.from_numpy(rng.standard_normal((B, L, J, I), dtype=np.float32)).bfloat16().cuda()
+        layer = bsp.BspLayer(W.float().cpu().numpy(), gamma, 8, 8, "bf16")
+        out = torch.full(shape, float("nan"), dtype=torch.bfloat16, device="cuda")
+        ran = kernels_of(lambda: layer.conv2d(X, (1, 1), (0, 0), out=out))
+    else:
+        W = torch.from_numpy(rng.integers(-127, 128, (O, 1, 1, I), dtype=np.int8)).cuda()
+        X = torch.from_numpy(rng.integers(-128, 128, (B, L, J, I), dtype=np.int8)).cuda()
+        layer = bsp.BspLayerI8(W.cpu().numpy(), gamma, 8, 8)
+        out = torch.full(shape, 77, dtype=torch.int8, device="cuda")
+        ran = kernels_of(lambda: layer.conv2d(X, (1, 1), (0, 0), shift=9, out=out))
+    assert any("conv_pws<" in k for k in ran), ran
+    want = conv_fp64(X, W * keep[:, None, None, :], 1, (0, 0))
+    if dtype == "i8":  # (whole numbers below 2^53: exact)
+        assert bool((out.double() == torch.floor(want / 512 + 0.5).clamp(-128, 127)).all())
+        return
+    scale = torch.maximum(want.abs(), want.pow(2).mean().sqrt())
+    assert bool(((out.double() - want).abs() <= 6e-3 * scale).all())  # one rounding to bf16 is 3.9e-3 at most
