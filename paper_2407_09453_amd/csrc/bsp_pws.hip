@@ -69,6 +69,9 @@ template <int KIND, int PT, int SW, int D, int QL, bool RES>
 __global__ __launch_bounds__(1024) void conv_pws(PwsArgs a) {
   constexpr int MT = 16 * PT;  // pixels of a tile
   constexpr bool CW4 = KIND == 4, I8 = KIND == 16;
+  // Strips of many 4-channel units: the places of two steps a word, in units (one byte each), or 16x4 layers of 13 to 16 steps
+  // with a residual spill (512->64 on 65536 pixels 27.8 us instead of 22.8, the pointwise kernel 26.6).
+  constexpr bool BYTES = CW4 && D > 8;
   constexpr int eb = I8 ? 1 : 2;
   kernarg_touch<PwsArgs>();
   extern __shared__ __align__(16) unsigned char lds[];
@@ -82,23 +85,40 @@ __global__ __launch_bounds__(1024) void conv_pws(PwsArgs a) {
   if (first >= end) return;
   const int range0 = ns * a.NS * 16;  // the workgroup's strips cover the channels from here on
 
-  // ---- the pieces of input this lane brings for every tile
-  uint32_t lpj[QL], pcj[QL], ldj[QL];
+  // ---- the pieces of input this lane brings for every tile: pixel, bytes in it, place in a buffer; four of them in a word
+  // each, pixel and place in pieces, decoded anew for every tile (registers held for them would spill)
+  constexpr bool WORDS = QL == 4;
+  uint32_t lpj[QL], pcj[WORDS ? 1 : QL], ldj[WORDS ? 1 : QL];
 #pragma unroll
   for (int j = 0; j < QL; ++j) {
     const uint32_t idx = (uint32_t)(tid + j * nthr);
     const uint32_t lp = fdiv(idx, a.d_cpx), piece = idx - lp * (uint32_t)a.cpx;
-    lpj[j] = lp;
-    pcj[j] = piece * 16u;
-    ldj[j] = lp * (uint32_t)a.pitch + pcj[j];
+    if constexpr (WORDS) {
+      lpj[j] = lp << 16 | (lp * ((uint32_t)a.pitch >> 4) + piece);
+    } else {
+      lpj[j] = lp;
+      pcj[j] = piece * 16u;
+      ldj[j] = lp * (uint32_t)a.pitch + pcj[j];
+    }
   }
+  struct Piece {
+    uint32_t lp, at, lds;
+  };
+  auto piece_of = [&](int j) __attribute__((always_inline)) {
+    if constexpr (!WORDS) return Piece{lpj[j], pcj[j], ldj[j]};
+    uint32_t v = lpj[j];
+    asm volatile("" : "+v"(v));
+    const uint32_t lp = v >> 16, ld = (v & 0xFFFFu) << 4;
+    return Piece{lp, ld - (uint32_t)__mul24((int)lp, a.pitch), ld};
+  };
   constexpr int AHEAD = D <= 4 ? 2 : 1;  // tiles asked for before their turn
   u32x4_t xr[AHEAD][QL];
   auto load_x = [&](u32x4_t (&x)[QL], int tile) {
 #pragma unroll
     for (int j = 0; j < QL; ++j) {
+      const Piece o = piece_of(j);
       // past the last pixel: that one again (a valid address, never used)
-      const uint32_t p = min((uint32_t)tile * (uint32_t)MT + lpj[j], (uint32_t)(a.P - 1));
+      const uint32_t p = min((uint32_t)tile * (uint32_t)MT + o.lp, (uint32_t)(a.P - 1));
       uint32_t ip = p;
       if (a.S > 1) {
         const uint32_t img = fdiv(p, a.d_mn), r2 = p - img * (uint32_t)a.MN;
@@ -106,13 +126,15 @@ __global__ __launch_bounds__(1024) void conv_pws(PwsArgs a) {
         ip = (img * (uint32_t)a.L + oy * (uint32_t)a.S) * (uint32_t)a.J + ox * (uint32_t)a.S;
       }
       asm volatile("" : "+v"(ip));  // one load after the branch, not one in either: the waits count them
-      x[j] = *(const u32x4_t*)(a.X + (ip * (uint32_t)a.cpx * 16u + pcj[j]));
+      x[j] = *(const u32x4_t*)(a.X + (ip * (uint32_t)a.cpx * 16u + o.at));
     }
   };
   auto write_x = [&](const u32x4_t (&x)[QL], uint32_t off) {
 #pragma unroll
-    for (int j = 0; j < QL; ++j)
-      if (lpj[j] < (uint32_t)MT) *(u32x4_t*)(lds + off + ldj[j]) = x[j];
+    for (int j = 0; j < QL; ++j) {
+      const Piece o = piece_of(j);
+      if (o.lp < (uint32_t)MT) *(u32x4_t*)(lds + off + o.lds) = x[j];
+    }
   };
   load_x(xr[0], first);
   if constexpr (AHEAD == 2) load_x(xr[AHEAD - 1], first + a.groups);
@@ -123,7 +145,7 @@ __global__ __launch_bounds__(1024) void conv_pws(PwsArgs a) {
   // behind each pixel of an image.
   using acc_t = typename std::conditional<I8, i32x4_t, f32x4_t>::type;
   u32x4_t w[SW][D];
-  uint32_t un[SW][CW4 ? D : (D + 1) / 2];
+  uint32_t un[SW][CW4 && !BYTES ? D : (D + 1) / 2];
   uint32_t img[SW], bch[SW];
   int nst[SW];
   i32x4_t cin[I8 ? SW : 1];
@@ -156,7 +178,9 @@ __global__ __launch_bounds__(1024) void conv_pws(PwsArgs a) {
       const uint32_t dv = *(const uint32_t*)(a.rdesc + (cs * 16u + (uint32_t)g * 4u));
       if (d >= n) w[s][d] = u32x4_t{0, 0, 0, 0};
       const uint32_t u0 = d < n ? (dv & 0xFFu) * (CW4 ? 8u : 16u) : none, u1 = d < n ? ((dv >> 16) & 0xFFu) * 8u : none;
-      if constexpr (CW4)
+      if constexpr (BYTES)
+        un[s][d / 2] = (d & 1 ? un[s][d / 2] : 0u) | ((dv & 0xFFu) | (dv >> 16 & 0xFFu) << 8) << (d & 1 ? 16 : 0);
+      else if constexpr (CW4)
         un[s][d] = u0 | u1 << 16;
       else if (d & 1)
         un[s][d / 2] |= u0 << 16;
@@ -224,13 +248,20 @@ __global__ __launch_bounds__(1024) void conv_pws(PwsArgs a) {
     auto read = [&](int s, int d) {
       u32x4_t (&fr)[PT] = f[(s * D + d) & 1];
       // decoded anew for every tile: kept across them, the steps' addresses would take the registers of the weights
-      uint32_t& u = un[s][CW4 ? d : d / 2];
+      uint32_t& u = un[s][CW4 && !BYTES ? d : d / 2];
       asm volatile("" : "+v"(u));
       if constexpr (CW4) {
+        uint32_t o0 = u & 0xFFFFu, o1 = u >> 16;
+        if constexpr (BYTES) {
+          const uint32_t v = d & 1 ? u >> 16 : u;
+          o0 = (v & 0xFFu) * 8u;
+          o1 = (v >> 8 & 0xFFu) * 8u;
+          if (d < U && d >= nst[s]) o0 = o1 = none;
+        }
 #pragma unroll
         for (int t = 0; t < PT; ++t) {
-          const u32x2_t x0 = *(const u32x2_t*)(lds + (t ? b1 : b0) + (u & 0xFFFFu));
-          const u32x2_t x1 = *(const u32x2_t*)(lds + (t ? b1 : b0) + (u >> 16));
+          const u32x2_t x0 = *(const u32x2_t*)(lds + (t ? b1 : b0) + o0);
+          const u32x2_t x1 = *(const u32x2_t*)(lds + (t ? b1 : b0) + o1);
           fr[t] = u32x4_t{x0.x, x0.y, x1.x, x1.y};
         }
       } else {

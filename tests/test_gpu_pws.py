@@ -28,6 +28,8 @@ BF16 = [
     (3, 89, 87, 512, 128, 1, (16, 4), 1.0, False, True),     # sixteen steps
     (2, 101, 99, 504, 264, 1, (8, 8), 1.0, True, False),
     (17, 64, 64, 256, 32, 1, (8, 8), 0.75, False, False),     # two strips on eight waves
+    (2, 101, 99, 1024, 256, 1, (16, 4), 0.4, True, True),    # units to 255, sixteen waves with two loads a lane
+    (2, 101, 99, 1024, 256, 1, (16, 4), 0.4, False, False),
 ]
 
 
@@ -134,3 +136,47 @@ def test_pixels_times_an_images_pixels_past_32_bits(dtype, B, L, J):
         return
     scale = torch.maximum(want.abs(), want.pow(2).mean().sqrt())
     assert bool(((out.double() - want).abs() <= 6e-3 * scale).all())  # one rounding to bf16 is 3.9e-3 at most
+
+
+def _instances():
+    """Kind, most steps, loads a lane and residual of every instance, and a layer that runs on it: its strips and the
+    16-byte pieces of its pixels."""
+    cases = []
+    for kind in (8, 4, 16):
+        for D in (1, 2, 4, 6, 8) if kind == 16 else (2, 4, 6, 8, 12, 16):
+            for QL in (1, 2) if D > 8 else (1, 2, 4):
+                strips, waves = (8, 4) if D == 1 else (8, 8)
+                pieces = QL * 64 * waves // (32 if D <= 8 else 16)
+                if pieces < 4 * D:  # sixteen waves bring more
+                    strips, pieces = 9, 2 * pieces
+                cases += [(kind, D, QL, res, strips, max(pieces - 1, 4 * D)) for res in ((False,) if kind == 16 else (False, True))]
+    return cases
+
+
+@pytest.mark.parametrize("kind,D,QL,residual,strips,pieces", _instances())
+def test_every_instance(kind, D, QL, residual, strips, pieces):
+    import torch
+    print("pws instance", kind, D, QL, residual, strips, pieces, flush=True)
+    bo, bi = (16, 4) if kind == 4 else (8, 8)
+    I, O = pieces * (16 if kind == 16 else 8), strips * 16
+    rng = np.random.default_rng(D)
+    units, step = (2 * pieces, 8) if kind == 4 else (pieces, 4)   # of the contraction: in all, in a step
+    gamma = np.zeros((O // bo, I // bi), np.uint8)
+    gamma[:, rng.permutation(units)[:D * step - 1] * (2 if kind == 16 else 1)] = 1  # every strip has the same, in D steps
+    B, L, J = 1, 300 if kind == 16 and D <= 2 else 200, 181
+    gen = torch.Generator("cuda").manual_seed(D)
+    if kind == 16:
+        layer = bsp.BspLayerI8(rng.integers(-127, 128, (O, 1, 1, I), dtype=np.int8), gamma, bo, bi, bias=rng.integers(-5000, 5001, O).astype(np.int32))
+        X = torch.randint(-128, 128, (B, L, J, I), generator=gen, device="cuda", dtype=torch.int8)
+        call, dtype, bits = (lambda y: layer.conv2d(X, (1, 1), (0, 0), shift=9, out=y)), torch.int8, torch.int8
+    else:
+        layer = bsp.BspLayer(torch.randn(O, 1, 1, I, generator=gen, device="cuda").bfloat16().float().cpu().numpy(), gamma, bo, bi, "bf16",
+                             bias=rng.standard_normal(O).astype(np.float32))
+        X = torch.randn(B, L, J, I, generator=gen, device="cuda").bfloat16()
+        R = torch.randn(B, L, J, O, generator=gen, device="cuda").bfloat16() if residual else None
+        call, dtype, bits = (lambda y: layer.conv2d(X, (1, 1), (0, 0), out=y, residual=R, relu=True)), torch.bfloat16, torch.int16
+    name = "conv_pws<%d, %d, %d, %d, %d, %s>" % (kind, 2 if D <= 8 else 1, 2 if D == 1 else 1, D, QL, str(residual).lower())
+    out = torch.empty((B, L, J, O), dtype=dtype, device="cuda")
+    ran = kernels_of(lambda: call(out))
+    assert any(name in k for k in ran), (name, ran)
+    _same(layer, call, (B, L, J, O), dtype, bits)
