@@ -463,12 +463,13 @@ int launch_pws(const ConvParams& p, int dtype, const void* plan_host, int shift,
       if (c < best) best = c, NW = nw;
     }
   }
-  int NS = std::min(nstrips, NW * SW), wgs = 256 * 16 / NW;
+  int NS = std::min(nstrips, NW * SW);
 #ifdef BSP_ROWS_TUNE  // experiments only: never defined in the product build
+  int tuned = 0;
   if (const char* e = std::getenv("BSP_PWS_TUNE")) {
     int q[5];
     if (std::atoi(e) == 0) return BSP_ERR_UNSUPPORTED;
-    if (sscanf(e, "%d,%d,%d,%d,%d", q, q + 1, q + 2, q + 3, q + 4) == 5) NW = q[0], SW = q[1], NS = std::min(q[2], nstrips), wgs = q[3], PT = q[4];
+    if (sscanf(e, "%d,%d,%d,%d,%d", q, q + 1, q + 2, q + 3, q + 4) == 5) NW = q[0], SW = q[1], NS = std::min(q[2], nstrips), tuned = q[3], PT = q[4];
   }
 #endif
   if (NS < nstrips) NS &= ~3;  // whole windows of output channels
@@ -479,6 +480,17 @@ int launch_pws(const ConvParams& p, int dtype, const void* plan_host, int shift,
   int QL = cdiv((int64_t)MT * a.cpx, threads);
   QL = QL == 3 ? 4 : QL;
   if (QL > 4) return BSP_ERR_UNSUPPORTED;
+  a.slot = MT * a.pitch;
+  a.opitch = NS * 16 * eb + 16;
+  a.out_off = 2 * a.slot;
+  a.oslot = MT * a.opitch;
+  a.bias_off = a.out_off + 2 * a.oslot;
+  const int64_t ldsb = a.bias_off + (int64_t)NS * 64;
+  if (ldsb > kLdsLimit) return BSP_ERR_UNSUPPORTED;
+  int wgs = bsp_pws_held(NW, ldsb);
+#ifdef BSP_ROWS_TUNE
+  if (tuned) wgs = tuned;
+#endif
   a.NS = NS;
   a.nsplit = cdiv(nstrips, NS);
   a.tiles = cdiv(p.P, MT);
@@ -487,14 +499,7 @@ int launch_pws(const ConvParams& p, int dtype, const void* plan_host, int shift,
 #ifdef BSP_ROWS_TUNE
   if (!std::getenv("BSP_PWS_TUNE"))
 #endif
-    if (!bsp_pws_beats(i8, nstrips, steps, p.residual != nullptr, (double)a.tiles * a.nsplit / wgs)) return BSP_ERR_UNSUPPORTED;
-  a.slot = MT * a.pitch;
-  a.opitch = NS * 16 * eb + 16;
-  a.out_off = 2 * a.slot;
-  a.oslot = MT * a.opitch;
-  a.bias_off = a.out_off + 2 * a.oslot;
-  const int64_t ldsb = a.bias_off + (int64_t)NS * 64;
-  if (ldsb > kLdsLimit) return BSP_ERR_UNSUPPORTED;
+    if (!bsp_pws_beats(i8, nstrips, steps, p.residual != nullptr, (double)a.tiles * a.nsplit / (256 * 16 / NW))) return BSP_ERR_UNSUPPORTED;
   const int32_t* sec = p.plan + hdr[BSP_PLAN_OFF_ROWS_W];
   a.X = (const unsigned char*)p.X;
   a.Y = (unsigned char*)p.Y;

@@ -136,6 +136,14 @@ inline bool bsp_pws_beats(bool i8, int64_t strips, int64_t steps, bool residual,
   return rounds > (strips <= 4 || (strips > 8 && steps > 8) ? 4 : strips > 8 && steps <= 2 ? (residual ? 7 : 3.2) : 2);
 }
 
+// The workgroups of that kernel that the chip holds (waves and bytes of LDS of each): 16 waves a CU, fewer where LDS is
+// short.  More than are held open twice: 512->128 at a tenth of the blocks (84480 bytes) on 42496 pixels 15.8 us instead of 14.8, on
+// 57344 19.3 instead of 17.5.  (The rounds above count 16 waves whatever the LDS.)
+inline int bsp_pws_held(int waves, int64_t lds) {
+  const int64_t fit = 160 * 1024 / lds;
+  return 256 * (int)(fit < 16 / waves ? fit : 16 / waves);
+}
+
 // 3x3 layers at stride 1 of at most 128 channels in: whether the kernel that streams bands past weights in registers takes
 // the layer from the band and LDS-resident kernels.  rounds: tiles for each workgroup the chip holds.  900 random layers
 // with cold data and with data in the caches, the other / here in us; below 4000 pixels 0.98 (long strips 0.64 to 0.9:

@@ -150,6 +150,12 @@ int main() {
   PWS(false, true, 16, 8, false, 2 * 14112 / 32 / 512.);                  // 7.0 / 7.3
   PWS(false, true, 4, 4, false, 100352 / 32 / 512.);                      // 256->64 8.9 / 9.7
   PWS(false, true, 16, 15, false, 100352 / 16 / 256.);
+  // its workgroups that the chip holds
+  is(bsp_pws_held(8, 84480) == 256, true, "512 channels in, eight strips, tiles of 32 pixels");
+  is(bsp_pws_held(8, 81920) == 512, true, "half a CU's LDS");
+  is(bsp_pws_held(8, 81936) == 256, true, "more than half a CU's LDS");
+  is(bsp_pws_held(4, 14848) == 1024, true, "four waves");
+  is(bsp_pws_held(16, 51200) == 256, true, "sixteen waves");
   // int8: slabs, window, pixels, channels out, matrix instructions: LDS-resident / any-shape, us
   LDS8(true, 1, 1, 6272, 256, 6272);                                      // 6.4 / 5.0
   LDS8(false, 1, 1, 100352, 256, 100352);                                 // 21 / 31
