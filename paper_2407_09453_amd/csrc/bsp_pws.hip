@@ -71,7 +71,7 @@ __global__ __launch_bounds__(1024) void conv_pws(PwsArgs a) {
   constexpr bool CW4 = KIND == 4, I8 = KIND == 16;
   // Strips of many 4-channel units: the places of two steps a word, in units (one byte each), or 16x4 layers of 13 to 16 steps
   // with a residual spill (512->64 on 65536 pixels 27.8 us instead of 22.8, the pointwise kernel 26.6).
-  constexpr bool BYTES = CW4 && D > 8;
+  constexpr bool BYTES = CW4 && D == 16 && QL == 2;
   constexpr int eb = I8 ? 1 : 2;
   kernarg_touch<PwsArgs>();
   extern __shared__ __align__(16) unsigned char lds[];
@@ -85,9 +85,10 @@ __global__ __launch_bounds__(1024) void conv_pws(PwsArgs a) {
   if (first >= end) return;
   const int range0 = ns * a.NS * 16;  // the workgroup's strips cover the channels from here on
 
-  // ---- the pieces of input this lane brings for every tile: pixel, bytes in it, place in a buffer; four of them in a word
-  // each, pixel and place in pieces, decoded anew for every tile (registers held for them would spill)
-  constexpr bool WORDS = QL == 4;
+  // ---- the pieces of input this lane brings for every tile: pixel, bytes in it, place in a buffer.  Where registers held
+  // for four of them would spill, a word each of pixel and place in pieces, decoded anew for every tile (1008->128 on 57344
+  // pixels 16.2 us, spilled 16.9; where nothing spills the decoding costs up to 9 %).
+  constexpr bool WORDS = I8 && QL == 4 && (D == 8 || SW == 2);
   uint32_t lpj[QL], pcj[WORDS ? 1 : QL], ldj[WORDS ? 1 : QL];
 #pragma unroll
   for (int j = 0; j < QL; ++j) {
@@ -101,24 +102,18 @@ __global__ __launch_bounds__(1024) void conv_pws(PwsArgs a) {
       ldj[j] = lp * (uint32_t)a.pitch + pcj[j];
     }
   }
-  struct Piece {
-    uint32_t lp, at, lds;
-  };
-  auto piece_of = [&](int j) __attribute__((always_inline)) {
-    if constexpr (!WORDS) return Piece{lpj[j], pcj[j], ldj[j]};
-    uint32_t v = lpj[j];
-    asm volatile("" : "+v"(v));
-    const uint32_t lp = v >> 16, ld = (v & 0xFFFFu) << 4;
-    return Piece{lp, ld - (uint32_t)__mul24((int)lp, a.pitch), ld};
-  };
   constexpr int AHEAD = D <= 4 ? 2 : 1;  // tiles asked for before their turn
   u32x4_t xr[AHEAD][QL];
   auto load_x = [&](u32x4_t (&x)[QL], int tile) {
 #pragma unroll
     for (int j = 0; j < QL; ++j) {
-      const Piece o = piece_of(j);
+      uint32_t lp = lpj[j];
+      if constexpr (WORDS) {
+        asm volatile("" : "+v"(lp));
+        lp >>= 16;
+      }
       // past the last pixel: that one again (a valid address, never used)
-      const uint32_t p = min((uint32_t)tile * (uint32_t)MT + o.lp, (uint32_t)(a.P - 1));
+      const uint32_t p = min((uint32_t)tile * (uint32_t)MT + lp, (uint32_t)(a.P - 1));
       uint32_t ip = p;
       if (a.S > 1) {
         const uint32_t img = fdiv(p, a.d_mn), r2 = p - img * (uint32_t)a.MN;
@@ -126,14 +121,24 @@ __global__ __launch_bounds__(1024) void conv_pws(PwsArgs a) {
         ip = (img * (uint32_t)a.L + oy * (uint32_t)a.S) * (uint32_t)a.J + ox * (uint32_t)a.S;
       }
       asm volatile("" : "+v"(ip));  // one load after the branch, not one in either: the waits count them
-      x[j] = *(const u32x4_t*)(a.X + (ip * (uint32_t)a.cpx * 16u + o.at));
+      uint32_t at;
+      if constexpr (WORDS)
+        at = (lpj[j] & 0xFFFFu) * 16u - (uint32_t)__mul24((int)lp, a.pitch);
+      else
+        at = pcj[j];
+      x[j] = *(const u32x4_t*)(a.X + (ip * (uint32_t)a.cpx * 16u + at));
     }
   };
   auto write_x = [&](const u32x4_t (&x)[QL], uint32_t off) {
 #pragma unroll
     for (int j = 0; j < QL; ++j) {
-      const Piece o = piece_of(j);
-      if (o.lp < (uint32_t)MT) *(u32x4_t*)(lds + off + o.lds) = x[j];
+      if constexpr (WORDS) {
+        uint32_t v = lpj[j];
+        asm volatile("" : "+v"(v));
+        if (v < (uint32_t)MT << 16) *(u32x4_t*)(lds + off + (v & 0xFFFFu) * 16u) = x[j];
+      } else {
+        if (lpj[j] < (uint32_t)MT) *(u32x4_t*)(lds + off + ldj[j]) = x[j];
+      }
     }
   };
   load_x(xr[0], first);
