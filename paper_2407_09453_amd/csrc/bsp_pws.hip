@@ -452,13 +452,15 @@ int launch_pws(const ConvParams& p, int dtype, const void* plan_host, int shift,
   a.pitch = (a.cpx + (a.cpx & 1 ? 2 : 1)) * 16;  // room for a piece of zeros, and an odd number of pieces: no two pixels of a lane tile share banks
   // Waves and strips of a workgroup (8900 random layers, their data cold, each on eight combinations).  One strip a
   // wave; two pay only where a strip is over after one step of int8 codes and its results are the work (5 to 7 %).
-  // Workgroups of eight waves (of four where there is less to do: 9 %), of sixteen where strips are long (a tile
-  // staged once for twice the strips: 5 %), of four where eight would leave strips over (18 strips, eight at a time,
-  // cost as 24 do), which costs 15 to 30 %, more in int8, where results then are half lines.  16 waves a CU: the
-  // tiles asked for ahead do what more waves did (24: 2 to 25 % slower).
+  // Workgroups of eight waves, of sixteen where strips are long (a tile staged once for twice the strips: 5 %), of four
+  // where eight would leave strips over (18 strips, eight at a time, cost as 24 do), which costs 15 to 30 %, more in
+  // int8, where results then are half lines.  16 waves a CU: the tiles asked for ahead do what more waves did (24: 2 to
+  // 25 % slower).  Where the waves so chosen cannot bring a tile in four loads a lane (17 to 20 strips of up to four steps and
+  // more than 256 channels, more than 512 channels past eight strips of up to eight steps) the layer stays with the pointwise
+  // kernel: on eight or sixteen waves the former take 0.89 to 1.6 times as long there as here, the latter 1.0 to 1.7.
   int PT = steps <= 8 ? 2 : 1, SW = i8 && steps <= 1 && nstrips > 4 ? 2 : 1, NW = 8;
   if (nstrips <= 8) {
-    if (SW == 2 || (nstrips <= 4 && steps <= 2)) NW = 4;
+    if (SW == 2) NW = 4;  // (four strips of two steps: not taken, see bsp_pws_beats)
   } else {
     double best = 1e9;
     for (int nw = SW == 2 ? 4 : 8; nw; nw = SW == 2 ? (nw == 4 ? 8 : 0) : nw == 8 ? 16 : nw == 16 ? 4 : 0) {
