@@ -160,7 +160,7 @@ __global__ __launch_bounds__(T) void conv_bands(BandsArgs a) {
   auto out_at = [&](Tile t, int it) {
     const uint32_t base = (uint32_t)((t.n * a.M + t.y0 + 2 * it) * a.N + t.x0) * (uint32_t)(a.O * 2);
     const int left = min(a.M - t.y0, BR) - 2 * it;
-    return ((int)orow < left) & (t.x0 + (int)ocol < a.N) ? base + gofs : kNone;
+    return (((int)orow < left) & (t.x0 + (int)ocol < a.N)) ? base + gofs : kNone;
   };
   u32x4_t res[RES ? NIT : 1];
   auto load_res = [&](Tile t) {

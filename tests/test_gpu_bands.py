@@ -31,6 +31,8 @@ CASES = [
     (16, 56, 56, 8, 184, 1, (8, 8), 1.0, True, False, False),
     (8, 56, 56, 8, 256, 0, (4, 16), 1.0, False, False, False),   # no bias
     (64, 16, 16, 8, 256, 1, (8, 8), 1.0, False, False, True),
+    (12, 64, 100, 72, 104, 1, (8, 8), 0.25, False, False, True),
+    (19, 60, 61, 56, 40, 1, (8, 8), 0.25, False, False, False),  # three strips of few steps: a strip that drops the last unit
 ]
 
 
@@ -56,7 +58,10 @@ def test_bands(n):
         assert any(kernel in k for k in ran), ran
         return out
 
-    out = run(X, "conv_bands<")
+    rows = layer.plan[layer.plan[24]:]   # the plan's row-band section
+    steps = int(rows[11])
+    depth = 3 if steps <= 3 else 5 if steps <= 5 else 6
+    out = run(X, "conv_bands<%d, %d, %s>" % (depth, 1024 if depth == 3 else 768, str(residual).lower()))
     Xinf = X.clone()
     Xinf[B - 1, 0, 2] = float("inf")
     Xinf[B // 2, L // 2, 4, I - 1] = float("nan")
@@ -65,6 +70,19 @@ def test_bands(n):
     for b, y, x in ((B - 1, 0, 2), (B // 2, L // 2, 4)):
         far[b, max(0, y - 2 + pad):y + 1 + pad, max(0, x - 2 + pad):x + 1 + pad] = False
     assert bool((oinf.view(torch.int16) == out.view(torch.int16))[far].all())
+    if not relu:                         # (an activation hides them)
+        # a strip's rows share what one of them keeps: what keeps the last unit has the NaN, strips without it do not
+        keeps = torch.from_numpy(np.repeat(gamma[:, (I - 1) // bi], bo)[:O].astype(bool)).cuda()
+        strip = rows[rows[5]:rows[5] + 4 * rows[0]].reshape(-1, 4)
+        shares = torch.zeros(O, dtype=torch.bool, device="cuda")
+        for first in strip.tolist():
+            chans = [c + k for c in first if c >= 0 for k in range(4)]
+            shares[chans] = bool(keeps[chans].any())
+        hit = ~far
+        hit[B - 1] &= B - 1 == B // 2    # (the other image's pixel is infinite in every channel)
+        assert bool(oinf[hit][:, keeps].isnan().all()) and bool(torch.isfinite(oinf[hit][:, ~shares]).all())
+        everything = torch.from_numpy(np.repeat(gamma.any(1), bo)[:O].copy()).cuda()
+        assert not bool(torch.isfinite(oinf[B - 1][~far[B - 1]][:, everything]).any())
     if band:
         layer.struct.kernels = bsp.BSP_KERNEL_BAND
         assert bool((out.view(torch.int16) == run(X, "conv_band3<").view(torch.int16)).all())

@@ -25,6 +25,7 @@ static void is(bool got, bool want, const char* what) {
 #define PWFEW(want, ...) is(bsp_pw_few_beats(__VA_ARGS__), want, #__VA_ARGS__)
 #define PWFEW8(want, ...) is(bsp_pw_few_beats_i8(__VA_ARGS__), want, #__VA_ARGS__)
 #define PWS(want, ...) is(bsp_pws_beats(__VA_ARGS__), want, #__VA_ARGS__)
+#define BANDS(want, ...) is(bsp_bands_beats(__VA_ARGS__), want, #__VA_ARGS__)
 #define X3(want, ...) is(bsp_f32x3_beats(__VA_ARGS__), want, #__VA_ARGS__)
 #define F32(want, ...) is(bsp_f32_general(__VA_ARGS__), want, #__VA_ARGS__)
 int main() {
@@ -156,6 +157,28 @@ int main() {
   is(bsp_pws_held(8, 81936) == 256, true, "more than half a CU's LDS");
   is(bsp_pws_held(4, 14848) == 1024, true, "four waves");
   is(bsp_pws_held(16, 51200) == 256, true, "sixteen waves");
+  // 3x3 at stride 1: strips, steps, pixels, channels in, rounds: the band or LDS-resident kernel / streamed
+  BANDS(true, 2, 3, 16 * 147 * 147, 32, 2.89);                            // 27.2 / 14.4
+  BANDS(true, 2, 3, 2 * 147 * 147, 32, 0.36);                             // 8.4 / 6.1
+  BANDS(true, 4, 3, 16 * 147 * 147, 32, 5.78);                            // 29.6 / 19.1
+  BANDS(true, 12, 6, 16 * 71 * 71, 80, 5.6);                              // 28.2 / 23.2
+  BANDS(true, 12, 4, 4107, 48, 1);
+  BANDS(false, 12, 4, 4107, 48, 0.35);                                    // 7.0 / 7.7
+  BANDS(true, 12, 3, 4107, 48, 0.35);
+  BANDS(true, 4, 5, 16 * 224 * 224, 64, 16.3);                            // 66.7 / 51.0
+  BANDS(true, 8, 5, 16 * 112 * 112, 64, 12.3);                            // 31.2 / 29.5
+  BANDS(true, 8, 6, 100000, 64, 4);
+  BANDS(false, 8, 6, 100000, 64, 3.99);
+  BANDS(false, 6, 5, 16 * 35 * 35, 64, 1.69);                             // 7.4 / 7.6
+  BANDS(true, 4, 5, 4 * 56 * 56, 64, 0.29);                               // 5.9 / 5.2
+  BANDS(true, 4, 5, 16 * 56 * 56, 64, 1.17);                              // 8.5 / 7.7
+  BANDS(true, 4, 5, 32 * 48 * 48, 64, 1.5);                               // 8.9 / 8.3
+  BANDS(false, 4, 5, 24 * 56 * 56, 64, 1.75);                             // 9.0 / 9.4
+  BANDS(true, 4, 3, 24 * 56 * 56, 64, 1.75);
+  BANDS(true, 4, 5, 24 * 56 * 56, 56, 1.75);
+  BANDS(false, 8, 7, 6 * 56 * 56, 128, 1);                                // 11.1 / 11.9
+  BANDS(true, 2, 3, 4000, 32, 0.2);
+  BANDS(false, 2, 3, 3999, 32, 0.2);                                      // 0.98 and less
   // int8: slabs, window, pixels, channels out, matrix instructions: LDS-resident / any-shape, us
   LDS8(true, 1, 1, 6272, 256, 6272);                                      // 6.4 / 5.0
   LDS8(false, 1, 1, 100352, 256, 100352);                                 // 21 / 31
