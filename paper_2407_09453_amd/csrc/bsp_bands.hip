@@ -44,7 +44,7 @@ struct BandsArgs {
   int32_t pieces;               // of a patch
   int32_t ctiles, cw;           // column tiles and columns of a tile
   int32_t tiles, per_xcd, groups, tpi, nchunks;  // tiles, of an XCD; workgroups of an XCD that share them; of an image; of a band
-  int32_t slot, out_off, oslot, opitch, single, spill;
+  int32_t slot, out_off, oslot, opitch, single, bias_off;
   FastDiv d_cpx, d_jp, d_tpi, d_nchunks, d_cpp, d_ns;
 };
 
@@ -71,16 +71,15 @@ __global__ __launch_bounds__(T) void conv_bands(BandsArgs a) {
 
   // ---- the pieces of input this lane brings for every tile
   uint32_t xofs[QL], xrc[QL], xlds[QL];  // offset from the patch's first pixel; row | column << 16; place in LDS
-  const uint32_t mine = (uint32_t)(a.spill + lane * 16);
 #pragma unroll
   for (int j = 0; j < QL; ++j) {
     const uint32_t idx = (uint32_t)(tid + j * nthr);
-    const bool some = idx < (uint32_t)a.pieces;
+    const bool some = bsp_bands_some((int)idx, a.pieces);
     const uint32_t px = fdiv(idx, a.d_cpx), piece = idx - px * (uint32_t)a.cpx;
     const uint32_t row = fdiv(px, a.d_jp), col = px - row * a.d_jp.d;
     xofs[j] = some ? (row * (uint32_t)a.J + col) * (uint32_t)(a.cpx * 16) + piece * 16u : 0u;
     xrc[j] = some ? row | col << 16 : 0x7FFFu;
-    xlds[j] = some ? row * (uint32_t)a.rowpitch + col * (uint32_t)a.pitch + piece * 16u : mine;
+    xlds[j] = some ? row * (uint32_t)a.rowpitch + col * (uint32_t)a.pitch + piece * 16u : 0u;
   }
   struct Tile {
     int n, y0, x0;
@@ -115,7 +114,8 @@ __global__ __launch_bounds__(T) void conv_bands(BandsArgs a) {
   };
   auto write_x = [&](uint32_t off) {
 #pragma unroll
-    for (int j = 0; j < QL; ++j) *(i32x4_t*)(lds + bsp_bands_place(xlds[j], off, mine)) = xr[j];
+    for (int j = 0; j < QL; ++j)
+      if (bsp_bands_some(tid + j * nthr, a.pieces)) *(i32x4_t*)(lds + off + xlds[j]) = xr[j];
   };
   Tile at = locate(first);
   load_x(at, true);
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(T) void conv_bands(BandsArgs a) {
     else
       ad[d / 2] = v;
   }
-  const uint32_t bias_at = bsp_bands_bias((uint32_t)a.spill, (uint32_t)wave, (uint32_t)g);
+  const uint32_t bias_at = bsp_bands_bias((uint32_t)a.bias_off, (uint32_t)wave, (uint32_t)g);
   if (c < 4) *(float*)(lds + bias_at + c * 4) = a.bias && chan >= 0 ? a.bias[chan + c] : 0.f;
   const uint32_t img = (uint32_t)(a.out_off + (ct * 16 + c) * a.opitch + (chan >= 0 ? chan * 2 : a.O * 2));
 
@@ -310,7 +310,7 @@ int bsp_launch_bands(const ConvParams& p, const void* plan_host, hipStream_t st)
   a.oslot = m.oslot;
   a.opitch = m.opitch;
   a.single = m.single;
-  a.spill = m.spill;
+  a.bias_off = m.bias;
   a.tpi = cdiv(p.M, BR) * a.nchunks;
   const int64_t tiles = (int64_t)p.B * a.tpi;
   if (tiles >= (1ll << 30) || tiles * std::max(a.tpi, a.nchunks) >= (1ll << 32) || (int64_t)QL * threads * std::max(a.cpx, Jp) >= (1ll << 32) ||

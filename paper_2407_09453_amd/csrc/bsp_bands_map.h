@@ -1,6 +1,5 @@
 // Where the kernel that streams bands past weights in registers (bsp_bands.hip) keeps what in LDS (library private; plain
-// C++, also compiled on the host by the tests): patches of the input, images of the output, a spill area for lanes
-// that have no piece of a patch to bring, biases.
+// C++, also compiled on the host by the tests): patches of the input, images of the output, biases.
 #ifndef BSP_BANDS_MAP_H
 #define BSP_BANDS_MAP_H
 
@@ -8,7 +7,6 @@
 
 constexpr int kBandsRows = 4;        // output rows of a tile
 constexpr int kBandsPieces = 4;      // pieces of input a lane brings for a tile
-constexpr int kBandsSpill = 1024;    // bytes: sixteen for each lane
 constexpr int kBandsLds = 160 * 1024;
 
 struct BandsMap {
@@ -17,7 +15,7 @@ struct BandsMap {
   int32_t cpx, pitch, rowpitch, pieces;  // 16-byte pieces of a pixel; LDS bytes of a staged one and of a staged row; pieces of a patch
   int32_t patch, opitch, image;      // LDS bytes of a patch, of a pixel of an image, of an image
   int32_t single, resident;          // one patch and one image instead of two; workgroups that a CU holds
-  int32_t slot, out_off, oslot, spill, lds;
+  int32_t slot, out_off, oslot, bias, lds;
 };
 
 // I, N, O: channels in, output columns, channels out.  False: a layer that the kernel does not hold.
@@ -44,7 +42,7 @@ constexpr bool bsp_bands_map(int I, int N, int O, int nstrips, int steps, BandsM
   // barrier, where a CU then holds more workgroups
   m->patch = (kBandsRows + 2) * m->rowpitch;
   m->image = kBandsRows * m->cw * m->opitch;
-  const int fixed = kBandsSpill + m->waves * 64;
+  const int fixed = m->waves * 64;
   auto resident = [&](int sets) { return least(held, kBandsLds / (sets * (m->patch + m->image) + fixed)); };
   m->single = resident(1) > resident(2);
   const int sets = m->single ? 1 : 2;
@@ -53,16 +51,15 @@ constexpr bool bsp_bands_map(int I, int N, int O, int nstrips, int steps, BandsM
   m->slot = m->single ? 0 : m->patch;
   m->out_off = sets * m->patch;
   m->oslot = m->single ? 0 : m->image;
-  m->spill = sets * (m->patch + m->image);
-  m->lds = m->spill + fixed;
+  m->bias = sets * (m->patch + m->image);
+  m->lds = m->bias + fixed;
   return true;
 }
 
-// Where a lane writes a piece that lies `at` bytes into a patch, for the patch that begins at `off`; a lane without one
-// has its own sixteen bytes of the spill area (`mine`) for `at`, which lie past all patches and belong to none.
-constexpr uint32_t bsp_bands_place(uint32_t at, uint32_t off, uint32_t mine) { return at + off < mine ? at + off : mine; }
+// The pieces that a lane brings: only the first `pieces` of the workgroup's are some, the others are not written.
+constexpr bool bsp_bands_some(int index, int pieces) { return index < pieces; }
 
 // Where a wave's four lane groups keep four biases each.
-constexpr uint32_t bsp_bands_bias(uint32_t spill, uint32_t wave, uint32_t group) { return spill + kBandsSpill + (wave * 4 + group) * 16; }
+constexpr uint32_t bsp_bands_bias(uint32_t bias, uint32_t wave, uint32_t group) { return bias + (wave * 4 + group) * 16; }
 
 #endif
