@@ -7,12 +7,14 @@
 // bounds turn what lies outside the image into zeros; the last tile's results leave as whole output lines; this
 // tile's products from LDS, a step's fragments read three patch rows ahead; results into an LDS image of the output; the
 // next tile's input to the other LDS buffer; one barrier.  Steps and their order are the band kernel's, so the
-// results are the same bits.
+// results are the same bits (the LDS-resident kernel's steps come in another order).  As in the band kernel, a strip's
+// rows share what one of them keeps: an infinity or NaN in a channel that a row drops reaches it through the strip's
+// other rows, and the first unit's through steps that are not full.
 //
-// What bounds it: memory and the products' reads, each about 45 us of 51 on 224x224x64 batch 16 (206 MB; matrix cores and
-// LDS 40 % busy).  The band kernel gives every tile a workgroup of its own, which walks launch, copy, weights,
-// products and results one after the other (66.7 us there); on 149x149x32 batch 16 the LDS-resident kernel took 27.2 and this
-// one takes 14.4.  Four rows rather than seven: a CU then holds twelve waves instead of eight (51 / 56 us), which is
+// What bounds it: memory, then the reads of the products (224x224x64 batch 16: 207 MB, 34 us at a copy's rate, in 48 to 51;
+// matrix cores busy 32 % of the cycles, LDS 34 %).  The band kernel gives every tile a workgroup of its own, which walks
+// launch, copy, weights, products and results one after the other (64 to 67 us there); on 149x149x32 batch 16 the
+// LDS-resident kernel took 27.2 and this one takes 14.4.  Four rows rather than seven: a CU then holds twelve waves instead of eight (51 / 56 us), which is
 // worth more than the halo rows; two tiles asked for ahead made no difference, a fragment read one row or five ahead
 // neither.  With a branch per step the compiler waits for every read, so there is straight code for every number of steps.
 #include "bsp_bands_map.h"

@@ -8,7 +8,7 @@
 // LDS image of the output; the next tile's input to the other LDS buffer; one barrier.  Both buffers and both images
 // are used in turn.  Steps, fragments and their order are the pointwise kernel's, so the results are the same bits.
 //
-// What bounds it: memory, at the rate of a copy of the same mix (data cold, pointwise / here: 64->256 with a residual at
+// What bounds it: memory, at the rate of a copy of the same mix (64->256 at 56x56 batch 32 66 MB in 11.7 us; data cold, pointwise / here: 64->256 with a residual at
 // 56x56 batch 32, 116 MB, 26.0 / 24.2 us; without 20.1 / 18.0; 256->128 there, 77 MB, 25.7 / 18.0), then LDS where strips
 // are long (512->256 at 28x28 21.0 / 16.1: a fragment read from LDS feeds one product), and the results' arithmetic in
 // int8 (64->256 13.4 / 9.2).  The pointwise kernel gives every tile a workgroup of its own, which walks launch, step

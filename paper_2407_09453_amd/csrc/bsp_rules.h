@@ -64,11 +64,11 @@ inline bool bsp_any_beats_bf16(BspRival rival, int bo, int H, int K, bool stride
 //     28x28x512 batch 16 52 / 40, 28x28x256->512 batch 16 27 / 24; 17x17x256->296 batch 4 10.4 / 12.7, 34x34x520->64
 //     batch 6 14.3 / 18.2.  At this line 1 of 120 taken layers is more than a tenth slower (0.85), and the
 //     geometric mean of the taken ones is 1.29 times faster.
-//   band kernel: never; its workgroups stage whole lines, 73x73x80->192 batch 16 26 / 36, 56x56x128->256 batch 16
-//     26.9 / 27.9 (76x76x112->208 batch 3 30 / 17 is an exception)
+//   band kernel: never; its workgroups stage whole lines, 73x73x80->192 batch 16 26 / 36 (bsp_bands_beats gives it to the
+//     kernel that streams bands), 56x56x128->256 batch 16 26.9 / 27.9 (76x76x112->208 batch 3 30 / 17 is an exception)
 //   LDS kernel (more strips than the band kernel has waves, 4-channel blocks, other widths): 104x104x72->344
-//     16x4 blocks batch 9 98 / 61, 52x52x72->432 batch 10 39 / 29; 33x33x64->448 16x4 batch 10 14.6 / 15.7 (thinner
-//     pixels or fewer strips: 149x149x32 batch 16 stays)
+//     16x4 blocks batch 9 98 / 61, 52x52x72->432 batch 10 39 / 29; 33x33x64->448 16x4 batch 10 14.6 / 15.7 (not
+//     thinner pixels or fewer strips, most of which the kernel that streams bands takes before either)
 //   Below 20 K matrix instructions a full chip's opening is longer than the layer.
 inline bool bsp_tall_beats(BspRival rival, int64_t mr, int64_t I, int64_t O, double cost, double rows_cost) {
   if (mr < 20000) return false;
@@ -147,7 +147,8 @@ inline int bsp_pws_held(int waves, int64_t lds) {
 // 3x3 layers at stride 1 of at most 128 channels in: whether the kernel that streams bands past weights in registers takes
 // the layer from the band and LDS-resident kernels.  rounds: tiles for each workgroup the chip holds.  900 random layers
 // with cold data and with data in the caches, the other / here in us; below 4000 pixels 0.98 (long strips 0.64 to 0.9:
-// every workgroup waits for all its weights before its first product).
+// every workgroup waits for all its weights before its first product).  Of 420 more, from 4000 pixels on, 145 are taken: 1.70
+// times faster cold, 1.68 in the caches, three of them 5 to 8 % slower.
 //   LDS kernel: 149x149x32 batch 16 27.2 / 14.4, 147x147x32->64 29.6 / 19.1, 97x83x72->104 batch 5 15.4 / 10.7
 //   band kernel, more than 8 strips: 73x73x80->192 batch 16 28.2 / 23.2, 83x83x64->144 batch 28 81 / 53, but 0.91 to 1.0
 //     below one round (37x37x48->184 batch 3 7.0 / 7.7)
@@ -166,7 +167,7 @@ inline bool bsp_bands_beats(int64_t strips, int64_t steps, int64_t P, int64_t I,
 // Several slabs: always for a window, 7x7x512 batch 32 15.2 / 11.5, 2x2 47x47x208->32 batch 61 21 / 14, 25x25x624->192
 // batch 29 41 / 35 (a few of many channels out go the other way, 28x28x512 batch 16 49 / 52, 3x1 73x73x192->160
 // batch 59 99 / 121, but their neighbours do not, 23x23x624->416 batch 37 102 / 73, 62x62x208->176 batch 45 57 /
-// 53).  Not narrow 1x1 layers of large images (65536 pixels and more, the pointwise kernel has the others):
+// 53).  Not narrow 1x1 layers of large images (pixels times an image's pixels past 2^32, the pointwise kernels have the others):
 // 600x600x640->16 57 / 95, ->32 58 / 69, ->48 62 / 62, 300x300x640->16 23 / 17.
 inline bool bsp_any_beats_lds_i8(int nslabs, int64_t HK, int64_t P, int64_t O, int64_t mm) {
   if (nslabs == 1) return mm <= 20000;
