@@ -6,15 +6,22 @@
 // 16 x 64-byte operand contiguous), so only chunks that some block of a strip keeps have steps.  A
 // chunk is 16 bytes of a pixel: eight bf16 channels or sixteen codes.
 //
-// What bounds it: on small layers the chain opening - patch - products - results, about 4 us with
-// the launch, which the split of a strip's steps over waves shortens; on large ones LDS (a step reads
-// 1 KB per matrix instruction, half the matrix rate at best) and, with few steps per tile, the same
+// What bounds it: on small layers the chain opening - patch - products - results, about 3.5 us with
+// the launch, which the split of a strip's steps over waves shortens; instructions count there (a wave issues one
+// per four clocks at best, its SIMD's second wave waits for the first, a taken branch is 28 clocks).  On large ones LDS (a
+// step reads 1 KB per matrix instruction, half the matrix rate at best) and, with few steps per tile, the same
 // chain times the tiles a CU works through, so what counts there is how many workgroups it holds:
 // every instance keeps to 128 registers (144 in the four-tile one: 1x1 28x28x128->512 int8 28 us
-// instead of 19).  Measured (general kernel / here): bf16 3x3 47x33x100->76 batch 3 36.9 / 7.1 us;
+// instead of 19).  Measured (general kernel / here): bf16 3x3 47x33x100->76 batch 3 36.9 / 5.9 us;
 // 3x3 14x14x300->300 batch 16 150 / 22; 5x5 100x90x37->50 batch 2 52 / 9.4; 1x1 14x14x1001->333 batch 8
 // 51 / 10.4; FC 32 x 1001 -> 999 28.6 / 5.4; int8 3x3 28x28x136->200 batch 8 28 / 8.2.  Which layers go
 // to the other kernels instead: bsp_rules.h.
+//
+// A wait for everything before the patch's barrier, results of at most 1 MiB straight from the accumulators, the
+// bias asked for in the opening, zeros for a slab's unused pairs in its last step only and a strip's own partial sums kept in
+// registers, together: 1x7 17x17x160 batch 16 8.1 -> 7.3 us, 5x5 35x35x48->64 12.4 -> 9.9, 3x3 14x14x256 batch 1 5.27 -> 5.03,
+// 7x7x512 6.92 -> 6.31.  Deeper rings for two and four tiles (eight and sixteen steps, one workgroup a CU) gave nothing:
+// 1x7 17x17x160 7.14 either way, int8 3x3 14x14x256 batch 32 8.8 with four and 9.1 with eight.
 #include "bsp_kept.h"
 #include "bsp_launch.h"
 #include "bsp_tile.h"
@@ -48,11 +55,12 @@ struct AnyArgs {
   int32_t nslabs, spst, nstages, slab_bytes;   // the plan's slabs, how many are staged at a time
   int32_t nstrips, NS, PG, ks, lpg, lks, nset; // strips per workgroup, pixel groups, waves that share a strip's steps; log2
   int32_t total, per_xcd;
-  int32_t opitch, stream;          // bytes per pixel of the output image; its pieces are whole output lines
+  int32_t opitch, stream, direct;  // bytes per pixel of the output image; its pieces are whole output lines; no image
   int32_t K, lbo;                  // log2 of the block rows' height (these and the two pointers: kept_only)
   const int32_t* plan;
   const unsigned char* payload;
-  FastDiv d_nset, d_tpc, d_nchunk, d_cw, d_tpw, d_ppp, d_opp;
+  FastDiv d_nset, d_tpc, d_nchunk, d_cw;
+  SmallDiv s_cw, s_tpw, s_ppp, s_opp;
 };
 
 template <int KIND>
@@ -123,10 +131,18 @@ __device__ __forceinline__ u32x4_t load_first(const unsigned char* p, int n) {
 
 template <int KIND>
 __device__ __forceinline__ f32x4_t bias4(const AnyArgs& a, int ch) {
-  uint32_t b[4];
+  u32x4_t b = {0u, 0u, 0u, 0u};
+  if (a.bias) {
+    const uint32_t* p = (const uint32_t*)a.bias + ch;
+    if (ch + 4 <= a.O) {
+      __builtin_memcpy(&b, p, 16);
+    } else {
 #pragma unroll
-  for (int r = 0; r < 4; ++r) b[r] = a.bias && ch + r < a.O ? ((const uint32_t*)a.bias)[ch + r] : 0u;
-  return __builtin_bit_cast(f32x4_t, u32x4_t{b[0], b[1], b[2], b[3]});
+      for (int r = 0; r < 3; ++r)
+        if (ch + r < a.O) b[r] = p[r];
+    }
+  }
+  return __builtin_bit_cast(f32x4_t, b);
 }
 
 // One (tile of PT * 16 * PG output pixels) x (NS strips) per workgroup.  A tile is consecutive
@@ -135,12 +151,14 @@ __device__ __forceinline__ f32x4_t bias4(const AnyArgs& a, int ch) {
 // LDS takes.  A staged pixel is an odd number of 16-byte pieces, so pixels of a matrix tile that lie in
 // one patch row read different banks; those of two rows can collide (bf16 3x3 47x33x100->76: 0.19 M of
 // 0.51 M LDS cycles).  Wave = (strip, pixel group, share of the strip's steps): a step's
-// weights come from the plan through a register ring of D, its activations from LDS one step ahead.
+// weights come from the plan through a register ring of D, its activations from LDS G steps ahead (one tile:
+// four, as each is one read and one product; 3x3 7x7x512 batch 1 6.9 -> 6.5 us with the ring of eight).
 template <int KIND, int PT, bool VEC>
 __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
   kernarg_touch<AnyArgs>();
   extern __shared__ __align__(16) unsigned char lds[];
-  constexpr int D = 4, ES = KIND == kI8 ? 1 : 2;
+    constexpr int ES = KIND == kI8 ? 1 : 2, U = 4;
+  constexpr int D = PT == 1 ? 8 : 4, G = PT == 1 ? (KIND == kI8 ? 2 : 4) : 1;  // the ring, and the steps whose activations are read together
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, jn = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nthreads = (int)blockDim.x;
@@ -154,7 +172,7 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
   const int p0 = (int)(tile - ic * (uint32_t)a.tpc) * px;
   const int img = (int)fdiv(ic, a.d_nchunk);
   const int col0 = (int)(ic - (uint32_t)img * (uint32_t)a.nchunk) * a.CW;
-  const int m0 = (int)fdiv((uint32_t)p0, a.d_cw);
+  const int m0 = (int)fdiv((uint32_t)p0, a.d_cw), rel0 = p0 - m0 * a.CW;  // the tile's first row, its first pixel there
   const int plast = min(p0 + px, a.M * a.CW) - 1;
   const int rows = ((int)fdiv((uint32_t)plast, a.d_cw) - m0) * a.lsh + a.H;  // staged rows
 
@@ -163,23 +181,55 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
   const bool active = si < a.NS && strip < a.nstrips;
   // the strip's step ranges, one slab boundary per lane
   const int tab = a.slab_ptr[(active ? strip : 0) * (a.nslabs + 1) + min(lane, a.nslabs)];
-
-  int base[PT];
-#pragma unroll
-  for (int t = 0; t < PT; ++t) {
-    const int p = min(p0 + (pg * PT + t) * 16 + jn, plast);
-    const int y = (int)fdiv((uint32_t)p, a.d_cw), x = p - y * a.CW;
-    base[t] = ((y - m0) * a.lsh * a.TPW + x * a.lsw) * a.pitch;
-  }
-  f32x4_t acc[PT];
-#pragma unroll
-  for (int t = 0; t < PT; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  f32x4_t bv;
 
   const int iy0 = m0 * a.sh - a.ph, ix0 = col0 * a.sw - a.pw;
   const int pieces = rows * a.TPW * a.ppp;
   const int rowb = a.I * ES;  // bytes of a pixel
   const unsigned char* xim = a.X + (int64_t)img * a.L * a.J * rowb;
   const int rowpitch = a.TPW * a.pitch;
+
+  // ---- staging: U 16-byte pieces per thread in flight
+  u32x4_t v[U];
+  int dst[U], off[U];
+  auto ask = [&](int f0, int c0) {  // f0: the wave's first piece, c0: first byte of a pixel that is staged
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      dst[u] = -1;
+      if (f0 + u * nthreads >= pieces) continue;
+      const int f = f0 + u * nthreads + lane;
+      const int pix = (int)sdiv((uint32_t)f, a.s_ppp), part = f - (int)__umul24(pix, a.ppp);
+      const int r = (int)sdiv((uint32_t)pix, a.s_tpw), x = pix - (int)__umul24(r, a.TPW);
+      const int iy = iy0 + (int)__umul24(r, a.gsh), ix = ix0 + (int)__umul24(x, a.gsw);
+      off[u] = c0 + part * 16;
+      if (f < pieces && off[u] < rowb) dst[u] = (int)__umul24(pix, a.pitch) + part * 16;
+      v[u] = u32x4_t{0u, 0u, 0u, 0u};
+      if (dst[u] >= 0 && (unsigned)iy < (unsigned)a.L && (unsigned)ix < (unsigned)a.J) {
+        const unsigned char* src = xim + (uint32_t)(iy * a.J + ix) * (uint32_t)rowb;
+        v[u] = VEC ? *(const u32x4_t*)(src + off[u]) : piece_ask(src, off[u], rowb);
+      }
+    }
+  };
+  auto place = [&] {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (!VEC) {
+        __builtin_amdgcn_sched_barrier(0);  // (one shift after the other: all at once take 40 registers)
+        v[u] = piece_place(v[u], off[u], rowb);
+      }
+      if (dst[u] >= 0) *(u32x4_t*)(lds + dst[u]) = v[u];
+    }
+  };
+  int base[PT];
+#pragma unroll
+  for (int t = 0; t < PT; ++t) {
+    const int p = min(rel0 + (pg * PT + t) * 16 + jn, plast - m0 * a.CW);
+    const int y = (int)sdiv((uint32_t)p, a.s_cw), x = p - (int)__umul24(y, a.CW);
+    base[t] = (int)__umul24(__umul24(__umul24(y, a.lsh), a.TPW) + __umul24(x, a.lsw), a.pitch);
+  }
+  f32x4_t acc[PT];
+#pragma unroll
+  for (int t = 0; t < PT; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   for (int stg = 0; stg < a.nstages; ++stg) {
     const int sl0 = stg * a.spst, sl1 = min(sl0 + a.spst, a.nslabs);
@@ -188,102 +238,97 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
 
     // ---- weights: a ring of D steps
     u32x4_t wr[D];
-    int dr[D], add[D], one[D];  // descriptors; where the step's slab lies in a staged pixel; is it its slab's first step
-    int fcs = slo + k, fsl = sl0, fadd = 0, fbeg = slo, fend = __builtin_amdgcn_readlane(tab, sl0 + 1);
+    int dr[D];  // descriptors
+    int fcs = slo + k;
     auto fetch = [&](int d) {
       const int cs = min(fcs, shi - 1);  // (past the end: the last step again, never used)
       fcs += a.ks;
-      while (cs >= fend) {
-        fadd += a.slab_bytes;
-        ++fsl;
-        fbeg = fend;
-        fend = __builtin_amdgcn_readlane(tab, fsl + 1);
-      }
       dr[d] = *(const int*)(a.xdesc + ((uint32_t)cs * 16u + (uint32_t)g * 4u));
       wr[d] = *(const u32x4_t*)(a.wfrag + ((uint32_t)cs * 1024u + (uint32_t)lane * 16u));
-      add[d] = fadd;
-      one[d] = cs == fbeg;
     };
-    if (n > 0) {  // their latency passes while the patch is staged
+    const int c0 = sl0 * a.slab_bytes;
 #pragma unroll
-      for (int d = 0; d < D; ++d) fetch(d);
-    }
-
-    // ---- stage: four 16-byte pieces per thread in flight
-    const int c0 = sl0 * a.slab_bytes;  // first byte of a pixel that is staged
+    for (int d = 0; d < D; ++d)
+      if (d < n) fetch(d);  // their latency passes while the patch is staged
+    if (stg == 0) bv = bias4<KIND>(a, active ? strip * BSP_STRIP + 4 * g : a.O);
     if (stg > 0) __syncthreads();
-    for (int f0 = tid; f0 < pieces; f0 += 4 * nthreads) {
-      u32x4_t v[4];
-      int dst[4], off[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int f = f0 + u * nthreads;
-        const int pix = (int)fdiv((uint32_t)f, a.d_ppp), part = f - pix * a.ppp;
-        const int r = (int)fdiv((uint32_t)pix, a.d_tpw), x = pix - r * a.TPW;
-        const int iy = iy0 + r * a.gsh, ix = ix0 + x * a.gsw;
-        off[u] = c0 + part * 16;
-        dst[u] = f < pieces && off[u] < rowb ? pix * a.pitch + part * 16 : -1;
-        v[u] = u32x4_t{0u, 0u, 0u, 0u};
-        if (dst[u] >= 0 && (unsigned)iy < (unsigned)a.L && (unsigned)ix < (unsigned)a.J) {
-          const unsigned char* src = xim + (uint32_t)(iy * a.J + ix) * (uint32_t)rowb;
-          v[u] = VEC ? *(const u32x4_t*)(src + off[u]) : piece_ask(src, off[u], rowb);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (!VEC) {
-          __builtin_amdgcn_sched_barrier(0);  // (one shift after the other: all at once take 40 registers)
-          v[u] = piece_place(v[u], off[u], rowb);
-        }
-        if (dst[u] >= 0) *(u32x4_t*)(lds + dst[u]) = v[u];
-      }
+    for (int f0 = wave * 64; f0 < pieces; f0 += U * nthreads) {
+      ask(f0, c0);
+      place();
     }
+    // (the weights asked for before the patch are there by now; the wait tells the compiler so, which otherwise
+    // waits for the whole ring at every step)
+    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
-    // ---- products
+    // ---- products.  Where the step read next lies in a staged pixel, the steps of its slab
+    int rcs = slo + k, rsl = sl0, radd = 0, rbeg = slo, rend = __builtin_amdgcn_readlane(tab, sl0 + 1);
     auto read = [&](int d, u32x4_t (&f)[PT]) {
+      const int cs = min(rcs, shi - 1);
+      rcs += a.ks;
+      while (cs >= rend) {
+        radd += a.slab_bytes;
+        ++rsl;
+        rbeg = rend;
+        rend = __builtin_amdgcn_readlane(tab, rsl + 1);
+      }
       uint32_t desc = (uint32_t)dr[d];
       asm volatile("" : "+v"(desc));  // decoded here, not where it is loaded: no early wait
-      const uint32_t o = ((desc & 0xFFFFu) << 4) + (uint32_t)add[d] + ((desc >> 16) & 0xFFu) * (uint32_t)rowpitch +
-                         (desc >> 24) * (uint32_t)a.pitch;
+      const uint32_t o = ((desc & 0xFFFFu) << 4) + (uint32_t)radd + __umul24((desc >> 16) & 0xFFu, rowpitch) +
+                         __umul24(desc >> 24, a.pitch);
 #pragma unroll
       for (int t = 0; t < PT; ++t) f[t] = *(const u32x4_t*)(lds + base[t] + o);
       if constexpr (KIND == kBf16) {
         // a pair that fills up a slab's last step multiplies zeros with zeros, not with whatever
         // (an infinity) lies at its descriptor's address
-        const bool real = desc != 0u || (g == 0 && one[d]);
+        if (cs == rend - 1) {
+          const bool real = desc != 0u || (g == 0 && cs == rbeg);
 #pragma unroll
-        for (int t = 0; t < PT; ++t) f[t] = real ? f[t] : u32x4_t{0u, 0u, 0u, 0u};
+          for (int t = 0; t < PT; ++t) f[t] = real ? f[t] : u32x4_t{0u, 0u, 0u, 0u};
+        }
       }
     };
     auto mfmas = [&](int d, const u32x4_t (&f)[PT]) {
 #pragma unroll
       for (int t = 0; t < PT; ++t) acc[t] = mma<KIND>(wr[d], f[t], acc[t]);
     };
-    u32x4_t fa[PT], fb[PT];
+    // (G steps' fragments are read ahead of the products of the G before them)
+    u32x4_t fa[G][PT], fb[G][PT];
+    auto reads = [&](int d, u32x4_t (&f)[G][PT], int left) {
+#pragma unroll
+      for (int j = 0; j < G; ++j)
+        if (j < left) read(d + j, f[j]);
+    };
+    auto products = [&](int d, const u32x4_t (&f)[G][PT], int left) {
+#pragma unroll
+      for (int j = 0; j < G; ++j)
+        if (j < left) mfmas(d + j, f[j]);
+    };
+    auto refill = [&](int d) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < G; ++j) fetch(d + j);
+      __builtin_amdgcn_sched_barrier(0);
+    };
     int i = 0;
-    if (n > 0) read(0, fa);
+    reads(0, fa, n);
     for (; i + D < n; i += D) {
 #pragma unroll
-      for (int d = 0; d < D; d += 2) {
-        read(d + 1, fb);
-        mfmas(d, fa);
-        __builtin_amdgcn_sched_barrier(0);
-        fetch(d);
-        __builtin_amdgcn_sched_barrier(0);
-        read((d + 2) % D, fa);
-        mfmas(d + 1, fb);
-        __builtin_amdgcn_sched_barrier(0);
-        fetch(d + 1);
-        __builtin_amdgcn_sched_barrier(0);
+      for (int d = 0; d < D; d += 2 * G) {
+        reads(d + G, fb, G);
+        products(d, fa, G);
+        refill(d);
+        reads((d + 2 * G) % D, fa, d + 2 * G < D ? G : n - i - D);
+        products(d + G, fb, G);
+        refill(d + G);
       }
     }
 #pragma unroll
-    for (int d = 0; d < D; d += 2) {
-      if (i + d + 1 < n) read(d + 1, fb);
-      if (i + d < n) mfmas(d, fa);
-      if (d + 2 < D && i + d + 2 < n) read(d + 2, fa);
-      if (i + d + 1 < n) mfmas(d + 1, fb);
+    for (int d = 0; d < D; d += 2 * G) {
+      reads(d + G, fb, n - i - d - G);
+      products(d, fa, n - i - d);
+      if (d + 2 * G < D) reads(d + 2 * G, fa, n - i - d - 2 * G);
+      products(d + G, fb, n - i - d - G);
     }
   }
 
@@ -293,7 +338,8 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
     __syncthreads();
     f32x4_t* red = (f32x4_t*)lds;  // [wave][PT][64]
 #pragma unroll
-    for (int t = 0; t < PT; ++t) red[(wave * PT + t) * 64 + lane] = acc[t];
+    for (int t = 0; t < PT; ++t)
+      if ((t & (a.ks - 1)) != k) red[(wave * PT + t) * 64 + lane] = acc[t];
     __syncthreads();
     const f32x4_t* first = red + (wave - k) * (PT * 64) + lane;
     // (all of a tile's sums are asked for at once: one after the other they took most of a
@@ -304,7 +350,7 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
         if ((t & (decltype(n)::value - 1)) != k) continue;
         f32x4_t v[decltype(n)::value];
 #pragma unroll
-        for (int s = 0; s < decltype(n)::value; ++s) v[s] = first[(s * PT + t) * 64];
+        for (int s = 0; s < decltype(n)::value; ++s) v[s] = s == k ? acc[t] : first[(s * PT + t) * 64];
 #pragma unroll
         for (int s = 1; s < decltype(n)::value; ++s) v[0] = add4<KIND>(v[0], v[s]);
         acc[t] = v[0];
@@ -317,60 +363,89 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
     else
       add_up(std::integral_constant<int, 2>{});
   }
-  __syncthreads();  // everybody is done with the patch (the partial sums)
-
-  // ---- results: bias and the one rounding (or the rescale), into an LDS image of the tile's
-  // output; then all waves copy that out, 16 contiguous bytes per lane, with the residual and ReLU
+  // ---- results: bias and the one rounding (or the rescale).  Small bf16 outputs leave from here, eight bytes per
+  // lane; the others go into an LDS image of the tile's output, and then all waves copy that out, 16 contiguous
+  // bytes per lane, with the residual and ReLU
   const int opitch = a.opitch;
+  int id = tid;
+  asm volatile("" : "+v"(id));  // (lane, column and group once more: no registers for them until here)
+  const int ln = id & 63, lg = ln >> 4, lj = ln & 15;
+  const int ch = strip * BSP_STRIP + 4 * lg;
+  u32x2_t out[PT];
+  uint32_t bad = 0;  // bit 15 or 31: a result that is not finite (an exponent of ones carries over)
+  auto not_finite = [](uint32_t pair) { return (pair & 0x7F807F80u) + 0x00800080u; };
+  if constexpr (KIND == kBf16) {
+#pragma unroll
+    for (int t = 0; t < PT; ++t) {
+      if ((t & (a.ks - 1)) != k) continue;
+      const f32x4_t v = acc[t] + bv;
+      out[t] = u32x2_t{pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)};
+      bad |= not_finite(out[t].x) | not_finite(out[t].y);
+    }
+    bad = active && __ballot(bad & 0x80008000u);
+  }
+  auto send = [&] {
+#pragma unroll
+    for (int t = 0; t < PT; ++t) {
+      if ((t & (a.ks - 1)) != k) continue;
+      const int i = (pg * PT + t) * 16 + lj, r = rel0 + i;
+      const int dy = (int)sdiv((uint32_t)r, a.s_cw), x = col0 + r - (int)__umul24(dy, a.CW);
+      if (p0 + i > plast || x >= a.N || ch >= a.O) continue;
+      const uint32_t o = (((uint32_t)img * (uint32_t)a.M + (uint32_t)(m0 + dy)) * (uint32_t)a.N + (uint32_t)x) * (uint32_t)a.O + (uint32_t)ch;
+      u32x2_t res = {0u, 0u};
+      if (a.residual) res = *(const u32x2_t*)(a.residual + o * 2u);
+      if (a.residual || a.relu) out[t] = post_bf16x4_reg(out[t], res, a.residual != nullptr, a.relu);
+      *(u32x2_t*)(a.Y + o * 2u) = out[t];
+    }
+  };
+  if (KIND == kBf16 && a.direct && active && !bad) send();
+  __syncthreads();  // everybody is done with the patch (the partial sums)
+  if (KIND == kBf16 && a.direct && !bad) return;
   if (active) {
-    int id = tid;
-    asm volatile("" : "+v"(id));  // (lane, column and group once more: no registers for them until here)
-    const int lane = id & 63, g = lane >> 4, jn = lane & 15;
-    const f32x4_t bv = bias4<KIND>(a, strip * BSP_STRIP + 4 * g);
+    unsigned char* ot = lds + (pg * PT * 16 + lj) * opitch;
     const RescaleI8 rescale(__builtin_bit_cast(i32x4_t, bv), KIND == kI8 ? a.shift : 0);
-    unsigned char* ot = lds + (pg * PT * 16 + jn) * opitch;
-    uint32_t bad = 0;  // bit 15 or 31: a result that is not finite (an exponent of ones carries over)
-    auto not_finite = [](uint32_t pair) { return (pair & 0x7F807F80u) + 0x00800080u; };
 #pragma unroll
     for (int t = 0; t < PT; ++t, ot += 16 * opitch) {
       if ((t & (a.ks - 1)) != k) continue;
-      const f32x4_t v = add4<KIND>(acc[t], bv);  // (int32 results)
-      const int c = si * BSP_STRIP + 4 * g;
-      if constexpr (KIND == kBf16) {
-        const u32x2_t b = {pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)};
-        *(u32x2_t*)(ot + c * 2) = b;
-        bad |= not_finite(b.x) | not_finite(b.y);
-      } else if (a.y32) {
-        *(f32x4_t*)(ot + c * 4) = v;
-      } else {
+      const int c = si * BSP_STRIP + 4 * lg;
+      if constexpr (KIND == kBf16)
+        *(u32x2_t*)(ot + c * 2) = out[t];
+      else if (a.y32)
+        *(f32x4_t*)(ot + c * 4) = add4<KIND>(acc[t], bv);
+      else
         *(uint32_t*)(ot + c) = rescale(__builtin_bit_cast(i32x4_t, acc[t]));
-      }
     }
     if constexpr (KIND == kBf16) {
-      if (__ballot(bad & 0x80008000u)) {
+      if (bad) {
         // (the arguments once more: what only this needs takes no scalar registers before)
         auto* again = (const __attribute__((address_space(4))) AnyArgs*)__builtin_amdgcn_kernarg_segment_ptr();
         asm volatile("" : "+s"(again));
         const AnyArgs& b = *(const AnyArgs*)again;
+        auto place = [&](int tile) { return (u32x2_t*)(lds + (tile * 16 + lj) * opitch + (si * BSP_STRIP + 4 * lg) * 2); };
 #pragma unroll 1
         for (int t = k; t < PT; t += b.ks) {
           const int tile = pg * PT + t;
-          auto place = [&] { return (u32x2_t*)(lds + (tile * 16 + jn) * opitch + (si * BSP_STRIP + 4 * g) * 2); };
-          if (!__ballot((not_finite(place()->x) | not_finite(place()->y)) & 0x80008000u)) continue;
-          const int p = min(p0 + tile * 16 + jn, plast);
+          if (!__ballot((not_finite(place(tile)->x) | not_finite(place(tile)->y)) & 0x80008000u)) continue;
+          const int p = min(p0 + tile * 16 + lj, plast);
           const int y = (int)fdiv((uint32_t)p, b.d_cw), x = col0 + p - y * b.CW;
-          const f32x4_t v = kept_only<VEC>(b, b.X + (int64_t)img * b.L * b.J * b.I * 2, strip, y * b.sh - b.ph, x * b.sw - b.pw, lane) +
-                            bias4<KIND>(b, strip * BSP_STRIP + 4 * g);
+          const f32x4_t v = kept_only<VEC>(b, b.X + (int64_t)img * b.L * b.J * b.I * 2, strip, y * b.sh - b.ph, x * b.sw - b.pw, ln) +
+                            bias4<KIND>(b, ch);
           asm volatile("" ::: "memory");  // (read again, not kept)
           auto take = [&](uint32_t was, uint32_t now) {  // those of the results that are not finite
             const uint32_t m = (not_finite(was) >> 15 & 0x00010001u) * 0xFFFFu;
             return (was & ~m) | (now & m);
           };
-          *place() = u32x2_t{take(place()->x, pack_bf16x2(v.x, v.y)), take(place()->y, pack_bf16x2(v.z, v.w))};
+          *place(tile) = u32x2_t{take(place(tile)->x, pack_bf16x2(v.x, v.y)), take(place(tile)->y, pack_bf16x2(v.z, v.w))};
+        }
+        if (a.direct) {
+#pragma unroll
+          for (int t = 0; t < PT; ++t) out[t] = *place(pg * PT + t);
+          send();
         }
       }
     }
   }
+  if (KIND == kBf16 && a.direct) return;
   __syncthreads();
   const int os = KIND == kBf16 ? 2 : a.y32 ? 4 : 1;  // bytes per result
   const int run = min(a.NS * BSP_STRIP, a.O - set * a.NS * BSP_STRIP) * os;  // a pixel's bytes here
@@ -378,8 +453,8 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
   const int npix = plast + 1 - p0;
   const int64_t ybase = ((int64_t)img * a.M * a.N) * a.O + set * a.NS * BSP_STRIP;
   for (int i = tid; i < npix * opp; i += nthreads) {
-    const int pix = (int)fdiv((uint32_t)i, a.d_opp), off = (i - pix * opp) * 16;
-    const int y = (int)fdiv((uint32_t)(p0 + pix), a.d_cw), x = col0 + p0 + pix - y * a.CW;
+    const int pix = (int)sdiv((uint32_t)i, a.s_opp), off = (i - pix * opp) * 16;
+    const int dy = (int)sdiv((uint32_t)(rel0 + pix), a.s_cw), y = m0 + dy, x = col0 + rel0 + pix - (int)__umul24(dy, a.CW);
     const int n = run - off;
     if (n <= 0 || x >= a.N) continue;
     const int64_t o = (ybase + ((int64_t)y * a.N + x) * a.O) * os + off;
@@ -588,25 +663,28 @@ int launch_kind(const ConvParams& p, const int32_t* hdr, int y32, int shift, hip
   if (total >= (1ll << 30)) return BSP_ERR_UNSUPPORTED;
   a.total = (int32_t)total;
   a.per_xcd = cdiv(total, 8);
-  // multiply-high divisions are exact while dividend * divisor < 2^32 (the staging loop runs up
-  // to four rounds of threads past the pieces, of which LDS holds at most 10240)
-  const int64_t over = 10240 + 4 * 512;
+  // multiply-high divisions are exact while dividend * divisor < 2^32; what lies in a tile or a patch (at most 10240
+  // pieces, 512 pixels) is divided and multiplied in 24 bits, input pixels per staged row or column too
   if ((total + 8) * a.nset >= (1ll << 32) || tiles * a.tpc >= (1ll << 32) ||
       (int64_t)B * a.nchunk * a.nchunk >= (1ll << 32) || (int64_t)a.tpc * px * a.CW >= (1ll << 32) ||
-      over * std::max(a.ppp, a.TPW) >= (1ll << 32) ||
-      ((int64_t)px * best.NS * os + 512) * best.NS * os >= (1ll << 32))
+      (a.gsh >= (1 << 24) && a.M > 1) || (a.gsw >= (1 << 24) && a.N > 1))
     return BSP_ERR_UNSUPPORTED;
   a.d_nset = make_fastdiv((uint32_t)a.nset);
   a.d_tpc = make_fastdiv((uint32_t)a.tpc);
   a.d_nchunk = make_fastdiv((uint32_t)a.nchunk);
   a.d_cw = make_fastdiv((uint32_t)a.CW);
-  a.d_tpw = make_fastdiv((uint32_t)a.TPW);
-  a.d_ppp = make_fastdiv((uint32_t)a.ppp);
-  a.d_opp = make_fastdiv((uint32_t)(best.NS * os));
+  a.s_cw = make_smalldiv((uint32_t)a.CW);
+  a.s_tpw = make_smalldiv((uint32_t)a.TPW);
+  a.s_ppp = make_smalldiv((uint32_t)a.ppp);
+  a.s_opp = make_smalldiv((uint32_t)(best.NS * os));
   a.opitch = best.NS * BSP_STRIP * os + 16;
   // whole 128-byte lines leave as streaming stores (nothing dirty is left for the kernel's end)
   a.stream = p.O * os % 16 == 0 && (reinterpret_cast<uintptr_t>(p.Y) & 15u) == 0 &&
              (best.NS >= a.nstrips ? flat || p.O * os >= 128 : p.O * os % 128 == 0 && best.NS * BSP_STRIP * os % 128 == 0);
+  // (of more results the whole lines are worth more than the barrier and the way through LDS: 5x5 35x35x48->64 batch 16, 2.5 MB,
+  // 9.80 us through the image, 10.05 without; 1.5 to 1.8 MB alike; 0.4 to 0.8 MB 0.25 us less without)
+  a.direct = KIND == kBf16 && p.O % 4 == 0 && ((reinterpret_cast<uintptr_t>(p.Y) | reinterpret_cast<uintptr_t>(p.residual)) & 7u) == 0 &&
+             (int64_t)p.P * p.O * 2 <= (1 << 20);
   const int threads = 64 * best.NS * best.PG * best.ks;
   switch (best.PT) {
     case 1: return launch_conv<KIND, 1>(a, vec, threads, (size_t)best.lds, st);

@@ -14,6 +14,8 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t x, FastDiv f) {
   return f.d == 1 ? x : q;
 }
 
+__device__ __forceinline__ uint32_t sdiv(uint32_t x, SmallDiv f) { return __umul24(x, f.mul) >> f.shift; }
+
 struct TileCfg {
   int32_t TH, TW;            // output tile, pixels
   int32_t TPH, TPW;          // staged input patch, pixels

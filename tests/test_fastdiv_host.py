@@ -61,6 +61,33 @@ def test_fastdiv_is_exact_inside_the_checked_range(tmp_path):
     assert known == 3                # x = 131069..131071 with d = 131072: x * d >= 2^32, all three wrong
 
 
+SMALL = r"""
+#include <cstdio>
+#include <cstdint>
+#include "bsp_fastdiv.h"
+int main() {
+  uint64_t wrong = 0, wide = 0;
+  for (uint32_t d = 1; d <= 32768; d = d < 600 ? d + 1 : d + d / 97 + 1) {
+    const SmallDiv f = make_smalldiv(d);
+    wide += f.mul >= (1u << 24) || f.shift > 31;
+    for (uint32_t x = 0; x < 32768; ++x) wrong += sdiv_host(x, f) != x / d;
+  }
+  const SmallDiv last = make_smalldiv(32768);
+  for (uint32_t x = 0; x < 32768; ++x) wrong += sdiv_host(x, last) != x / 32768;
+  printf("%llu %llu\n", (unsigned long long)wrong, (unsigned long long)wide);
+  return 0;
+}
+"""
+
+
+def test_small_division_is_exact_below_two_to_the_fifteen(tmp_path):
+    src = tmp_path / "sd.cpp"
+    src.write_text(SMALL)
+    exe = tmp_path / "sd"
+    subprocess.run(["g++", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "paper_2407_09453_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    assert subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split() == ["0", "0"]
+
+
 def test_launchers_state_the_condition():
     """Every source that builds a divider also bounds its dividends (a 2^32 comparison nearby)."""
     csrc = os.path.join(ROOT, "paper_2407_09453_amd", "csrc")

@@ -131,6 +131,43 @@ def test_infinities_reach_the_rows_that_keep_their_channel_and_no_others(bo, bi)
         assert_close(np.where(ok, y, 0.0), np.where(ok, want, 0.0), "bf16", f"case {n}")
 
 
+def _without(c, X):
+    """The oracle's results for what the first block row keeps: an input whose infinities are zeros."""
+    x = to_host(X)
+    return oracle.conv2d(np.where(np.isfinite(x), x, 0.0).astype(np.float32), c.W, c.bias, c.gamma, 8, 8, c.stride, c.pad)
+
+
+@pytest.mark.parametrize("B,L,J,I,O,H", [
+    (1, 64, 128, 20, 64, 3),   # 1 MiB of results: they leave straight from the accumulators
+    (1, 65, 128, 20, 64, 3),   # one row more: through the image of the output
+    (1, 9, 11, 20, 66, 3),     # few results, but a lane's four channels can end past the last one
+    (1, 7, 9, 64, 16, 3),      # 1 .. 4 and 16 to 17 steps a wave: either side of the rings' ends
+    (1, 5, 5, 512, 16, 3), (1, 8, 8, 1024, 36, 3), (2, 6, 6, 96, 64, 5), (4, 15, 15, 136, 24, 3),
+])
+def test_both_ways_out(B, L, J, I, O, H):
+    """Results with bias, residual and ReLU, and an infinity in a dropped block, on both ways out of the kernel."""
+    import torch
+    pad = (H // 2, H // 2)
+    c = draw_layer("t", B=B, L=L, J=J, I=I, O=O, H=H, K=H, stride=(1, 1), pad=pad, bo=8, bi=8, dtype="bf16", mask_kind="bernoulli", density=0.5,
+                   seed=9600 + I + L, b_std=0.5)
+    c.gamma[0, 1], c.gamma[1, 1] = 0, 1  # two rows of one strip: the second keeps what the first drops
+    layer, X = make_layer(c), to_device(c)
+    y0 = layer.conv2d(X, c.stride, c.pad)
+    R = torch.randn(y0.shape, device="cuda", generator=torch.Generator("cuda").manual_seed(I)).bfloat16()
+    y = layer.conv2d(X, c.stride, c.pad, residual=R, relu=True)
+    torch.cuda.synchronize()
+    assert_close(to_host(y0), oracle.conv2d(c.X, c.W, c.bias, c.gamma, 8, 8, c.stride, c.pad), "bf16")
+    assert torch.equal(y, torch.relu(y0.float() + R.float()).bfloat16())
+    X[0, 2, 3, 8:16] = float("inf")
+    z = layer.conv2d(X, c.stride, c.pad)
+    torch.cuda.synchronize()
+    assert_close(to_host(z[..., :8]), _without(c, X)[..., :8], "bf16")
+    assert not torch.isfinite(z[0, 2, 3, 8:16]).any()
+    far = torch.ones(z.shape[:3], dtype=torch.bool, device="cuda")
+    far[0, max(0, 2 - H // 2):3 + H // 2, max(0, 3 - H // 2):4 + H // 2] = False
+    assert torch.equal(z[far], y0[far])
+
+
 def test_calls_go_to_the_current_stream():
     import torch
     from paper_2407_09453_amd.binding import _current_stream
