@@ -119,32 +119,41 @@ __global__ __launch_bounds__(MAXT) void conv_pw(Args a) {
                  : "memory");
   }
 
-  // ---- stage the tile: request rq fills LDS bytes [rq * 1024, rq * 1024 + 1024)
+  // ---- stage the tile: request rq fills LDS bytes [rq * 1024, rq * 1024 + 1024).  No lane is masked: a pixel past
+  // the layer's last asks for the last one's bytes, a piece past a pixel's channels for the pixel's last piece (no
+  // descriptor names it), so a request is a dozen instructions and no branch, and four go out between two jumps
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
   {
-    // lane state: the staged pixel its 16 bytes belong to and their offset in it; from one
-    // request of this wave to the next both advance by constants
+    // lane state: the pixel its 16 bytes belong to and their offset in it; from one request of this wave to the
+    // next both advance by constants
     const uint32_t o0 = (uint32_t)wave * 1024u + (uint32_t)lane * 16u;
-    uint32_t lp = fdiv(o0, a.d_pitch);
-    uint32_t rem = o0 - lp * (uint32_t)a.pitch;
-    for (int rq = wave; rq < a.nreq; rq += nwaves) {
-      const uint32_t piece = (rem >> 4) ^ ((lp >> a.swz_shift) & (uint32_t)a.swz_mask);
-      const uint32_t p = (uint32_t)pix0 + lp;
-      uint32_t ip = p;
-      if (a.S > 1) {
-        const uint32_t img = fdiv(p, a.d_mn), r2 = p - img * (uint32_t)a.MN;
+    const uint32_t lp0 = fdiv(o0, a.d_pitch);
+    uint32_t rem = o0 - lp0 * (uint32_t)a.pitch, p = (uint32_t)pix0 + lp0;  // (tiles are whole sixteens of pixels: p permutes as lp)
+    const uint32_t rowb = (uint32_t)a.I * 2u, last = (uint32_t)a.P - 1u, swzm = (uint32_t)a.swz_mask << 4;
+    const int swzs = 4 - a.swz_shift;
+    auto request = [&](int rq, auto strided) {
+      const uint32_t off = min(rem ^ ((p << swzs) & swzm), rowb - 16u);
+      uint32_t ip = min(p, last);
+      if constexpr (decltype(strided)::value) {
+        const uint32_t img = fdiv(ip, a.d_mn), r2 = ip - img * (uint32_t)a.MN;
         const uint32_t oy = fdiv(r2, a.d_n), ox = r2 - oy * (uint32_t)a.N;
         ip = (img * (uint32_t)a.L + oy * (uint32_t)a.S) * (uint32_t)a.J + ox * (uint32_t)a.S;
       }
-      if (p < (uint32_t)a.P && piece * 8u < (uint32_t)a.I)
-        __builtin_amdgcn_global_load_lds((gptr_t)(a.X + (ip * (uint32_t)a.I + piece * 8u) * 2u),
-                                         (lptr_t)(uintptr_t)(lds0 + (uint32_t)rq * 1024u), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((gptr_t)(a.X + (ip * rowb + off)), (lptr_t)(uintptr_t)(lds0 + (uint32_t)rq * 1024u), 16, 0, 0);
       rem += (uint32_t)a.adv_rem;
-      lp += (uint32_t)a.adv_pix;
-      if (rem >= (uint32_t)a.pitch) {
-        rem -= (uint32_t)a.pitch;
-        ++lp;
+      const bool over = rem >= (uint32_t)a.pitch;
+      p += (uint32_t)a.adv_pix + (over ? 1u : 0u);
+      rem = over ? rem - (uint32_t)a.pitch : rem;
+    };
+    int rq = wave;
+    if (a.S == 1) {
+      for (; rq + 3 * nwaves < a.nreq; rq += 4 * nwaves) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) request(rq + u * nwaves, std::false_type{});
       }
+      for (; rq < a.nreq; rq += nwaves) request(rq, std::false_type{});
+    } else {
+      for (; rq < a.nreq; rq += nwaves) request(rq, std::true_type{});
     }
   }
   PW_MARK(1);
@@ -503,7 +512,21 @@ PwChoice pw_choose(int P, int I, int O, int nstrips, int pitch, bool windowed, b
   ns = std::min(ns, nstrips);
   if (ns >= 4) ns &= ~3;
   c.NS = std::max(ns, 1);
-  // enough workgroups for the chip: fewer strips each first, then smaller pixel tiles
+  // enough waves for the chip: with fewer than five a CU, two lane tiles (and half as many pixels to stage) beat four by
+  // 0.3 to 0.5 us (35x35x192->64 batch 16 4.65 -> 4.31, 14x14x512 batch 8 4.95 -> 4.51, 28x28x256->128 batch 8 4.26 -> 3.86; with
+  // six a CU 14x14x1024->256 batch 32 7.19 / 7.99), with fewer than two a CU one beats two (8x8x2048->192 batch 16
+  // 6.29 -> 5.36, with three 2048->384 6.52 / 7.09).  Eight strips share a tile then where they come in eights; where they
+  // do not, a tile that several workgroups stage stays wide on many pixels (9 strips, 20x20x936->136 batch 19 6.9 / 8.8; 17 strips,
+  // 28x28x800->272 batch 5 6.3 / 7.8) but not on few (15 strips, 12x12x888->232 batch 31 11.1 / 8.5)
+  const int64_t tiles = cdiv(P, 64);
+  const bool few = tiles < 96 && nstrips <= 16;
+  if (pitch > 128 && P > 64) {
+    const int two = nstrips <= 8 ? nstrips : nstrips % 8 == 0 ? 8 : 4, sets = cdiv(nstrips, two), pt0 = c.PT;
+    if (c.PT == 4 && (few || (tiles * nstrips < 1280 && (sets == 1 || (int64_t)P * sets * pitch <= (25 << 20))))) c.PT = 2;
+    if (c.PT == 2 && (int64_t)cdiv(P, 32) * nstrips < 448) c.PT = 1;
+    if (c.PT < pt0) c.NS = c.PT == 1 ? std::min(nstrips, 4) : two;
+  }
+  // enough workgroups: fewer strips each first, then smaller pixel tiles
   while ((int64_t)cdiv(P, 16 * c.PT) * cdiv(nstrips, c.NS) < 160) {
     if (c.NS >= 8)
       c.NS = (c.NS / 2) & ~3;
@@ -512,15 +535,16 @@ PwChoice pw_choose(int P, int I, int O, int nstrips, int pitch, bool windowed, b
     else
       break;
   }
-  // few pixel tiles and few strips (a narrow layer on a small image): measured, tiles of 32
-  // pixels, two workgroups or so per CU, beat tiles of 64 by about half a microsecond
-  if (c.PT == 4 && cdiv(P, 64) < 96 && nstrips <= 16) {
+  // (thin tiles by their number alone: 56x56x64->256 batch 1 3.27 -> 3.03)
+  if ((pitch <= 128 || P <= 64) && c.PT == 4 && few) {
     c.PT = 2;
     c.NS = nstrips <= 8 ? nstrips : 4;
   }
   if (i8 && nstrips < 4) c.PT = bsp_pw_thin(c.PT, pitch, c.NS);
   const int64_t xb = (int64_t)16 * c.PT * pitch, ob = (int64_t)16 * c.PT * (c.NS * 32 + 16);
-  c.wout = windowed && (c.NS % 4 == 0 || c.NS >= nstrips) && O >= I && xb + ob <= kLdsLimit;
+  // (narrowing layers too where eight strips make two whole lines of a pixel and a CU holds as many workgroups with the image)
+  const bool lines = O >= I || (c.NS == 8 && kLdsLimit / (xb + ob) == kLdsLimit / xb);
+  c.wout = windowed && (c.NS % 4 == 0 || c.NS >= nstrips) && lines && xb + ob <= kLdsLimit;
   return c;
 }
 
