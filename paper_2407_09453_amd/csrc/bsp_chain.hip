@@ -41,7 +41,7 @@ struct ChainArgs {
   const unsigned char* residual;
   LayerPlan l1, l2, l3;
   int32_t B, L, J, I, C, O;
-  int32_t nbands;
+  int32_t nbands, share;  // share: bands of an XCD
   int32_t Jp;                        // T1 row pitch in pixels (J + 2)
   int32_t CT;                        // lane tiles per chunk of phase A
   int32_t pitchX, xs_shift, xs_mask; // staged input pixel: bytes, swizzle
@@ -78,7 +78,10 @@ __global__ __launch_bounds__(1024) void conv_chain(ChainArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n = (int)blockIdx.x / a.nbands, band = (int)blockIdx.x - n * a.nbands;
+  // an XCD takes an eighth of all bands, one after the other (bsp_tile.h: XCD)
+  const int item = (int)(blockIdx.x & 7) * a.share + (int)(blockIdx.x >> 3);
+  const int n = item / a.nbands, band = item - n * a.nbands;
+  if (n >= a.B) return;
   const int y0 = band * BR;
   const int ra = max(y0 - 1, 0), rb = min(y0 + BR + 1, a.L);
   const int npx = (rb - ra) * a.J;          // input pixels of the band, contiguous in X
@@ -545,7 +548,7 @@ int bsp_launch_chain(const bsp_weights* w1, const bsp_weights* w2, const bsp_wei
         a.d_ct = make_fastdiv((uint32_t)a.CT);
         // multiply-high divisions are exact while dividend * divisor < 2^32
         if ((int64_t)(BR + 2) * J * J >= (1ll << 32) || (int64_t)a.xbuf * a.pitchX >= (1ll << 32) ||
-            (int64_t)a.l1.nstrips * a.CT * a.CT >= (1ll << 32) || (int64_t)B * a.nbands >= (1ll << 31))
+            (int64_t)a.l1.nstrips * a.CT * a.CT >= (1ll << 32) || (int64_t)B * a.nbands >= (1ll << 31) - 8)
           return BSP_ERR_UNSUPPORTED;
         // Every band streams all three layers' weights: worth it only while that stays below
         // what the intermediates would have cost in memory traffic (their round trips are about
@@ -554,7 +557,9 @@ int bsp_launch_chain(const bsp_weights* w1, const bsp_weights* w2, const bsp_wei
         const bool forced = ((w1->kernels | w2->kernels | w3->kernels) & BSP_KERNEL_CHAIN) != 0;
         const int64_t wtraffic = (a.l1.wbytes + a.l2.wbytes + a.l3.wbytes) * B * a.nbands;
         if (!forced && wtraffic > (int64_t)B * L * J * (a.I + a.O) * 2) return BSP_ERR_UNSUPPORTED;
-        dim3 grid((unsigned)(B * a.nbands));
+        a.B = B;
+        a.share = (int32_t)(((int64_t)B * a.nbands + 7) / 8);
+        dim3 grid((unsigned)(8 * a.share));
         switch (BR) {
           case 7: return launch_chain<7>(a, grid, (size_t)ldsb, st);
           case 4: return launch_chain<4>(a, grid, (size_t)ldsb, st);

@@ -27,7 +27,7 @@ struct FirstArgs {
   const unsigned char* frag;
   int32_t relu;
   int32_t B, L, J, C, O, M, N, H, K, S, ph, pw;
-  int32_t BR, PR, nbands, tiles_x;
+  int32_t BR, PR, nbands, tiles_x, share;  // share: bands of an XCD
   int32_t lead;    // bytes before a staged row's first (halo) pixel: makes image column 0 dword aligned
   int32_t lpitch;  // bytes per staged row (a multiple of four)
   int32_t Kt;      // H * K * C
@@ -44,11 +44,9 @@ __global__ __launch_bounds__(256) void conv_first(FirstArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // consecutive workgroups go to different XCDs: all bands of an image are given to one XCD, so
-  // that the halo rows two neighbouring bands share are fetched from HBM once
-  const int xcd = blockIdx.x & 7, slot_wg = blockIdx.x >> 3;
-  const int grp8 = (int)fdiv((uint32_t)slot_wg, a.d_nbands), band = slot_wg - grp8 * a.nbands;
-  const int n = xcd + 8 * grp8;
+  // consecutive workgroups go to different XCDs: each is given an eighth of all bands, one after the other (bsp_tile.h: XCD)
+  const int item = (int)(blockIdx.x & 7) * a.share + (int)(blockIdx.x >> 3);
+  const int n = (int)fdiv((uint32_t)item, a.d_nbands), band = item - n * a.nbands;
   if (n >= a.B) return;
   const int y0 = band * a.BR, iy0 = y0 * a.S - a.ph;
   const int data0 = a.lead + a.pw * a.C * 2;  // where image column 0 lies in a staged row
@@ -288,7 +286,8 @@ int bsp_launch_first(const ConvParams& p, int dtype, const void* plan_host, hipS
   a.d_kc = make_fastdiv((uint32_t)(p.K * p.I));
   a.d_halo = make_fastdiv((uint32_t)std::max(a.halo, 1));
   // multiply-high divisions are exact while dividend * divisor < 2^32
-  const int64_t nwg = (int64_t)((p.B + 7) / 8) * a.nbands * 8;  // eight images at a time, one per XCD
+  const int64_t nwg = ((int64_t)p.B * a.nbands + 7) / 8 * 8;  // as many bands to every XCD
+  a.share = (int32_t)(nwg / 8);
   if (nwg * a.nbands >= (1ll << 32) || nwg >= (1ll << 31) || (int64_t)(a.PR * a.units + 2048) * a.units >= (1ll << 32) ||
       (int64_t)a.PR * a.halo * std::max(a.halo, 1) >= (1ll << 32))
     return BSP_ERR_UNSUPPORTED;

@@ -61,7 +61,8 @@ struct LdsCfg {
                           // pixel's chunks lie side by side, the plane size when every chunk
                           // index has a plane of its own (then t.row_bytes is 16)
   int32_t groups;         // strip groups (of four)
-  int32_t wg_per_group;   // workgroups sharing one strip group
+  int32_t wg_per_group;   // workgroups sharing one strip group (an XCD's, where tpx is set)
+  int32_t tpx;            // tiles of an XCD, one after the other (bsp_tile.h: XCD), or 0
   int32_t off_slab, off_xdesc, off_wfrag;  // plan sections, in words (read on the host)
   // advancing a thread's patch piece by the number of loader threads: uniform steps of
   // (channel part, patch column), of the LDS offset, of the element offset from the patch
@@ -131,10 +132,12 @@ __global__ __launch_bounds__(kThreads, 1) void conv_lds(ConvParams p, TileCfg t,
   const bool loader = wave_all >= 4 * kPH;
 
   const uint32_t bid = blockIdx.x;
-  const int cidx = (int)fdiv(bid, c.d_groups);
-  const int sg = (int)bid - cidx * c.groups;
-  int tile = cidx;
-  if (tile >= t.ntiles) return;
+  const uint32_t slot = c.tpx ? bid >> 3 : bid;
+  const int cidx = (int)fdiv(slot, c.d_groups);
+  const int sg = (int)slot - cidx * c.groups;
+  const int tile0 = (int)(bid & 7u) * c.tpx, tend = c.tpx ? min(tile0 + c.tpx, t.ntiles) : t.ntiles;
+  int tile = tile0 + cidx;
+  if (tile >= tend) return;
 
   const int tpi = t.tiles_y * t.tiles_x;
   const int nsl1 = t.nslabs + 1;
@@ -151,7 +154,7 @@ __global__ __launch_bounds__(kThreads, 1) void conv_lds(ConvParams p, TileCfg t,
       *nsl = 0;
       *ntl = tl + c.wg_per_group;
     }
-    return *ntl < t.ntiles;
+    return *ntl < tend;
   };
 
   if (loader) {
@@ -666,7 +669,13 @@ int launch_lds(const ConvParams& p_in, int dtype, const void* plan_host, int shi
   int64_t slots = device_cus() / c.groups;
   if (slots < 1) slots = 1;
   c.wg_per_group = (int32_t)(ntiles < slots ? ntiles : slots);
-  const int64_t nwg = (int64_t)c.wg_per_group * c.groups;
+  int64_t nwg = (int64_t)c.wg_per_group * c.groups;
+  c.tpx = 0;
+  if (32 % c.groups == 0 && device_cus() == 256) {  // (other numbers of groups would leave CUs idle)
+    c.tpx = (int32_t)((ntiles + 7) / 8);
+    c.wg_per_group = (int32_t)std::min<int64_t>(c.tpx, 32 / c.groups);
+    nwg = 8ll * c.wg_per_group * c.groups;
+  }
   const int64_t npieces = (int64_t)t.TPH * t.TPW * (t.slab / BSP_CHUNK);
   // the multiply-high divisions of a tile number (by tiles per image, then by tiles per row;
   // of a workgroup number by the strip groups) are exact while dividend * divisor < 2^32
