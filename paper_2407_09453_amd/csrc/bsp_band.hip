@@ -44,7 +44,7 @@ struct BandArgs {
   int32_t opitch;   // bytes per pixel of the output image
   int32_t llpp;     // log2 of the 16-byte slots per staged pixel
   FastDiv d_rpr, d_ctiles, d_cpp, d_nbands, d_nchunks, d_rowp;
-  int32_t share;    // bands of an XCD
+  int32_t share;    // SHARED: bands of an XCD
 #ifdef BSP_ROWS_TUNE
   long long* trace;
 #endif
@@ -62,17 +62,23 @@ struct BandArgs {
 typedef __attribute__((address_space(1))) const void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
-template <int BR, int D>
+// SHARED: the images are no multiple of eight, and an XCD is given an eighth of all bands, one after the other (with whole
+// images to some XCDs and none to the others 56x56x128->256 took 18.5 us instead of 9.7 at batch 1, 112x112x128 24.3
+// instead of 8.2, 41 instead of 30 at batch 9).  An instance of its own: with the choice made in the kernel
+// 56x56x64 batch 32 took 8.88 us instead of 8.84 (medians of eight runs), and with this order for every batch 9.13 instead
+// of 9.05, while the networks' stacks took as long with either (VGG-16 batch 16 478 us, ResNet-50 batch 32 690).
+template <int BR, int D, bool SHARED>
 __global__ __launch_bounds__(1024) void conv_band3(BandArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
   kernarg_touch<BandArgs>();
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nwaves = (int)(blockDim.x >> 6);
-  // consecutive workgroups go to different XCDs: each is given an eighth of all bands, one after the other, so that the halo
-  // rows of neighbours and what the layer before left of these pixels come from its L2 (bsp_tile.h: XCD)
-  const int item = (int)(blockIdx.x & 7) * a.share + (int)(blockIdx.x >> 3);
-  const int n = (int)fdiv((uint32_t)item, a.d_nbands), bc = item - n * a.nbands;  // nbands counts (band, chunk) pairs
+  // consecutive workgroups go to different XCDs: all bands of an image are given to one XCD, so that the halo rows two
+  // neighbouring bands share are fetched from HBM once
+  const int xcd = blockIdx.x & 7, item = (SHARED ? xcd * a.share : 0) + (int)(blockIdx.x >> 3);
+  const int q = (int)fdiv((uint32_t)item, a.d_nbands), bc = item - q * a.nbands;  // nbands counts (band, chunk) pairs
+  const int n = SHARED ? q : xcd + 8 * q;
   if (n >= a.B) return;
   const int band = (int)fdiv((uint32_t)bc, a.d_nchunks), chunk = bc - band * a.nchunks;
   const int y0 = band * BR, x0 = chunk * a.cw;
@@ -285,16 +291,16 @@ __global__ __launch_bounds__(1024) void conv_band3(BandArgs a) {
 
 constexpr int kLdsLimit = 160 * 1024;
 
-template <int BR>
+template <int BR, bool SHARED>
 int launch_band(const BandArgs& a, dim3 grid, int threads, size_t ldsb, hipStream_t st) {
   static bool raised = false;  // dynamic LDS above 64 KB has to be allowed once per kernel
   if (!raised) {
-    if (hipFuncSetAttribute((const void*)conv_band3<BR, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit) !=
+    if (hipFuncSetAttribute((const void*)conv_band3<BR, 2, SHARED>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit) !=
         hipSuccess)
       return BSP_ERR_HIP;
     raised = true;
   }
-  hipLaunchKernelGGL((conv_band3<BR, 2>), grid, dim3(threads), ldsb, st, a);
+  hipLaunchKernelGGL((conv_band3<BR, 2, SHARED>), grid, dim3(threads), ldsb, st, a);
   return hipGetLastError() == hipSuccess ? BSP_OK : BSP_ERR_HIP;
 }
 
@@ -401,5 +407,6 @@ int bsp_launch_band(const ConvParams& p, int dtype, const void* plan_host, hipSt
   a.share = (int)(nwg / 8);
   const int threads = 64 * nstrips * a.ctiles;
   dim3 grid((unsigned)nwg);
-  return BR == 7 ? launch_band<7>(a, grid, threads, (size_t)ldsb, st) : launch_band<4>(a, grid, threads, (size_t)ldsb, st);
+  if (p.B % 8) return BR == 7 ? launch_band<7, true>(a, grid, threads, (size_t)ldsb, st) : launch_band<4, true>(a, grid, threads, (size_t)ldsb, st);
+  return BR == 7 ? launch_band<7, false>(a, grid, threads, (size_t)ldsb, st) : launch_band<4, false>(a, grid, threads, (size_t)ldsb, st);
 }

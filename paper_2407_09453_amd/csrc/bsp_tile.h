@@ -18,8 +18,9 @@ __device__ __forceinline__ uint32_t sdiv(uint32_t x, SmallDiv f) { return __umul
 
 // XCD: consecutive workgroups of a launch go to the eight XCDs in turn, and each of those has an L2 of its own (4 MB) that
 // keeps its lines from one launch to the next.  So a layer's kernel gives XCD x the x-th eighth of the batch's pixels, in
-// order, whatever it cuts them into: what the layer before wrote there lies in that L2.  (16.8 MB as 64 KB a CU, written by
-// the launch before on the same XCD and on another: landed in LDS after 0.62 and 2.0 us; 33.6 MB 1.2 and 4.0.)
+// order, whatever it cuts them into: what the layer before wrote there lies in that L2 (the band kernel only where the batch
+// is no multiple of eight).  (16.8 MB as 64 KB a CU, written by the launch before on the same XCD and on another: landed in
+// LDS after 0.62 and 2.0 us; 33.6 MB 1.2 and 4.0.)
 
 struct TileCfg {
   int32_t TH, TW;            // output tile, pixels
