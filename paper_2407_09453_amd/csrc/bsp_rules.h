@@ -26,6 +26,15 @@ enum BspRival { BSP_RIVAL_BAND, BSP_RIVAL_ROWS, BSP_RIVAL_LDS, BSP_RIVAL_TILE };
 //     470 K) 5.4 / 5.9
 //   3x3, the others: 10x10x112->336 batch 5 (15 904) 8.6 / 5.4; 111x11x40->16 batch 30 (20 610) 5.6 / 6.9;
 //     stride 2 35x35x72->224 batch 7 (58 424) 14.3 / 10.2, 39x39x8->160 batch 21 (59 910, po 5.1 M) 8.4 / 14.0
+//   row-band kernel, windows of three rows or one column: 630 layers of at least 128 channels in on both sides, once the
+//     any-shape kernel waited for one slot of its ring at a time (row-band / here): 3x3 17x17x192->320 batch 16 stride 2
+//     (66 K) 11.0 / 8.1, 8x8x448->384 batch 16 (155 K) 11.2 / 9.6, 26x26x240->96 batch 6 (103 K) 12.9 / 7.6, 14x14x256
+//     batch 8 (91 K) 7.7 / 7.5, 24x24x192->152 batch 6 (94 K) 8.7 / 9.1; past them 21x22x304->280 batch 4 (179 K) 10.6 /
+//     13.2, 14x14x168->320 batch 22 (205 K) 9.4 / 11.1; few strips of many pixels 54x54x248->56 batch 2 (48 K) 7.0 / 7.6,
+//     more of them 50x50x232->80 batch 4 9.2 / 11.0 (and from 8 192 pixels the persistent kernel's), of few pixels
+//     58x58x584->32 batch 1 (65 K) 16.1 / 7.6; 7x1 goes either way past its line (17x17x192 batch 16 (117 K) 10.7 / 8.9,
+//     30x32x216->144 batch 6 (123 K) 10.3 / 14.3); 3x1 8x8x384 batch 16 (44 K) 8.5 / 6.5, past it 32x32x496->56 batch
+//     21 (200 K) 11.9 / 13.6; strided 3x1 1.3 to 2.3 times
 //   larger windows, row-band kernel (three or seven rows): 3x5 13x13x184->24 batch 8 (6 860) 8.8 / 5.3,
 //     34x11x168->24 batch 27 (99 856) 7.9 / 14.4; 7x7 11x9x144->8 batch 6 (3 268) 8.0 / 5.8,
 //     18x10x288->112 batch 15 (489 086) 16.5 / 31.5
@@ -37,18 +46,22 @@ enum BspRival { BSP_RIVAL_BAND, BSP_RIVAL_ROWS, BSP_RIVAL_LDS, BSP_RIVAL_TILE };
 inline bool bsp_any_beats_bf16(BspRival rival, int bo, int H, int K, bool strided, int64_t mm, int64_t po, int64_t I, int64_t O) {
   if (H == 1 && K == 1) return rival == BSP_RIVAL_TILE;
   if (H == 1) {
-    if (rival == BSP_RIVAL_ROWS) return bo == 16 || mm <= (I <= 208 ? 240000 : 120000);
+    if (rival == BSP_RIVAL_ROWS) return bo == 16 || mm <= (I <= 208 ? 240000 : O > 32 ? 200000 : 120000);
     return rival == BSP_RIVAL_TILE || strided || (mm <= (bo == 16 ? 1000000 : 120000) && po <= 4000000);
   }
   if (K == 1) {
     if (rival == BSP_RIVAL_TILE) return true;
-    if (H <= 3) return mm <= 45000 && po <= 4000000;
+    if (H <= 3 && rival == BSP_RIVAL_ROWS && strided) return mm <= 340000 && po <= 10000000;
+    if (H <= 3) return mm <= (rival == BSP_RIVAL_ROWS && bo == 8 && O > 32 ? 80000 : 45000) && po <= 4000000;
     if (rival == BSP_RIVAL_ROWS) return strided || mm <= 100000;
     return (mm <= 100000 && po <= 4000000) || (strided && po <= 10000000);
   }
   if (H <= 3 && K <= 3) {
     if (rival == BSP_RIVAL_TILE) return true;
     if (rival == BSP_RIVAL_BAND) return mm <= 25000 && po <= 250000;
+    if (rival == BSP_RIVAL_ROWS && strided) return mm <= 180000 && po <= 3000000;
+    if (rival == BSP_RIVAL_ROWS)
+      return po <= 3000000 && mm <= (po > (O <= 64 ? 5500 : 8000) * O ? 30000 : O <= 64 ? 60000 : bo == 8 && 3 * O >= I ? 160000 : 115000);
     return mm <= (strided ? 60000 : 30000) && po <= 3000000;
   }
   if (rival == BSP_RIVAL_ROWS) return H <= 3 ? mm <= 80000 && po <= 300000 : mm <= 30000;

@@ -50,6 +50,27 @@ def test_bf16_layers(n):
     assert bool(((out.double() - want).abs() <= 6e-3 * scale).all())   # one rounding to bf16 is 3.9e-3 at most
 
 
+@pytest.mark.parametrize("B,L,J,I,O,H,K,stride,any_shape", [
+    (16, 17, 17, 192, 320, 3, 3, 2, True), (32, 35, 35, 288, 384, 3, 3, 2, False),     # 3x3 strided: 66 K, some 400 K
+    (16, 8, 8, 448, 384, 3, 3, 1, True), (22, 14, 14, 168, 320, 3, 3, 1, False),       # a third of the channels in: 155 K, 205 K
+    (1, 58, 58, 584, 32, 3, 3, 1, True), (4, 50, 50, 232, 80, 3, 3, 1, False),         # few strips, and too many pixels
+    (16, 8, 8, 384, 384, 3, 1, 1, True), (21, 32, 32, 496, 56, 3, 1, 1, False), (4, 20, 20, 200, 104, 3, 1, 2, True),
+    (16, 8, 8, 448, 384, 1, 3, 1, True), (30, 32, 32, 320, 192, 1, 3, 1, False),
+])
+def test_any_shape_or_row_bands(B, L, J, I, O, H, K, stride, any_shape):
+    """Either side of the lines between the any-shape and the row-band kernel (or the one that goes before it)."""
+    import torch
+    X, W, gamma, keep = _draw(I + O, B, L, J, I, O, H, K, 8, 8)
+    X, W, pad = X.bfloat16(), W.bfloat16(), (H // 2, K // 2)
+    layer = bsp.BspLayer(W.float().cpu().numpy(), gamma, 8, 8, "bf16")
+    out = torch.full(layer.out_shape(B, L, J, (stride, stride), pad), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ran = kernels_of(lambda: layer.conv2d(X, (stride, stride), pad, out=out))
+    assert any("conv_any" in k for k in ran) == any_shape, ran
+    want = conv_fp64(X, W * keep, stride, pad)
+    scale = torch.maximum(want.abs(), want.pow(2).mean().sqrt())
+    assert bool(((out.double() - want).abs() <= 6e-3 * scale).all())   # one rounding to bf16 is 3.9e-3 at most
+
+
 F32 = [
     (34, 15, 15, 5, 125, 1, 1, 1, (16, 4), "conv_general"), (25, 49, 49, 79, 180, 1, 1, 1, (16, 4), "conv_f32<"),
     (6, 14, 14, 11, 118, 1, 1, 1, (8, 8), "conv_general"), (4, 13, 21, 64, 102, 1, 3, 1, (8, 8), "conv_f32x3<"),
