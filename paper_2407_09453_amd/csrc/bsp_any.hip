@@ -708,7 +708,7 @@ const int32_t* plan_of(const ConvParams& p, int dtype, const void* plan_host) {
 bool bsp_any_beats(const ConvParams& p, const void* plan_host, BspRival rival) {
   const int32_t* hdr = plan_of(p, BSP_BF16, plan_host);
   return hdr && bsp_any_beats_bf16(rival, hdr[BSP_PLAN_BO_W], p.H, p.K, p.sh > 1 || p.sw > 1,
-                                   (int64_t)((p.P + 15) / 16) * hdr[BSP_PLAN_NSTEPS_W], (int64_t)p.P * p.O, p.I, p.O);
+                                   (int64_t)((p.P + 15) / 16) * hdr[BSP_PLAN_NSTEPS_W], (int64_t)p.P * p.O, p.I, p.O, p.N);
 }
 
 bool bsp_any_beats_i8(const ConvParams& p, const void* plan_host) {

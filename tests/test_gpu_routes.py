@@ -53,6 +53,7 @@ def test_bf16_layers(n):
 @pytest.mark.parametrize("B,L,J,I,O,H,K,stride,any_shape", [
     (16, 17, 17, 192, 320, 3, 3, 2, True), (32, 35, 35, 288, 384, 3, 3, 2, False),     # 3x3 strided: 66 K, some 400 K
     (16, 8, 8, 448, 384, 3, 3, 1, True), (22, 14, 14, 168, 320, 3, 3, 1, False),       # a third of the channels in: 155 K, 205 K
+    (8, 7, 7, 512, 512, 3, 3, 1, True), (5, 10, 10, 512, 512, 3, 3, 1, False), (8, 14, 14, 512, 512, 3, 3, 2, False),  # many weights
     (1, 58, 58, 584, 32, 3, 3, 1, True), (4, 50, 50, 232, 80, 3, 3, 1, False),         # few strips, and too many pixels
     (16, 8, 8, 384, 384, 3, 1, 1, True), (21, 32, 32, 496, 56, 3, 1, 1, False), (4, 20, 20, 200, 104, 3, 1, 2, True),
     (16, 8, 8, 448, 384, 1, 3, 1, True), (30, 32, 32, 320, 192, 1, 3, 1, False),
