@@ -96,3 +96,29 @@ def test_pw_kernel_declines_what_it_cannot_do():
     with pytest.raises(bsp.BspError) as e:
         _run_pw(c)
     assert e.value.code == -6
+
+
+@pytest.mark.parametrize("P,I,O,tiles", [
+    (1024, 2048, 192, 1), (1040, 2048, 384, 2),  # fewer than two waves a CU, and more
+    (65, 72, 16, 1), (1569, 512, 512, 2),        # the fewest pixels; eight strips to a tile, one pixel past it
+    (6271, 256, 128, 2), (6273, 264, 120, 2),    # whole lines of a narrowing layer; a line that ends early
+    (7600, 936, 136, 4), (4464, 888, 232, 2),    # nine strips on many pixels, fifteen on fewer
+    (12600, 256, 128, 4), (100, 64, 64, 1),      # waves enough; few workgroups whatever the tile
+])
+def test_pw_lane_tiles(P, I, O, tiles):
+    """Either side of the lines between four, two and one lane tiles: the instance that runs, and its results against fp64."""
+    import torch
+    from gpu_util import conv_fp64, kernels_of
+    gen = torch.Generator("cuda").manual_seed(P)
+    gamma = (np.random.default_rng(P).random((O // 8, I // 8)) < 0.5).astype(np.uint8)
+    gamma[0, -1], gamma[0, 0] = 1, 0
+    keep = torch.from_numpy(np.kron(gamma, np.ones((8, 8), np.uint8))).cuda()[:, None, None, :]
+    X = torch.randn(1, P, 1, I, generator=gen, device="cuda").bfloat16()
+    W = (torch.randn(O, 1, 1, I, generator=gen, device="cuda") * (2.0 / I) ** 0.5).bfloat16()
+    layer = bsp.BspLayer(W.float().cpu().numpy(), gamma, 8, 8, "bf16")
+    Y = torch.full((1, P, 1, O), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ran = kernels_of(lambda: layer.conv2d(X, (1, 1), (0, 0), out=Y, family=bsp.BSP_KERNEL_PW))
+    assert any("conv_pw<%d, 8," % tiles in k for k in ran), ran
+    want = conv_fp64(X, W * keep, 1, (0, 0))
+    scale = torch.maximum(want.abs(), want.pow(2).mean().sqrt())
+    assert bool(((Y.double() - want).abs() <= 6e-3 * scale).all())   # one rounding to bf16 is 3.9e-3 at most
