@@ -198,3 +198,33 @@ def test_fixed_scratch_refuses_what_it_refused():
         else:
             call()
             assert torch.equal(Y, layer.fc(X))
+
+
+@pytest.mark.parametrize("dtype", ("bf16", "i8"))
+@pytest.mark.parametrize("O", (1, 2, 3, 4, 5, 18, 24, 35, 41))
+def test_bias_of_the_last_channels(O, dtype):
+    """Last strips of every remainder of four and sixteen channels: each channel gets its own bias, and
+    nothing is taken from past the bias's end (a large value stands there)."""
+    import torch
+    rng = np.random.default_rng(O)
+    B, L, I = 2, 9, 72
+    nbr, nbc = -(-O // 8), -(-I // 8)
+    gamma = np.ones((nbr, nbc), np.uint8)
+    bias = rng.integers(-3000, 3000, O + 16).astype(np.int32 if dtype == "i8" else np.float32)
+    bias[O:] = 1 << 20
+    X = rng.integers(-4, 5, (B, L, L, I)).astype(np.int8)
+    W = rng.integers(-3, 4, (O, 3, 3, I)).astype(np.int8)
+    want = oracle.conv2d_i8(X, W, bias[:O].astype(np.int32), gamma, 8, 8, (1, 1), (1, 1), shift=None)
+    if dtype == "i8":
+        layer, x = bsp.BspLayerI8(W, gamma, 8, 8, bias=bias[:O]), torch.from_numpy(X).cuda()
+    else:
+        layer, x = bsp.BspLayer(W.astype(np.float32), gamma, 8, 8, "bf16", bias=bias[:O]), torch.from_numpy(X).cuda().bfloat16()
+    layer.d_bias = torch.from_numpy(bias).cuda()
+    for relu in ((False, True) if dtype == "bf16" else (False,)):
+        y = layer.conv2d(x, (1, 1), (1, 1), **({"relu": relu} if dtype == "bf16" else {"shift": None}))
+        torch.cuda.synchronize()
+        w = torch.from_numpy(np.asarray(want)).cuda()
+        if dtype == "i8":
+            assert torch.equal(y, w.int())
+        else:  # whole numbers below 2^24: the sums are exact and rounded once
+            assert torch.equal(y, (w.relu() if relu else w).float().bfloat16())
