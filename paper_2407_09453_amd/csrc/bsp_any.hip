@@ -55,7 +55,7 @@ struct AnyArgs {
   int32_t nslabs, spst, nstages, slab_bytes;   // the plan's slabs, how many are staged at a time
   int32_t nstrips, NS, PG, ks, lpg, lks, nset; // strips per workgroup, pixel groups, waves that share a strip's steps; log2
   int32_t total, per_xcd;
-  int32_t opitch, stream, direct;  // bytes per pixel of the output image; its pieces are whole output lines; no image
+  int32_t opitch, stream;          // bytes per pixel of the output image; its pieces are whole output lines
   int32_t K, lbo;                  // log2 of the block rows' height (these and the two pointers: kept_only)
   const int32_t* plan;
   const unsigned char* payload;
@@ -155,7 +155,7 @@ __device__ __forceinline__ f32x4_t bias4(const AnyArgs& a, int ch) {
 // 0.51 M LDS cycles).  Wave = (strip, pixel group, share of the strip's steps): a step's
 // weights come from the plan through a register ring of D, its activations from LDS G steps ahead (one tile:
 // four, as each is one read and one product; 3x3 7x7x512 batch 1 6.9 -> 6.5 us with the ring of eight).
-template <int KIND, int PT, bool VEC>
+template <int KIND, int PT, bool VEC, bool DIRECT>
 __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
   kernarg_touch<AnyArgs>();
   extern __shared__ __align__(16) unsigned char lds[];
@@ -394,7 +394,7 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
     }
     bad = active && __ballot(bad & 0x80008000u);
   }
-  auto send = [&] {
+  [[maybe_unused]] auto send = [&] {
 #pragma unroll
     for (int t = 0; t < PT; ++t) {
       if ((t & (a.ks - 1)) != k) continue;
@@ -408,9 +408,11 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
       *(u32x2_t*)(a.Y + o * 2u) = out[t];
     }
   };
-  if (KIND == kBf16 && a.direct && active && !bad) send();
+  if constexpr (DIRECT)
+    if (active && !bad) send();
   __syncthreads();  // everybody is done with the patch (the partial sums)
-  if (KIND == kBf16 && a.direct && !bad) return;
+  if constexpr (DIRECT)
+    if (!bad) return;
   if (active) {
     unsigned char* ot = lds + (pg * PT * 16 + lj) * opitch;
     const RescaleI8 rescale(__builtin_bit_cast(i32x4_t, bv), KIND == kI8 ? a.shift : 0);
@@ -447,7 +449,7 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
           };
           *place(tile) = u32x2_t{take(place(tile)->x, pack_bf16x2(v.x, v.y)), take(place(tile)->y, pack_bf16x2(v.z, v.w))};
         }
-        if (a.direct) {
+        if constexpr (DIRECT) {
 #pragma unroll
           for (int t = 0; t < PT; ++t) out[t] = *place(pg * PT + t);
           send();
@@ -455,7 +457,7 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
       }
     }
   }
-  if (KIND == kBf16 && a.direct) return;
+  if constexpr (DIRECT) return;
   __syncthreads();
   const int os = KIND == kBf16 ? 2 : a.y32 ? 4 : 1;  // bytes per result
   const int run = min(a.NS * BSP_STRIP, a.O - set * a.NS * BSP_STRIP) * os;  // a pixel's bytes here
@@ -540,22 +542,24 @@ Pick choose(int B, int M, int N, int os, int nstrips, int steps, int nslabs, int
   return best;
 }
 
-template <int KIND, int PT, bool VEC>
+template <int KIND, int PT, bool VEC, bool DIRECT>
 int launch_inst(const AnyArgs& a, int threads, size_t ldsb, hipStream_t st) {
   static bool raised = false;  // dynamic LDS above 64 KB has to be allowed once per kernel
   if (!raised) {
-    if (hipFuncSetAttribute((const void*)conv_any<KIND, PT, VEC>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) !=
+    if (hipFuncSetAttribute((const void*)conv_any<KIND, PT, VEC, DIRECT>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) !=
         hipSuccess)
       return BSP_ERR_HIP;
     raised = true;
   }
-  hipLaunchKernelGGL((conv_any<KIND, PT, VEC>), dim3((unsigned)(a.per_xcd * 8)), dim3(threads), ldsb, st, a);
+  hipLaunchKernelGGL((conv_any<KIND, PT, VEC, DIRECT>), dim3((unsigned)(a.per_xcd * 8)), dim3(threads), ldsb, st, a);
   return hipGetLastError() == hipSuccess ? BSP_OK : BSP_ERR_HIP;
 }
-// vec: pixels of X are whole 16-byte pieces
+// vec: pixels of X are whole 16-byte pieces; direct: results leave from the accumulators
 template <int KIND, int PT>
-int launch_conv(const AnyArgs& a, bool vec, int threads, size_t ldsb, hipStream_t st) {
-  return vec ? launch_inst<KIND, PT, true>(a, threads, ldsb, st) : launch_inst<KIND, PT, false>(a, threads, ldsb, st);
+int launch_conv(const AnyArgs& a, bool vec, bool direct, int threads, size_t ldsb, hipStream_t st) {
+  if constexpr (KIND == kBf16)
+    if (direct) return vec ? launch_inst<KIND, PT, true, true>(a, threads, ldsb, st) : launch_inst<KIND, PT, false, true>(a, threads, ldsb, st);
+  return vec ? launch_inst<KIND, PT, true, false>(a, threads, ldsb, st) : launch_inst<KIND, PT, false, false>(a, threads, ldsb, st);
 }
 
 template <int KIND>
@@ -692,14 +696,15 @@ int launch_kind(const ConvParams& p, const int32_t* hdr, int y32, int shift, hip
   a.stream = p.O * os % 16 == 0 && (reinterpret_cast<uintptr_t>(p.Y) & 15u) == 0 &&
              (best.NS >= a.nstrips ? flat || p.O * os >= 128 : p.O * os % 128 == 0 && best.NS * BSP_STRIP * os % 128 == 0);
   // (of more results the whole lines are worth more than the barrier and the way through LDS: 5x5 35x35x48->64 batch 16, 2.5 MB,
-  // 9.80 us through the image, 10.05 without; 1.5 to 1.8 MB alike; 0.4 to 0.8 MB 0.25 us less without)
-  a.direct = KIND == kBf16 && p.O % 4 == 0 && ((reinterpret_cast<uintptr_t>(p.Y) | reinterpret_cast<uintptr_t>(p.residual)) & 7u) == 0 &&
-             (int64_t)p.P * p.O * 2 <= (1 << 20);
+  // 9.80 us through the image, 10.05 without; 1.5 to 1.8 MB alike; 0.4 to 0.8 MB 0.25 us less without.  Instances of their own:
+  // with the choice made in the kernel the others paid for its registers and code, 3x1 82x108x43->347 batch 3 16.6 -> 17.4 us)
+  // (the entry points take results and residuals at multiples of 16 bytes only)
+  const bool direct = KIND == kBf16 && p.O % 4 == 0 && (int64_t)p.P * p.O * 2 <= (1 << 20);
   const int threads = 64 * best.NS * best.PG * best.ks;
   switch (best.PT) {
-    case 1: return launch_conv<KIND, 1>(a, vec, threads, (size_t)best.lds, st);
-    case 2: return launch_conv<KIND, 2>(a, vec, threads, (size_t)best.lds, st);
-    case 4: return launch_conv<KIND, 4>(a, vec, threads, (size_t)best.lds, st);
+    case 1: return launch_conv<KIND, 1>(a, vec, direct, threads, (size_t)best.lds, st);
+    case 2: return launch_conv<KIND, 2>(a, vec, direct, threads, (size_t)best.lds, st);
+    case 4: return launch_conv<KIND, 4>(a, vec, direct, threads, (size_t)best.lds, st);
   }
   return BSP_ERR_UNSUPPORTED;
 }
