@@ -153,14 +153,16 @@ __device__ __forceinline__ f32x4_t bias4(const AnyArgs& a, int ch) {
 // LDS takes.  A staged pixel is an odd number of 16-byte pieces, so pixels of a matrix tile that lie in
 // one patch row read different banks; those of two rows can collide (bf16 3x3 47x33x100->76: 0.19 M of
 // 0.51 M LDS cycles).  Wave = (strip, pixel group, share of the strip's steps): a step's
-// weights come from the plan through a register ring of D, its activations from LDS G steps ahead (one tile:
-// four, as each is one read and one product; 3x3 7x7x512 batch 1 6.9 -> 6.5 us with the ring of eight).
+// weights come from the plan through a register ring of D, its activations from LDS one step ahead.  (A ring of eight
+// with two or four steps read together, for one tile: 3x3 7x7x512 batch 1 as fast, 6.7 us, but a register budget that
+// holds four waves a SIMD instead of five, and scalars in scratch; FC int8 20600 -> 120 batch 5 19.5 us instead of 17.7.)
+// The bf16 instances keep up to a dozen scalars that only the results need in lanes of a vector register.  Reading
+// them from the argument block again there spills none and costs more: 232 small layers 1.3 to 1.7 % slower, 350 others 0.6 %.
 template <int KIND, int PT, bool VEC, bool DIRECT>
 __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
   kernarg_touch<AnyArgs>();
   extern __shared__ __align__(16) unsigned char lds[];
-    constexpr int ES = KIND == kI8 ? 1 : 2, U = 4;
-  constexpr int D = PT == 1 ? 8 : 4, G = PT == 1 ? (KIND == kI8 ? 2 : 4) : 1;  // the ring, and the steps whose activations are read together
+  constexpr int D = 4, ES = KIND == kI8 ? 1 : 2, U = 4;
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, jn = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nthreads = (int)blockDim.x;
@@ -242,11 +244,18 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
 
     // ---- weights: a ring of D steps
     u32x4_t wr[D];
-    int dr[D];  // descriptors
-    int fcs = slo + k;
+    int dr[D], pos[D];  // descriptors; where the step's slab lies in a staged pixel, and is it the slab's first (1), its last (2) step
+    int fcs = slo + k, fsl = sl0, fadd = 0, fbeg = slo, fend = __builtin_amdgcn_readlane(tab, sl0 + 1);
     auto fetch = [&](int d) {
       const int cs = min(fcs, shi - 1);  // (past the end: the last step again, never used)
       fcs += a.ks;
+      while (cs >= fend) {
+        fadd += a.slab_bytes;
+        ++fsl;
+        fbeg = fend;
+        fend = __builtin_amdgcn_readlane(tab, fsl + 1);
+      }
+      pos[d] = fadd | (KIND == kBf16 ? (cs == fbeg) + 2 * (cs == fend - 1) : 0);  // (a slab is whole 16-byte pieces)
       dr[d] = *(const int*)(a.xdesc + ((uint32_t)cs * 16u + (uint32_t)g * 4u));
       wr[d] = *(const u32x4_t*)(a.wfrag + ((uint32_t)cs * 1024u + (uint32_t)lane * 16u));
     };
@@ -271,28 +280,19 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
-    // ---- products.  Where the step read next lies in a staged pixel, the steps of its slab
-    int rcs = slo + k, rsl = sl0, radd = 0, rbeg = slo, rend = __builtin_amdgcn_readlane(tab, sl0 + 1);
+    // ---- products
     auto read = [&](int d, u32x4_t (&f)[PT]) {
-      const int cs = min(rcs, shi - 1);
-      rcs += a.ks;
-      while (cs >= rend) {
-        radd += a.slab_bytes;
-        ++rsl;
-        rbeg = rend;
-        rend = __builtin_amdgcn_readlane(tab, rsl + 1);
-      }
       uint32_t desc = (uint32_t)dr[d];
       asm volatile("" : "+v"(desc));  // decoded here, not where it is loaded: no early wait
-      const uint32_t o = ((desc & 0xFFFFu) << 4) + (uint32_t)radd + __umul24((desc >> 16) & 0xFFu, rowpitch) +
+      const uint32_t o = ((desc & 0xFFFFu) << 4) + (uint32_t)(pos[d] & ~15) + __umul24((desc >> 16) & 0xFFu, rowpitch) +
                          __umul24(desc >> 24, a.pitch);
 #pragma unroll
       for (int t = 0; t < PT; ++t) f[t] = *(const u32x4_t*)(lds + base[t] + o);
       if constexpr (KIND == kBf16) {
         // a pair that fills up a slab's last step multiplies zeros with zeros, not with whatever
         // (an infinity) lies at its descriptor's address
-        if (cs == rend - 1) {
-          const bool real = desc != 0u || (g == 0 && cs == rbeg);
+        if (pos[d] & 2) {
+          const bool real = desc != 0u || (g == 0 && (pos[d] & 1));
 #pragma unroll
           for (int t = 0; t < PT; ++t) f[t] = real ? f[t] : u32x4_t{0u, 0u, 0u, 0u};
         }
@@ -302,43 +302,31 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
 #pragma unroll
       for (int t = 0; t < PT; ++t) acc[t] = mma<KIND>(wr[d], f[t], acc[t]);
     };
-    // (G steps' fragments are read ahead of the products of the G before them)
-    u32x4_t fa[G][PT], fb[G][PT];
-    auto reads = [&](int d, u32x4_t (&f)[G][PT], int left) {
-#pragma unroll
-      for (int j = 0; j < G; ++j)
-        if (j < left) read(d + j, f[j]);
-    };
-    auto products = [&](int d, const u32x4_t (&f)[G][PT], int left) {
-#pragma unroll
-      for (int j = 0; j < G; ++j)
-        if (j < left) mfmas(d + j, f[j]);
-    };
     auto refill = [&](int d) {
       __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int j = 0; j < G; ++j) fetch(d + j);
+      fetch(d);
       __builtin_amdgcn_sched_barrier(0);
     };
+    u32x4_t fa[PT], fb[PT];
     int i = 0;
-    reads(0, fa, n);
+    if (n > 0) read(0, fa);
     for (; i + D < n; i += D) {
 #pragma unroll
-      for (int d = 0; d < D; d += 2 * G) {
-        reads(d + G, fb, G);
-        products(d, fa, G);
+      for (int d = 0; d < D; d += 2) {
+        read(d + 1, fb);
+        mfmas(d, fa);
         refill(d);
-        reads((d + 2 * G) % D, fa, d + 2 * G < D ? G : n - i - D);
-        products(d + G, fb, G);
-        refill(d + G);
+        read((d + 2) % D, fa);
+        mfmas(d + 1, fb);
+        refill(d + 1);
       }
     }
 #pragma unroll
-    for (int d = 0; d < D; d += 2 * G) {
-      reads(d + G, fb, n - i - d - G);
-      products(d, fa, n - i - d);
-      if (d + 2 * G < D) reads(d + 2 * G, fa, n - i - d - 2 * G);
-      products(d + G, fb, n - i - d - G);
+    for (int d = 0; d < D; d += 2) {
+      if (i + d + 1 < n) read(d + 1, fb);
+      if (i + d < n) mfmas(d, fa);
+      if (d + 2 < D && i + d + 2 < n) read(d + 2, fa);
+      if (i + d + 1 < n) mfmas(d + 1, fb);
     }
   }
 
