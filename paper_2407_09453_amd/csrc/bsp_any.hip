@@ -17,7 +17,7 @@
 // 51 / 10.4; FC 32 x 1001 -> 999 28.6 / 5.4; int8 3x3 28x28x136->200 batch 8 28 / 8.2.  Which layers go
 // to the other kernels instead: bsp_rules.h.
 //
-// A wait for everything before the patch's barrier, results of at most 1 MiB straight from the accumulators, the
+// A wait for everything before the patch's barrier, small outputs straight from the accumulators (bsp_any_direct), the
 // bias asked for in the opening, zeros for a slab's unused pairs in its last step only and a strip's own partial sums kept in
 // registers, together: 1x7 17x17x160 batch 16 8.1 -> 7.3 us, 5x5 35x35x48->64 12.4 -> 9.9, 3x3 14x14x256 batch 1 5.27 -> 5.03,
 // 7x7x512 6.92 -> 6.31.  Deeper rings for two and four tiles (eight and sixteen steps, one workgroup a CU) gave nothing:
@@ -683,11 +683,7 @@ int launch_kind(const ConvParams& p, const int32_t* hdr, int y32, int shift, hip
   // whole 128-byte lines leave as streaming stores (nothing dirty is left for the kernel's end)
   a.stream = p.O * os % 16 == 0 && (reinterpret_cast<uintptr_t>(p.Y) & 15u) == 0 &&
              (best.NS >= a.nstrips ? flat || p.O * os >= 128 : p.O * os % 128 == 0 && best.NS * BSP_STRIP * os % 128 == 0);
-  // (of more results the whole lines are worth more than the barrier and the way through LDS: 5x5 35x35x48->64 batch 16, 2.5 MB,
-  // 9.80 us through the image, 10.05 without; 1.5 to 1.8 MB alike; 0.4 to 0.8 MB 0.25 us less without.  Instances of their own:
-  // with the choice made in the kernel the others paid for its registers and code, 3x1 82x108x43->347 batch 3 16.6 -> 17.4 us)
-  // (the entry points take results and residuals at multiples of 16 bytes only)
-  const bool direct = KIND == kBf16 && p.O % 4 == 0 && (int64_t)p.P * p.O * 2 <= (1 << 20);
+  const bool direct = KIND == kBf16 && bsp_any_direct(p.O, (int64_t)p.P * p.O);
   const int threads = 64 * best.NS * best.PG * best.ks;
   switch (best.PT) {
     case 1: return launch_conv<KIND, 1>(a, vec, direct, threads, (size_t)best.lds, st);

@@ -78,6 +78,17 @@ inline bool bsp_any_beats_bf16(BspRival rival, int bo, int H, int K, bool stride
   return H * K <= 25 ? O < 272 || po <= 1000000 : O < 136 || po <= 800000;
 }
 
+// bf16 layers on the any-shape kernel: whether results leave straight from the accumulators, eight bytes a lane (po: results).
+// That saves a barrier and the way through LDS; past some size an image's whole lines are worth more, and a narrow layer's
+// pixels are part lines anyway.  1470 random layers, the geometric mean of direct / image (the slowest of a class):
+//   fewer than 64 channels: 20 to 160 K results 0.94 to 0.96 (1.00), 160 to 200 K 0.96 (1.09; 40 channels), 320 to 460 K 1.01
+//     (1.19), 460 K and more 1.03 (1.21; 3x1 50x50x64->48 batch 4 5.11 / 5.47 us)
+//   others: 20 to 200 K 0.94 to 0.97 (1.00), 320 to 400 K 0.96 (1.03), 460 K and more 0.99 (1.09); 2.5 MB, 5x5 35x35x48->64
+//     batch 16, 9.80 us through the image, 10.05 direct
+// Instances of their own: with the choice made in the kernel the others paid for its registers and code, 3x1 82x108x43->347
+// batch 3 16.6 -> 17.4 us.  (The entry points take results and residuals at multiples of 16 bytes only.)
+inline bool bsp_any_direct(int64_t O, int64_t po) { return O % 4 == 0 && po <= (O < 64 ? 160000 : 400000); }
+
 // bf16 windows of three rows at stride 1: whether the persistent kernel takes a layer from `rival`.  mr: matrix
 // instructions of the row-band section's steps; cost: the two kernels' own models of a layer, which put
 // the persistent one at 0.95 (0.85 to 1.10) of what it takes and the row-band kernel at 1.47 times (1.12 to 2.0)

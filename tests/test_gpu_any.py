@@ -7,7 +7,7 @@ import oracle
 import paper_2407_09453_amd as bsp
 from synthetic import draw_layer
 
-from gpu_util import assert_close, make_layer, to_device, to_host
+from gpu_util import assert_close, kernels_of, make_layer, to_device, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -138,8 +138,9 @@ def _without(c, X):
 
 
 @pytest.mark.parametrize("B,L,J,I,O,H", [
-    (1, 64, 128, 20, 64, 3),   # 1 MiB of results: they leave straight from the accumulators
-    (1, 65, 128, 20, 64, 3),   # one row more: through the image of the output
+    (1, 64, 128, 20, 64, 3), (1, 65, 128, 20, 64, 3),  # many results: through the image of the output
+    (1, 50, 125, 20, 64, 3), (1, 51, 125, 20, 64, 3),  # the last and the first past the line, and the same of narrow layers
+    (1, 50, 100, 20, 32, 3), (1, 51, 100, 20, 32, 3),
     (1, 9, 11, 20, 66, 3),     # few results, but a lane's four channels can end past the last one
     (1, 7, 9, 64, 16, 3),      # 1 .. 4 and 16 to 17 steps a wave: either side of the rings' ends
     (1, 5, 5, 512, 16, 3), (1, 8, 8, 1024, 36, 3), (2, 6, 6, 96, 64, 5), (4, 15, 15, 136, 24, 3),
@@ -153,6 +154,10 @@ def test_both_ways_out(B, L, J, I, O, H):
     c.gamma[0, 1], c.gamma[1, 1] = 0, 1  # two rows of one strip: the second keeps what the first drops
     layer, X = make_layer(c), to_device(c)
     y0 = layer.conv2d(X, c.stride, c.pad)
+    # the last template argument of the kernel that ran: straight from the accumulators, or through the image
+    ran = [k for k in kernels_of(lambda: layer.conv2d(X, c.stride, c.pad)) if "conv_any<" in k]
+    if ran:
+        assert (", true>" in ran[0]) == (O % 4 == 0 and B * L * J * O <= (160000 if O < 64 else 400000)), ran
     R = torch.randn(y0.shape, device="cuda", generator=torch.Generator("cuda").manual_seed(I)).bfloat16()
     y = layer.conv2d(X, c.stride, c.pad, residual=R, relu=True)
     torch.cuda.synchronize()

@@ -18,6 +18,7 @@ static void is(bool got, bool want, const char* what) {
 }
 #define BEATS(want, ...) is(bsp_any_beats_bf16(__VA_ARGS__), want, #__VA_ARGS__)
 #define FEW(want, ...) is(bsp_any_few(__VA_ARGS__), want, #__VA_ARGS__)
+#define DIRECT(want, ...) is(bsp_any_direct(__VA_ARGS__), want, #__VA_ARGS__)
 #define LDS8(want, ...) is(bsp_any_beats_lds_i8(__VA_ARGS__), want, #__VA_ARGS__)
 #define GEN8(want, ...) is(bsp_i8_general(__VA_ARGS__), want, #__VA_ARGS__)
 #define THIN(want, ...) is(bsp_pw_thin(__VA_ARGS__) == want, true, #__VA_ARGS__)
@@ -73,6 +74,14 @@ int main() {
   FEW(true, 16, 61, 1656, 4406, true);                                    // 16.7 / 10.2
   FEW(true, 8, 64, 2048, 4096, true);                                     // 14.3 / 13.2
   FEW(true, 4, 49, 2048, 4096, false);                                    // a window
+  // channels out, results: direct / through the image
+  DIRECT(true, 32, 160000);                                               // 0.95, none slower
+  DIRECT(false, 48, 192000);                                              // up to 1.09
+  DIRECT(false, 48, 480000);                                              // 5.11 / 5.47
+  DIRECT(true, 64, 400000);                                               // 0.96
+  DIRECT(false, 64, 480000);                                              // up to 1.09
+  DIRECT(true, 60, 160000);
+  DIRECT(false, 66, 1000);                                                // channels come in fours
   // rival, matrix instructions, channels in and out, both models: the other / persistent, us
   TALL(true, BSP_RIVAL_ROWS, 1964952, 544, 336, 44422, 53418);            // 71 / 29
   TALL(true, BSP_RIVAL_ROWS, 2474304, 256, 256, 41416, 47991);            // 47 / 42
