@@ -19,8 +19,9 @@
 // weights and steps are byte for byte the same; the launcher counts input channels in pairs of codes.
 // A lane's four results are four bytes, so they always leave through the LDS image of the output.
 //
-// Staged pixels past the layer's last pixel are never written to LDS and never stored: each
-// MFMA column depends on its own pixel only.
+// A tile's pixels past the layer's last one are staged as copies of that one, and a pixel's pieces past its channels as copies of
+// its last piece, so that no lane of a request is masked.  Nothing of either reaches a result: each MFMA column depends on its
+// own pixel only and columns past the last pixel are not stored, and no descriptor names a piece past the channels.
 #include "bsp_kept.h"
 #include "bsp_launch.h"
 #include "bsp_tile.h"
@@ -307,7 +308,7 @@ __global__ __launch_bounds__(MAXT) void conv_pw(Args a) {
     bool bad = false;
 #pragma unroll
     for (int t = 0; t < PT; ++t)
-      if (chan >= 0 && ptile0 + t * 16 + c < a.P) {  // (the other lanes' pixels were never staged)
+      if (chan >= 0 && ptile0 + t * 16 + c < a.P) {  // (the other lanes hold copies of the last pixel)
 #pragma unroll
         for (int r = 0; r < 4; ++r) bad |= (__float_as_uint(acc[t][r]) & 0x7F800000u) == 0x7F800000u;
       }
@@ -492,65 +493,7 @@ int launch_pt(const Args& a, int PT, int depth, dim3 grid, int threads, size_t l
   return BSP_ERR_UNSUPPORTED;
 }
 
-struct PwChoice {
-  int PT, PG, NS;
-  int wout;      // results leave through an LDS image of whole output lines
-};
-
 inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
-
-// Tile choice, from per-shape timings of ResNet50-, VGG16- and InceptionV3-shaped pointwise
-// layers (several configurations each): one pixel group; four lane tiles per wave unless the
-// tile's channels then exceed 128 KiB of LDS; few strips per workgroup while pixels are
-// plentiful or the tile is thin (many small workgroups hide each other's latencies), many when they are not
-// (every strip group re-reads the tile from L2, which is what bounds deep layers); whole-line
-// output for layers that widen (their output is the bulk of the traffic).
-PwChoice pw_choose(int P, int I, int O, int nstrips, int pitch, bool windowed, bool i8) {
-  PwChoice c{4, 1, 1, 0};
-  while (c.PT > 1 && 16 * c.PT * pitch > 128 * 1024) c.PT /= 2;
-  int ns = (P >= 50000 || (I <= 128 && P >= 20000)) ? 4 : (I >= 512 ? 16 : 8);
-  ns = std::min(ns, nstrips);
-  if (ns >= 4) ns &= ~3;
-  c.NS = std::max(ns, 1);
-  // enough waves for the chip: with fewer than five a CU, two lane tiles (and half as many pixels to stage) beat four by
-  // 0.3 to 0.5 us (35x35x192->64 batch 16 4.65 -> 4.31, 14x14x512 batch 8 4.95 -> 4.51, 28x28x256->128 batch 8 4.26 -> 3.86; with
-  // six a CU 14x14x1024->256 batch 32 7.19 / 7.99), with fewer than two a CU one beats two (8x8x2048->192 batch 16
-  // 6.29 -> 5.36, with three 2048->384 6.52 / 7.09).  Eight strips share a tile then where they come in eights; where they
-  // do not, a tile that several workgroups stage stays wide on many pixels (9 strips, 20x20x936->136 batch 19 6.9 / 8.8; 17 strips,
-  // 28x28x800->272 batch 5 6.3 / 7.8) but not on few (15 strips, 12x12x888->232 batch 31 11.1 / 8.5)
-  const int64_t tiles = cdiv(P, 64);
-  const bool few = tiles < 96 && nstrips <= 16;
-  if (pitch > 128 && P > 64) {
-    const int two = nstrips <= 8 ? nstrips : nstrips % 8 == 0 ? 8 : 4, sets = cdiv(nstrips, two), pt0 = c.PT;
-    if (c.PT == 4 && (few || (tiles * nstrips < 1280 && (sets == 1 || (int64_t)P * sets * pitch <= (25 << 20))))) c.PT = 2;
-    if (c.PT == 2 && (int64_t)cdiv(P, 32) * nstrips < 448) c.PT = 1;
-    if (c.PT < pt0) c.NS = c.PT == 1 ? std::min(nstrips, 4) : two;
-  }
-  // enough workgroups: fewer strips each first, then smaller pixel tiles
-  while ((int64_t)cdiv(P, 16 * c.PT) * cdiv(nstrips, c.NS) < 160) {
-    if (c.NS >= 8)
-      c.NS = (c.NS / 2) & ~3;
-    else if (c.PT > 1)
-      c.PT /= 2;
-    else
-      break;
-  }
-  // (thin tiles by their number alone: 56x56x64->256 batch 1 3.27 -> 3.03)
-  if ((pitch <= 128 || P <= 64) && c.PT == 4 && few) {
-    c.PT = 2;
-    c.NS = nstrips <= 8 ? nstrips : 4;
-  }
-  if (i8 && nstrips < 4) c.PT = bsp_pw_thin(c.PT, pitch, c.NS);
-  const int64_t xb = (int64_t)16 * c.PT * pitch, ob = (int64_t)16 * c.PT * (c.NS * 32 + 16);
-  // (narrowing layers too where eight strips make two whole lines of a pixel and a CU holds as many workgroups with the image)
-  const bool lines = O >= I || (c.NS == 8 && kLdsLimit / (xb + ob) == kLdsLimit / xb);
-  c.wout = windowed && (c.NS % 4 == 0 || c.NS >= nstrips) && lines && xb + ob <= kLdsLimit;
-  return c;
-}
-
-}  // namespace
-
-namespace {
 
 int launch_pw(const ConvParams& p, int dtype, const void* plan_host, int shift, bool few, hipStream_t st) {
   const bool i8 = dtype == BSP_I8;
@@ -573,11 +516,11 @@ int launch_pw(const ConvParams& p, int dtype, const void* plan_host, int shift, 
 #endif
   const int maxsteps = rs[BSP_ROWS_MAXSTRIPSTEPS_W];
   const int depth = maxsteps <= 2 ? 2 : maxsteps <= 4 ? 4 : 8;
-  PwChoice ch = pw_choose(p.P, raw / 2, i8 ? (1 << 30) : p.O, nstrips, pitch, rs[BSP_ROWS_WINDOW_W] == 4, i8);
+  BspPwChoice ch = bsp_pw_choose(p.P, raw / 2, i8 ? (1 << 30) : p.O, nstrips, pitch, rs[BSP_ROWS_WINDOW_W] == 4, i8);
 #ifdef BSP_ROWS_TUNE  // experiments only: never defined in the product build
   if (const char* e = std::getenv("BSP_PWK_TUNE")) {
     int q[4];
-    if (sscanf(e, "%d,%d,%d,%d", q, q + 1, q + 2, q + 3) == 4) ch = PwChoice{q[0], q[1], q[2], q[3]};
+    if (sscanf(e, "%d,%d,%d,%d", q, q + 1, q + 2, q + 3) == 4) ch = BspPwChoice{q[0], q[1], q[2], q[3]};
   }
   if (const char* e = std::getenv("BSP_PW_TRACE_PTR")) a_trace = (long long*)std::strtoull(e, nullptr, 16);
   if (std::getenv("BSP_ROWS_VERBOSE"))

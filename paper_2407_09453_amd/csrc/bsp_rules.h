@@ -232,6 +232,71 @@ inline int bsp_pw_thin(int PT, int64_t pitch, int NS) {
   return PT;
 }
 
+// Pointwise kernel: tile of a layer of P pixels, I pairs of bytes per pixel in (2-byte channels, or pairs of codes) and O channels out (int8:
+// any large number), pitch bytes per staged pixel; windowed: the plan keeps the strips in fours of neighbours.
+//
+// One pixel group; four lane tiles a wave unless the tile's channels then exceed 128 KiB of LDS; few strips per workgroup
+// while pixels are plentiful or the tile is thin (many small workgroups hide each other's latencies), many when they are not (every
+// strip group re-reads the tile from L2, which is what bounds deep layers).
+//
+// Then enough waves for the chip.  With fewer than five a CU, two lane tiles (and half as many pixels to stage) beat four by 0.3
+// to 0.5 us (35x35x192->64 batch 16 4.65 -> 4.31, 14x14x512 batch 8 4.95 -> 4.51, 28x28x256->128 batch 8 4.26 -> 3.86; with six a CU
+// 14x14x1024->256 batch 32 7.19 / 7.99), of many strips by more (18x18x1536->1504 int8 batch 2 10.4 -> 6.3), with fewer than two a CU one beats two (8x8x2048->192 batch 16
+// 6.29 -> 5.36, with three 2048->384 6.52 / 7.09).  Eight strips share a tile then where they come in eights; where they do
+// not, a tile that several workgroups stage stays wide on many pixels (9 strips, 20x20x936->136 batch 19 6.9 / 8.8; 17 strips,
+// 28x28x800->272 batch 5 6.3 / 7.8) but not on few (15 strips, 12x12x888->232 batch 31 11.1 / 8.5).  Thinner tiles go by their number
+// alone (56x56x64->256 batch 1 3.27 -> 3.03).  The line at five waves a CU over 2500 layers between one and eight, cold data, with all of this / four lane
+// tiles or fewer strips: geometric mean 0.983; 38 layers gain a quarter or more, 9 lose 5 to 11 %, all within a tenth of the line
+// (dense 32x32x376->120 batch 9 6.7 / 7.5, 25x25x288->272 stride 2 batch 28 5.4 / 5.9, int8 21x21x880->128 batch 22 7.4 / 7.9).
+//
+// Whole-line output for layers that widen (their output is the bulk of the traffic), and for narrowing ones whose channels come
+// in eight strips, two whole lines of a pixel, where a CU holds as many workgroups with the image (cold 25x25x648->512 batch 6 9.0
+// -> 8.4; 42 strips, 11x11x712->664 batch 17 7.0 / 7.9; 9 strips, 37x37x688->144 batch 8 8.8 / 9.4; 504 channels, 38x38x1360
+// stride 2 batch 5 8.0 / 8.5).
+struct BspPwChoice {
+  int PT, PG, NS;
+  int wout;      // results leave through an LDS image of whole output lines
+};
+inline BspPwChoice bsp_pw_choose(int64_t P, int I, int O, int nstrips, int pitch, bool windowed, bool i8) {
+  constexpr int64_t lds = 160 * 1024;
+  auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  auto least = [](int a, int b) { return a < b ? a : b; };
+  BspPwChoice c{4, 1, 1, 0};
+  while (c.PT > 1 && 16 * c.PT * pitch > 128 * 1024) c.PT /= 2;
+  int ns = least((P >= 50000 || (I <= 128 && P >= 20000)) ? 4 : (I >= 512 ? 16 : 8), nstrips);
+  if (ns >= 4) ns &= ~3;
+  c.NS = ns > 1 ? ns : 1;
+  const int64_t tiles = cdiv(P, 64);
+  const bool few = tiles < 96 && nstrips <= 16;
+  if (pitch > 128 && P > 64) {
+    const int two = nstrips <= 8 ? nstrips : nstrips % 8 == 0 ? 8 : 4, sets = (int)cdiv(nstrips, two), pt0 = c.PT;
+    if (c.PT == 4 && (few || (tiles * nstrips < 1280 && (sets == 1 || P * sets * pitch <= (25 << 20))))) c.PT = 2;
+    if (c.PT == 2 && cdiv(P, 32) * nstrips < 448) c.PT = 1;
+    if (c.PT < pt0) c.NS = c.PT == 1 ? least(nstrips, 4) : two;
+  }
+  // enough workgroups: fewer strips each first, then smaller pixel tiles (six strips in one workgroup, 42x42x848->88 batch 2, or
+  // four and two with twice the pixels: 6.7 / 6.0)
+  while (cdiv(P, 16 * c.PT) * cdiv(nstrips, c.NS) < 160) {
+    if (c.NS >= 8)
+      c.NS = (c.NS / 2) & ~3;
+    else if (c.NS > 4)
+      c.NS = 4;
+    else if (c.PT > 1)
+      c.PT /= 2;
+    else
+      break;
+  }
+  if ((pitch <= 128 || P <= 64) && c.PT == 4 && few) {
+    c.PT = 2;
+    c.NS = nstrips <= 8 ? nstrips : 4;
+  }
+  if (i8 && nstrips < 4) c.PT = bsp_pw_thin(c.PT, pitch, c.NS);
+  const int64_t xb = (int64_t)16 * c.PT * pitch, ob = (int64_t)16 * c.PT * (c.NS * 32 + 16);
+  const bool lines = O >= I || (c.NS == 8 && O % 128 == 0 && lds / (xb + ob) == lds / xb);
+  c.wout = windowed && (c.NS % 4 == 0 || c.NS >= nstrips) && lines && xb + ob <= lds;
+  return c;
+}
+
 // fp32: whether the general kernel is to take the layer.  It sums a strip of sixteen channels chunk by
 // chunk and tap by tap (`pairs` of them over all strips), straight from memory: few of those are over
 // before the other kernel has staged its first patch, and its results leave in longer runs.  Timed on

@@ -19,6 +19,14 @@ static void is(bool got, bool want, const char* what) {
 #define BEATS(want, ...) is(bsp_any_beats_bf16(__VA_ARGS__), want, #__VA_ARGS__)
 #define FEW(want, ...) is(bsp_any_few(__VA_ARGS__), want, #__VA_ARGS__)
 #define DIRECT(want, ...) is(bsp_any_direct(__VA_ARGS__), want, #__VA_ARGS__)
+static void pw(int PT, int NS, int wout, int P, int I, int O, bool i8) {
+  const int raw = i8 ? I : 2 * I, pitch = raw <= 128 ? 128 : (raw + 255) & ~255;
+  const BspPwChoice c = bsp_pw_choose(P, raw / 2, i8 ? 1 << 30 : O, (O + 15) / 16, pitch, true, i8);
+  if (c.PT != PT || c.NS != NS || c.wout != wout) {
+    std::printf("P %d I %d O %d: %d %d %d, not %d %d %d\n", P, I, O, c.PT, c.NS, c.wout, PT, NS, wout);
+    ++wrong;
+  }
+}
 #define LDS8(want, ...) is(bsp_any_beats_lds_i8(__VA_ARGS__), want, #__VA_ARGS__)
 #define GEN8(want, ...) is(bsp_i8_general(__VA_ARGS__), want, #__VA_ARGS__)
 #define THIN(want, ...) is(bsp_pw_thin(__VA_ARGS__) == want, true, #__VA_ARGS__)
@@ -212,6 +220,24 @@ int main() {
   GEN8(false, 40, 16, 1, 1000);
   GEN8(false, 17, 16, 1, 1000);
   GEN8(false, 16, 16, 3, 1000);
+  // pointwise tiles: lane tiles, strips a workgroup, whole lines; pixels, channels in and out, int8
+  pw(2, 4, 0, 16 * 1225, 192, 64, false);                                 // 4.65 -> 4.31, four strips: 1228 waves
+  pw(4, 4, 0, 16 * 1281, 192, 64, false);                                 // 1284
+  pw(2, 8, 1, 8 * 196, 512, 512, false);                                  // 4.95 -> 4.51
+  pw(2, 8, 0, 8 * 784, 256, 128, false);                                  // 4.26 -> 3.86
+  pw(4, 8, 1, 32 * 196, 1024, 256, false);                                // 7.19 / 7.99: 1568
+  pw(2, 4, 1, 2 * 324, 1536, 1504, true);                                 // 10.4 -> 6.3
+  pw(1, 4, 0, 16 * 64, 2048, 192, false);                                 // 6.29 -> 5.36: 384
+  pw(2, 4, 0, 16 * 64, 2048, 384, false);                                 // 6.52 / 7.09: 768
+  pw(4, 8, 0, 19 * 400, 936, 136, false);                                 // 6.9 / 8.8: 27 MB staged
+  pw(4, 8, 0, 5 * 784, 800, 272, false);                                  // 6.3 / 7.8
+  pw(2, 4, 0, 31 * 144, 888, 232, false);                                 // 11.1 / 8.5
+  pw(2, 4, 0, 2 * 1764, 848, 88, false);                                  // 6.0 / 6.7 as one lane tile of six strips
+  pw(4, 8, 0, 17 * 121, 712, 664, false);                                 // 7.0 / 7.9 as whole lines: 42 strips
+  pw(4, 8, 0, 8 * 1369, 688, 144, false);                                 // 8.8 / 9.4: 9 strips
+  pw(4, 8, 1, 6 * 625, 648, 512, false);                                  // cold 9.0 -> 8.4 as whole lines
+  pw(2, 8, 0, 5 * 441, 848, 504, false);                                  // 8.1 / 8.4
+  pw(2, 4, 1, 3136, 64, 256, false);                                      // 3.27 -> 3.03: thin tiles by their number
   // lane tiles, bytes of a pixel, strips
   THIN(2, 4, 256, 1);
   THIN(1, 4, 512, 1);
