@@ -476,6 +476,7 @@ inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 struct Pick {
   int32_t PT, PG, NS, ks, CW, nchunk, tpc, TPW, spst, lds;
+  double cost;
 };
 
 // Tile, staging and split by a model of the busiest CU in clocks: the workgroups it runs, each with
@@ -516,7 +517,7 @@ Pick choose(int B, int M, int N, int os, int nstrips, int steps, int nslabs, int
               const double cost = percu * (comp + stage + fix);
               if (cost < best_cost) {
                 best_cost = cost;
-                best = Pick{PT, PG, NS, ks, cw, (int32_t)nchunk, (int32_t)tpc, tpw, spst, (int32_t)ldsb};
+                best = Pick{PT, PG, NS, ks, cw, (int32_t)nchunk, (int32_t)tpc, tpw, spst, (int32_t)ldsb, cost};
               }
             }
           if (spst == 1) break;
@@ -704,10 +705,34 @@ const int32_t* plan_of(const ConvParams& p, int dtype, const void* plan_host) {
 
 }  // namespace
 
+// The models of both kernels, weighed: a pure function of the layer, its plan and the device, so its answers are kept.
+static bool model_beats_rows(const ConvParams& p, const int32_t* hdr, int64_t mm) {
+  if (p.sh != p.sw || p.sh > 2 || hdr[BSP_PLAN_OFF_ROWS_W] == 0) return false;
+  const int32_t* rs = hdr + hdr[BSP_PLAN_OFF_ROWS_W];
+  const int nstrips = hdr[BSP_PLAN_NSTRIPS_W], nsteps = hdr[BSP_PLAN_NSTEPS_W];
+  static std::mutex mu;
+  static std::map<std::array<int32_t, 13>, bool> memo;
+  const std::array<int32_t, 13> key = {p.B, p.M, p.N, p.I, p.O, p.H * 4 + p.K, p.sh, p.ph * 65536 + p.pw, nsteps, hdr[BSP_PLAN_NSLABS_W], rs[BSP_ROWS_NCS_W], rs[BSP_ROWS_NSTRIPS_W],
+                                       rs[BSP_ROWS_CW_W] * 4096 + rs[BSP_ROWS_SLAB_W]};
+  std::unique_lock<std::mutex> lock(mu);
+  const auto it = memo.find(key);
+  if (it != memo.end()) return it->second;
+  lock.unlock();  // other layers' launches do not wait for this one's searches
+  const Pick pick = choose(p.B, p.M, p.N, 2, nstrips, cdiv(nsteps, nstrips), hdr[BSP_PLAN_NSLABS_W], hdr[BSP_PLAN_SLAB_W] / 8, cdiv(p.I, 8), p.H, p.K, p.sh, p.sw, false);
+  const bool beats = pick.PT && bsp_any_model_beats(p.sh > 1, mm, p.N, pick.cost, bsp_rows_cost(p, rs));
+  lock.lock();
+  if (memo.size() > 4096) memo.clear();
+  memo.emplace(key, beats);
+  return beats;
+}
+
 bool bsp_any_beats(const ConvParams& p, const void* plan_host, BspRival rival) {
   const int32_t* hdr = plan_of(p, BSP_BF16, plan_host);
-  return hdr && bsp_any_beats_bf16(rival, hdr[BSP_PLAN_BO_W], p.H, p.K, p.sh > 1 || p.sw > 1,
-                                   (int64_t)((p.P + 15) / 16) * hdr[BSP_PLAN_NSTEPS_W], (int64_t)p.P * p.O, p.I, p.O, p.N);
+  if (!hdr) return false;
+  const int64_t mm = (int64_t)((p.P + 15) / 16) * hdr[BSP_PLAN_NSTEPS_W];
+  const bool strided = p.sh > 1 || p.sw > 1;
+  if (bsp_any_beats_bf16(rival, hdr[BSP_PLAN_BO_W], p.H, p.K, strided, mm, (int64_t)p.P * p.O, p.I, p.O)) return true;
+  return rival == BSP_RIVAL_ROWS && bsp_any_models_decide(p.H, p.K, strided, mm, p.P, p.O) && model_beats_rows(p, hdr, mm);
 }
 
 bool bsp_any_beats_i8(const ConvParams& p, const void* plan_host) {

@@ -26,20 +26,9 @@ enum BspRival { BSP_RIVAL_BAND, BSP_RIVAL_ROWS, BSP_RIVAL_LDS, BSP_RIVAL_TILE };
 //     470 K) 5.4 / 5.9
 //   3x3, the others: 10x10x112->336 batch 5 (15 904) 8.6 / 5.4; 111x11x40->16 batch 30 (20 610) 5.6 / 6.9;
 //     stride 2 35x35x72->224 batch 7 (58 424) 14.3 / 10.2, 39x39x8->160 batch 21 (59 910, po 5.1 M) 8.4 / 14.0
-//   row-band kernel, windows of three rows or one column: 630 layers of at least 128 channels in on both sides, once
-//     the any-shape kernel waited for one slot of its ring at a time (row-band / here): 3x3 17x17x192->320 batch 16
-//     stride 2 (66 K) 11.0 / 8.1, 8x8x448->384 batch 16 (155 K) 11.2 / 9.6, 26x26x240->96 batch 6 (103 K) 12.9 / 7.6,
-//     14x14x256 batch 8 (91 K) 7.7 / 7.5, 24x24x192->152 batch 6 (94 K) 8.7 / 9.1; past them 21x22x304->280 batch 4
-//     (179 K) 10.6 / 13.2, 14x14x168->320 batch 22 (205 K) 9.4 / 11.1; few strips of many pixels 54x54x248->56 batch
-//     2 (48 K) 7.0 / 7.6, more of them 50x50x232->80 batch 4 9.2 / 11.0 (and from 8 192 pixels the persistent
-//     kernel's), of few pixels 58x58x584->32 batch 1 (65 K) 16.1 / 7.6; 7x1 goes either way past its line (17x17x192
-//     batch 16 (117 K) 10.7 / 8.9, 30x32x216->144 batch 6 (123 K) 10.3 / 14.3); 3x1 8x8x384 batch 16 (44 K) 8.5 /
-//     6.5, past it 32x32x496->56 batch 21 (200 K) 11.9 / 13.6; strided 3x1 1.3 to 2.3 times.  Between 115 and 160 K
-//     only rows of at most eight results, where two bands in a lane tile of the row-band kernel meet in the banks;
-//     and with weights that come from memory (142 of 400 random layers change sides and take 0.77 of their time,
-//     seven of them 5 to 30 % more) many of them are better asked for by few workgroups: 10x10x512 batch 5 12.0 /
-//     13.3 (from the caches 10.2 / 10.1), 7x7x512 batch 8 12.5 / 10.7; stride 2 14x14x512 batch 8 14.0 / 15.6,
-//     35x35x488->288 batch 3 (151 K) 21.5 / 29.5
+//   one column, row-band kernel, 8x8 blocks, more than 32 channels: 284 layers; 3x1 8x8x384 batch 16 (44 K) 8.5 / 6.5, 35x35x488->88 batch 3
+//     (63 480, 3675 pixels) 0.54, 12x12x384->280 batch 15 (69 120, 2160) 1.12 the other way; past 5000 pixels as many lose as gain
+//     (28x28x216->64 batch 18, 74 088, 1.24); strided ones 1.1 to 2.3 times faster here, all 92 up to 340 K
 //   larger windows, row-band kernel (three or seven rows): 3x5 13x13x184->24 batch 8 (6 860) 8.8 / 5.3,
 //     34x11x168->24 batch 27 (99 856) 7.9 / 14.4; 7x7 11x9x144->8 batch 6 (3 268) 8.0 / 5.8,
 //     18x10x288->112 batch 15 (489 086) 16.5 / 31.5
@@ -48,34 +37,46 @@ enum BspRival { BSP_RIVAL_BAND, BSP_RIVAL_ROWS, BSP_RIVAL_LDS, BSP_RIVAL_TILE };
 //   larger windows, ring-tile kernel: 5x5 25x25x248->16 batch 3 (po 30 K) 43 / 8.3, 85x85x16->448 batch 3
 //     (po 9.7 M) 15.3 / 21.8; 7x7 32x32x232->32 batch 4 (po 131 K) 66 / 13, 37x8x64->144 batch 27 (po
 //     1.2 M) 18.7 / 24.2
-inline bool bsp_any_beats_bf16(BspRival rival, int bo, int H, int K, bool strided, int64_t mm, int64_t po, int64_t I, int64_t O,
-                               int64_t N = 0) {
+inline bool bsp_any_beats_bf16(BspRival rival, int bo, int H, int K, bool strided, int64_t mm, int64_t po, int64_t I, int64_t O) {
   if (H == 1 && K == 1) return rival == BSP_RIVAL_TILE;
   if (H == 1) {
-    if (rival == BSP_RIVAL_ROWS) return bo == 16 || mm <= (I <= 208 ? 240000 : O > 32 ? 200000 : 120000);
+    if (rival == BSP_RIVAL_ROWS) return bo == 16 || mm <= (I <= 208 ? 240000 : 200000);
     return rival == BSP_RIVAL_TILE || strided || (mm <= (bo == 16 ? 1000000 : 120000) && po <= 4000000);
   }
   if (K == 1) {
     if (rival == BSP_RIVAL_TILE) return true;
     if (H <= 3 && rival == BSP_RIVAL_ROWS && strided) return mm <= 340000 && po <= 10000000;
-    if (H <= 3) return mm <= (rival == BSP_RIVAL_ROWS && bo == 8 && O > 32 ? 80000 : 45000) && po <= 4000000;
+    if (H <= 3) return mm <= (rival == BSP_RIVAL_ROWS && bo == 8 && O > 32 && po <= 5000 * O ? 80000 : 45000) && po <= 4000000;
     if (rival == BSP_RIVAL_ROWS) return strided || mm <= 100000;
     return (mm <= 100000 && po <= 4000000) || (strided && po <= 10000000);
   }
   if (H <= 3 && K <= 3) {
     if (rival == BSP_RIVAL_TILE) return true;
     if (rival == BSP_RIVAL_BAND) return mm <= 25000 && po <= 250000;
-    if (rival == BSP_RIVAL_ROWS && po <= 3000000) {
-      const bool heavy = I * O > 230000;
-      if (strided) return mm <= (heavy ? 60000 : 140000);
-      if (po > (O <= 64 ? 5500 : 8000) * O) return mm <= 30000;
-      return mm <= (O <= 64 ? 60000 : bo == 8 && 3 * O >= I && N <= 8 ? 160000 : heavy && N > 8 ? 30000 : 115000);
-    }
     return mm <= (strided ? 60000 : 30000) && po <= 3000000;
   }
   if (rival == BSP_RIVAL_ROWS) return H <= 3 ? mm <= 80000 && po <= 300000 : mm <= 30000;
   if (rival == BSP_RIVAL_LDS) return mm <= (bo == 4 ? 25000 : 80000) && po <= 3000000;
   return H * K <= 25 ? O < 272 || po <= 1000000 : O < 136 || po <= 800000;
+}
+
+// 3x3 windows past those lines: whether the two kernels' own models of the layer decide between the any-shape and the row-band
+// kernel, and how (`any`: clocks of the busiest CU, `rows`: rough ns).  Neither model knows the other's scale, and the row-band
+// one misses by a fifth either way, so the line is a ratio, drawn where few lose.  Of 3630 random layers of at least 128 channels in,
+// with data in the caches, with cold weights and with all data cold, those past the lines above:
+//   stride 1, up to 8000 pixels (5000 of up to 64 channels out) and 115 K, of few pixels 200 K: 666 of 2009 are taken, 0.76 of their time in
+//     the mean; 7 lose more than 5 % somewhere (the worst 18x24x224->144 batch 8 1.25 to 1.28, 12x12x480->40 batch 22 1.16 to 1.27;
+//     of 1500 others, also of the class below, 25x25x480->32 batch 11 1.18 to 1.24).  By matrix instructions, channels and rows alone
+//     893 were taken, 79 of them at a loss (cold 52x52x368->32 stride 2 batch 17 16 / 30, 15x11x480->136 batch 11 11.0 / 14.7,
+//     24x24x392->88 batch 6 10.3 / 13.0, 35x35x176->488 batch 2 9.8 / 12.0)
+//   stride 2, more than 40 channels out, up to 300 K: 151 of 431, 0.72 of their time, 6 lose more than 5 % (before: 254, 49).  Short
+//     rows lose the row-band kernel a part of every lane tile, so up to 100 K they go by another ratio (17x17x192->320 batch 16 11.0 / 8.1)
+inline bool bsp_any_models_decide(int H, int K, bool strided, int64_t mm, int64_t P, int64_t O) {
+  if (H > 3 || K > 3 || H == 1 || K == 1 || P * O > 3000000) return false;
+  return strided ? mm <= 300000 && O > 40 : mm <= (P <= 1500 ? 200000 : 115000) && P <= (O <= 64 ? 5000 : 8000);
+}
+inline bool bsp_any_model_beats(bool strided, int64_t mm, int64_t N, double any, double rows) {
+  return any < (!strided ? 3.0 : N <= 16 && mm <= 100000 ? 2.4 : 2.0) * rows;
 }
 
 // bf16 layers on the any-shape kernel: whether results leave straight from the accumulators, eight bytes a lane (po: results).

@@ -72,6 +72,30 @@ def test_any_shape_or_row_bands(B, L, J, I, O, H, K, stride, any_shape):
     assert bool(((out.double() - want).abs() <= 6e-3 * scale).all())   # one rounding to bf16 is 3.9e-3 at most
 
 
+@pytest.mark.parametrize("B,L,I,O,H,K,stride,least,most,any_shape", [
+    (4, 24, 360, 264, 1, 7, 1, 120000, 200000, True), (7, 24, 360, 264, 1, 7, 1, 200000, 300000, False),
+    (4, 35, 488, 88, 3, 1, 1, 45000, 80000, True), (18, 28, 216, 64, 3, 1, 1, 45000, 80000, False),     # up to 5000 pixels, and more
+    (28, 30, 360, 256, 3, 1, 2, 45000, 340000, True),
+    (7, 48, 280, 88, 3, 3, 2, 60000, 300000, True), (2, 56, 416, 56, 3, 3, 2, 30000, 60000, True), (20, 47, 416, 40, 3, 3, 2, 60000, 300000, False),
+    (5, 16, 488, 176, 3, 3, 1, 30000, 115000, True), (6, 24, 392, 88, 3, 3, 1, 30000, 115000, False),   # by the kernels' models
+    (14, 8, 448, 384, 3, 3, 1, 115000, 200000, True), (16, 14, 256, 256, 3, 3, 1, 115000, 300000, False),  # few pixels, and more
+])
+def test_lines_to_the_row_band_kernel(B, L, I, O, H, K, stride, least, most, any_shape):
+    """Layers inside each band of matrix instructions that bsp_rules.h gives the any-shape or the row-band kernel (or the one before it)."""
+    import torch
+    X, W, gamma, keep = _draw(I + O, B, L, L, I, O, H, K, 8, 8)
+    X, W, pad = X.bfloat16(), W.bfloat16(), (H // 2, K // 2)
+    layer = bsp.BspLayer(W.float().cpu().numpy(), gamma, 8, 8, "bf16")
+    out = torch.full(layer.out_shape(B, L, L, (stride, stride), pad), float("nan"), dtype=torch.bfloat16, device="cuda")
+    mm = -(-out.numel() // O // 16) * int(layer.plan[18])  # steps of all strips
+    assert least < mm <= most, mm
+    ran = kernels_of(lambda: layer.conv2d(X, (stride, stride), pad, out=out))
+    assert any("conv_any" in k for k in ran) == any_shape, ran
+    want = conv_fp64(X, W * keep, stride, pad)
+    scale = torch.maximum(want.abs(), want.pow(2).mean().sqrt())
+    assert bool(((out.double() - want).abs() <= 6e-3 * scale).all())   # one rounding to bf16 is 3.9e-3 at most
+
+
 F32 = [
     (34, 15, 15, 5, 125, 1, 1, 1, (16, 4), "conv_general"), (25, 49, 49, 79, 180, 1, 1, 1, (16, 4), "conv_f32<"),
     (6, 14, 14, 11, 118, 1, 1, 1, (8, 8), "conv_general"), (4, 13, 21, 64, 102, 1, 3, 1, (8, 8), "conv_f32x3<"),

@@ -27,6 +27,7 @@ static void pw(int PT, int NS, int wout, int P, int I, int O, bool i8) {
     ++wrong;
   }
 }
+#define MODELS(want, ...) is(bsp_any_models_decide(__VA_ARGS__), want, #__VA_ARGS__)
 #define LDS8(want, ...) is(bsp_any_beats_lds_i8(__VA_ARGS__), want, #__VA_ARGS__)
 #define GEN8(want, ...) is(bsp_i8_general(__VA_ARGS__), want, #__VA_ARGS__)
 #define THIN(want, ...) is(bsp_pw_thin(__VA_ARGS__) == want, true, #__VA_ARGS__)
@@ -67,6 +68,41 @@ int main() {
   BEATS(false, BSP_RIVAL_TILE, 16, 5, 5, false, 230350, 9710400, 16, 448);    // 15.3 / 21.8
   BEATS(true, BSP_RIVAL_TILE, 8, 7, 7, false, 182272, 131072, 232, 32);       // 66 / 13
   BEATS(false, BSP_RIVAL_TILE, 8, 7, 7, false, 326500, 1150848, 64, 144);     // 18.7 / 24.2
+  // row-band kernel, one row of more than 208 channels in: up to 200 K
+  BEATS(true, BSP_RIVAL_ROWS, 8, 1, 7, false, 166181, 836352, 296, 384);      // 0.72 to 0.76 of the time here
+  BEATS(true, BSP_RIVAL_ROWS, 8, 1, 7, false, 197010, 842400, 344, 160);      // 0.46
+  BEATS(false, BSP_RIVAL_ROWS, 8, 1, 7, false, 216216, 658944, 384, 176);     // 1.05 to 1.14
+  // one column: 8x8 blocks, more than 32 channels and up to 5000 pixels to 80 K, else to 45 K; strided to 340 K
+  BEATS(true, BSP_RIVAL_ROWS, 8, 3, 1, false, 63480, 323400, 488, 88);        // 0.54
+  BEATS(false, BSP_RIVAL_ROWS, 8, 3, 1, false, 74088, 903168, 216, 64);       // 1.24: 14 112 pixels
+  BEATS(false, BSP_RIVAL_ROWS, 8, 3, 1, false, 48320, 618240, 208, 32);       // 1.23 to 1.39
+  BEATS(false, BSP_RIVAL_ROWS, 4, 3, 1, false, 74556, 496128, 408, 136);      // 1.06 to 1.13
+  BEATS(false, BSP_RIVAL_ROWS, 8, 3, 1, false, 83897, 1183200, 376, 232);     // 1.07 to 1.10
+  BEATS(true, BSP_RIVAL_ROWS, 8, 3, 1, true, 214336, 1612800, 360, 256);      // 0.82 to 0.85
+  BEATS(false, BSP_RIVAL_ROWS, 8, 3, 1, true, 351890, 5378688, 208, 368);     // not timed past the line but here (0.53 to 0.63)
+  // 3x3: 30 K and, strided, 60 K; past them the two kernels' models decide
+  BEATS(true, BSP_RIVAL_ROWS, 8, 3, 3, false, 29000, 300000, 256, 128);
+  BEATS(false, BSP_RIVAL_ROWS, 8, 3, 3, false, 30001, 300000, 256, 128);
+  BEATS(true, BSP_RIVAL_ROWS, 8, 3, 3, true, 60000, 300000, 256, 128);
+  BEATS(false, BSP_RIVAL_ROWS, 8, 3, 3, true, 60001, 300000, 256, 128);
+  // window, strided, matrix instructions, pixels, channels out
+  MODELS(true, 3, 3, false, 115000, 8000, 128);
+  MODELS(false, 3, 3, false, 115001, 8000, 128);
+  MODELS(false, 3, 3, false, 115000, 8001, 128);
+  MODELS(true, 3, 3, false, 115000, 5000, 64);
+  MODELS(false, 3, 3, false, 115000, 5001, 64);                           // 57x35x224->24 batch 5 1.11 to 1.25
+  MODELS(true, 3, 3, false, 200000, 1500, 128);
+  MODELS(false, 3, 3, false, 200001, 1500, 128);
+  MODELS(false, 3, 3, true, 117916, 11492, 32);                           // 52x52x368->32 stride 2 batch 17 16 / 30
+  MODELS(true, 3, 3, true, 300000, 11492, 48);
+  MODELS(false, 3, 3, true, 300001, 11492, 48);
+  MODELS(false, 3, 3, false, 100000, 7000, 432);                          // more than 3 M results
+  MODELS(false, 3, 1, false, 60000, 4000, 128);
+  MODELS(false, 5, 3, false, 60000, 4000, 128);
+  is(bsp_any_model_beats(false, 90000, 14, 2999., 1000.) && !bsp_any_model_beats(false, 90000, 14, 3000., 1000.), true, "models at stride 1");
+  is(bsp_any_model_beats(true, 100001, 14, 1999., 1000.) && !bsp_any_model_beats(true, 100001, 14, 2000., 1000.), true, "models at stride 2");
+  is(!bsp_any_model_beats(true, 100000, 17, 2000., 1000.), true, "models at stride 2, long rows");
+  is(bsp_any_model_beats(true, 100000, 16, 2399., 1000.) && !bsp_any_model_beats(true, 100000, 16, 2400., 1000.), true, "models at stride 2, short rows");
   // pointwise layers: never before the specialised kernels, before the ring-tile kernel always
   BEATS(false, BSP_RIVAL_ROWS, 8, 1, 1, false, 100, 1000, 64, 64);
   BEATS(false, BSP_RIVAL_LDS, 8, 1, 1, false, 100, 1000, 64, 64);
