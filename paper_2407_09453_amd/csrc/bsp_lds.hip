@@ -21,6 +21,7 @@
 //
 // Only kept blocks have steps (paper Section I, advantages 3-4): work and weight traffic
 // shrink with the mask, the patch traffic does not.
+#include "bsp_deal.h"
 #include "bsp_launch.h"
 #include "bsp_tile.h"
 
@@ -132,11 +133,14 @@ __global__ __launch_bounds__(kThreads, 1) void conv_lds(ConvParams p, TileCfg t,
   const bool loader = wave_all >= 4 * kPH;
 
   const uint32_t bid = blockIdx.x;
-  const uint32_t slot = c.tpx ? bid >> 3 : bid;
+  const uint32_t slot = bsp_lds_slot(c.tpx, bid);
   const int cidx = (int)fdiv(slot, c.d_groups);
   const int sg = (int)slot - cidx * c.groups;
-  const int tile0 = (int)(bid & 7u) * c.tpx, tend = c.tpx ? min(tile0 + c.tpx, t.ntiles) : t.ntiles;
-  int tile = tile0 + cidx;
+  // (the share's end takes a scalar register all through: the int8 instances that load weights again spill 20 to 22 scalars to lanes of a
+  // vector register, 9 to 11 when every workgroup walked all tiles.  Formed from the argument block at each tile's end
+  // instead it spills 5 to 13 and 400 layers take 0.6 % more: the loads wait where the spilled lanes do not)
+  const int tend = bsp_lds_end(c.tpx, bid, t.ntiles);
+  int tile = bsp_lds_first(c.tpx, bid) + cidx;
   if (tile >= tend) return;
 
   const int tpi = t.tiles_y * t.tiles_x;
@@ -666,16 +670,10 @@ int launch_lds(const ConvParams& p_in, int dtype, const void* plan_host, int shi
   if ((int64_t)ldsb > kLdsPerCu) return BSP_ERR_UNSUPPORTED;
   c.groups = (t.nstrips + 3) / 4;
   // persistent grid: one workgroup per CU, shared out among the strip groups
-  int64_t slots = device_cus() / c.groups;
-  if (slots < 1) slots = 1;
-  c.wg_per_group = (int32_t)(ntiles < slots ? ntiles : slots);
-  int64_t nwg = (int64_t)c.wg_per_group * c.groups;
-  c.tpx = 0;
-  if (32 % c.groups == 0 && device_cus() == 256) {  // (other numbers of groups would leave CUs idle)
-    c.tpx = (int32_t)((ntiles + 7) / 8);
-    c.wg_per_group = (int32_t)std::min<int64_t>(c.tpx, 32 / c.groups);
-    nwg = 8ll * c.wg_per_group * c.groups;
-  }
+  const LdsDeal deal = bsp_lds_deal(ntiles, c.groups, device_cus());
+  c.wg_per_group = deal.wg_per_group;
+  c.tpx = deal.tpx;
+  const int64_t nwg = deal.nwg;
   const int64_t npieces = (int64_t)t.TPH * t.TPW * (t.slab / BSP_CHUNK);
   // the multiply-high divisions of a tile number (by tiles per image, then by tiles per row;
   // of a workgroup number by the strip groups) are exact while dividend * divisor < 2^32
@@ -692,7 +690,6 @@ int launch_lds(const ConvParams& p_in, int dtype, const void* plan_host, int shi
   t.d_tpw = make_fastdiv(t.TPW);
   t.d_tw = make_fastdiv(t.TW);
   t.d_tpr = make_fastdiv(t.TW >= 8 ? t.TW >> 3 : 1);
-  t.d_ntiles = make_fastdiv((uint32_t)ntiles);
   t.d_tpi = make_fastdiv(t.tiles_y * t.tiles_x);
   t.d_tiles_x = make_fastdiv(t.tiles_x);
   c.d_groups = make_fastdiv(c.groups);

@@ -124,6 +124,24 @@ def test_lds_int8_kernel_alone_bit_exact(bo, bi):
             assert (Y.cpu().numpy() == oracle.requant_shift(acc, shift)).all(), (shape, bo, bi, shift)
 
 
+@pytest.mark.parametrize("B,L,O", [
+    (1, 8, 16), (1, 40, 64), (3, 46, 64), (9, 46, 16),      # one strip group: fewer tiles than XCDs, no multiple of eight, more than CUs
+    (3, 46, 128), (9, 46, 128), (2, 46, 256),               # two and four groups
+    (3, 46, 192), (9, 46, 160), (1, 8, 192),                # three: no divisor of an XCD's CUs
+])
+def test_lds_int8_kernel_deals_every_tile(B, L, O):
+    """Through the LDS-resident kernel alone: every tile of every strip group is there, and no other bytes are written."""
+    import torch
+    X, W, bias, gamma, s, p = _draw((B, L, L, 32, O, 3, 3, (1, 1), (1, 1)), 500 + O + L, 8, 8)
+    layer = bsp.BspLayerI8(W, gamma, 8, 8, bias=bias)
+    layer.struct.kernels = bsp.BSP_KERNEL_LDS
+    Y = torch.full((B + 2, L, L, O), 77, dtype=torch.int8, device="cuda")
+    ran = kernels_of(lambda: layer.conv2d(torch.from_numpy(X).cuda(), s, p, shift=9, out=Y[1:-1]))
+    assert any("conv_lds" in k for k in ran), ran
+    want = oracle.conv2d_i8(X, W, bias, gamma, 8, 8, s, p, shift=9)
+    assert (Y[1:-1].cpu().numpy() == want).all() and bool((Y[0] == 77).all()) and bool((Y[-1] == 77).all())
+
+
 def test_int8_config1_full_size():
     import torch
     from synthetic import config_cases
