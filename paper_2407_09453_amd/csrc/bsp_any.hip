@@ -156,7 +156,7 @@ __device__ __forceinline__ f32x4_t bias4(const AnyArgs& a, int ch) {
 // weights come from the plan through a register ring of D, its activations from LDS one step ahead.  (A ring of eight
 // with two or four steps read together, for one tile: 3x3 7x7x512 batch 1 as fast, 6.7 us, but a register budget that
 // holds four waves a SIMD instead of five, and scalars in scratch; FC int8 20600 -> 120 batch 5 19.5 us instead of 17.7.)
-// The bf16 instances keep up to a dozen scalars that only the results need in lanes of a vector register.  Reading
+// The bf16 instances keep up to eight scalars that only the results need in lanes of a vector register.  Reading
 // them from the argument block again there spills none and costs more: 232 small layers 1.3 to 1.7 % slower, 350 others 0.6 %.
 template <int KIND, int PT, bool VEC, bool DIRECT>
 __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
 
   // ---- staging: U 16-byte pieces per thread in flight.  Rounds of U pieces go out without a branch between them, the last
   // pieces one by one (not where the registers for both would not do)
-  constexpr bool ROUNDS = VEC || KIND == kI8 || PT < 4;
+  constexpr bool ROUNDS = VEC || PT < 4;
   u32x4_t v[U];
   int dst[U], off[U];
   auto ask = [&](int f0, int c0, auto whole) {  // f0: the wave's first piece, c0: first byte of a pixel that is staged
@@ -244,18 +244,28 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
 
     // ---- weights: a ring of D steps
     u32x4_t wr[D];
-    int dr[D], pos[D];  // descriptors; where the step's slab lies in a staged pixel, and is it the slab's first (1), its last (2) step
+    int dr[D];  // descriptors
+    // Where a step's slab lies in a staged pixel, its first step, the next slab's first.  int8 finds that when it asks for a step,
+    // bf16, which needs to know a slab's last step too, when it reads the step's activations (found at the request: 5x5
+    // 35x35x48->64 batch 16 10.5 -> 11.2 us, 1500 random layers 1.5 % more; int8 the other way round, 3x3 65x65x264->24 batch 4
+    // with 16x4 blocks 10.5 -> 11.1).
+    [[maybe_unused]] int pos[D];
     int fcs = slo + k, fsl = sl0, fadd = 0, fbeg = slo, fend = __builtin_amdgcn_readlane(tab, sl0 + 1);
-    auto fetch = [&](int d) {
-      const int cs = min(fcs, shi - 1);  // (past the end: the last step again, never used)
-      fcs += a.ks;
+    auto find = [&](int cs) {
       while (cs >= fend) {
         fadd += a.slab_bytes;
         ++fsl;
         fbeg = fend;
         fend = __builtin_amdgcn_readlane(tab, fsl + 1);
       }
-      pos[d] = fadd | (KIND == kBf16 ? (cs == fbeg) + 2 * (cs == fend - 1) : 0);  // (a slab is whole 16-byte pieces)
+    };
+    auto fetch = [&](int d) {
+      const int cs = min(fcs, shi - 1);  // (past the end: the last step again, never used)
+      fcs += a.ks;
+      if constexpr (KIND == kI8) {
+        find(cs);
+        pos[d] = fadd;
+      }
       dr[d] = *(const int*)(a.xdesc + ((uint32_t)cs * 16u + (uint32_t)g * 4u));
       wr[d] = *(const u32x4_t*)(a.wfrag + ((uint32_t)cs * 1024u + (uint32_t)lane * 16u));
     };
@@ -281,18 +291,24 @@ __global__ __launch_bounds__(512, 4) void conv_any(AnyArgs a) {
     __syncthreads();
 
     // ---- products
+    [[maybe_unused]] int rcs = slo + k;
     auto read = [&](int d, u32x4_t (&f)[PT]) {
+      [[maybe_unused]] const int cs = min(rcs, shi - 1);
+      if constexpr (KIND == kBf16) {
+        rcs += a.ks;
+        find(cs);
+      }
       uint32_t desc = (uint32_t)dr[d];
       asm volatile("" : "+v"(desc));  // decoded here, not where it is loaded: no early wait
-      const uint32_t o = ((desc & 0xFFFFu) << 4) + (uint32_t)(pos[d] & ~15) + __umul24((desc >> 16) & 0xFFu, rowpitch) +
+      const uint32_t o = ((desc & 0xFFFFu) << 4) + (uint32_t)(KIND == kI8 ? pos[d] : fadd) + __umul24((desc >> 16) & 0xFFu, rowpitch) +
                          __umul24(desc >> 24, a.pitch);
 #pragma unroll
       for (int t = 0; t < PT; ++t) f[t] = *(const u32x4_t*)(lds + base[t] + o);
       if constexpr (KIND == kBf16) {
         // a pair that fills up a slab's last step multiplies zeros with zeros, not with whatever
         // (an infinity) lies at its descriptor's address
-        if (pos[d] & 2) {
-          const bool real = desc != 0u || (g == 0 && (pos[d] & 1));
+        if (cs == fend - 1) {
+          const bool real = desc != 0u || (g == 0 && cs == fbeg);
 #pragma unroll
           for (int t = 0; t < PT; ++t) f[t] = real ? f[t] : u32x4_t{0u, 0u, 0u, 0u};
         }
@@ -719,7 +735,7 @@ static bool model_beats_rows(const ConvParams& p, const int32_t* hdr, int64_t mm
   if (it != memo.end()) return it->second;
   lock.unlock();  // other layers' launches do not wait for this one's searches
   const Pick pick = choose(p.B, p.M, p.N, 2, nstrips, cdiv(nsteps, nstrips), hdr[BSP_PLAN_NSLABS_W], hdr[BSP_PLAN_SLAB_W] / 8, cdiv(p.I, 8), p.H, p.K, p.sh, p.sw, false);
-  const bool beats = pick.PT && bsp_any_model_beats(p.sh > 1, mm, p.N, pick.cost, bsp_rows_cost(p, rs));
+  const bool beats = pick.PT && bsp_any_model_beats(p.sh > 1, mm, p.O, pick.cost, bsp_rows_cost(p, rs));
   lock.lock();
   if (memo.size() > 4096) memo.clear();
   memo.emplace(key, beats);

@@ -73,10 +73,10 @@ inline bool bsp_any_beats_bf16(BspRival rival, int bo, int H, int K, bool stride
 //     rows lose the row-band kernel a part of every lane tile, so up to 100 K they go by another ratio (17x17x192->320 batch 16 11.0 / 8.1)
 inline bool bsp_any_models_decide(int H, int K, bool strided, int64_t mm, int64_t P, int64_t O) {
   if (H > 3 || K > 3 || H == 1 || K == 1 || P * O > 3000000) return false;
-  return strided ? mm <= 300000 && O > 40 : mm <= (P <= 1500 ? 200000 : 115000) && P <= (O <= 64 ? 5000 : 8000);
+  return strided ? mm <= 300000 && O > 40 : mm <= (P <= 1500 ? 200000 : 115000) && P <= (O <= 64 ? 6500 : 8000);
 }
-inline bool bsp_any_model_beats(bool strided, int64_t mm, int64_t N, double any, double rows) {
-  return any < (!strided ? 3.0 : N <= 16 && mm <= 100000 ? 2.4 : 2.0) * rows;
+inline bool bsp_any_model_beats(bool strided, int64_t mm, int64_t O, double any, double rows) {
+  return any < (!strided ? 3.3 : mm <= 140000 && O > 72 ? 2.6 : 2.1) * rows;
 }
 
 // bf16 layers on the any-shape kernel: whether results leave straight from the accumulators, eight bytes a lane (po: results).

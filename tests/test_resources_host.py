@@ -42,10 +42,10 @@ def _kernels(tmp_path):
 @pytest.mark.skipif(not os.path.exists(READELF) or not shutil.which("hipcc"), reason="no ROCm toolchain")
 def test_any_shape_kernel_keeps_its_registers(tmp_path):
     """No scratch and no spilled vector register in any instance, one lane tile in the registers of five waves a SIMD
-    (512 / 5 in eights); a dozen scalars at most wait in lanes of a vector register until the results need them."""
+    (512 / 5 in eights); eight scalars at most wait in lanes of a vector register until the results need them."""
     found = {k: v for k, v in _kernels(tmp_path).items() if "conv_anyILi" in k}
     assert len(found) == 18, sorted(found)  # bf16: three lane tiles, aligned pixels or not, two ways out; int8: one way out
     for name, r in found.items():
         assert r["private_segment_fixed_size"] == 0 and r["vgpr_spill_count"] == 0, (name, r)
-        assert r["sgpr_spill_count"] <= 12, (name, r)
+        assert r["sgpr_spill_count"] <= 8, (name, r)
         assert r["vgpr_count"] <= (96 if "ELi1ELb" in name else 128), (name, r)

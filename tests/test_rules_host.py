@@ -89,8 +89,8 @@ int main() {
   MODELS(true, 3, 3, false, 115000, 8000, 128);
   MODELS(false, 3, 3, false, 115001, 8000, 128);
   MODELS(false, 3, 3, false, 115000, 8001, 128);
-  MODELS(true, 3, 3, false, 115000, 5000, 64);
-  MODELS(false, 3, 3, false, 115000, 5001, 64);                           // 57x35x224->24 batch 5 1.11 to 1.25
+  MODELS(true, 3, 3, false, 115000, 6500, 64);
+  MODELS(false, 3, 3, false, 115000, 6501, 64);                           // 57x35x224->24 batch 5 1.11 to 1.25
   MODELS(true, 3, 3, false, 200000, 1500, 128);
   MODELS(false, 3, 3, false, 200001, 1500, 128);
   MODELS(false, 3, 3, true, 117916, 11492, 32);                           // 52x52x368->32 stride 2 batch 17 16 / 30
@@ -99,10 +99,10 @@ int main() {
   MODELS(false, 3, 3, false, 100000, 7000, 432);                          // more than 3 M results
   MODELS(false, 3, 1, false, 60000, 4000, 128);
   MODELS(false, 5, 3, false, 60000, 4000, 128);
-  is(bsp_any_model_beats(false, 90000, 14, 2999., 1000.) && !bsp_any_model_beats(false, 90000, 14, 3000., 1000.), true, "models at stride 1");
-  is(bsp_any_model_beats(true, 100001, 14, 1999., 1000.) && !bsp_any_model_beats(true, 100001, 14, 2000., 1000.), true, "models at stride 2");
-  is(!bsp_any_model_beats(true, 100000, 17, 2000., 1000.), true, "models at stride 2, long rows");
-  is(bsp_any_model_beats(true, 100000, 16, 2399., 1000.) && !bsp_any_model_beats(true, 100000, 16, 2400., 1000.), true, "models at stride 2, short rows");
+  is(bsp_any_model_beats(false, 90000, 64, 3299., 1000.) && !bsp_any_model_beats(false, 90000, 64, 3300., 1000.), true, "models at stride 1");
+  is(bsp_any_model_beats(true, 140000, 80, 2599., 1000.) && !bsp_any_model_beats(true, 140000, 80, 2600., 1000.), true, "models at stride 2");
+  is(bsp_any_model_beats(true, 140001, 80, 2099., 1000.) && !bsp_any_model_beats(true, 140001, 80, 2100., 1000.), true, "models at stride 2, large");
+  is(bsp_any_model_beats(true, 140000, 72, 2099., 1000.) && !bsp_any_model_beats(true, 140000, 72, 2100., 1000.), true, "models at stride 2, narrow");
   // pointwise layers: never before the specialised kernels, before the ring-tile kernel always
   BEATS(false, BSP_RIVAL_ROWS, 8, 1, 1, false, 100, 1000, 64, 64);
   BEATS(false, BSP_RIVAL_LDS, 8, 1, 1, false, 100, 1000, 64, 64);
