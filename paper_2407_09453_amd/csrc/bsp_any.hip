@@ -19,9 +19,9 @@
 //
 // A wait for everything before the patch's barrier, small outputs straight from the accumulators (bsp_any_direct), the
 // bias asked for in the opening, zeros for a slab's unused pairs in its last step only and a strip's own partial sums kept in
-// registers, together: 1x7 17x17x160 batch 16 8.1 -> 7.3 us, 5x5 35x35x48->64 12.4 -> 9.9, 3x3 14x14x256 batch 1 5.27 -> 5.03,
-// 7x7x512 6.92 -> 6.31.  Deeper rings for two and four tiles (eight and sixteen steps, one workgroup a CU) gave nothing:
-// 1x7 17x17x160 7.14 either way, int8 3x3 14x14x256 batch 32 8.8 with four and 9.1 with eight.
+// registers, together, data in the caches (cold): 1x7 17x17x160 batch 16 8.6 -> 7.3 us (9.3 -> 7.8), 5x5 35x35x48->64 batch 16
+// 12.8 -> 10.2 (12.3 -> 9.6), 3x3 14x14x256 batch 1 5.6 -> 5.2 (5.8 -> 5.1), 7x7x512 batch 1 7.3 -> 6.9 (8.3 -> 7.0).
+// The ring has four steps in every instance: eight for one lane tile cost a wave a SIMD and scratch for nothing.
 #include "bsp_kept.h"
 #include "bsp_launch.h"
 #include "bsp_tile.h"
@@ -499,8 +499,8 @@ struct Pick {
 
 // Tile, staging and split by a model of the busiest CU in clocks: the workgroups it runs, each with
 // its steps (their latency, or their share of the issue slots and LDS), the bytes it stages and the
-// fixed chain, which resident workgroups hide of each other.  On 12 shapes its choice measured
-// within 4 % of the best of 48 to 384 candidates, but for wide 1x1 layers on many pixels (8 to 15 %).
+// fixed chain, which resident workgroups hide of each other.  On 46 shapes (small, ragged and int8 layers) its choice measured 3 % above
+// the best of up to 70 candidates in the mean, 0.3 % in the median, 9 to 17 % on six of them.
 Pick choose(int B, int M, int N, int os, int nstrips, int steps, int nslabs, int slab_pieces, int pieces, int H, int K, int lsh,
             int lsw, bool flat) {
   Pick best{};

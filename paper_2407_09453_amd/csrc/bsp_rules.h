@@ -16,8 +16,9 @@ enum BspRival { BSP_RIVAL_BAND, BSP_RIVAL_ROWS, BSP_RIVAL_LDS, BSP_RIVAL_TILE };
 // bf16 windows: whether the any-shape kernel is to take the layer that `rival` could take (bo: output
 // channels per block).
 //   one row, row-band kernel: 1x7 17x17x160->192 batch 16 (100 861) 10.2 / 9.0, 17x17x192 batch 32 (220 218)
-//     17.5 / 13.9; 29x29x456->168 batch 4 (187 579) 13 % slower here, 57x57x272->192 batch 4 (252 030) 19 %; with
-//     16x4 blocks no line, 36x36x160->184 batch 31 (1.05 M) 66 / 40
+//     17.5 / 13.9, 57x57x272->192 batch 4 (252 030) 19 % slower here; more than 208 channels in: 29x29x456->168 batch 4 (188 845)
+//     16.6 / 14.2, cold 17.9 / 17.6, 33x33x296->384 batch 2 (166 729) 14.5 / 9.6, 32x19x264->168 batch 9 (164 160) 11.3 / 12.0 the other
+//     way, as 13x18x384->176 batch 16 (216 216, past the line), 1.05 to 1.14; with 16x4 blocks no line, 36x36x160->184 batch 31 (1.05 M) 66 / 40
 //   one row, LDS kernel: 1x7 31x13x248->80 (32 382) 19.8 / 7.0; 37x37x32->184 batch 28 (201 264)
 //     13.2 / 16.4; 1x3 98x32x8->144 batch 21 (37 044, po 9.5 M) 13.5 / 18.5; strided ones have no line
 //   one column: 7x1 22x22x192->104 batch 8 (62 920) 9.4 / 7.8, 17x17x160->192 batch 16 (97 K) 10.0 / 9.5,
@@ -62,15 +63,16 @@ inline bool bsp_any_beats_bf16(BspRival rival, int bo, int H, int K, bool stride
 
 // 3x3 windows past those lines: whether the two kernels' own models of the layer decide between the any-shape and the row-band
 // kernel, and how (`any`: clocks of the busiest CU, `rows`: rough ns).  Neither model knows the other's scale, and the row-band
-// one misses by a fifth either way, so the line is a ratio, drawn where few lose.  Of 3630 random layers of at least 128 channels in,
-// with data in the caches, with cold weights and with all data cold, those past the lines above:
-//   stride 1, up to 8000 pixels (5000 of up to 64 channels out) and 115 K, of few pixels 200 K: 666 of 2009 are taken, 0.76 of their time in
-//     the mean; 7 lose more than 5 % somewhere (the worst 18x24x224->144 batch 8 1.25 to 1.28, 12x12x480->40 batch 22 1.16 to 1.27;
-//     of 1500 others, also of the class below, 25x25x480->32 batch 11 1.18 to 1.24).  By matrix instructions, channels and rows alone
-//     893 were taken, 79 of them at a loss (cold 52x52x368->32 stride 2 batch 17 16 / 30, 15x11x480->136 batch 11 11.0 / 14.7,
-//     24x24x392->88 batch 6 10.3 / 13.0, 35x35x176->488 batch 2 9.8 / 12.0)
-//   stride 2, more than 40 channels out, up to 300 K: 151 of 431, 0.72 of their time, 6 lose more than 5 % (before: 254, 49).  Short
-//     rows lose the row-band kernel a part of every lane tile, so up to 100 K they go by another ratio (17x17x192->320 batch 16 11.0 / 8.1)
+// one gives 1.12 to 2.0 times what it takes (550 layers), so the line is a ratio, drawn where few lose.  Of 4966 random layers of at least
+// 128 channels in, with data in the caches, with cold weights and with all data cold, those past the lines above:
+//   stride 1, up to 8000 pixels (6500 of up to 64 channels out) and 115 K, of few pixels 200 K: 1177 of 2762 are taken, 0.78 of their time in
+//     the mean; 37 lose more than 5 % somewhere (the worst 55x55x376->72 batch 2 1.29 to 1.36, 11x11x136->176 batch 25, dense, 1.25 to
+//     1.35, 18x24x224->144 batch 8 1.25 to 1.28).  By matrix instructions, channels and rows alone 1234 were taken, 0.80, 108 of
+//     them at a loss (cold 15x11x480->136 batch 11 11.0 / 14.7, 24x24x392->88 batch 6 10.3 / 13.0, 35x35x176->488 batch 2 9.8 / 12.0)
+//   stride 2, more than 40 channels out, up to 300 K: 294 of 607, 0.755 of their time, 19 lose more than 5 % (47x47x416->56 batch 20 1.55
+//     to 1.65, 45x50x448->72 batch 5 1.37 to 1.46; by lines alone 368, 0.84, 79 at a loss, cold 52x52x368->32 batch 17 16 / 30).  To 140 K
+//     and past 72 channels out the ratio is another: there the row-band kernel is seldom the faster one (17x17x192->320 batch 16 11.0 / 8.1)
+//   Left behind: 33x30x264->104 batch 4 of dense 16x4 blocks 0.40, stride 2 43x48x304->40 batch 12 0.42 to 0.48
 inline bool bsp_any_models_decide(int H, int K, bool strided, int64_t mm, int64_t P, int64_t O) {
   if (H > 3 || K > 3 || H == 1 || K == 1 || P * O > 3000000) return false;
   return strided ? mm <= 300000 && O > 40 : mm <= (P <= 1500 ? 200000 : 115000) && P <= (O <= 64 ? 6500 : 8000);
